@@ -170,9 +170,21 @@ struct Cuts {
         const long v = start(c);
         return v < U ? (int)v : U;
     }
-    __device__ int span_of(int pos) const // the span that holds cost unit pos < U
+    // The span that holds cost unit pos < U; `from`: a span that starts at or before pos.  (Most items lie in one or two
+    // spans, so an item's last one is looked for from its first one on, in steps that double.)
+    __device__ int span_of(int pos, int from = -1) const
     {
         int c = 0, hi = waves; // invariant: start(c) <= pos < start(hi)
+        if (from >= 0) {
+            c = from;
+            for (int step = 1; c + step < waves; step <<= 1) {
+                if (start(c + step) > pos) {
+                    hi = c + step;
+                    break;
+                }
+                c += step;
+            }
+        }
         while (hi - c > 1) {
             const int mid = (c + hi) >> 1;
             if (start(mid) <= pos) c = mid;
@@ -215,14 +227,24 @@ __device__ __forceinline__ void rows_phase(const Launch &a, const RowsBuf &R, in
     int4 *tab = R.tab;
     const int32_t *len_src = a.seq_lens, *grp_src = a.seq_group, *poff = a.pfx_off;
     // one trip to memory for everything the schedule depends on
+    // (a thread's loads are issued together: element by element each would wait for the one before)
     if (R.len) {
-#pragma unroll 1
-        for (int b = tid; b < B; b += THREADS) {
-            R.len[b] = a.seq_lens[b];
-            R.grp[b] = NG ? a.seq_group[b] : -1;
+        constexpr int N = kPlanCap / THREADS;
+        int32_t L[N], g[N], po[N];
+#pragma unroll
+        for (int k = 0; k < N; k++) {
+            const int i = tid + k * THREADS;
+            L[k] = i < B ? a.seq_lens[i] : 0;
+            g[k] = NG && i < B ? a.seq_group[i] : -1;
+            po[k] = NG && i <= NG ? a.pfx_off[i] : 0;
         }
-#pragma unroll 1
-        for (int g = tid; g <= NG; g += THREADS) R.poff[g] = NG ? a.pfx_off[g] : 0;
+        if (tid == 0 && NG == kPlanCap) R.poff[NG] = a.pfx_off[NG]; // (the one entry past the registers' reach)
+#pragma unroll
+        for (int k = 0; k < N; k++) {
+            const int i = tid + k * THREADS;
+            if (i < B) R.len[i] = L[k], R.grp[i] = g[k];
+            if (i <= NG && i < kPlanCap) R.poff[i] = po[k];
+        }
         len_src = R.len, grp_src = R.grp, poff = R.poff;
     }
 #pragma unroll 1
@@ -256,7 +278,7 @@ __device__ __forceinline__ void rows_phase(const Launch &a, const RowsBuf &R, in
         unsigned long long todo = __ballot(g >= 0);
 #pragma unroll 1
         while (todo) {
-            const int gl = __shfl(g, __ffsll((long long)todo) - 1);
+            const int gl = __builtin_amdgcn_readlane(g, __ffsll((long long)todo) - 1); // (uniform: no trip through LDS)
             const unsigned long long same = __ballot(g == gl);
             if (g == gl) {
                 pos = __popcll(same & ((1ull << lane) - 1ull));
@@ -469,14 +491,16 @@ __device__ __forceinline__ void merge_desc_of(const Launch &a, const Cuts &cut, 
         if (ic > 0) {
             const int n = (ic - a.cost_item) / kCostSuffix;
             const int S = a.Hkv * row_start[r] + kvh * ic + a.cost_item;
-            own = make_int4(n, cut.span_of(S), cut.span_of(S + kCostSuffix * (n - 1)), 0);
+            const int c0 = cut.span_of(S);
+            own = make_int4(n, c0, cut.span_of(S + kCostSuffix * (n - 1), c0), 0);
         }
     }
     if (prow >= 0) {
         const int ic = row_start[prow + 1] - row_start[prow];
         const int n = (ic - a.cost_item_pfx) / a.cost_prefix;
         const int S = a.Hkv * row_start[prow] + kvh * ic + a.cost_item_pfx;
-        pfx = make_int4(n, cut.span_of(S), cut.span_of(S + a.cost_prefix * (n - 1)), 0);
+        const int c0 = cut.span_of(S);
+        pfx = make_int4(n, c0, cut.span_of(S + a.cost_prefix * (n - 1), c0), 0);
     }
     a.ws.merge_desc[2 * i] = own;
     a.ws.merge_desc[2 * i + 1] = pfx;
@@ -518,10 +542,12 @@ __global__ __launch_bounds__(kSpanThreads) void plan_spans_kernel(Launch a)
 }
 
 // The whole schedule in one launch, for batches whose tables fit in LDS (up to kPlanCap sequences and groups): every
-// workgroup works the rows out for itself, which costs less than a second launch and a trip through memory.
-// Workgroup 0 publishes what the other kernels read (members, prefix rows, counts) and writes the merge descriptors;
-// the others write the spans' work lists.
-__global__ __launch_bounds__(kPlanThreads) void plan_fused_kernel(Launch a)
+// workgroup works the rows out for itself, which costs less than a second launch and a trip through memory.  The first
+// span_wgs workgroups then write the spans' work lists, a thread per span (workgroup 0 also publishes what the other
+// kernels read: members, prefix rows, counts), the others the merge descriptors, a thread per (sequence, kv head): a
+// descriptor is two binary searches in the share table, and written by one workgroup they were 22 of the kernel's 43 us
+// on 1024 sequences of two kv heads (128 groups, 2048 spans); the kernel takes 15 us there now, 8.5 of them the rows.
+__global__ __launch_bounds__(kPlanThreads) void plan_fused_kernel(Launch a, int span_wgs)
 {
     touch_args(a);
     __shared__ RowsLds L;
@@ -529,37 +555,47 @@ __global__ __launch_bounds__(kPlanThreads) void plan_fused_kernel(Launch a)
     __shared__ int32_t l_cum[kMaxWaves + 1];
     const int tid = threadIdx.x;
     const Workspace &w = a.ws;
-    for (int i = tid; i <= a.waves; i += kPlanThreads) l_cum[i] = a.wave_cum[i];
+    // the share table: on its way while the rows are worked out
+    constexpr int NC = (kMaxWaves + kPlanThreads) / kPlanThreads;
+    int32_t cum[NC];
+#pragma unroll
+    for (int k = 0; k < NC; k++) cum[k] = tid + k * kPlanThreads <= a.waves ? a.wave_cum[tid + k * kPlanThreads] : 0;
     RowsBuf R;
     plan_rows_buf(R, a, L, true, l_row_tab, blockIdx.x == 0);
     int nR, nPR;
     rows_phase<kPlanThreads>(a, R, nR, nPR, tid);
+#pragma unroll
+    for (int k = 0; k < NC; k++)
+        if (tid + k * kPlanThreads <= a.waves) l_cum[tid + k * kPlanThreads] = cum[k];
+    __syncthreads();
     const int32_t *row_start = R.row_start;
     Cuts cut;
     make_cuts(a, a.Hkv * row_start[nR], cut, l_cum);
-    if (blockIdx.x == 0) {
-        if (tid == 0) {
-            w.hdr[0] = cut.U;
-            w.hdr[2] = nR;
-            w.hdr[3] = nPR;
-            w.hdr[7] = cut.waves;
-        }
-        for (int i = tid; i < a.B * a.Hkv; i += kPlanThreads) merge_desc_of(a, cut, row_start, nPR, i, L.seq_rank[i / a.Hkv]);
+    const int wg = blockIdx.x;
+    if (wg == 0 && tid == 0) {
+        w.hdr[0] = cut.U;
+        w.hdr[2] = nR;
+        w.hdr[3] = nPR;
+        w.hdr[7] = cut.waves;
+    }
+    if (wg < span_wgs) {
+        spans_phase(a, cut, row_start, l_row_tab, nR, nPR, wg * kPlanThreads + tid, span_wgs * kPlanThreads);
     } else {
-        spans_phase(a, cut, row_start, l_row_tab, nR, nPR, (blockIdx.x - 1) * kPlanThreads + tid, (gridDim.x - 1) * kPlanThreads);
+        for (int i = (wg - span_wgs) * kPlanThreads + tid; i < a.B * a.Hkv; i += (gridDim.x - span_wgs) * kPlanThreads)
+            merge_desc_of(a, cut, row_start, nPR, i, L.seq_rank[i / a.Hkv]);
     }
 }
 
 hipError_t launch_plan(const Launch &a, hipStream_t s)
 {
-    const int work = a.waves; // one thread per span
     if (a.B <= kPlanCap && (a.share ? a.num_groups : 0) <= kPlanCap) {
-        hipLaunchKernelGGL(plan_fused_kernel, dim3(1 + (work + kPlanThreads - 1) / kPlanThreads), dim3(kPlanThreads), 0, s, a);
+        // (at most 64 workgroups for the descriptors: beyond that a thread takes several)
+        const int span_wgs = (a.waves + kPlanThreads - 1) / kPlanThreads, items = (a.B * a.Hkv + kPlanThreads - 1) / kPlanThreads;
+        hipLaunchKernelGGL(plan_fused_kernel, dim3(span_wgs + (items < 64 ? items : 64)), dim3(kPlanThreads), 0, s, a, span_wgs);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(plan_rows_kernel, dim3(1), dim3(kPlanThreads), 0, s, a);
-    // ... and per (sequence, kv head)
-    const int n = work > a.B * a.Hkv ? work : a.B * a.Hkv;
+    const int n = a.waves > a.B * a.Hkv ? a.waves : a.B * a.Hkv; // a thread per span and per (sequence, kv head)
     hipLaunchKernelGGL(plan_spans_kernel, dim3((n + kSpanThreads - 1) / kSpanThreads), dim3(kSpanThreads), 0, s, a);
     return hipGetLastError();
 }

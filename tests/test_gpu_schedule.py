@@ -145,3 +145,15 @@ def test_schedule_of_random_batches(dec):
         p.q = np.zeros((p.B, p.Hq, p.D), dtype=np.uint16)
         p.k_pool = p.v_pool = np.zeros((1, Hkv, 16, 64), dtype=np.uint16)
         check_schedule(dec, p, True, "random %d" % trial)
+
+
+@pytest.mark.parametrize("groups,R,Hkv,G", [(171, 3, 2, 4), (128, 8, 2, 4), (1, 1400, 8, 1), (256, 8, 16, 2), (683, 3, 2, 1)])
+def test_schedule_of_batches_with_a_schedule_kernel(dec, groups, R, Hkv, G):
+    # 513 and 1024 sequences; one group of 1400; more (sequence, kv head) descriptors than the launch has threads; one
+    # sequence past what the one-kernel schedule takes
+    rng = np.random.default_rng(groups + R)
+    p = workload.build_problem("wide", Hkv * G, Hkv, 64, rng.choice([0, 20, 64], size=groups), R, rng.integers(0, 300, size=groups * R),
+                               seed=R, make_values=False)
+    p.q = np.zeros((p.B, p.Hq, p.D), dtype=np.uint16)
+    p.k_pool = p.v_pool = np.zeros((1, Hkv, 16, 64), dtype=np.uint16)
+    check_schedule(dec, p, True, "wide %d x %d" % (groups, R))
