@@ -1719,14 +1719,12 @@ struct PartList {
     int64_t ostride, lstride;
 };
 
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const int4 *__restrict__ merge_desc,
-                                                               const int32_t *__restrict__ seq_pfx_row,
-                                                               const int32_t *__restrict__ seq_rank_in_row)
+// The partials of (sequence b, kv head kvh) = `item`: pl[0] of its shared-prefix row, pl[1] of its own pages.
+__device__ __forceinline__ void merge_lists(const Launch &a, const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
+                                            const int32_t *__restrict__ seq_rank_in_row, int item, int b, int kvh, PartList (&pl)[2])
 {
-    touch_args(a);
     const Workspace &w = a.ws;
-    const int item = blockIdx.x, b = item / a.Hkv, kvh = item - b * a.Hkv;
-    const int D = a.D, tpr = D / 4; // threads per output row
+    const int D = a.D;
     int4 own = merge_desc[2 * item], pfx = merge_desc[2 * item + 1];
     int prow = seq_pfx_row[b];
     const int row0 = seq_rank_in_row[b] * a.G;
@@ -1736,7 +1734,6 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const in
         if (a.seq_lens[b] <= 0 || a.max_pages <= 0) own.y = pfx.y = 0, own.z = pfx.z = -1;
         if (pfx.y > pfx.z) prow = -1;
     }
-    PartList pl[2];
     {
         PartList &p = pl[1];
         p.c_lo = own.y, p.c_hi = own.z;
@@ -1754,6 +1751,42 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const in
         p.ostride = (int64_t)a.prefix_rows * D;
         p.lstride = a.prefix_rows;
     }
+}
+
+// Adds up to N partials (the i-th has log2-sum-exp l[i], -inf for none, and output v[i]) to a running (M, wsum, acc).
+template <int N> __device__ __forceinline__ void merge_add(const float (&l)[N], const f32x4 (&v)[N], float &M, float &wsum, f32x4 &acc)
+{
+    float mn = M;
+#pragma unroll
+    for (int i = 0; i < N; i++) mn = fmaxf(mn, l[i]);
+    const float alpha = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn);
+    M = mn;
+    wsum *= alpha;
+    acc *= alpha;
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const float wgt = l[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(l[i] - mn);
+        wsum += wgt;
+        acc += wgt * v[i];
+    }
+}
+__device__ __forceinline__ void merge_write(const Launch &a, int64_t bh, int d4, float M, float wsum, f32x4 acc)
+{
+    const bool empty = wsum == 0.f;
+    const float inv = empty ? 0.f : 1.0f / wsum;
+    *(bf16x4 *)(a.out + bh * a.D + d4) = __builtin_convertvector(acc * inv, bf16x4);
+    if (d4 == 0) a.lse[bh] = empty ? -INFINITY : (M + __builtin_amdgcn_logf(wsum)) * 0.6931471805599453f;
+}
+
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const int4 *__restrict__ merge_desc,
+                                                               const int32_t *__restrict__ seq_pfx_row,
+                                                               const int32_t *__restrict__ seq_rank_in_row)
+{
+    touch_args(a);
+    const int item = blockIdx.x, b = item / a.Hkv, kvh = item - b * a.Hkv;
+    const int D = a.D, tpr = D / 4; // threads per output row
+    PartList pl[2];
+    merge_lists(a, merge_desc, seq_pfx_row, seq_rank_in_row, item, b, kvh, pl);
     const int npfx = pl[0].c_hi - pl[0].c_lo + 1, nown = pl[1].c_hi - pl[1].c_lo + 1;
     for (int hl = threadIdx.x / tpr; hl < a.G; hl += kMergeThreads / tpr) {
         const int d4 = (threadIdx.x % tpr) * 4;
@@ -1772,40 +1805,87 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const in
                 l[i] = have ? p.lse[c * p.lstride + hl] : -INFINITY;
                 v[i] = have ? *(const f32x4 *)(p.o + c * p.ostride + (int64_t)hl * D + d4) : f32x4{0.f, 0.f, 0.f, 0.f};
             }
-#pragma unroll
-            for (int i = 0; i < NP; i++) M = fmaxf(M, l[i]);
-#pragma unroll
-            for (int i = 0; i < NP; i++) {
-                const float wgt = l[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(l[i] - M);
-                wsum += wgt;
-                acc += wgt * v[i];
-            }
+            merge_add<NP>(l, v, M, wsum, acc);
         } else {
+            // one item of many spans among items of few: four partials at a time
+            constexpr int NP = 4;
             for (int k = 0; k < 2; k++)
-                for (int c = pl[k].c_lo; c <= pl[k].c_hi; c++) M = fmaxf(M, pl[k].lse[c * pl[k].lstride + hl]);
-            for (int k = 0; k < 2; k++)
-                for (int c = pl[k].c_lo; c <= pl[k].c_hi; c++) {
-                    const float lv = pl[k].lse[c * pl[k].lstride + hl];
-                    const float wgt = lv == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(lv - M);
-                    wsum += wgt;
-                    acc += wgt * *(const f32x4 *)(pl[k].o + c * pl[k].ostride + (int64_t)hl * D + d4);
+                for (int c0 = pl[k].c_lo; c0 <= pl[k].c_hi; c0 += NP) {
+                    float l[NP];
+                    f32x4 v[NP];
+#pragma unroll
+                    for (int i = 0; i < NP; i++) {
+                        const int c = c0 + i;
+                        const bool have = c <= pl[k].c_hi;
+                        l[i] = have ? pl[k].lse[c * pl[k].lstride + hl] : -INFINITY;
+                        v[i] = have ? *(const f32x4 *)(pl[k].o + c * pl[k].ostride + (int64_t)hl * D + d4) : f32x4{0.f, 0.f, 0.f, 0.f};
+                    }
+                    merge_add<NP>(l, v, M, wsum, acc);
                 }
         }
-        const bool empty = wsum == 0.f;
-        const float inv = empty ? 0.f : 1.0f / wsum;
-        const int64_t bh = (int64_t)b * a.Hq + kvh * a.G + hl;
-        bf16x4 ob = __builtin_convertvector(acc * inv, bf16x4);
-        *(bf16x4 *)(a.out + bh * D + d4) = ob;
-        if (d4 == 0) a.lse[bh] = empty ? -INFINITY : (M + __builtin_amdgcn_logf(wsum)) * 0.6931471805599453f;
+        merge_write(a, (int64_t)b * a.Hq + kvh * a.G + hl, d4, M, wsum, acc);
     }
+}
+
+// The merge of batches whose items are cut into many spans each (few sequences: more attention waves than items).  A
+// workgroup takes one head of one item; its threads form lanes of D / 4, which take the partials turn about, four at a
+// time each, so that up to 32 (D = 128) are on their way together; the lanes' sums meet in LDS, in lane order.  One
+// partial after the other is what bound the kernel above there: 13.2 us for 48 items of 21 spans (D = 128, five heads), 4.7 here.
+__global__ __launch_bounds__(kMergeThreads) void merge_wide_kernel(Launch a, const int4 *__restrict__ merge_desc,
+                                                                   const int32_t *__restrict__ seq_pfx_row,
+                                                                   const int32_t *__restrict__ seq_rank_in_row)
+{
+    touch_args(a);
+    __shared__ f32x4 s_acc[kMergeThreads];
+    __shared__ float s_m[kMergeThreads / 16], s_w[kMergeThreads / 16];
+    const int item = blockIdx.x / a.G, hl = blockIdx.x - item * a.G, b = item / a.Hkv, kvh = item - b * a.Hkv;
+    const int D = a.D, tpr = D / 4, lanes = kMergeThreads / tpr;
+    const int me = threadIdx.x / tpr, d4 = (threadIdx.x % tpr) * 4;
+    PartList pl[2];
+    merge_lists(a, merge_desc, seq_pfx_row, seq_rank_in_row, item, b, kvh, pl);
+    const int npfx = pl[0].c_hi - pl[0].c_lo + 1, nown = pl[1].c_hi - pl[1].c_lo + 1, total = npfx + nown;
+    float M = -INFINITY, wsum = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    constexpr int NP = 4;
+    for (int i0 = me; i0 < total; i0 += NP * lanes) {
+        float l[NP];
+        f32x4 v[NP];
+#pragma unroll
+        for (int k = 0; k < NP; k++) {
+            const int i = i0 + k * lanes;
+            const PartList &p = pl[i < npfx ? 0 : 1];
+            const int c = p.c_lo + (i < npfx ? i : i - npfx);
+            const bool have = i < total;
+            l[k] = have ? p.lse[c * p.lstride + hl] : -INFINITY;
+            v[k] = have ? *(const f32x4 *)(p.o + c * p.ostride + (int64_t)hl * D + d4) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        merge_add<NP>(l, v, M, wsum, acc);
+    }
+    s_acc[threadIdx.x] = acc;
+    if (d4 == 0) s_m[me] = M, s_w[me] = wsum;
+    __syncthreads();
+    if (me != 0) return;
+    float Mt = -INFINITY, wt = 0.f;
+    f32x4 at = {0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < lanes; k++) Mt = fmaxf(Mt, s_m[k]);
+    for (int k = 0; k < lanes; k++) {
+        const float wgt = s_m[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[k] - Mt);
+        wt += wgt * s_w[k];
+        at += wgt * s_acc[k * tpr + threadIdx.x];
+    }
+    merge_write(a, (int64_t)b * a.Hq + kvh * a.G + hl, d4, Mt, wt, at);
 }
 
 hipError_t launch_merge(const Launch &a, hipStream_t s)
 {
     if (a.B == 0) return hipSuccess;
     const Workspace &w = a.ws;
-    hipLaunchKernelGGL(merge_kernel, dim3(a.B * a.Hkv), dim3(kMergeThreads), 0, s, a, w.merge_desc, w.seq_pfx_row,
-                       w.seq_rank_in_row);
+    // An item is cut about waves / items times.
+    if (a.waves >= 3 * a.B * a.Hkv)
+        hipLaunchKernelGGL(merge_wide_kernel, dim3(a.B * a.Hkv * a.G), dim3(kMergeThreads), 0, s, a, w.merge_desc, w.seq_pfx_row,
+                           w.seq_rank_in_row);
+    else
+        hipLaunchKernelGGL(merge_kernel, dim3(a.B * a.Hkv), dim3(kMergeThreads), 0, s, a, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row);
     return hipGetLastError();
 }
 

@@ -571,3 +571,21 @@ def test_wave_weights_move_work_not_results(dec):
             ra.rollout_attn_set_wave_weights(dec.ctx, np.full(n - 1, 1000), ra.RA_KV_BF16, p.D)
     finally:
         ra.rollout_attn_set_wave_weights(dec.ctx, np.full(n, 1000), ra.RA_KV_BF16, p.D)
+
+
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("Hq,Hkv,D,prompts,R,resp", [
+    (1, 1, 64, [0], 1, [5000]),                        # one item, cut as often as the shortest span allows
+    (16, 1, 128, [0], 1, [9001]),
+    (28, 4, 128, [2000], 3, [0, 1, 3000]),             # many spans of the shared row; a member without pages of its own
+    (10, 2, 128, [0, 0], 2, [0, 16, 17, 700]),         # an empty sequence beside items of a few spans
+    (8, 4, 128, [0] * 129, 1, [9000] + [20] * 128),    # one item of many spans in a batch of more items than a third of the waves
+    (8, 4, 64, [0] * 129, 1, [33] * 128 + [9000]),
+])
+def test_merge_of_items_cut_into_many_spans(dec, kvd, Hq, Hkv, D, prompts, R, resp):
+    from gpu_util import compare
+    p = workload.build_problem("cut", Hq, Hkv, D, prompts, R, resp, kv_dtype=kvd, seed=31)
+    log("case", Hq, Hkv, D, R, resp[:3], kvd)
+    # (outputs of one to three tokens are as large as single V entries: rounding them to bf16 alone is 2^-9 of that)
+    ref_out, ref_lse = oracle.decode(p)
+    compare(*run(dec, p).results(), ref_out, ref_lse, "cut", abs_rel=2.0 ** -8)
