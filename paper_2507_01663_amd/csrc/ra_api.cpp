@@ -26,7 +26,7 @@ struct ra_ctx {
     int xcd_w[8];              // default share of the page stream per accelerator die, per mille of the mean
     int32_t *wave_cum[2][2];   // device: running sums of the workgroups' shares, [e4m3 KV][D == 128], kMaxWaves + 1 each
     uint32_t *tickets;         // device: the streaming probe's ticket counter (cleared by every launch that uses it)
-    int prefill_stay;          // -1: the prefill launch chooses by prompt length; else ROLLOUT_ATTN_PREFILL_WGS_PER_DIE
+    int prefill_stay;          // -1: one prefill workgroup per compute unit; else ROLLOUT_ATTN_PREFILL_WGS_PER_DIE
     void *zeros;  // 256 bytes of zeros on the device
     int self_plan; // attention waves may plan their spans themselves (no schedule kernel)
     int32_t *host_flags; // pinned, for RA_FLAG_VALIDATE
@@ -515,7 +515,7 @@ ra_status rollout_attn_prefill(ra_ctx *c, const ra_prefill *p, void *stream)
     int prev = 0;
     hipError_t e = hipGetDevice(&prev);
     if (e == hipSuccess && prev != c->device) e = hipSetDevice(c->device);
-    if (e == hipSuccess && p->k_pool) e = ra::launch_prefill_write(a, (hipStream_t)stream);
+    if (e == hipSuccess && p->k_pool && !ra::prefill_writes_cache(a)) e = ra::launch_prefill_write(a, (hipStream_t)stream);
     if (e == hipSuccess) e = ra::launch_prefill(a, (hipStream_t)stream);
     if (prev != c->device) (void)hipSetDevice(prev);
     if (e != hipSuccess) { set_err(c, "HIP: %s", hipGetErrorString(e)); return RA_ERR_DEVICE; }

@@ -69,14 +69,17 @@ struct PrefillLaunch {
     int32_t num_prompts, max_len, Hq, Hkv, D, G;
     int32_t num_cus;             // compute units of the device
     int32_t stay;                // prefill workgroups per die that stay and take block after block (at most one per
-                                 // compute unit); 0: one workgroup per block; -1: chosen by prompt length
+                                 // compute unit); 0: one workgroup per block; -1: as many as there are compute units
+    int32_t fused_write;         // the attention kernel writes the cache too (set by launch_prefill)
+    int32_t group;               // prompts whose blocks are dealt together (set by launch_prefill)
+    uint32_t magic_g, magic_heads; // ceil(2^32 / n) for n = G and n = Hkv / gcd(Hkv, 8) (set by launch_prefill)
     const uint16_t *q, *k, *v;   // bf16 [T][Hq][D], [T][Hkv][D]
     const int32_t *cu;           // [num_prompts + 1] first token of each prompt
     float scale_log2;            // softmax_scale * log2(e)
     uint16_t *out;               // bf16 [T][Hq][D]
     float *lse;                  // [T][Hq]
     const void *zeros;           // >= 16 bytes of zeros
-    // cache write (launch_prefill_write)
+    // cache write
     int32_t kv_fp8, num_pages;
     uint8_t *k_pool, *v_pool;
     int64_t stride_page_b, stride_head_b; // bytes
@@ -113,6 +116,8 @@ hipError_t launch_append(const Launch &a, const void *k_new, const void *v_new, 
 // Once per device, before the first launch_prefill: lets the prefill kernels have the LDS they ask for.
 hipError_t prefill_config();
 hipError_t launch_prefill(const PrefillLaunch &a, hipStream_t s);
+// Whether launch_prefill writes the cache as well (then launch_prefill_write is not called).
+bool prefill_writes_cache(const PrefillLaunch &a);
 hipError_t launch_prefill_write(const PrefillLaunch &a, hipStream_t s);
 hipError_t launch_gather(const Launch &a, int b, int kvh, void *k_out, void *v_out, int64_t cap, hipStream_t s);
 

@@ -3,8 +3,8 @@
 // several responses are sampled for one prompt: paper Sec. 7.1).
 //
 // Unlike the decode step this is a dense contraction, bound by the matrix cores.  A workgroup of eight waves
-// (two per SIMD, so that one wave's vector work runs while the other's MFMAs do) takes 256 consecutive query
-// rows of one (prompt, head), 32 rows per wave.  K and V stream through an LDS ring in chunks of two stages of 32
+// (two per SIMD, so that one wave's vector work runs while the other's MFMAs do) takes eight (32-row tile, head) units
+// of one (prompt, kv head), one per wave.  K and V stream through an LDS ring in chunks of two stages of 32
 // keys (K0 K1 V0 V1 | K2 K3 V2 V3, one 16-key tile loaded by each wave with direct global->LDS loads); every wave
 // multiplies every stage with its own query rows, held in registers:
 //   S^T[key, row] = K . Q^T,   O^T[d, row] += V^T . P^T     (32x32x16 MFMA, fp32 accumulation)
@@ -230,52 +230,131 @@ __device__ __forceinline__ void pf_scores(const uint8_t *k_stage, const PfLane<D
     sn += s2;
 }
 
-// A block: 256 consecutive query rows of one (prompt, head), with the keys 0 .. its last row.  All fields are the same
-// in every lane.
+// A unit of work of a wave: one head's 32 query rows of one tile, with the keys 0 .. its last row.  The units of a
+// (prompt, kv head) pair are numbered from the last tile down, the G heads of a tile together, and a block is eight
+// consecutive ones: under the causal mask they need the same keys but for a tile or two, so the waves of a workgroup
+// have the same work and leave the block together.  (A block of 256 rows of one head streams the keys of its last row
+// past all of its waves: 24 stages of 32 keys for the 512 rows of a head of a 512-token prompt, 18 this way, and half
+// of the waves idle at the end of it.)
+//
+// Which workgroup takes which blocks is fixed by the inputs.  Workgroups are dealt to the eight dies round-robin, and
+// each die has its own L2, so the blocks of a pair go to few dies: with gg = gcd(Hkv, 8), die x takes the kv heads
+// congruent x mod gg, and the 8 / gg dies that take the same heads take the blocks of a pair in turn.  Every die so gets
+// the same share of every prompt, however ragged the lengths are.  A die's blocks are ordered by length, longest first
+// (block number from the short end of its pair, which is its length to within a tile, over all prompts at once) and
+// dealt to its workgroups back and forth, which keeps their sums within a few percent of one another.
 struct PfBlock {
-    int h, kvh, q0, t0, len; // head, kv head, first query row; first token and length of the prompt
-    int nst, nchunks;        // stages of 32 keys, chunks of two stages
+    int g, kvh, t0, len; // prompt, kv head; first token of the prompt, its tokens
+    int u0, nst;        // first unit of the block, stages of 32 keys
+    __device__ __forceinline__ int tiles() const { return (len + 31) >> 5; }
+    __device__ __forceinline__ int chunks() const { return (nst + 1) >> 1; } // of two stages
 };
 
-// Workgroups are dealt to the eight dies round-robin, and each die has its own L2.  All blocks of a (prompt, kv
-// head) pair, which read the same K and V, therefore go to one die: die x takes the pairs x, x + 8, ... one after
-// the other, each with its query blocks from the longest down and the heads of the kv head together.  `turn` counts
-// a die's blocks in that order; false past the die's last pair.  A block past its prompt's length has no stages.
-__device__ __forceinline__ bool pf_block_of(const PrefillLaunch &a, int die, int turn, PfBlock &b)
+// A place in a die's order of blocks.  Lane l knows the length of prompt base + l.
+struct PfCursor {
+    int base, lane0;    // the 64 prompts that the lanes hold, and the first lane of the group of prompts
+    int j, top, o;      // level (blocks left in the pair's share behind this one), the group's highest, place in the level
+    int round;          // blocks of this workgroup so far
+    int lens, cnt;      // this lane's prompt: tokens, blocks of one kv head on this die
+};
+
+struct PfDeal {
+    int lane, wg, wgs, gg_shift, heads, s_shift, share, limit; // see pf_deal
+};
+
+__device__ __forceinline__ PfDeal pf_deal(const PrefillLaunch &a)
 {
-    const int nqb = (a.max_len + kPfBlock - 1) / kPfBlock;
-    const int per_pair = nqb * a.G;
-    const int pair = (turn / per_pair) * 8 + die, r = turn % per_pair;
-    if (pair >= a.num_prompts * a.Hkv) return false;
-    const int g = pair / a.Hkv;
-    b.kvh = pair % a.Hkv;
-    b.h = b.kvh * a.G + r % a.G;
-    b.q0 = (nqb - 1 - r / a.G) * kPfBlock;
+    PfDeal d;
+    const int die = blockIdx.x & 7;
+    d.lane = threadIdx.x & 63;
+    d.wg = blockIdx.x >> 3;
+    d.wgs = gridDim.x >> 3;
+    d.gg_shift = (a.Hkv & 7) == 0 ? 3 : (a.Hkv & 3) == 0 ? 2 : (a.Hkv & 1) == 0 ? 1 : 0;
+    d.heads = a.Hkv >> d.gg_shift;
+    d.s_shift = 3 - d.gg_shift;
+    d.share = die >> d.gg_shift;
+    d.limit = (a.max_len + kPfBlock - 1) / kPfBlock * kPfBlock; // rows past it are left alone
+    return d;
+}
+
+// x / n for x * n < 2^32, with m = ceil(2^32 / n) (n == 1: m is not used)
+__device__ __forceinline__ int pf_div(int x, int n, uint32_t m) { return n == 1 ? x : (int)__umulhi((uint32_t)x, m); }
+
+__device__ __forceinline__ int pf_blocks(int tokens, int G) { return (((tokens + 31) >> 5) * G + 7) >> 3; }
+
+// Goes to the first level of the group of prompts that starts at lane c.lane0 of c.base (first loads the lanes' prompts
+// where that is lane 0).
+__device__ __forceinline__ void pf_enter(const PrefillLaunch &a, const PfDeal &d, PfCursor &c)
+{
+    if (c.lane0 == 0) {
+        const int g = c.base + d.lane;
+        int len = 0;
+        if (g < a.num_prompts) len = a.cu[g + 1] - a.cu[g];
+        len = len < 0 ? 0 : (len < d.limit ? len : d.limit);
+        c.lens = len;
+        // this die's share of the pair's blocks: numbers s, s + 8 / gg, ... (s moves on with the prompt, or one die would
+        // get every pair's longest block)
+        const int S = 1 << d.s_shift, s = (d.share + g) & (S - 1), nb = pf_blocks(len, a.G);
+        c.cnt = nb > s ? (nb - s + S - 1) >> d.s_shift : 0;
+    }
+    const bool in = (d.lane & -a.group) == c.lane0;
+    int top = -1; // the largest j with cnt > j in some lane of the group
+#pragma unroll 1
+    for (int bit = 1 << 24; bit; bit >>= 1)
+        if (__any(in && c.cnt > top + bit)) top += bit;
+    c.top = top;
+    c.j = ((c.base + c.lane0) / a.group) & 1 ? 0 : top;
+}
+
+__device__ __forceinline__ unsigned long long pf_level(const PrefillLaunch &a, const PfDeal &d, const PfCursor &c)
+{
+    return __ballot((d.lane & -a.group) == c.lane0 && c.cnt > c.j);
+}
+
+// Moves the cursor n blocks on; false past the die's last block.
+__device__ __forceinline__ bool pf_seek(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, int n)
+{
+    c.o += n;
+    for (;;) {
+        const int step = ((c.base + c.lane0) / a.group) & 1 ? 1 : -1;
+        while (c.j >= 0 && c.j <= c.top) {
+            const int here = __popcll(pf_level(a, d, c)) * d.heads;
+            if (c.o < here) return true;
+            c.o -= here;
+            c.j += step;
+        }
+        c.lane0 += a.group;
+        if (c.lane0 >= 64) c.lane0 = 0, c.base += 64;
+        if (c.base + c.lane0 >= a.num_prompts) return false;
+        pf_enter(a, d, c);
+    }
+}
+
+// The workgroup's next block (its first one when c.round is 0); false when it has no more.
+__device__ __forceinline__ bool pf_next(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, PfBlock &b)
+{
+    // back and forth: places wg, 2 wgs - 1 - wg, 2 wgs + wg, ...
+    const int n = c.round == 0 ? d.wg : (c.round & 1) ? 2 * (d.wgs - d.wg) - 1 : 2 * d.wg + 1;
+    c.round++;
+    if (!pf_seek(a, d, c, n)) return false;
+    const unsigned long long m = pf_level(a, d, c);
+    const int nth = pf_div(c.o, d.heads, a.magic_heads), x = c.o - nth * d.heads;
+    const int rank = __popcll(m & ((1ull << d.lane) - 1ull));
+    const int l = __ffsll((long long)(m & __ballot(rank == nth))) - 1;
+    const int g = c.base + l, S = 1 << d.s_shift, s = (d.share + g) & (S - 1);
+    b.len = __builtin_amdgcn_readlane(c.lens, l);
+    b.g = g;
     b.t0 = uniform_load(a.cu, g);
-    b.len = uniform_load(a.cu, g + 1) - b.t0;
-    int kend = b.q0 + kPfBlock;
-    kend = kend < b.len ? kend : b.len;
-    b.nst = b.q0 < b.len ? (kend + 31) >> 5 : 0;
-    b.nchunks = (b.nst + 1) >> 1;
+    b.kvh = ((int)blockIdx.x & ((1 << d.gg_shift) - 1)) + (x << d.gg_shift);
+    b.u0 = 8 * (s + ((__builtin_amdgcn_readlane(c.cnt, l) - 1 - c.j) << d.s_shift));
+    b.nst = b.tiles() - pf_div(b.u0, a.G, a.magic_g);
     return true;
 }
 
-// The first block with stages at or after `turn` among the turns turn, turn + step, ... of the die (turn comes back
-// as that block's turn); false when the die has none left.
-__device__ __forceinline__ bool pf_next_block(const PrefillLaunch &a, int die, int &turn, int step, PfBlock &b)
-{
-    while (pf_block_of(a, die, turn, b)) {
-        if (b.nst > 0) return true;
-        turn += step;
-    }
-    return false;
-}
-
-// STAY: the workgroups stay: gridDim.x / 8 of them per die, and workgroup i of a die takes the die's blocks i, i + that
-// many, ...  K and V of one block after the other stream through one ring, so the first chunks of the next block
-// (and its query rows, into registers) are loaded while the last stages of the current one are being multiplied: a
-// block starts without a trip to memory.  Without STAY a workgroup takes the one block its number names (the launch
-// has one workgroup per block then).  max_len is the host's upper bound of a prompt's length.
+// STAY: the workgroups stay: as many per die as it has compute units, each taking its blocks one after the other.  K and
+// V of one block after the other stream through one ring, so the first chunks of the next block (and its query rows,
+// into registers) are loaded while the last stages of the current one are being multiplied: a block starts without a
+// trip to memory.  Without STAY there is a workgroup per block.  max_len is the host's upper bound of a prompt's length.
 template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void prefill_kernel(PrefillLaunch a)
 {
     using G = Geo<D, 2>;
@@ -286,13 +365,16 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     const uint32_t lds_addr = (uint32_t)(uintptr_t)lds;
     const int lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int die = blockIdx.x & 7, step = gridDim.x >> 3;
 
-    // two cursors over the same sequence of blocks: the one being multiplied, and the one whose chunks are being loaded
+    // two cursors over the same sequence of blocks: the one whose chunks are being loaded, and the one after the block
+    // that is being multiplied
+    const PfDeal deal = pf_deal(a);
+    PfCursor lcur;
+    lcur.base = lcur.lane0 = 0, lcur.o = 0, lcur.round = 0;
+    pf_enter(a, deal, lcur);
     PfBlock cb, lb;
-    int cturn = blockIdx.x >> 3;
-    if (!pf_next_block(a, die, cturn, step, cb)) return; // the whole workgroup
-    int lturn = cturn;
+    if (__builtin_expect(!pf_next(a, deal, lcur, cb), 0)) return; // the whole workgroup
+    PfCursor ncur = lcur;
     lb = cb;
     bool l_ok = true;
 
@@ -312,13 +394,13 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     int lchunk = 0;  // chunks of the block being loaded that have been issued
     int tok = 0;     // first key of the wave's tile in the chunk to load next
     const uint8_t *src = nullptr;
-    auto load_from = [&](const PfBlock &b) {
+    auto load_from = [&](const PfBlock &b) __attribute__((always_inline)) {
         tok = kPage * (tile & 1);
         src = (const uint8_t *)((tile < 2 ? a.k : a.v) + ((int64_t)(b.t0 + tok) * a.Hkv + b.kvh) * D);
         lchunk = 0;
     };
     load_from(lb);
-    auto issue = [&]() { // the next chunk of the sequence, if there is one
+    auto issue = [&]() __attribute__((always_inline)) { // the next chunk of the sequence, if there is one
         if (!l_ok) return;
         if (loader) {
             const uint32_t d = dst + (issued & (NSL - 1)) * 2 * G::kStage;
@@ -328,9 +410,8 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
         src += 64 * tok_bytes;
         tok += 64;
         issued++;
-        if (++lchunk == lb.nchunks) {
-            lturn += step;
-            l_ok = STAY && pf_next_block(a, die, lturn, step, lb);
+        if (++lchunk == lb.chunks()) {
+            l_ok = STAY && pf_next(a, deal, lcur, lb);
             if (l_ok) load_from(lb);
         }
     };
@@ -341,27 +422,98 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     // c (before the first step that reads its K) says that every wave's loads of the chunk have landed and that
     // every wave has left the last step that read chunk c - 2, whose slot then takes chunk c + 2 (the first two
     // chunks are loaded up front).  Chunks are numbered over all blocks, so the same holds across a block's end.
-    auto open_chunk = [&](int c) {
+    // The cache write, from the tiles that stream through the ring anyway (16 keys of a kv head: a page).  A stage's K and
+    // V are written by the block that holds the first head's unit of the stage's tile, which spreads them evenly over the
+    // blocks; wave w takes tile w of the chunk that has just been opened.
+    int w_lo = 1 << 30, w_hi = -1; // the block's stages to be written
+    auto pages_of_block = [&]() __attribute__((always_inline)) {
+        const int units = cb.tiles() * a.G, end = (cb.u0 + 8 < units ? cb.u0 + 8 : units) - 1;
+        w_hi = cb.tiles() - 1 - pf_div(cb.u0 + a.G - 1, a.G, a.magic_g);
+        w_lo = cb.tiles() - 1 - pf_div(end, a.G, a.magic_g);
+    };
+    auto write_page = [&](int c, int stage) __attribute__((always_inline)) { // chunk (counted over all blocks), stage of the block
+        const int pi = 2 * stage + (wave & 1), p0 = uniform_load(a.page_off, cb.g), is_v = wave & 2;
+        int rows = cb.len - kPage * pi;
+        if (rows <= 0 || kPage * pi >= a.max_len || pi >= uniform_load(a.page_off, cb.g + 1) - p0) return;
+        rows = rows < kPage ? rows : kPage;
+        const int pid = uniform_load(a.pages, (int64_t)p0 + pi);
+        if (pid < 0 || pid >= a.num_pages) return;
+        int ln = lane;
+        asm volatile("" : "+v"(ln)); // (nothing of this is to be kept in registers through the block)
+        const uint8_t *const tile = lds + (c & (NSL - 1)) * 2 * G::kStage + (wave >> 2) * G::kStage + (wave & 3) * G::kTile + 16 * ln;
+        uint8_t *const page = (is_v ? a.v_pool : a.k_pool) + (int64_t)pid * a.stride_page_b + (int64_t)cb.kvh * a.stride_head_b;
+        auto piece = [&](int x) __attribute__((always_inline)) { return *(const uint4 *)(tile + 1024 * x); };
+        auto row_of = [&](int x) __attribute__((always_inline)) { return 64 / G::kUnits * x + ln / G::kUnits; };
+        auto byte_of = [&](int x) __attribute__((always_inline)) { return 16 * (ln % G::kUnits ^ (swz(row_of(x)) & (G::kUnits - 1))); };
+        if (!a.kv_fp8) {
+#pragma unroll
+            for (int x = 0; x < G::kDmaPerTile; x++) {
+                const uint4 w = piece(x);
+                if (row_of(x) < rows) *(uint4 *)(page + (int64_t)row_of(x) * a.stride_token_b + byte_of(x)) = w;
+            }
+            return;
+        }
+        // (rows past the end hold zeros: they do not change the maximum)
+        uint32_t m = 0;
+#pragma unroll
+        for (int x = 0; x < G::kDmaPerTile; x++) m = bf16_mag_max(m, piece(x));
+        m = bf16_mag_reduce(m);
+        float amax = __uint_as_float(m << 16);
+        if (__builtin_expect(m > 0x7f80, 0)) { // a NaN does not take part in the maximum
+            amax = 0.f;
+#pragma unroll 1
+            for (int x = 0; x < G::kDmaPerTile; x++) {
+                const uint4 w = piece(x);
+                amax = fmaxf(amax, fmaxf(fmaxf(fabsf(bf16_lo(w.x)), fabsf(bf16_hi(w.x))), fmaxf(fabsf(bf16_lo(w.y)), fabsf(bf16_hi(w.y)))));
+                amax = fmaxf(amax, fmaxf(fmaxf(fabsf(bf16_lo(w.z)), fabsf(bf16_hi(w.z))), fmaxf(fabsf(bf16_lo(w.w)), fabsf(bf16_hi(w.w)))));
+            }
+#pragma unroll 1
+            for (int sh = 32; sh >= 1; sh >>= 1) amax = fmaxf(amax, __shfl_xor(amax, sh));
+        }
+        const float scale = amax > 0.f ? amax / 448.0f : 1.0f;
+        const E4m3Scale sc = {scale, 1.0f / scale};
+        const bool fast = m <= 0x7f80 && E4m3Scale::ok(amax);
+#pragma unroll 1
+        for (int x = 0; x < G::kDmaPerTile; x++) {
+            const uint4 w = piece(x);
+            const uint2 codes = fast ? e4m3_codes8(sc, w) : e4m3_codes8_any(scale, w);
+            if (row_of(x) < rows) *(uint2 *)(page + (int64_t)row_of(x) * a.stride_token_b + byte_of(x) / 2) = codes;
+        }
+        if (ln == 0) (is_v ? a.v_scale : a.k_scale)[(int64_t)pid * a.Hkv + cb.kvh] = scale;
+    };
+    auto open_chunk = [&](int c, int s0) __attribute__((always_inline)) { // s0: the block's stage that the chunk starts with
         if (loader) WaitTail<NSL - 1, DPW>::run(issued - 1 - c);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_s_barrier();
         issue();
+        const int stage = s0 + (wave >> 2);
+        if (stage >= w_lo && stage <= w_hi) write_page(c, stage);
     };
 
-    // The wave's 32-row tile.  Waves w and w + 4 share a SIMD; tiles w and 7 - w have the same work between them
-    // under the causal mask whatever w is.
-    const int T = wave < 4 ? wave : 11 - wave;
+    // The wave's unit of a block: waves w and w + 4 share a SIMD, so the longest and the shortest go together.  Past the
+    // pair's last unit a wave repeats that one and stores nothing.
+    const int order = wave < 4 ? wave : 11 - wave;
+    auto unit_of = [&](const PfBlock &b, int &head, int &tile_q) -> bool {
+        const int units = b.tiles() * a.G;
+        int u = b.u0 + order;
+        const bool own = u < units;
+        u = own ? u : units - 1;
+        const int q = pf_div(u, a.G, a.magic_g);
+        tile_q = b.tiles() - 1 - q;
+        head = b.kvh * a.G + (u - q * a.G);
+        return own;
+    };
     // A lane's part of its query row (a row past the prompt's end reads the prompt's last row instead, and is
     // zeroed by keep_q when the registers are taken into use: nothing writes the registers but the loads themselves,
     // so the compiler has no reason to wait for older loads before them).
-    auto load_q = [&](const PfBlock &b, bf16x8 (&qf)[D / 16]) {
-        int row = b.q0 + kPfRows * T + n;
+    auto load_q = [&](const PfBlock &b, int head, int tile_q, bf16x8 (&qf)[D / 16]) {
+        int row = kPfRows * tile_q + n;
         row = row < b.len ? row : b.len - 1;
 #pragma unroll
-        for (int i = 0; i < D / 16; i++) qf[i] = *(const bf16x8 *)(a.q + ((int64_t)(b.t0 + row) * a.Hq + b.h) * D + 16 * i + 8 * hh);
+        for (int i = 0; i < D / 16; i++) qf[i] = *(const bf16x8 *)(a.q + ((int64_t)(b.t0 + row) * a.Hq + head) * D + 16 * i + 8 * hh);
     };
-    auto keep_q = [&](const PfBlock &b, bf16x8 (&qf)[D / 16]) {
-        const bool ok = b.q0 + kPfRows * T + n < b.len;
+    auto keep_q = [&](const PfBlock &b, int tile_q, bf16x8 (&qf)[D / 16]) {
+        const bool ok = kPfRows * tile_q + n < b.len;
 #pragma unroll
         for (int i = 0; i < D / 16; i++) {
             if (!ok) qf[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
@@ -370,24 +522,24 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     };
     // the wave's staging area behind the ring (32 rows of 128 bytes)
     uint8_t *const stage = lds + NSL * 2 * G::kStage + kPfStageBytes * wave;
-    const uint32_t stage_addr = lds_addr + NSL * 2 * G::kStage + kPfStageBytes * wave;
-    // Query rows come straight from memory, 16 bytes per lane and row.  A workgroup that stays asks for those of the
-    // block after the current one (into qn) when the current block has its first scores, and waits for them when its
-    // last step is done: qn and st.qf change places there.  (The empty asm statements pin the compiler's wait for the
-    // loads to these places; left to the first use it would sit inside a block and wait for younger loads as well.)
+    // Query rows come straight from memory, 16 bytes per lane and row.  Those of the block after the current one are
+    // asked for (into qn) when the current block has its first scores, and waited for when its last step is done: qn and
+    // st.qf change places there.  (The empty asm statements pin the compiler's wait for the loads to these places; left
+    // to the first use it would sit inside a block and wait for younger loads as well.)
     PfState<D> st;
     bf16x8 qn[D / 16];
-    load_q(cb, st.qf);
-    keep_q(cb, st.qf);
+    int head, T;        // of the current block: the wave's head and tile
+    bool own = unit_of(cb, head, T);
+    load_q(cb, head, T, st.qf);
+    keep_q(cb, T, st.qf);
     PfBlock nb;
-    int nturn = cturn + step;
-    bool n_ok = STAY && pf_next_block(a, die, nturn, step, nb);
+    bool n_ok = STAY && pf_next(a, deal, ncur, nb);
     int chunk0 = 0; // number of the current block's first chunk
 
     for (;;) {
-        const int nst = cb.nst, q0 = cb.q0, len = cb.len;
+        const int nst = cb.nst;
         const int stage0 = 2 * chunk0;
-        const int row = q0 + kPfRows * T + n;
+        const int row = kPfRows * T + n;
         st.lsum = 0.f;
 #pragma unroll
         for (int dt = 0; dt < D / 32; dt++) {
@@ -395,10 +547,10 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
             for (int e = 0; e < 16; e++) st.o[dt][e] = 0.f;
         }
         // the stage that holds the tile's diagonal is the last one the wave works on; earlier ones lie wholly below it
-        int last = (q0 >> 5) + T;
-        last = last < nst ? last : nst - 1;
+        const int last = T;
 
-        open_chunk(chunk0);
+        if (a.fused_write) pages_of_block();
+        open_chunk(chunk0, 0);
         pf_scores<D>(lds + (stage0 & (2 * NSL - 1)) * G::kStage, pl, st.qf, st.s);
         if (last == 0) {
 #pragma unroll
@@ -414,26 +566,16 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
             const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
             st.m = max3(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[1])) * a.scale_log2;
         }
-        // A workgroup that has no further block of its own (one workgroup per block: long prompts) cannot ask for the
-        // next block's query rows, and they are the one input no workgroup has touched before, so every block would
-        // start with a trip to HBM.  Such a block therefore touches (one dword per 64-byte line) the query rows of the
-        // block that the same die starts a generation of workgroups later (one per compute unit), which then finds
-        // them in the die's L2.  The dwords go to the wave's staging area (a load into registers would write them at a
-        // time the compiler does not know of).
-        if (n_ok) load_q(nb, qn);
-        const bool touched = !n_ok;
-        if (touched) {
-            PfBlock tb;
-            const bool ok = pf_block_of(a, die, cturn + a.num_cus / 8, tb);
-            const int row2 = tb.q0 + kPfRows * wave + (lane >> 1);
-            const uint16_t *p2 = ok && row2 < tb.len ? a.q + ((int64_t)(tb.t0 + row2) * a.Hq + tb.h) * D + 32 * (lane & 1) : a.q;
-#pragma unroll
-            for (int x = 0; x < D * 2 / 128; x++) dma4(p2 + 64 * x, stage_addr);
+        int nhead = 0, nT = 0;
+        bool nown = false;
+        if (n_ok) {
+            nown = unit_of(nb, nhead, nT);
+            load_q(nb, nhead, nT, qn);
         }
         // every wave keeps the ring going for all the stages; it computes up to its own last stage: full steps, then
         // the step whose new scores cross the diagonal, then the step without new scores
         auto ring = [&](int s) __attribute__((always_inline)) { // before step s
-            if ((s & 1) && s + 1 < nst) open_chunk(chunk0 + ((s + 1) >> 1));
+            if ((s & 1) && s + 1 < nst) open_chunk(chunk0 + ((s + 1) >> 1), s + 1);
         };
 #define PF_STEP(MASK, NEXT)                                                                                                \
     pf_step<D, MASK, NEXT>(st, lds + ((stage0 + s + 1) & (2 * NSL - 1)) * G::kStage,                                       \
@@ -453,18 +595,17 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
         for (s++; s < nst; s++) ring(s);
 #undef PF_STEP
 
-        // the next block's query rows take their place (the staging area is free for the results after that)
-        const PfBlock done = cb;
+        // the next block's query rows take their place
+        const int t0 = cb.t0, len = own ? cb.len : 0, dhead = head, tile_row = kPfRows * T;
         const bool more = n_ok;
         if (more) {
 #pragma unroll
             for (int i = 0; i < D / 16; i++) st.qf[i] = qn[i];
-            keep_q(nb, st.qf);
-            chunk0 += cb.nchunks;
+            keep_q(nb, nT, st.qf);
+            chunk0 += cb.chunks();
             cb = nb;
-            cturn = nturn;
-            nturn = cturn + step;
-            n_ok = STAY && pf_next_block(a, die, nturn, step, nb);
+            head = nhead, T = nT, own = nown;
+            n_ok = STAY && pf_next(a, deal, ncur, nb);
         }
 
         // a row's sum is spread over its two lanes
@@ -474,18 +615,16 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
             l = __uint_as_float(r[0]) + __uint_as_float(r[1]);
         }
         const float inv = 1.0f / l;
-        const int64_t rh = (int64_t)(done.t0 + row) * a.Hq + done.h;
-        // A workgroup that stays sends its results through the wave's staging area, 64 d (128 bytes of every row) at a
-        // time: a lane holds four consecutive d of its own row per accumulator quarter, and storing from there is 32
-        // separate pieces of 16 bytes per instruction, which keeps the compute unit's one memory pipeline busy for
-        // microseconds per block; read back eight lanes to a row, an instruction stores whole 128-byte lines.  (A
-        // workgroup with one long block stores directly: the detour's latency would be the last thing before it ends.)
-        if (STAY && touched) wait_vmcnt<0>(); // the dwords of the touch above land in this area
+        const int64_t rh = (int64_t)(t0 + row) * a.Hq + dhead;
+        // Results go through the wave's staging area, 64 d (128 bytes of every row) at a time: a lane holds four consecutive
+        // d of its own row per accumulator quarter, and storing from there is 32 separate pieces of 16 bytes per
+        // instruction, which keeps the compute unit's one memory pipeline busy for microseconds per block; read back eight
+        // lanes to a row, an instruction stores whole 128-byte lines.
         int sl = lane;
-        if (STAY) asm volatile("" : "+v"(sl));
+        asm volatile("" : "+v"(sl));
         const int sn = sl & 31, sh = sl >> 5;
 #pragma unroll
-        for (int p = 0; p < (STAY ? D / 64 : 0); p++) {
+        for (int p = 0; p < D / 64; p++) {
 #pragma unroll
             for (int dtl = 0; dtl < 2; dtl++) {
 #pragma unroll
@@ -500,28 +639,8 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
             for (int m = 0; m < 4; m++) {
                 const int r = 8 * m + (sl >> 3), c = sl & 7; // row of the tile, 16-byte piece of its 128 bytes
                 const u32x4 v = *(const u32x4 *)(stage + kPfStageRow * r + 16 * (c ^ pf_stage_swz(r)));
-                const int orow = q0 + kPfRows * T + r;
-                if (orow < len) *(u32x4 *)(a.out + ((int64_t)(done.t0 + orow) * a.Hq + done.h) * D + 64 * p + 8 * c) = v;
-            }
-        }
-#pragma unroll
-        for (int dt = 0; dt < (STAY ? 0 : D / 32); dt++) {
-#pragma unroll
-            for (int qp = 0; qp < 2; qp++) {
-                // elements 8 qp .. + 3 are d = 32 dt + 16 qp + 4 hh .. + 3, elements 8 qp + 4 .. + 7 the same 8 further on;
-                // the two lanes of a row trade halves so that each holds eight consecutive d
-                f32x4 lo, hi;
-#pragma unroll
-                for (int x = 0; x < 4; x++) {
-                    lo[x] = st.o[dt][8 * qp + x] * inv;
-                    hi[x] = st.o[dt][8 * qp + 4 + x] * inv;
-                }
-                const bf16x4 blo = __builtin_convertvector(lo, bf16x4), bhi = __builtin_convertvector(hi, bf16x4);
-                const u32x2 wlo = __builtin_bit_cast(u32x2, blo), whi = __builtin_bit_cast(u32x2, bhi);
-                const u32x2 s0 = __builtin_amdgcn_permlane32_swap(wlo[0], whi[0], false, false);
-                const u32x2 s1 = __builtin_amdgcn_permlane32_swap(wlo[1], whi[1], false, false);
-                // lane hh = 0 now has d = 32 dt + 16 qp + 0..7, lane hh = 1 has + 8..15
-                if (row < len) *(u32x4 *)(a.out + rh * D + 32 * dt + 16 * qp + 8 * hh) = u32x4{s0[0], s1[0], s0[1], s1[1]};
+                const int orow = tile_row + r;
+                if (orow < len) *(u32x4 *)(a.out + ((int64_t)(t0 + orow) * a.Hq + dhead) * D + 64 * p + 8 * c) = v;
             }
         }
         if (row < len && hh == 0) a.lse[rh] = (st.m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
@@ -532,6 +651,10 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
 
 // LDS of a prefill workgroup: the ring and the waves' staging areas
 template <int D> constexpr int prefill_lds_bytes() { return kPfSlots * 2 * Geo<D, 2>::kStage + kPfStageBytes * kPfWaves; }
+
+// The attention kernel writes the cache from its ring where a block has few stages to write; with fewer than four query
+// heads per kv head it would be up to eight of them per block (a block is eight units), and the copy kernel below does it.
+bool prefill_writes_cache(const PrefillLaunch &a) { return a.k_pool && a.G >= 4; }
 
 hipError_t prefill_config()
 {
@@ -545,26 +668,32 @@ hipError_t prefill_config()
     return hipSuccess;
 }
 
-hipError_t launch_prefill(const PrefillLaunch &a, hipStream_t s)
+hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
 {
-    const int nqb = (a.max_len + kPfBlock - 1) / kPfBlock;
-    const int64_t pairs = (int64_t)a.num_prompts * a.Hkv; // dealt to eight dies, see the kernel
-    const int64_t turns = ((pairs + 7) / 8) * nqb * a.G;  // blocks of a die
-    if (turns == 0) return hipSuccess;
-    if (turns > INT32_MAX / 16) return hipErrorInvalidValue;
-    // Short prompts (one or two blocks of query rows each): the blocks are alike and a block's start-up is a third of
-    // its time, so the workgroups stay, one per compute unit (the ring takes most of a unit's LDS), and each takes
-    // every (units per die)-th block of its die.  Longer prompts: blocks differ by up to the prompt's length and
-    // start-up is small beside them, so there is one workgroup per block and the hardware hands them out as units
-    // become free (the same kernel: a workgroup that finds no further block of its own ends).
-    int per_die = a.num_cus / 8;
+    PrefillLaunch a = given;
+    a.fused_write = prefill_writes_cache(a);
+    // blocks of a die at most: its kv heads' share of every prompt's
+    const int gg = (a.Hkv & 7) == 0 ? 8 : (a.Hkv & 3) == 0 ? 4 : (a.Hkv & 1) == 0 ? 2 : 1, share = 8 / gg;
+    const int64_t tiles = (int64_t)(a.max_len + kPfBlock - 1) / kPfBlock * (kPfBlock / 32);
+    const int64_t per_pair = (tiles * a.G + 7) / 8;
+    const int64_t blocks = (int64_t)a.num_prompts * (a.Hkv / gg) * ((per_pair + share - 1) / share);
+    if (blocks == 0) return hipSuccess;
+    if (blocks > INT32_MAX / 16 || (int64_t)a.Hq * a.D >= (int64_t)1 << 25) return hipErrorInvalidValue; // (32-bit offsets inside a tile)
+    int64_t per_die = a.num_cus / 8;
     per_die = per_die < 1 ? 1 : per_die;
-    if (a.stay > 0 && a.stay < per_die) per_die = a.stay; // fewer were asked for
-    const bool stay = a.stay < 0 ? nqb <= 2 : a.stay != 0;
-    const bool one_each = !stay || turns <= per_die;
-    if (one_each) per_die = (int)turns;
+    if (a.stay > 0 && a.stay < per_die) per_die = a.stay;    // fewer were asked for
+    if (tiles * a.G * (int64_t)a.G >= (int64_t)1 << 31 || blocks * (a.Hkv / gg) >= (int64_t)1 << 31) return hipErrorInvalidValue; // (pf_div)
+    a.magic_g = (uint32_t)((((uint64_t)1 << 32) + a.G - 1) / a.G);
+    a.magic_heads = (uint32_t)((((uint64_t)1 << 32) + a.Hkv / gg - 1) / (a.Hkv / gg));
+    // Prompts whose blocks are dealt together: few enough for their K and V to stay in a die's 4 MB L2 while the die's
+    // workgroups share them, enough for an even deal of ragged lengths.  Measured with 64, 16, 8 and 4: 121.0, 115.5, 119.9,
+    // 131.3 us on 32 prompts of 512 tokens (seven heads per kv head), 1287, 1289, 1268, 1277 us on 16 of 2048 (eight),
+    // 28.7, 28.7, 28.7, 35.8 us on 8 of 37 to 701.
+    a.group = (int64_t)16 * a.max_len * 4 * a.D * (a.Hkv / gg) <= (4 << 20) ? 16 : 8;
+    const bool one_each = a.stay == 0 || blocks <= per_die;
+    if (one_each) per_die = blocks;
 #define RA_PF_LAUNCH(DD, ST)                                                                                                \
-    hipLaunchKernelGGL((prefill_kernel<DD, ST>), dim3(8u * per_die), dim3(64 * kPfWaves), prefill_lds_bytes<DD>(), s, a)
+    hipLaunchKernelGGL((prefill_kernel<DD, ST>), dim3(8u * (unsigned)per_die), dim3(64 * kPfWaves), prefill_lds_bytes<DD>(), s, a)
     if (a.D == 128) {
         if (one_each) RA_PF_LAUNCH(128, false);
         else RA_PF_LAUNCH(128, true);
@@ -602,27 +731,31 @@ __device__ __forceinline__ void write_tile(const PrefillLaunch &a, const uint16_
         }
         return;
     }
-    float amax = 0.f; // a NaN input does not take part in the maximum
+    uint32_t m = 0;
 #pragma unroll
-    for (int i = 0; i < kIter; i++) {
+    for (int i = 0; i < kIter; i++) m = bf16_mag_max(m, __builtin_bit_cast(uint4, x[i]));
+    m = bf16_mag_reduce(m);
+    float amax = __uint_as_float(m << 16);
+    if (m > 0x7f80) { // a NaN input does not take part in the maximum
+        amax = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf((float)x[i][e]));
+        for (int i = 0; i < kIter; i++) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) amax = fmaxf(amax, fabsf((float)x[i][e]));
+        }
+#pragma unroll
+        for (int sh = 32; sh >= 1; sh >>= 1) amax = fmaxf(amax, __shfl_xor(amax, sh));
     }
-#pragma unroll
-    for (int sh = 32; sh >= 1; sh >>= 1) amax = fmaxf(amax, __shfl_xor(amax, sh));
-    const float sc = amax > 0.f ? amax / 448.0f : 1.0f;
+    const E4m3Scale sc = {amax > 0.f ? amax / 448.0f : 1.0f, 1.0f / (amax > 0.f ? amax / 448.0f : 1.0f)};
+    const bool fast = m <= 0x7f80 && E4m3Scale::ok(amax);
 #pragma unroll
     for (int i = 0; i < kIter; i++) {
         const int u = lane + 64 * i, r = u / kUnits, c = u % kUnits;
-        uint32_t lo = 0, hi = 0;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-            lo |= e4m3_nearest((float)x[i][e] / sc) << (8 * e);
-            hi |= e4m3_nearest((float)x[i][4 + e] / sc) << (8 * e);
-        }
-        if (r < n) *(uint2 *)(dst + (int64_t)r * a.stride_token_b + 8 * c) = make_uint2(lo, hi);
+        const uint4 w = __builtin_bit_cast(uint4, x[i]);
+        const uint2 codes = fast ? e4m3_codes8(sc, w) : e4m3_codes8_any(sc.s, w);
+        if (r < n) *(uint2 *)(dst + (int64_t)r * a.stride_token_b + 8 * c) = codes;
     }
-    if (lane == 0) *scale = sc;
+    if (lane == 0) *scale = sc.s;
 }
 
 template <int D> __global__ __launch_bounds__(64) void prefill_write_kernel(PrefillLaunch a)

@@ -303,3 +303,53 @@ def test_rejected_arguments(dec):
         setattr(d.c, field, old)
     dec.prefill(d.c)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("Hq,Hkv,D", [(3, 3, 128), (8, 4, 64), (12, 4, 128), (8, 2, 128), (10, 2, 64), (21, 3, 128), (16, 1, 64), (48, 6, 128)])
+def test_cache_write_of_every_head_ratio(dec, kv_dtype, Hq, Hkv, D):
+    # written by the attention kernel (four query heads per kv head and more) or by the copy kernel: the same bits.  Values
+    # that a quantiser may treat apart: a page of zeros, signed zeros, scales far below and above the usual range,
+    # magnitudes that differ by 2^40 inside a page, NaN.  (Only the pools are looked at: no output is finite here.)
+    b = workload.build_prefill("pf", Hq, Hkv, D, [1, 31, 32, 33, 0, 300, 47, 129], seed=Hq + D)
+    k, v = bf16_bits_to_f32(b.k).copy(), bf16_bits_to_f32(b.v).copy()
+    c = b.cu_seqlens
+    k[c[5]:c[5] + 16] = 0.0
+    v[c[5] + 16:c[5] + 32] *= np.float32(1e-30)
+    k[c[5] + 32:c[5] + 48] *= np.float32(1e33)
+    v[c[5] + 48:c[5] + 64, :, ::3] *= np.float32(2.0 ** -40)
+    k[c[5] + 64:c[5] + 80, :, 1::2] = -0.0
+    v[c[5] + 81, :, 5] = np.nan
+    v[c[6] + 46, :, 3] = 7.0
+    b.k, b.v = workload.f32_to_bf16_bits(k), workload.f32_to_bf16_bits(v)
+    d = DevicePrefill(b, kv_dtype=kv_dtype)
+    dec.prefill(d.c)
+    torch.cuda.synchronize()
+    kp, vp, ks, vs = expected_pools(b, kv_dtype)
+    view = (lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)) if kv_dtype == "bf16" else (lambda t: t.cpu().numpy())
+    np.testing.assert_array_equal(view(d.k_pool), kp)
+    np.testing.assert_array_equal(view(d.v_pool), vp)
+    if kv_dtype != "bf16":
+        np.testing.assert_array_equal(d.k_scale.cpu().numpy().view(np.uint32), ks.view(np.uint32))
+        np.testing.assert_array_equal(d.v_scale.cpu().numpy().view(np.uint32), vs.view(np.uint32))
+
+
+@pytest.mark.parametrize("Hq,Hkv,D,n,longest", [(14, 2, 64, 150, 70), (6, 3, 128, 70, 40), (16, 1, 64, 3, 700), (5, 1, 128, 1, 1000), (12, 12, 64, 17, 90)])
+def test_deal_of_many_and_of_few_prompts(dec, Hq, Hkv, D, n, longest):
+    # every block of every prompt is taken once: more prompts than a wave has lanes, kv heads that share dies or not,
+    # fewer blocks than workgroups
+    lens = np.random.default_rng(n).integers(0, longest + 1, size=n).tolist()
+    lens[0], lens[-1] = longest, max(1, lens[-1])
+    b = workload.build_prefill("pf", Hq, Hkv, D, lens, seed=n)
+    check_all(dec, b, "%d prompts, Hq=%d Hkv=%d" % (n, Hq, Hkv))
+
+
+def test_a_row_maximum_that_keeps_growing(dec):
+    # the exponent's reference point follows the row maximum from a distance: keys whose scores grow by several powers of two
+    # from stage to stage, past the float range of exp if the point stayed
+    b = workload.build_prefill("pf", 14, 2, 128, [640], seed=3)
+    k, q = bf16_bits_to_f32(b.k).copy(), bf16_bits_to_f32(b.q).copy()
+    k[:] = np.abs(k[:1]) * np.exp2(np.arange(640, dtype=np.float32) / 80.0)[:, None, None]
+    q[:, ::2] = np.abs(q[:, ::2])
+    b.k, b.q = workload.f32_to_bf16_bits(k), workload.f32_to_bf16_bits(q)
+    check_all(dec, b, "growing scores")
