@@ -74,6 +74,33 @@ def test_append_stream_is_bit_exact_and_attention_follows(kvd, Hq, Hkv, D):
     compare(*dp.results(), ref_out, ref_lse, "attention after %d appends (%s)" % (steps, kvd))
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_append_requantises_every_code_at_every_slot(D):
+    """A row that sets a new scale after 0..15 stored rows of arbitrary codes (NaN codes among them, in either sign), from
+    scales of zero, of ordinary size, so small that the new one makes every code zero, and too large or too small for
+    quotients by the reciprocal; rows with infinities and NaN.  The bytes are decided by the definition: no tolerance."""
+    Hkv = 2
+    lens = np.tile(np.arange(16), 8)
+    p = growing_problem("fp8_e4m3", 4, Hkv, D, lens, 1, seed=9)
+    r = np.random.default_rng(5)
+    for pool in (p.k_pool, p.v_pool):
+        pool[...] = r.integers(0, 256, size=pool.shape, dtype=np.uint8)
+    old = np.array([0.0, 1e-3, 1e-3, 1e-3, 1e-12, 1e-30, 1e30, 1e-3], dtype=np.float32)
+    amp = np.array([1.0, 0.5, 0.6, 100.0, 1.0, 1e-20, 3e37, 1.0], dtype=np.float32)  # 448 * old is 0.448 where old is 1e-3
+    kn, vn = (f32_to_bf16_bits(np.clip(r.standard_normal((p.B, Hkv, D)), -4, 4).astype(np.float32) * np.repeat(amp, 16)[:, None, None])
+              for _ in range(2))
+    kn[-16:, 0, 3] = 0x7FC0                                    # a NaN
+    vn[-16:, 1, 5] = 0xFF80                                    # an infinity
+    for b in range(p.B):
+        pg = p.block_table[b, lens[b] // 16]
+        p.k_scale[pg], p.v_scale[pg] = old[b // 16], old[b // 16]
+    dp = DeviceProblem(p)
+    assert oracle.append(p, kn, vn) == 0
+    ra.Decoder(0).append(dp.c, bits_to_bf16(kn, "cuda:0"), bits_to_bf16(vn, "cuda:0"))
+    for got, want, what in zip(pools_of(dp), (p.k_pool, p.v_pool, p.k_scale, p.v_scale), ("K pool", "V pool", "K scales", "V scales")):
+        np.testing.assert_array_equal(got.reshape(want.shape), want, err_msg=what)
+
+
 def test_append_skips_what_it_must_not_write():
     p = growing_problem("bf16", 4, 2, 64, [5, 20, 33], 1, seed=3)
     p.seq_lens[0] = p.block_table.shape[1] * 16      # no room in the table row
