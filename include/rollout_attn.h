@@ -63,7 +63,7 @@ enum {
     RA_FLAG_NO_PREFIX_SHARING = 2u, /* ignore the prompt-group hint (for A/B comparison) */
     RA_FLAG_REUSE_SCHEDULE = 4u     /* skip the schedule (its kernels for a large batch; for a smaller one, which the
                                        attention workgroups plan for themselves, their planning pass: each takes the
-                                       list it kept) and use the schedule that the previous rollout_attn_decode call
+                                       list it kept; the smallest have none) and use the schedule that the previous rollout_attn_decode call
                                        without this flag on the same context left in the same workspace.
                                        For the layers of one decode step: the schedule depends only on B, the head
                                        counts, D, max_pages_per_seq, seq_lens, seq_group, prefix_page_offsets and
@@ -138,7 +138,8 @@ uint32_t rollout_attn_abi_version(void);
  *                                   written in mid-stream (default: 16 for bf16 pools, 48 for e4m3 pools)
  *   ROLLOUT_ATTN_SELF_PLAN=0        always launch the schedule kernels (default: batches of up to 512 sequences and
  *                                   511 groups are scheduled by the attention workgroups themselves, each for its own
- *                                   share of the work, which saves a kernel; the schedule is the same either way)
+ *                                   share of the work, which saves a kernel; the schedule is the same either way; the
+ *                                   smallest batches are split by their table's width, without a schedule)
  *   ROLLOUT_ATTN_PREFILL_WGS_PER_DIE=0..64   prefill: one workgroup per block of query rows (0), or that many
  *                                   per die (at most one per compute unit) that stay and take block after block,
  *                                   loading the next one's inputs under the current one's last keys; default: one
@@ -343,8 +344,8 @@ ra_status rollout_attn_debug_stream_tail(ra_ctx *ctx, const void *buf, size_t bu
 /* Per-kernel timing for benchmarks.  While enabled, rollout_attn_decode records HIP events on its stream
  * around its three phases (schedule, attention, merge); rollout_attn_get_timing waits for the events of the
  * most recent decode call and returns the three durations in milliseconds (schedule: 0 when that call launched
- * no schedule kernel, because its attention workgroups planned their spans themselves or the schedule was
- * reused; the attention phase then starts at the call's first event).  Off by default: the events cost
+ * no schedule kernel, because its attention workgroups planned their spans themselves, the batch was too small to need
+ * a schedule or the schedule was reused; the attention phase then starts at the call's first event).  Off by default: the events cost
  * a little time between kernels.  The numbers are measurements, not part of the result (the decode step is
  * memory-bound, paper Sec. 2.1.1, so the attention phase is the one to watch). */
 ra_status rollout_attn_set_timing(ra_ctx *ctx, int enable);

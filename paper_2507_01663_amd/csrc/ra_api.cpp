@@ -128,6 +128,8 @@ void fill_launch(ra::Launch &a, const ra_ctx *ctx, const ra_problem *p)
     a.out = (uint16_t *)p->out; a.lse = p->lse;
     a.zeros = ctx ? ctx->zeros : nullptr;
     a.self_plan = ctx && ctx->self_plan && ra::can_self_plan(a.D, a.kv_fp8, a.stages, a.B, a.share ? a.num_groups : 0, a.members_per_row);
+    a.splits = ctx ? ra::direct_splits(a.B, a.Hkv, a.D, a.kv_fp8, a.max_pages, ctx->num_cus, a.waves) : 0;
+    if (a.splits) a.self_plan = 1; // (no schedule kernel)
     a.reuse_lists = a.self_plan && (p->flags & RA_FLAG_REUSE_SCHEDULE) != 0;
 }
 
@@ -222,6 +224,7 @@ ra_status rollout_attn_create(ra_ctx **out, int device)
     for (int f = 0; f < 2; f++)
         for (int d = 0; d < 2; d++)
             if (e == hipSuccess) e = ra::attention_config(d ? 128 : 64, f, c->num_cus, &c->stages[f][d], &c->waves[f][d]);
+    if (e == hipSuccess) e = ra::direct_config();
     if (e == hipSuccess) e = ra::prefill_config();
     for (int f = 0; f < 2; f++)
         for (int d = 0; d < 2; d++) {
@@ -320,7 +323,8 @@ static ra_status enqueue_decode(ra_ctx *c, const ra_problem *p, const ra::Launch
     }
     const bool tm = c->timing != 0;
     if (e == hipSuccess && tm) e = hipEventRecord(c->ev[0], s);
-    // no schedule kernel when the batch's tables fit in the attention waves' LDS (they plan their spans themselves)
+    // no schedule kernel when the batch's tables fit in the attention waves' LDS (they plan their spans themselves) or the
+    // batch needs no schedule
     const bool reuse = (p->flags & RA_FLAG_REUSE_SCHEDULE) != 0;
     const bool planned = !reuse && !a.self_plan;
     if (e == hipSuccess && planned) e = ra::launch_plan(a, s);

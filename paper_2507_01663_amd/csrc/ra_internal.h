@@ -60,6 +60,7 @@ struct Launch {
     float *lse;
     const void *zeros;                    // >= 16 bytes of zeros
     int32_t self_plan;                    // the attention waves plan their spans themselves: no schedule kernel
+    int32_t splits;                       // > 0: a small batch, no schedule: workgroups per (sequence, kv head)
     int32_t reuse_lists;                  // ... and take the lists that an earlier call's waves kept in the workspace
     Workspace ws;
 };
@@ -99,6 +100,9 @@ size_t carve_workspace(Workspace &ws, void *base, int B, int Hkv, int G, int D, 
 // launch on the current device, for head dim D: as many as are resident at once (bf16 pools: one per SIMD; e4m3 pools:
 // up to two per SIMD, as many as the ring's LDS lets in).
 hipError_t attention_config(int D, int kv_fp8, int num_cus, int *stages, int *waves);
+// Workgroups per (sequence, kv head) of a batch that is too small to be worth a schedule; 0: it is not.
+int direct_splits(int B, int Hkv, int D, int kv_fp8, int max_pages, int num_cus, int waves);
+hipError_t direct_config(); // once per device, before the first such launch
 // Whether a batch's schedule tables fit in the LDS of an attention wave (then no schedule kernel is needed).
 bool can_self_plan(int D, int kv_fp8, int stages, int B, int num_groups, int members_per_row);
 

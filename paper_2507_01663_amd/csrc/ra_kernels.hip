@@ -1597,8 +1597,179 @@ hipError_t attention_config(int D, int kv_fp8, int num_cus, int *stages, int *wa
     return hipSuccess;
 }
 
+// ------------------------------------------------------------------------------------------------------
+// merge arithmetic, shared by the kernels that add partials up
+// ------------------------------------------------------------------------------------------------------
+
+// Adds up to N partials (the i-th has log2-sum-exp l[i], -inf for none, and output v[i]) to a running (M, wsum, acc).
+template <int N> __device__ __forceinline__ void merge_add(const float (&l)[N], const f32x4 (&v)[N], float &M, float &wsum, f32x4 &acc)
+{
+    float mn = M;
+#pragma unroll
+    for (int i = 0; i < N; i++) mn = fmaxf(mn, l[i]);
+    const float alpha = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn);
+    M = mn;
+    wsum *= alpha;
+    acc *= alpha;
+#pragma unroll
+    for (int i = 0; i < N; i++) {
+        const float wgt = l[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(l[i] - mn);
+        wsum += wgt;
+        acc += wgt * v[i];
+    }
+}
+__device__ __forceinline__ void merge_write(const Launch &a, int64_t bh, int d4, float M, float wsum, f32x4 acc)
+{
+    const bool empty = wsum == 0.f;
+    const float inv = empty ? 0.f : 1.0f / wsum;
+    *(bf16x4 *)(a.out + bh * a.D + d4) = __builtin_convertvector(acc * inv, bf16x4);
+    if (d4 == 0) a.lse[bh] = empty ? -INFINITY : (M + __builtin_amdgcn_logf(wsum)) * 0.6931471805599453f;
+}
+
+// ------------------------------------------------------------------------------------------------------
+// Small batches: no schedule at all.
+//
+// What bounds a small step is the chain of dependent trips, not bytes: planning (7 us: rows, cut, list) and the merge of
+// many short spans (4 to 10 us and a launch) took most of the 33 us of a step over eight sequences of 500 to 2000 tokens.
+// Here a workgroup of four waves takes one (sequence, kv head), or a fixed part of it, straight from the block table: its
+// waves stream equal numbers of stages and meet in LDS.  With one workgroup per item that is the whole step (one kernel);
+// otherwise the workgroups' partials go to the merge kernels like spans do.  The split is by the table's width (the host
+// does not know the lengths), and shared prompt pages are read once per member, from the caches mostly: so this is for
+// batches whose pages take little longer than planning even if every sequence were as long as the table is wide.  With
+// more than a quarter as many items as compute units, one long sequence among short ones has few units: a lower bound.
+// Measured (MI355X, scheduled -> here, us a step): four sequences of up to 256 tokens, D = 64: 15.7 -> 6.5; eight of one
+// prompt, 500 to 2000, D = 128: 33.4 -> 10.7; 256 items of up to 256 tokens, D = 128: 19 -> 7; 1024 items of 32 tokens,
+// D = 128: 20 -> 14, D = 64: 18 -> 8; 8 to 64 items whose table addresses 80 MB: all full 25 to 28 -> 19 (bf16), 28 to 32
+// -> 20 (e4m3), all but one of them short 19 to 22 -> 13 (bf16), 20 to 26 -> 17 (e4m3); 128 MB: 33 to 36 -> 26 and 20 to
+// 25 -> 17 (bf16), but 20 -> 23 where one of 64 e4m3 items is long.
+// ------------------------------------------------------------------------------------------------------
+
+constexpr int kDirectWaves = 4;                  // waves of a workgroup, one per SIMD
+constexpr int kDirectItems = 4;                  // items per compute unit at most (its LDS holds one workgroup or two)
+constexpr int64_t kDirectBytes = (int64_t)32 << 20;    // K and V that the batch's table can address, at most ...
+constexpr int64_t kDirectFewBytes = (int64_t)96 << 20; // ... and where every item has four compute units or more to itself
+constexpr int kDirectStages = 4;                 // stages of a wave up to which an item is not split over workgroups
+
+template <int D, int KVB> struct DirectLds {
+    using M = LdsMap<D, KVB, 2>;
+    static constexpr int kWave = M::kQBase + M::kQTile; // a wave's ring and query slot
+    static constexpr int kBytes = kDirectWaves * kWave;
+    static_assert(kWave % 256 == 0 && kPage * D * 4 + 64 <= M::kQBase, "a wave's partial fits its ring");
+};
+
+template <int D, int KVB>
+__global__ __launch_bounds__(64 * kDirectWaves) void direct_kernel(Launch a, const uint16_t *__restrict__ q,
+                                                                   const int32_t *__restrict__ block_table)
+{
+    using X = DirectLds<D, KVB>;
+    extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    touch_args(a);
+    const int item = blockIdx.x / a.splits, part = blockIdx.x - item * a.splits, b = item / a.Hkv, kvh = item - b * a.Hkv;
+    int L = uniform_load(a.seq_lens, b);
+    L = L < 0 ? 0 : (L > a.max_pages * kPage ? a.max_pages * kPage : L); // never walk past the table row
+    const int n = (L + kPage - 1) / kPage, nst = (n + 1) >> 1;
+    const int k = part * kDirectWaves + wave, all = a.splits * kDirectWaves;
+    uint8_t *const mine = lds + wave * X::kWave;
+    const uint32_t mine_addr = (uint32_t)(uintptr_t)mine;
+    Segment sg;
+    sg.pages = block_table + (int64_t)b * a.max_pages;
+    const int lo = (int)((int64_t)nst * k / all), hi = (int)((int64_t)nst * (k + 1) / all);
+    sg.pg_lo = 2 * lo;
+    sg.pg_hi = 2 * hi < n ? 2 * hi : n;
+    sg.limit = min(L, sg.pg_hi * kPage);
+    sg.kvh = kvh, sg.prefix = 0, sg.b = b, sg.moff = 0, sg.nrows = a.G, sg.slot = 0, sg.mvec = 0;
+    Pending<D> res, none[1];
+    res.lse2 = -INFINITY;
+#pragma unroll
+    for (int dt = 0; dt < D / 16; dt++) res.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (lo < hi) {
+        LaneConst<D, KVB> lc;
+        lane_setup<D, KVB>(lc, lane, a.stride_token_b);
+        Ring ring = {0, 0};
+        issue_q<D, KVB, 2>(a, q, lc, sg, mine_addr, lane);
+        const int id0 = uniform_load(sg.pages, sg.pg_lo), id1 = sg.pg_lo + 1 < sg.pg_hi ? uniform_load(sg.pages, sg.pg_lo + 1) : 0;
+        issue_stage<D, KVB, 2>(a, lc, sg, 0, id0, id1, 0, mine_addr, lane);
+        ring.issued++;
+        run_segment<D, KVB, 1, 2>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane);
+    }
+    // every wave's partial into its own ring (nothing is in flight any more), then the workgroup adds them up
+    {
+        const int row = lane & 15, j = lane >> 4;
+        float *const o = (float *)mine;
+#pragma unroll
+        for (int dt = 0; dt < D / 16; dt++) *(f32x4 *)(o + row * D + 16 * dt + 4 * j) = res.o[dt];
+        if (j == 0) o[kPage * D + row] = res.lse2;
+    }
+    __syncthreads();
+    constexpr int TPR = D / 4;
+    for (int t = threadIdx.x; t < a.G * TPR; t += 64 * kDirectWaves) {
+        const int hl = t / TPR, d4 = (t % TPR) * 4;
+        float l[kDirectWaves], M = -INFINITY, wsum = 0.f;
+        f32x4 v[kDirectWaves], acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < kDirectWaves; w++) {
+            const float *const o = (const float *)(lds + w * X::kWave);
+            l[w] = o[kPage * D + hl];
+            v[w] = *(const f32x4 *)(o + hl * D + d4);
+        }
+        merge_add<kDirectWaves>(l, v, M, wsum, acc);
+        if (a.splits == 1) {
+            merge_write(a, (int64_t)b * a.Hq + kvh * a.G + hl, d4, M, wsum, acc);
+        } else {
+            // (slot item + span with span = item * (splits - 1) + part: see the descriptor below)
+            const int64_t row = ((int64_t)item * a.splits + part) * a.G + hl;
+            *(f32x4 *)(a.ws.suf_o + row * D + d4) = wsum == 0.f ? acc : acc * (1.0f / wsum);
+            if (d4 == 0) a.ws.suf_lse[row] = wsum == 0.f ? -INFINITY : M + __builtin_amdgcn_logf(wsum);
+        }
+    }
+    if (a.splits > 1 && part == 0 && threadIdx.x == 0) {
+        const int first = item * (a.splits - 1);
+        a.ws.merge_desc[2 * item] = make_int4(n, first, first + a.splits - 1, 0);
+        a.ws.merge_desc[2 * item + 1] = make_int4(0, 0, -1, 0);
+    }
+}
+
+int direct_splits(int B, int Hkv, int D, int kv_fp8, int max_pages, int num_cus, int waves)
+{
+    const int64_t items = (int64_t)B * Hkv;
+    if (items < 1 || max_pages < 1) return 0;
+    const int64_t bytes = items * max_pages * (2 * kPage * D * (kv_fp8 ? 1 : 2));
+    if (items > kDirectItems * num_cus || bytes > (4 * items <= num_cus ? kDirectFewBytes : kDirectBytes)) return 0;
+    const int per_wave = ((max_pages + 1) / 2 + kDirectWaves - 1) / kDirectWaves;
+    if (per_wave <= kDirectStages) return 1;
+    int64_t s = num_cus / items;                         // workgroups that run side by side
+    if (s > (per_wave + 1) / 2) s = (per_wave + 1) / 2;  // two stages for a wave
+    if (items * (s - 1) > waves) s = 1 + waves / items;  // what the workspace has room for
+    return s < 1 ? 1 : (int)s;
+}
+
+static hipError_t launch_direct(const Launch &a, hipStream_t s)
+{
+#define RA_DIRECT(DD, KVB) hipLaunchKernelGGL((direct_kernel<DD, KVB>), dim3(a.B * a.Hkv * a.splits), dim3(64 * kDirectWaves), (DirectLds<DD, KVB>::kBytes), s, a, a.q, a.block_table)
+    if (a.D == 128) {
+        if (a.kv_fp8) RA_DIRECT(128, 1);
+        else RA_DIRECT(128, 2);
+    } else {
+        if (a.kv_fp8) RA_DIRECT(64, 1);
+        else RA_DIRECT(64, 2);
+    }
+#undef RA_DIRECT
+    return hipGetLastError();
+}
+
+hipError_t direct_config()
+{
+    hipError_t e = hipFuncSetAttribute((const void *)direct_kernel<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<128, 2>::kBytes);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)direct_kernel<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<128, 1>::kBytes);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)direct_kernel<64, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<64, 2>::kBytes);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)direct_kernel<64, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<64, 1>::kBytes);
+    return e;
+}
+
 hipError_t launch_attention(const Launch &a, hipStream_t s)
 {
+    if (a.splits) return launch_direct(a, s);
     size_t lds = attention_lds_bytes(a.D, a.kv_fp8, a.stages);
     const Workspace &w = a.ws;
 #define RA_LAUNCH(K)                                                                                                      \
@@ -1753,31 +1924,6 @@ __device__ __forceinline__ void merge_lists(const Launch &a, const int4 *__restr
     }
 }
 
-// Adds up to N partials (the i-th has log2-sum-exp l[i], -inf for none, and output v[i]) to a running (M, wsum, acc).
-template <int N> __device__ __forceinline__ void merge_add(const float (&l)[N], const f32x4 (&v)[N], float &M, float &wsum, f32x4 &acc)
-{
-    float mn = M;
-#pragma unroll
-    for (int i = 0; i < N; i++) mn = fmaxf(mn, l[i]);
-    const float alpha = M == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(M - mn);
-    M = mn;
-    wsum *= alpha;
-    acc *= alpha;
-#pragma unroll
-    for (int i = 0; i < N; i++) {
-        const float wgt = l[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(l[i] - mn);
-        wsum += wgt;
-        acc += wgt * v[i];
-    }
-}
-__device__ __forceinline__ void merge_write(const Launch &a, int64_t bh, int d4, float M, float wsum, f32x4 acc)
-{
-    const bool empty = wsum == 0.f;
-    const float inv = empty ? 0.f : 1.0f / wsum;
-    *(bf16x4 *)(a.out + bh * a.D + d4) = __builtin_convertvector(acc * inv, bf16x4);
-    if (d4 == 0) a.lse[bh] = empty ? -INFINITY : (M + __builtin_amdgcn_logf(wsum)) * 0.6931471805599453f;
-}
-
 __global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const int4 *__restrict__ merge_desc,
                                                                const int32_t *__restrict__ seq_pfx_row,
                                                                const int32_t *__restrict__ seq_rank_in_row)
@@ -1880,8 +2026,9 @@ hipError_t launch_merge(const Launch &a, hipStream_t s)
 {
     if (a.B == 0) return hipSuccess;
     const Workspace &w = a.ws;
+    if (a.splits == 1) return hipSuccess; // every item's one workgroup has written its result
     // An item is cut about waves / items times.
-    if (a.waves >= 3 * a.B * a.Hkv)
+    if (a.splits ? a.splits >= 3 : a.waves >= 3 * a.B * a.Hkv)
         hipLaunchKernelGGL(merge_wide_kernel, dim3(a.B * a.Hkv * a.G), dim3(kMergeThreads), 0, s, a, w.merge_desc, w.seq_pfx_row,
                            w.seq_rank_in_row);
     else

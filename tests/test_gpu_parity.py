@@ -589,3 +589,27 @@ def test_merge_of_items_cut_into_many_spans(dec, kvd, Hq, Hkv, D, prompts, R, re
     # (outputs of one to three tokens are as large as single V entries: rounding them to bf16 alone is 2^-9 of that)
     ref_out, ref_lse = oracle.decode(p)
     compare(*run(dec, p).results(), ref_out, ref_lse, "cut", abs_rel=2.0 ** -8)
+
+
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("Hq,Hkv,D,prompts,R,resp", [
+    (8, 2, 64, [0, 16], 4, [0, 1, 15, 16, 17, 32, 33, 100]),   # waves without pages, one page, one stage; a workgroup per item
+    (16, 1, 128, [0], 1, [1]),
+    (28, 4, 128, [48], 8, [0, 5, 100, 300, 464, 700, 701, 1900]),  # several workgroups per item, some of them without pages
+    (8, 4, 128, [0] * 25, 1, [640] * 12 + [1] * 12 + [623]),    # two (bf16), at the bound on the table's bytes ...
+    (8, 4, 128, [0] * 25, 1, [641] * 12 + [1] * 12 + [623]),    # ... and a page past it: scheduled
+    (4, 1, 64, [0], 1, [12000]),                                # one item over as many as there may be
+    (4, 1, 64, [0] * 1024, 1, [127, 128] * 512),                # four items per compute unit
+    (4, 1, 64, [0] * 1025, 1, [127, 128, 0, 1, 33] * 205),      # one more than that: scheduled
+    (2, 2, 128, [0] * 4, 1, [24560, 3, 24576, 70]),             # few items, the table's bytes at their bound (bf16) ...
+    (2, 2, 128, [0] * 4, 1, [24560, 3, 24577, 70]),             # ... and a page past it: scheduled
+    (8, 4, 64, [0] * 16, 1, [3000, 1, 0, 900] * 4),             # the most items that count as few ...
+    (8, 4, 64, [0] * 17, 1, [5000, 1, 0, 900] * 4 + [7]),       # ... and more of them: scheduled
+])
+def test_small_batches_without_a_schedule(dec, kvd, Hq, Hkv, D, prompts, R, resp):
+    from gpu_util import compare
+    p = workload.build_problem("small", Hq, Hkv, D, prompts, R, resp, kv_dtype=kvd, seed=37)
+    log("case", Hq, Hkv, D, R, resp[:3], kvd)
+    # (outputs of one to three tokens are as large as single V entries: rounding them to bf16 alone is 2^-9 of that)
+    ref_out, ref_lse = oracle.decode(p)
+    compare(*run(dec, p).results(), ref_out, ref_lse, "small", abs_rel=2.0 ** -8)
