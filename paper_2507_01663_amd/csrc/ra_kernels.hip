@@ -2011,10 +2011,11 @@ __global__ __launch_bounds__(kMergeThreads) void merge_wide_kernel(Launch a, con
     if (d4 == 0) s_m[me] = M, s_w[me] = wsum;
     __syncthreads();
     if (me != 0) return;
+    const int used = total < lanes ? total : lanes; // (lanes that had a partial; a batch in a wide table has few)
     float Mt = -INFINITY, wt = 0.f;
     f32x4 at = {0.f, 0.f, 0.f, 0.f};
-    for (int k = 0; k < lanes; k++) Mt = fmaxf(Mt, s_m[k]);
-    for (int k = 0; k < lanes; k++) {
+    for (int k = 0; k < used; k++) Mt = fmaxf(Mt, s_m[k]);
+    for (int k = 0; k < used; k++) {
         const float wgt = s_m[k] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(s_m[k] - Mt);
         wt += wgt * s_w[k];
         at += wgt * s_acc[k * tpr + threadIdx.x];
@@ -2022,13 +2023,20 @@ __global__ __launch_bounds__(kMergeThreads) void merge_wide_kernel(Launch a, con
     merge_write(a, (int64_t)b * a.Hq + kvh * a.G + hl, d4, Mt, wt, at);
 }
 
+constexpr int kMergeWideMax = 512; // workgroups of merge_wide_kernel, at most
+
 hipError_t launch_merge(const Launch &a, hipStream_t s)
 {
     if (a.B == 0) return hipSuccess;
     const Workspace &w = a.ws;
     if (a.splits == 1) return hipSuccess; // every item's one workgroup has written its result
-    // An item is cut about waves / items times.
-    if (a.splits ? a.splits >= 3 : a.waves >= 3 * a.B * a.Hkv)
+    // An item is cut about waves / items times (split exactly a.splits times in a small batch); four own partials are one
+    // trip of the kernel that takes an item per workgroup.  The one that takes a head per workgroup pays while those are
+    // few: 256 of them (128 items of 2 heads, D = 64, 5000 tokens) 28.2 -> 27.5 us a step, 448 (64 items of 7, D = 128) 20.5
+    // -> 20.1 at 1500 tokens and 31.1 -> 28.3 at 5000, but 18.9 -> 19.2 at 250; 896 (128 items of 7) 18.9 -> 19.4 at 250 and
+    // 45.2 -> 45.0 at 5000; 2560 (512 items of 5, e4m3) 20.3 -> 24.2 and 80.7 -> 92.8.
+    const int64_t items = (int64_t)a.B * a.Hkv;
+    if (items * a.G <= kMergeWideMax && (a.splits ? a.splits > 4 : a.waves >= 3 * items))
         hipLaunchKernelGGL(merge_wide_kernel, dim3(a.B * a.Hkv * a.G), dim3(kMergeThreads), 0, s, a, w.merge_desc, w.seq_pfx_row,
                            w.seq_rank_in_row);
     else
