@@ -136,10 +136,13 @@ uint32_t rollout_attn_abi_version(void);
  *                                   of a segment (a page of a sequence's own weighs 4)
  *   ROLLOUT_ATTN_COST_ITEM_PREFIX=0..1024   ... of a segment of shared-prefix pages, whose partial result is
  *                                   written in mid-stream (default: 16 for bf16 pools, 48 for e4m3 pools)
- *   ROLLOUT_ATTN_SELF_PLAN=0        always launch the schedule kernels (default: batches of up to 512 sequences and
- *                                   511 groups are scheduled by the attention workgroups themselves, each for its own
- *                                   share of the work, which saves a kernel; the schedule is the same either way; the
- *                                   smallest batches are split by their table's width, without a schedule)
+ *   ROLLOUT_ATTN_DIRECT=0           every batch has a schedule (default: the smallest batches, by what their block
+ *                                   table can address, are split by the table's width instead)
+ *   ROLLOUT_ATTN_SELF_PLAN=0        a batch that has a schedule gets it from the schedule kernels (default: batches of
+ *                                   up to 512 sequences and 511 groups are scheduled by the attention workgroups
+ *                                   themselves, each for its own share of the work, which saves a kernel; the schedule
+ *                                   is the same either way).  With ROLLOUT_ATTN_DIRECT=0 too, every batch is scheduled
+ *                                   by the kernels
  *   ROLLOUT_ATTN_PREFILL_WGS_PER_DIE=0..64   prefill: one workgroup per block of query rows (0), or that many
  *                                   per die (at most one per compute unit) that stay and take block after block,
  *                                   loading the next one's inputs under the current one's last keys; default: one

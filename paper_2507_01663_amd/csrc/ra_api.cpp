@@ -29,6 +29,7 @@ struct ra_ctx {
     int prefill_stay;          // -1: one prefill workgroup per compute unit; else ROLLOUT_ATTN_PREFILL_WGS_PER_DIE
     void *zeros;  // 256 bytes of zeros on the device
     int self_plan; // attention waves may plan their spans themselves (no schedule kernel)
+    int direct;    // the smallest batches may go without a schedule
     int32_t *host_flags; // pinned, for RA_FLAG_VALIDATE
     int timing;          // record events around the phases
     int timed;           // a decode call has recorded them (2: with a schedule launch between the first two)
@@ -128,7 +129,7 @@ void fill_launch(ra::Launch &a, const ra_ctx *ctx, const ra_problem *p)
     a.out = (uint16_t *)p->out; a.lse = p->lse;
     a.zeros = ctx ? ctx->zeros : nullptr;
     a.self_plan = ctx && ctx->self_plan && ra::can_self_plan(a.D, a.kv_fp8, a.stages, a.B, a.share ? a.num_groups : 0, a.members_per_row);
-    a.splits = ctx ? ra::direct_splits(a.B, a.Hkv, a.D, a.kv_fp8, a.max_pages, ctx->num_cus, a.waves) : 0;
+    a.splits = ctx && ctx->direct ? ra::direct_splits(a.B, a.Hkv, a.D, a.kv_fp8, a.max_pages, ctx->num_cus, a.waves) : 0;
     if (a.splits) a.self_plan = 1; // (no schedule kernel)
     a.reuse_lists = a.self_plan && (p->flags & RA_FLAG_REUSE_SCHEDULE) != 0;
 }
@@ -197,6 +198,8 @@ ra_status rollout_attn_create(ra_ctx **out, int device)
     }
     c->self_plan = 1;
     if (const char *ev = getenv("ROLLOUT_ATTN_SELF_PLAN")) c->self_plan = atoi(ev) != 0;
+    c->direct = 1;
+    if (const char *ev = getenv("ROLLOUT_ATTN_DIRECT")) c->direct = atoi(ev) != 0;
     if (const char *ev = getenv("ROLLOUT_ATTN_COST_PREFIX")) {
         int v = atoi(ev);
         if (v >= 1 && v <= 16) c->cost_prefix[0] = c->cost_prefix[1] = v;

@@ -1,11 +1,44 @@
 """Helpers for the GPU tests: upload a workload.Problem, run the HIP library through its C ABI, compare."""
+import os
+
 import numpy as np
 
+import paper_2507_01663_amd as ra
 from paper_2507_01663_amd.torch_util import DeviceProblem, bits_to_bf16  # noqa: F401  (the tests import them from here)
 
 ABS_TOL = 1e-2      # max |out_gpu - out_ref| over all elements
 REL_TOL = 1e-2      # per (b, h) row: ||out_gpu - out_ref||_2 / ||out_ref||_2
 LSE_TOL = 1e-3      # |lse_gpu - lse_ref|
+
+
+def context(**env):
+    """A Decoder made with these environment settings (they are read when the context is made, and nowhere else)."""
+    names = {k: "ROLLOUT_ATTN_" + k for k in env}
+    old = {k: os.environ.get(n) for k, n in names.items()}
+    for k, n in names.items():
+        os.environ[n] = str(env[k])
+    try:
+        d = ra.Decoder(0)
+    finally:
+        for k, n in names.items():
+            if old[k] is None:
+                os.environ.pop(n, None)
+            else:
+                os.environ[n] = old[k]
+    d.settings = dict(env)
+    return d
+
+
+def scheduled(dec, p):
+    """Whether a decode step of this problem has a schedule (the smallest batches have none), by the library's own rule:
+    the function is no entry point of the C ABI, so it is called by the name the compiler gave it."""
+    if str(getattr(dec, "settings", {}).get("DIRECT", 1)) == "0":
+        return True
+    fp8 = p.kv_dtype != "bf16"
+    waves = ra.rollout_attn_wave_count(dec.ctx, ra.RA_KV_FP8_E4M3 if fp8 else ra.RA_KV_BF16, p.D)
+    import torch
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return ra.load_library()._ZN2ra13direct_splitsEiiiiiii(p.B, p.Hkv, p.D, int(fp8), p.block_table.shape[1], cus, waves) == 0
 
 
 def compare(out, lse, ref_out, ref_lse, what="", abs_rel=0.0):

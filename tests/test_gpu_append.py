@@ -10,7 +10,7 @@ import oracle
 import paper_2507_01663_amd as ra
 import workload
 from workload.gen import build_problem, f32_to_bf16_bits
-from gpu_util import DeviceProblem, compare, bits_to_bf16
+from gpu_util import DeviceProblem, bits_to_bf16, compare, context, scheduled
 
 pytestmark = pytest.mark.gpu
 
@@ -68,10 +68,14 @@ def test_append_stream_is_bit_exact_and_attention_follows(kvd, Hq, Hkv, D):
             if ks is not None:
                 np.testing.assert_array_equal(ks, p.k_scale, err_msg="K scales after step %d" % t)
                 np.testing.assert_array_equal(vs, p.v_scale, err_msg="V scales after step %d" % t)
-    # the cache the library wrote serves the library's attention, checked against the oracle on the oracle's cache
-    dec.decode(dp.c)
+    # the cache the library wrote serves the library's attention, checked against the oracle on the oracle's cache: as the
+    # library takes this batch, without a schedule, and scheduled
     ref_out, ref_lse = oracle.decode(p)
-    compare(*dp.results(), ref_out, ref_lse, "attention after %d appends (%s)" % (steps, kvd))
+    assert not scheduled(dec, p)
+    for d in (dec, context(DIRECT=0)):
+        dp.out.fill_(float("nan"))
+        d.decode(dp.c)
+        compare(*dp.results(), ref_out, ref_lse, "attention after %d appends (%s)" % (steps, kvd))
 
 
 @pytest.mark.parametrize("D", [64, 128])

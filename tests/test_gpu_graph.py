@@ -8,15 +8,15 @@ import torch
 
 import oracle
 import workload
-from gpu_util import DeviceProblem, bits_to_bf16, compare
+from gpu_util import DeviceProblem, bits_to_bf16, compare, scheduled
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.fixture(scope="module")
-def dec():
-    import paper_2507_01663_amd as ra
-    d = ra.Decoder(0)
+@pytest.fixture(scope="module", params=["the library's choice", "every batch scheduled"])
+def dec(request):
+    from gpu_util import context
+    d = context() if request.param == "the library's choice" else context(DIRECT=0)
     yield d
     d.close()
 
@@ -34,6 +34,7 @@ def capture(fn):
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
 def test_decode_step_replayed_from_a_graph(dec, kv_dtype):
     p = workload.make_problem("mid7b", seed=3, kv_dtype=kv_dtype)
+    assert scheduled(dec, p) or (kv_dtype != "bf16" and dec.settings == {})  # (e4m3: small enough to go without one)
     dp = DeviceProblem(p)
     dec.decode(dp.c)                       # the decoder's workspace exists before the capture
     torch.cuda.synchronize()

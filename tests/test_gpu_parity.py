@@ -15,11 +15,27 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.fixture(scope="module")
-def dec():
-    import paper_2507_01663_amd as ra
-    d = ra.Decoder(0)
+def dec_default():
+    from gpu_util import context
+    d = context()
     yield d
     d.close()
+
+
+@pytest.fixture(scope="module")
+def dec_planned():
+    """A context that schedules every batch, the small ones too; those of up to 512 sequences in the attention waves."""
+    from gpu_util import context
+    d = context(DIRECT=0)
+    yield d
+    d.close()
+
+
+@pytest.fixture(scope="module", params=["the library's choice", "every batch scheduled"])
+def dec(request, dec_default, dec_planned):
+    """The smallest batches take a path without a schedule unless that is switched off.  Most batches of this file are
+    small, and several are here for what the schedule does with them: every test runs both ways."""
+    return dec_default if request.param == "the library's choice" else dec_planned
 
 
 def run(dec, p, flags=0, use_hint=True):
@@ -168,33 +184,52 @@ def test_batch_beyond_the_schedules_lds_tables(dec):
 def dec_sched():
     """A context that always launches the schedule kernels (the path of batches too large for the attention waves to
     plan for themselves); the setting is read when the context is made."""
-    import os
-    import paper_2507_01663_amd as ra
-    old = os.environ.get("ROLLOUT_ATTN_SELF_PLAN")
-    os.environ["ROLLOUT_ATTN_SELF_PLAN"] = "0"
-    try:
-        d = ra.Decoder(0)
-    finally:
-        if old is None:
-            os.environ.pop("ROLLOUT_ATTN_SELF_PLAN", None)
-        else:
-            os.environ["ROLLOUT_ATTN_SELF_PLAN"] = old
+    from gpu_util import context
+    d = context(SELF_PLAN=0, DIRECT=0)
     yield d
     d.close()
 
 
 @pytest.mark.parametrize("name,kv", [("tiny", "bf16"), ("mid7b", "bf16"), ("mid32b", "fp8_e4m3"), ("mid72b", "bf16"), ("grpo7b", "bf16")])
-def test_parity_with_the_schedule_kernels(dec_sched, dec, name, kv):
-    """Small batches normally take the path where every attention wave plans its own span; the same batches through
-    the schedule kernels must give the same answer within tolerance (the spans are the same, so in fact the same bytes)."""
-    from gpu_util import compare
+def test_parity_with_the_schedule_kernels(dec_sched, dec_planned, name, kv):
+    """Batches of up to 512 sequences that have a schedule take the path where every attention wave plans its own span; the
+    same batches through the schedule kernels must give the same answer within tolerance (the spans are the same, so in
+    fact the same bytes)."""
+    from gpu_util import compare, scheduled
     p = workload.make_problem(name, seed=0, kv_dtype=kv)
+    assert scheduled(dec_sched, p) and scheduled(dec_planned, p)
     ref = oracle.decode(p)
     a = run(dec_sched, p)
     compare(*a.results(), *ref, "%s %s (schedule kernels)" % (name, kv))
-    b = run(dec, p)
+    b = run(dec_planned, p)
     torch.cuda.synchronize()
     assert torch.equal(a.out.view(torch.int16), b.out.view(torch.int16)) and torch.equal(a.lse, b.lse)
+
+
+@pytest.mark.parametrize("name,kv", [("tiny", "bf16"), ("midd64", "fp8_e4m3"), ("mid32b", "fp8_e4m3")])
+def test_the_path_without_a_schedule_can_be_switched_off(dec_default, dec_planned, dec_sched, name, kv):
+    """ROLLOUT_ATTN_DIRECT=0: the smallest batches are scheduled like any other, by the kernels (then there is a schedule
+    phase) or in the attention waves, to the same bytes; reusing the schedule gives those bytes again."""
+    import paper_2507_01663_amd as ra
+    from gpu_util import compare, scheduled
+    p = workload.make_problem(name, seed=0, kv_dtype=kv)
+    assert not scheduled(dec_default, p)
+    ref = oracle.decode(p)
+    compare(*run(dec_default, p).results(), *ref, "%s %s without a schedule" % (name, kv))
+    got = []
+    for d, kernels in ((dec_sched, True), (dec_planned, False)):
+        ra.rollout_attn_set_timing(d.ctx, True)
+        try:
+            got.append(run(d, p))
+            ms = ra.rollout_attn_get_timing(d.ctx)
+        finally:
+            ra.rollout_attn_set_timing(d.ctx, False)
+        assert (ms[0] > 0) == kernels, (d.settings, ms)
+        got.append(run(d, p, flags=ra.RA_FLAG_REUSE_SCHEDULE))
+    compare(*got[0].results(), *ref, "%s %s scheduled" % (name, kv))
+    torch.cuda.synchronize()
+    for other in got[1:]:
+        assert torch.equal(got[0].out.view(torch.int16), other.out.view(torch.int16)) and torch.equal(got[0].lse, other.lse)
 
 
 def test_phase_timing_reports_only_the_launches_made(dec_sched, dec):
@@ -221,17 +256,8 @@ def test_phase_timing_reports_only_the_launches_made(dec_sched, dec):
 @pytest.fixture(scope="module")
 def dec_few_waves():
     """A context with one attention workgroup per compute unit instead of four: four times longer spans."""
-    import os
-    import paper_2507_01663_amd as ra
-    old = os.environ.get("ROLLOUT_ATTN_WAVES_PER_CU")
-    os.environ["ROLLOUT_ATTN_WAVES_PER_CU"] = "1"
-    try:
-        d = ra.Decoder(0)
-    finally:
-        if old is None:
-            os.environ.pop("ROLLOUT_ATTN_WAVES_PER_CU", None)
-        else:
-            os.environ["ROLLOUT_ATTN_WAVES_PER_CU"] = old
+    from gpu_util import context
+    d = context(WAVES_PER_CU=1, DIRECT=0)
     yield d
     d.close()
 
@@ -393,40 +419,40 @@ def test_workspace_too_small_and_bad_arguments(dec):
     assert torch.isnan(dp.out.float()).all()
 
 
-def test_full_size_grpo7b_against_oracle(dec):
+def test_full_size_grpo7b_against_oracle(dec_default):
     """The benchmark workload at full size, every row (the oracle needs about a second for it)."""
     from gpu_util import compare
     p = workload.make_problem("grpo7b", seed=0)
     log("grpo7b: kv tokens", p.kv_tokens(), "pages", p.num_pages)
     ref_out, ref_lse = oracle.decode(p)
-    dp = run(dec, p)
+    dp = run(dec_default, p)
     errs = compare(*dp.results(), ref_out, ref_lse, "grpo7b")
     log("grpo7b abs %.2e rel %.2e lse %.2e" % errs)
-    dp2 = run(dec, p, use_hint=False)
+    dp2 = run(dec_default, p, use_hint=False)
     compare(*dp2.results(), ref_out, ref_lse, "grpo7b no hint")
 
 
-def test_full_size_grpo7b_fp8_against_oracle(dec):
+def test_full_size_grpo7b_fp8_against_oracle(dec_default):
     from gpu_util import compare
     p = workload.make_problem("grpo7b", seed=0, kv_dtype="fp8_e4m3")
     ref_out, ref_lse = oracle.decode(p)
-    errs = compare(*run(dec, p).results(), ref_out, ref_lse, "grpo7b fp8")
+    errs = compare(*run(dec_default, p).results(), ref_out, ref_lse, "grpo7b fp8")
     log("grpo7b fp8 abs %.2e rel %.2e lse %.2e" % errs)
 
 
-def test_full_size_tail32b_against_oracle(dec):
+def test_full_size_tail32b_against_oracle(dec_default):
     """32B-shaped long-tail batch at full size (B=512, lognormal lengths up to 17408 tokens): every (b, h) row."""
     from gpu_util import compare
     p = workload.make_problem("tail32b", seed=0)
     log("tail32b: kv tokens", p.kv_tokens(), "pages", p.num_pages, "max len", int(p.seq_lens.max()))
     ref_out, ref_lse = oracle.decode(p)
     log("tail32b: oracle done")
-    dp = run(dec, p)
+    dp = run(dec_default, p)
     errs = compare(*dp.results(), ref_out, ref_lse, "tail32b")
     log("tail32b %d rows: abs %.2e rel %.2e lse %.2e" % ((p.B * p.Hq,) + errs))
 
 
-def test_full_size_stream72b_steps(dec):
+def test_full_size_stream72b_steps(dec_default):
     """72B-shaped streaming batch at full size: static pool, lengths advance and the block table is re-drawn every
     step; every (b, h) row of steps 0, 1, 31 and 63 is checked."""
     from gpu_util import DeviceProblem, bits_to_bf16, compare
@@ -456,7 +482,7 @@ def test_full_size_stream72b_steps(dec):
             dp.out.fill_(float("nan"))
             dp.set()
             p.block_table, p.max_pages_per_seq = bt, width
-        dec.decode(dp.c)
+        dec_default.decode(dp.c)
         out, lse = dp.results()
         log("stream72b step %d: GPU done, oracle over all %d rows ..." % (step, p.B * p.Hq))
         ref_out, ref_lse = oracle.decode(p)
@@ -485,11 +511,12 @@ def test_schedule_reused_for_another_layer(dec):
     compare(*d2.results(), *oracle.decode(p2), "layer 2 on layer 1's schedule")
 
 
-@pytest.mark.parametrize("which", ["self-planned", "schedule kernels", "few waves"])
-def test_random_batches_against_the_oracle(dec, dec_sched, dec_few_waves, which):
+@pytest.mark.parametrize("which", ["self-planned", "schedule kernels", "few waves", "the library's choice"])
+def test_random_batches_against_the_oracle(dec_default, dec_planned, dec_sched, dec_few_waves, which):
     """Seeded random shapes: head counts, head dim, group sizes, prompts that are not whole pages, empty and one-token
     responses beside long ones, relabelled and missing group ids, both pool types, hint on and off, and a second call on
-    the first one's schedule.  Every element against the oracle, on each of the schedule's three paths.
+    the first one's schedule.  Every element against the oracle, on each of the schedule's three paths and on the path
+    that the library takes of its own accord (which for most of these batches is the one without a schedule).
     Sequences of one to three tokens do not average: their outputs are as large as single V entries (up to about 4.5
     with N(0,1) values), where the two bf16 roundings of the arithmetic (the weights, with the e4m3 scale folded in,
     and the output itself, 2^-9 relative each) already exceed 1e-2 absolute; the element-wise bound is therefore
@@ -497,8 +524,8 @@ def test_random_batches_against_the_oracle(dec, dec_sched, dec_few_waves, which)
     import paper_2507_01663_amd as ra
     from gpu_util import compare
     ulp = 2.0 ** -8
-    d = {"self-planned": dec, "schedule kernels": dec_sched, "few waves": dec_few_waves}[which]
-    rng = np.random.default_rng({"self-planned": 101, "schedule kernels": 202, "few waves": 303}[which])
+    d = {"self-planned": dec_planned, "schedule kernels": dec_sched, "few waves": dec_few_waves, "the library's choice": dec_default}[which]
+    rng = np.random.default_rng({"self-planned": 101, "schedule kernels": 202, "few waves": 303, "the library's choice": 404}[which])
     for case in range(10):
         Hkv = int(rng.choice([1, 2, 4, 8]))
         G = int(rng.choice([1, 2, 3, 4, 5, 7, 8, 16]))
@@ -523,14 +550,15 @@ def test_random_batches_against_the_oracle(dec, dec_sched, dec_few_waves, which)
         compare(*run(d, p, use_hint=False).results(), *ref, what + ", no hint", abs_rel=ulp)
 
 
-@pytest.mark.parametrize("which", ["self-planned", "schedule kernels", "few waves"])
-def test_reused_schedule_gives_the_same_bytes(dec, dec_sched, dec_few_waves, which):
+@pytest.mark.parametrize("which", ["self-planned", "schedule kernels", "few waves", "the library's choice"])
+def test_reused_schedule_gives_the_same_bytes(dec_default, dec_planned, dec_sched, dec_few_waves, which):
     """A call that reuses the schedule (RA_FLAG_REUSE_SCHEDULE) streams exactly the spans of the call that made it:
     the same problem with and without the flag must give the same bytes, whether the schedule came from the schedule
     kernels, from attention waves that kept their lists, or from waves whose spans did not fit one list (those plan
     again).  bf16 and e4m3 pools; after a call on another batch the flag must not be used, and is not here."""
     import paper_2507_01663_amd as ra
-    d = {"self-planned": dec, "schedule kernels": dec_sched, "few waves": dec_few_waves}[which]
+    from gpu_util import scheduled
+    d = {"self-planned": dec_planned, "schedule kernels": dec_sched, "few waves": dec_few_waves, "the library's choice": dec_default}[which]
     cases = [workload.make_problem("mid7b", seed=2), workload.make_problem("mid32b", seed=2, kv_dtype="fp8_e4m3"),
              workload.make_problem("grpo7b", seed=1)]
     if which == "few waves":
@@ -539,6 +567,7 @@ def test_reused_schedule_gives_the_same_bytes(dec, dec_sched, dec_few_waves, whi
         resp[::70] = 111000
         cases.append(workload.build_problem("fragments", 4, 4, 128, [16] * 6, 70, resp, seed=31))
     for p in cases:
+        assert scheduled(d, p) or which == "the library's choice", p.name
         plain = run(d, p)
         again = run(d, p, flags=ra.RA_FLAG_REUSE_SCHEDULE)
         third = run(d, p, flags=ra.RA_FLAG_REUSE_SCHEDULE)
@@ -548,12 +577,15 @@ def test_reused_schedule_gives_the_same_bytes(dec, dec_sched, dec_few_waves, whi
         assert bool(torch.isfinite(plain.lse[torch.from_numpy(p.seq_lens > 0).to(plain.lse.device)]).all())
 
 
-def test_wave_weights_move_work_not_results(dec):
+def test_wave_weights_move_work_not_results():
     """The shares of the page stream that the attention workgroups get can be set per workgroup; any weights give the
-    same answer within tolerance, and the same weights the same bytes."""
+    same answer within tolerance, and the same weights the same bytes.  (A context of its own: the weights it ends with
+    are not the ones a context starts with.)"""
     import paper_2507_01663_amd as ra
-    from gpu_util import compare
+    from gpu_util import compare, context, scheduled
+    dec = context()
     p = workload.make_problem("mid7b", seed=4)
+    assert scheduled(dec, p)
     ref = oracle.decode(p)
     n = ra.rollout_attn_wave_count(dec.ctx, ra.RA_KV_BF16, p.D)
     assert n > 0 and n % 8 == 0
@@ -570,7 +602,7 @@ def test_wave_weights_move_work_not_results(dec):
         with pytest.raises(ra.RolloutAttnError):
             ra.rollout_attn_set_wave_weights(dec.ctx, np.full(n - 1, 1000), ra.RA_KV_BF16, p.D)
     finally:
-        ra.rollout_attn_set_wave_weights(dec.ctx, np.full(n, 1000), ra.RA_KV_BF16, p.D)
+        dec.close()
 
 
 @pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
@@ -583,9 +615,11 @@ def test_wave_weights_move_work_not_results(dec):
     (8, 4, 64, [0] * 129, 1, [33] * 128 + [9000]),
 ])
 def test_merge_of_items_cut_into_many_spans(dec, kvd, Hq, Hkv, D, prompts, R, resp):
-    from gpu_util import compare
+    from gpu_util import compare, scheduled
     p = workload.build_problem("cut", Hq, Hkv, D, prompts, R, resp, kv_dtype=kvd, seed=31)
-    log("case", Hq, Hkv, D, R, resp[:3], kvd)
+    log("case", Hq, Hkv, D, R, resp[:3], kvd, "scheduled" if scheduled(dec, p) else "no schedule")
+    # (the rows of few items are scheduled only where that is asked for; the last two always are)
+    assert scheduled(dec, p) or (dec.settings == {} and p.B < 129)
     # (outputs of one to three tokens are as large as single V entries: rounding them to bf16 alone is 2^-9 of that)
     ref_out, ref_lse = oracle.decode(p)
     compare(*run(dec, p).results(), ref_out, ref_lse, "cut", abs_rel=2.0 ** -8)
@@ -606,10 +640,13 @@ def test_merge_of_items_cut_into_many_spans(dec, kvd, Hq, Hkv, D, prompts, R, re
     (8, 4, 64, [0] * 16, 1, [3000, 1, 0, 900] * 4),             # the most items that count as few ...
     (8, 4, 64, [0] * 17, 1, [5000, 1, 0, 900] * 4 + [7]),       # ... and more of them: scheduled
 ])
-def test_small_batches_without_a_schedule(dec, kvd, Hq, Hkv, D, prompts, R, resp):
-    from gpu_util import compare
+def test_small_batches_without_a_schedule(dec_default, kvd, Hq, Hkv, D, prompts, R, resp):
+    from gpu_util import compare, scheduled
+    dec = dec_default
     p = workload.build_problem("small", Hq, Hkv, D, prompts, R, resp, kv_dtype=kvd, seed=37)
     log("case", Hq, Hkv, D, R, resp[:3], kvd)
+    # the rows said to be scheduled are, in e4m3 (half the bytes) those two that are beyond the bound there as well
+    assert scheduled(dec, p) == (p.B in (17, 1025) or (kvd == "bf16" and max(resp) in (641, 24577)))
     # (outputs of one to three tokens are as large as single V entries: rounding them to bf16 alone is 2^-9 of that)
     ref_out, ref_lse = oracle.decode(p)
     compare(*run(dec, p).results(), ref_out, ref_lse, "small", abs_rel=2.0 ** -8)

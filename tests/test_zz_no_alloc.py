@@ -9,13 +9,14 @@ import torch
 import oracle
 import paper_2507_01663_amd as ra
 import workload
-from gpu_util import DeviceProblem, compare
+from gpu_util import DeviceProblem, compare, context
 
 pytestmark = pytest.mark.gpu
 
 
-def test_static_workspace_entry_point_matches_the_workspace_one():
-    dec = ra.Decoder(0)
+@pytest.mark.parametrize("settings", [{}, {"DIRECT": 0}], ids=["the library's choice", "every batch scheduled"])
+def test_static_workspace_entry_point_matches_the_workspace_one(settings):
+    dec = context(**settings)
     try:
         for name, kv in (("mid7b", "bf16"), ("tiny", "bf16"), ("mid32b", "fp8_e4m3"), ("tiny", "fp8_e4m3")):
             p = workload.make_problem(name, seed=3, kv_dtype=kv)
