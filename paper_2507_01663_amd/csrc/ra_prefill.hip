@@ -259,7 +259,7 @@ struct PfCursor {
 };
 
 struct PfDeal {
-    int lane, wg, wgs, gg_shift, heads, s_shift, share, limit; // see pf_deal
+    int lane, wg, wgs, gg_shift, heads, s_shift, share; // see pf_deal
 };
 
 __device__ __forceinline__ PfDeal pf_deal(const PrefillLaunch &a)
@@ -273,12 +273,17 @@ __device__ __forceinline__ PfDeal pf_deal(const PrefillLaunch &a)
     d.heads = a.Hkv >> d.gg_shift;
     d.s_shift = 3 - d.gg_shift;
     d.share = die >> d.gg_shift;
-    d.limit = (a.max_len + kPfBlock - 1) / kPfBlock * kPfBlock; // rows past it are left alone
     return d;
 }
 
-// x / n for x * n < 2^32, with m = ceil(2^32 / n) (n == 1: m is not used)
-__device__ __forceinline__ int pf_div(int x, int n, uint32_t m) { return n == 1 ? x : (int)__umulhi((uint32_t)x, m); }
+// x / n for 0 <= x < 2^31, with m = ceil(2^32 / n) (n == 1: m is not used).  The product overestimates the quotient by
+// less than x / 2^32, so by one at most.
+__device__ __forceinline__ int pf_div(int x, int n, uint32_t m)
+{
+    if (n == 1) return x;
+    const int q = (int)__umulhi((uint32_t)x, m);
+    return q - ((int64_t)q * n > x);
+}
 
 __device__ __forceinline__ int pf_blocks(int tokens, int G) { return (((tokens + 31) >> 5) * G + 7) >> 3; }
 
@@ -290,7 +295,7 @@ __device__ __forceinline__ void pf_enter(const PrefillLaunch &a, const PfDeal &d
         const int g = c.base + d.lane;
         int len = 0;
         if (g < a.num_prompts) len = a.cu[g + 1] - a.cu[g];
-        len = len < 0 ? 0 : (len < d.limit ? len : d.limit);
+        len = len < 0 ? 0 : (len < a.limit ? len : a.limit);
         c.lens = len;
         // this die's share of the pair's blocks: numbers s, s + 8 / gg, ... (s moves on with the prompt, or one die would
         // get every pair's longest block)
@@ -670,19 +675,21 @@ hipError_t prefill_config()
 
 hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
 {
+    const int64_t pairs = (int64_t)given.num_prompts * given.Hkv;
+    const int64_t rows = ((int64_t)given.max_len + kPfBlock - 1) / kPfBlock * kPfBlock;
+    if (pairs == 0 || rows == 0) return hipSuccess;
+    if (rows > INT32_MAX || (pairs + 7) / 8 * (rows / kPfBlock) * given.G > INT32_MAX / 16) return hipErrorInvalidValue;
     PrefillLaunch a = given;
     a.fused_write = prefill_writes_cache(a);
+    if (a.fused_write && ((int64_t)a.max_len + kPage - 1) / kPage * pairs > INT32_MAX) return hipErrorInvalidValue;
+    a.limit = (int32_t)rows;
     // blocks of a die at most: its kv heads' share of every prompt's
     const int gg = (a.Hkv & 7) == 0 ? 8 : (a.Hkv & 3) == 0 ? 4 : (a.Hkv & 1) == 0 ? 2 : 1, share = 8 / gg;
-    const int64_t tiles = (int64_t)(a.max_len + kPfBlock - 1) / kPfBlock * (kPfBlock / 32);
-    const int64_t per_pair = (tiles * a.G + 7) / 8;
+    const int64_t per_pair = (rows / 32 * a.G + 7) / 8;
     const int64_t blocks = (int64_t)a.num_prompts * (a.Hkv / gg) * ((per_pair + share - 1) / share);
-    if (blocks == 0) return hipSuccess;
-    if (blocks > INT32_MAX / 16 || (int64_t)a.Hq * a.D >= (int64_t)1 << 25) return hipErrorInvalidValue; // (32-bit offsets inside a tile)
     int64_t per_die = a.num_cus / 8;
     per_die = per_die < 1 ? 1 : per_die;
     if (a.stay > 0 && a.stay < per_die) per_die = a.stay;    // fewer were asked for
-    if (tiles * a.G * (int64_t)a.G >= (int64_t)1 << 31 || blocks * (a.Hkv / gg) >= (int64_t)1 << 31) return hipErrorInvalidValue; // (pf_div)
     a.magic_g = (uint32_t)((((uint64_t)1 << 32) + a.G - 1) / a.G);
     a.magic_heads = (uint32_t)((((uint64_t)1 << 32) + a.Hkv / gg - 1) / (a.Hkv / gg));
     // Prompts whose blocks are dealt together: few enough for their K and V to stay in a die's 4 MB L2 while the die's
@@ -690,7 +697,7 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     // 131.3 us on 32 prompts of 512 tokens (seven heads per kv head), 1287, 1289, 1268, 1277 us on 16 of 2048 (eight),
     // 28.7, 28.7, 28.7, 35.8 us on 8 of 37 to 701.
     a.group = (int64_t)16 * a.max_len * 4 * a.D * (a.Hkv / gg) <= (4 << 20) ? 16 : 8;
-    const bool one_each = a.stay == 0 || blocks <= per_die;
+    const bool one_each = blocks <= per_die || (a.stay == 0 && blocks <= INT32_MAX / 16);
     if (one_each) per_die = blocks;
 #define RA_PF_LAUNCH(DD, ST)                                                                                                \
     hipLaunchKernelGGL((prefill_kernel<DD, ST>), dim3(8u * (unsigned)per_die), dim3(64 * kPfWaves), prefill_lds_bytes<DD>(), s, a)

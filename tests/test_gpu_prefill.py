@@ -305,6 +305,32 @@ def test_rejected_arguments(dec):
     torch.cuda.synchronize()
 
 
+def test_bounds_far_above_the_lengths_and_very_many_heads(dec):
+    # the bound on the prompt length is the caller's and may be generous; heads without end share one kv head.  What the
+    # launch refuses is a grid that cannot be: blocks of 256 rows (of a die), or pages of the cache, past 2^31
+    b = workload.build_prefill("pf", 256, 1, 64, [70, 3], seed=4)
+    ref = oracle.prefill(b.q, b.k, b.v, b.cu_seqlens, b.softmax_scale)
+    d = DevicePrefill(b, max_len=1 << 20)
+    dec.prefill(d.c)
+    compare(*d.results(), *ref, "256 heads, a bound of a million")
+    Hq = 1 << 18
+    q = torch.ones((1, Hq, 128), dtype=torch.bfloat16, device=DEV)
+    k, v = (torch.randn((1, 1, 128), device=DEV).to(torch.bfloat16) for _ in range(2))
+    out, lse = torch.zeros_like(q), torch.zeros((1, Hq), device=DEV)
+    dec.prefill(ra.prefill_from_tensors(q, k, v, torch.tensor([0, 1], dtype=torch.int32, device=DEV), 1, out, lse, 1.0))
+    assert torch.equal(out, v.expand_as(out))               # one key: the weight is 1
+    assert float((lse - k.double().sum()).abs().max()) < 1e-4
+    d = DevicePrefill(b, max_len=(1 << 31) - 1)
+    with pytest.raises(ra.RolloutAttnError):
+        dec.prefill(d.c)
+    b = workload.build_prefill("pf", 16, 4, 64, [3] * 8, seed=4)
+    d = DevicePrefill(b, kv_dtype="bf16", max_len=1 << 30)  # 2^26 pages of each of 32 (prompt, kv head) pairs
+    with pytest.raises(ra.RolloutAttnError):
+        dec.prefill(d.c)
+    torch.cuda.synchronize()
+    assert torch.isnan(d.out.float()).all() and torch.isnan(d.k_pool.float()).all()
+
+
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
 @pytest.mark.parametrize("Hq,Hkv,D", [(3, 3, 128), (8, 4, 64), (12, 4, 128), (8, 2, 128), (10, 2, 64), (21, 3, 128), (16, 1, 64), (48, 6, 128)])
 def test_cache_write_of_every_head_ratio(dec, kv_dtype, Hq, Hkv, D):
