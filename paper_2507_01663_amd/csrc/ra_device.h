@@ -214,6 +214,23 @@ __device__ __forceinline__ uint32_t e4m3_nearest(float z)
     return sign | (code > 0x7e ? 0x7e : code);
 }
 
+// Exclusive scan of x over the 64 lanes; total: the sum.  Data-parallel-primitive moves on the VALU (no LDS trip per
+// step): shifts by 1, 2, 4, 8 inside the rows of 16 lanes, then each row's last lane broadcast into the next row
+// (rows 1 and 3) and lane 31 into the upper half; lanes without a source add 0.
+__device__ __forceinline__ int wave_scan(int x, int lane, int &total)
+{
+    int v = x;
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false); // row_shr:1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false); // row_shr:2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false); // row_shr:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false); // row_shr:8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // row_bcast:15
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false); // row_bcast:31
+    total = __builtin_amdgcn_readlane(v, 63);
+    (void)lane;
+    return v - x;
+}
+
 // Many codes with one scale: nearest E4M3 of x / s for finite |x| <= about 448 s, bit for bit what e4m3_nearest(x / s)
 // gives, in 7 instructions an element instead of 35.  The quotient by the reciprocal is corrected twice with the exact
 // remainder, which rounds it correctly (Markstein: a faithful quotient and a correctly rounded reciprocal), the format

@@ -1064,23 +1064,6 @@ __device__ __forceinline__ void carve_wave_tables(WaveTables &T, void *base, int
     T.rs = take(rows + 1);
 }
 
-// Exclusive scan of x over the 64 lanes; total: the sum.  Data-parallel-primitive moves on the VALU (no LDS trip per
-// step): shifts by 1, 2, 4, 8 inside the rows of 16 lanes, then each row's last lane broadcast into the next row
-// (rows 1 and 3) and lane 31 into the upper half; lanes without a source add 0.
-__device__ __forceinline__ int wave_scan(int x, int lane, int &total)
-{
-    int v = x;
-    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false); // row_shr:1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false); // row_shr:2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false); // row_shr:4
-    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false); // row_shr:8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false); // row_bcast:15
-    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false); // row_bcast:31
-    total = __builtin_amdgcn_readlane(v, 63);
-    (void)lane;
-    return v - x;
-}
-
 // The rows and where they start in the cost stream, by one wave for itself (see rows_phase for what a row is and
 // costs).  A lane takes runs of consecutive sequences and of consecutive groups and keeps them in registers; the
 // tables in LDS are what the listing below looks up.

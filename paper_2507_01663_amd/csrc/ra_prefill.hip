@@ -240,9 +240,10 @@ __device__ __forceinline__ void pf_scores(const uint8_t *k_stage, const PfLane<D
 // Which workgroup takes which blocks is fixed by the inputs.  Workgroups are dealt to the eight dies round-robin, and
 // each die has its own L2, so the blocks of a pair go to few dies: with gg = gcd(Hkv, 8), die x takes the kv heads
 // congruent x mod gg, and the 8 / gg dies that take the same heads take the blocks of a pair in turn.  Every die so gets
-// the same share of every prompt, however ragged the lengths are.  A die's blocks are ordered by length, longest first
-// (block number from the short end of its pair, which is its length to within a tile, over all prompts at once) and
-// dealt to its workgroups back and forth, which keeps their sums within a few percent of one another.
+// the same share of every prompt, however ragged the lengths are.  A die takes the prompts in groups of a.group (see
+// launch_prefill), the blocks of a group ordered by length, longest first (block number from the short end of its pair,
+// which is its length to within a tile, over all prompts of the group at once), and deals them to its workgroups back and
+// forth, which keeps their sums within a few percent of one another.
 struct PfBlock {
     int g, kvh, t0, len; // prompt, kv head; first token of the prompt, its tokens
     int u0, nst;        // first unit of the block, stages of 32 keys
@@ -250,12 +251,16 @@ struct PfBlock {
     __device__ __forceinline__ int chunks() const { return (nst + 1) >> 1; } // of two stages
 };
 
-// A place in a die's order of blocks.  Lane l knows the length of prompt base + l.
+// A workgroup's way through its die's order of blocks.  Lane l has prompt base + l of the 64 that are in use.
 struct PfCursor {
-    int base, lane0;    // the 64 prompts that the lanes hold, and the first lane of the group of prompts
-    int j, top, o;      // level (blocks left in the pair's share behind this one), the group's highest, place in the level
-    int round;          // blocks of this workgroup so far
-    int lens, cnt;      // this lane's prompt: tokens, blocks of one kv head on this die
+    int base, done, all; // first of those prompts; blocks (of this die) of the prompts before it and of the 64
+    int round;           // blocks of this workgroup so far
+    int lane0, before, blocks; // the group that the last block came from: its first lane, blocks of the 64 before it, its own
+    bool turned;               // it runs from short to long
+    int first, len;      // this lane's prompt: first token, tokens
+    int cnt, sum;        // ... its blocks of one kv head on this die, those of the lanes up to it
+    int up;              // blocks of the group from level step * lane up (see pf_next)
+    int nfirst, nend;    // first token and end for the 64 prompts after these: asked for when these are taken into use
 };
 
 struct PfDeal {
@@ -282,76 +287,94 @@ __device__ __forceinline__ int pf_div(int x, int n, uint32_t m)
 {
     if (n == 1) return x;
     const int q = (int)__umulhi((uint32_t)x, m);
-    return q - ((int64_t)q * n > x);
+    return q - ((uint32_t)q * (uint32_t)n > (uint32_t)x);
 }
 
-__device__ __forceinline__ int pf_blocks(int tokens, int G) { return (((tokens + 31) >> 5) * G + 7) >> 3; }
-
-// Goes to the first level of the group of prompts that starts at lane c.lane0 of c.base (first loads the lanes' prompts
-// where that is lane 0).
-__device__ __forceinline__ void pf_enter(const PrefillLaunch &a, const PfDeal &d, PfCursor &c)
+// Asks for 64 prompts; takes them into use (and asks for the 64 after them).
+__device__ __forceinline__ void pf_ask(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, int base)
 {
-    if (c.lane0 == 0) {
-        const int g = c.base + d.lane;
-        int len = 0;
-        if (g < a.num_prompts) len = a.cu[g + 1] - a.cu[g];
-        len = len < 0 ? 0 : (len < a.limit ? len : a.limit);
-        c.lens = len;
-        // this die's share of the pair's blocks: numbers s, s + 8 / gg, ... (s moves on with the prompt, or one die would
-        // get every pair's longest block)
-        const int S = 1 << d.s_shift, s = (d.share + g) & (S - 1), nb = pf_blocks(len, a.G);
-        c.cnt = nb > s ? (nb - s + S - 1) >> d.s_shift : 0;
-    }
-    const bool in = (d.lane & -a.group) == c.lane0;
-    int top = -1; // the largest j with cnt > j in some lane of the group
-#pragma unroll 1
-    for (int bit = 1 << 24; bit; bit >>= 1)
-        if (__any(in && c.cnt > top + bit)) top += bit;
-    c.top = top;
-    c.j = ((c.base + c.lane0) / a.group) & 1 ? 0 : top;
+    const int g = base + d.lane;
+    c.nfirst = c.nend = 0;
+    if (g < a.num_prompts) c.nfirst = a.cu[g], c.nend = a.cu[g + 1];
 }
-
-__device__ __forceinline__ unsigned long long pf_level(const PrefillLaunch &a, const PfDeal &d, const PfCursor &c)
+__device__ __forceinline__ void pf_take(const PrefillLaunch &a, const PfDeal &d, PfCursor &c)
 {
-    return __ballot((d.lane & -a.group) == c.lane0 && c.cnt > c.j);
+    const int len = c.nend - c.nfirst;
+    c.first = c.nfirst;
+    c.len = len < 0 ? 0 : (len < a.limit ? len : a.limit);
+    if (c.base + 64 < a.num_prompts) pf_ask(a, d, c, c.base + 64);
+    // this die's share of a pair's blocks: numbers s, s + S, ... (s moves on with the prompt, or one die would get every
+    // pair's longest block)
+    const int S = 1 << d.s_shift, s = (d.share + c.base + d.lane) & (S - 1);
+    const int nb = (((c.len + 31) >> 5) * a.G + 7) >> 3;
+    c.cnt = nb > s ? (nb - s + S - 1) >> d.s_shift : 0;
+    c.sum = c.cnt + wave_scan(c.cnt, d.lane, c.all);
+    c.all *= d.heads;
+    c.lane0 = c.before = c.blocks = 0;
 }
 
-// Moves the cursor n blocks on; false past the die's last block.
-__device__ __forceinline__ bool pf_seek(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, int n)
-{
-    c.o += n;
-    for (;;) {
-        const int step = ((c.base + c.lane0) / a.group) & 1 ? 1 : -1;
-        while (c.j >= 0 && c.j <= c.top) {
-            const int here = __popcll(pf_level(a, d, c)) * d.heads;
-            if (c.o < here) return true;
-            c.o -= here;
-            c.j += step;
-        }
-        c.lane0 += a.group;
-        if (c.lane0 >= 64) c.lane0 = 0, c.base += 64;
-        if (c.base + c.lane0 >= a.num_prompts) return false;
-        pf_enter(a, d, c);
-    }
-}
-
-// The workgroup's next block (its first one when c.round is 0); false when it has no more.
+// The workgroup's next block (its first one when c.round is 0); false when it has no more.  The instructions on the way to
+// a block count, every wave issues them: prompts are passed by 64 at a time, and a block's place is found without a walk.
+// (Walked to prompt by prompt, by two cursors, 25 votes to a group of 16, against so: 876 -> 71 us for 4096 prompts of 16
+// tokens, four heads on one kv head, D = 64; 421 -> 260 for 1024 of 64 and 110 -> 104 for 32 of 512, 28 on four, D = 128.
+// A call of this is about 0.3 us.)
 __device__ __forceinline__ bool pf_next(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, PfBlock &b)
 {
     // back and forth: places wg, 2 wgs - 1 - wg, 2 wgs + wg, ...
-    const int n = c.round == 0 ? d.wg : (c.round & 1) ? 2 * (d.wgs - d.wg) - 1 : 2 * d.wg + 1;
+    const int place = c.round * d.wgs + (c.round & 1 ? d.wgs - 1 - d.wg : d.wg);
     c.round++;
-    if (!pf_seek(a, d, c, n)) return false;
-    const unsigned long long m = pf_level(a, d, c);
-    const int nth = pf_div(c.o, d.heads, a.magic_heads), x = c.o - nth * d.heads;
+    while (place - c.done >= c.all) {
+        if (c.base + 64 >= a.num_prompts) return false;
+        c.done += c.all;
+        c.base += 64;
+        pf_take(a, d, c);
+    }
+    int o = place - c.done;
+    // A block's level is the number of blocks left in its pair's share behind it: the highest level first.  Level j has a
+    // block of every (prompt, head) with more than j, so the levels from j up hold heads * sum(max(cnt - j, 0)), and the
+    // place's level is the last one for which that exceeds o: every lane tries one level, every `step`th at first.
+    auto from_level = [&](int j) __attribute__((always_inline)) {
+        const int left = a.num_prompts - c.base - c.lane0, prompts = left < a.group ? left : a.group;
+        int n = 0;
+#pragma unroll 1
+        for (int i0 = 0; i0 < prompts; i0 += 8) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+                const int over = __builtin_amdgcn_readlane(c.cnt, c.lane0 + i0 + i) - j;
+                n += over > 0 ? over : 0;
+            }
+        }
+        return n * d.heads;
+    };
+    int step = (a.levels + 63) >> 6;
+    if (o >= c.before + c.blocks) { // another group of prompts
+        c.lane0 = (__ffsll((long long)__ballot(c.sum * d.heads > o)) - 1) & -a.group;
+        c.before = c.lane0 ? __builtin_amdgcn_readlane(c.sum, c.lane0 - 1) * d.heads : 0;
+        c.blocks = __builtin_amdgcn_readlane(c.sum, c.lane0 + a.group - 1) * d.heads - c.before;
+        c.up = from_level(d.lane * step);
+        c.turned = (c.base + c.lane0) / a.group & 1; // every other group runs from short to long
+    }
+    o -= c.before;
+    if (c.turned) o = c.blocks - 1 - o;
+    int j = 0, up = c.up, left;
+    for (;;) {
+        const int k = __popcll(__ballot(up > o)) - 1;
+        left = __builtin_amdgcn_readlane(up, k); // blocks of level j and up
+        j += k * step;
+        if (step == 1) break;
+        step = (step + 63) >> 6;
+        up = from_level(j + d.lane * step);
+    }
+    const unsigned long long m = __ballot((d.lane & -a.group) == c.lane0 && c.cnt > j);
+    o -= left - __popcll(m) * d.heads; // the place inside the level
+    const int nth = pf_div(o, d.heads, a.magic_heads), x = o - nth * d.heads;
     const int rank = __popcll(m & ((1ull << d.lane) - 1ull));
     const int l = __ffsll((long long)(m & __ballot(rank == nth))) - 1;
-    const int g = c.base + l, S = 1 << d.s_shift, s = (d.share + g) & (S - 1);
-    b.len = __builtin_amdgcn_readlane(c.lens, l);
-    b.g = g;
-    b.t0 = uniform_load(a.cu, g);
+    b.g = c.base + l;
+    b.t0 = __builtin_amdgcn_readlane(c.first, l);
+    b.len = __builtin_amdgcn_readlane(c.len, l);
     b.kvh = ((int)blockIdx.x & ((1 << d.gg_shift) - 1)) + (x << d.gg_shift);
-    b.u0 = 8 * (s + ((__builtin_amdgcn_readlane(c.cnt, l) - 1 - c.j) << d.s_shift));
+    b.u0 = (((d.share + b.g) & ((1 << d.s_shift) - 1)) + ((__builtin_amdgcn_readlane(c.cnt, l) - 1 - j) << d.s_shift)) << 3;
     b.nst = b.tiles() - pf_div(b.u0, a.G, a.magic_g);
     return true;
 }
@@ -371,17 +394,21 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     const int lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
 
-    // two cursors over the same sequence of blocks: the one whose chunks are being loaded, and the one after the block
-    // that is being multiplied
+    // the block that is being multiplied, and the ones after it: loading is two chunks ahead, so at most three blocks
     const PfDeal deal = pf_deal(a);
-    PfCursor lcur;
-    lcur.base = lcur.lane0 = 0, lcur.o = 0, lcur.round = 0;
-    pf_enter(a, deal, lcur);
-    PfBlock cb, lb;
-    if (__builtin_expect(!pf_next(a, deal, lcur, cb), 0)) return; // the whole workgroup
-    PfCursor ncur = lcur;
-    lb = cb;
-    bool l_ok = true;
+    PfCursor cur;
+    cur.base = cur.done = cur.round = 0, cur.turned = false, cur.up = 0;
+    pf_ask(a, deal, cur, 0);
+    pf_take(a, deal, cur);
+    PfBlock cb, n1, n2, n3;
+    if (__builtin_expect(!pf_next(a, deal, cur, cb), 0)) return; // the whole workgroup
+    int ahead = 0;      // blocks in n1, n2, n3: three until there are no more (STAY)
+    bool last_known = false;
+    auto look_ahead = [&](PfBlock &b) __attribute__((always_inline)) {
+        if (!STAY || last_known) return;
+        last_known = !pf_next(a, deal, cur, b);
+        if (!last_known) ahead++;
+    };
 
     LaneConst<D, 2> lc;
     lane_setup<D, 2>(lc, lane, a.Hkv * D * 2);
@@ -398,31 +425,38 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     int issued = 0;  // chunks issued, counted over all blocks: chunk number c lives in ring slot c % NSL
     int lchunk = 0;  // chunks of the block being loaded that have been issued
     int tok = 0;     // first key of the wave's tile in the chunk to load next
+    int l_len = 0, l_chunks = 0; // the block being loaded: tokens of its prompt, chunks
+    int lb = 0;                  // which one it is: 0 cb, 1 n1, ...; past `ahead`: there is none
     const uint8_t *src = nullptr;
-    auto load_from = [&](const PfBlock &b) __attribute__((always_inline)) {
+    auto load_from = [&](int t0, int kvh, int len, int chunks) __attribute__((always_inline)) {
         tok = kPage * (tile & 1);
-        src = (const uint8_t *)((tile < 2 ? a.k : a.v) + ((int64_t)(b.t0 + tok) * a.Hkv + b.kvh) * D);
+        src = (const uint8_t *)((tile < 2 ? a.k : a.v) + ((int64_t)(t0 + tok) * a.Hkv + kvh) * D);
+        l_len = len, l_chunks = chunks;
         lchunk = 0;
     };
-    load_from(lb);
-    auto issue = [&]() __attribute__((always_inline)) { // the next chunk of the sequence, if there is one
-        if (!l_ok) return;
+    auto load_chunk = [&]() __attribute__((always_inline)) { // the next chunk of the sequence
         if (loader) {
             const uint32_t d = dst + (issued & (NSL - 1)) * 2 * G::kStage;
-            issue_tile<D, 2>(lc, src, lb.len - tok, d, a.zeros); // keys past the end read zeros
-            issue_tile<D, 2>(lc, src + 32 * tok_bytes, lb.len - tok - 32, d + G::kStage, a.zeros);
+            issue_tile<D, 2>(lc, src, l_len - tok, d, a.zeros); // keys past the end read zeros
+            issue_tile<D, 2>(lc, src + 32 * tok_bytes, l_len - tok - 32, d + G::kStage, a.zeros);
         }
         src += 64 * tok_bytes;
         tok += 64;
         issued++;
-        if (++lchunk == lb.chunks()) {
-            l_ok = STAY && pf_next(a, deal, lcur, lb);
-            if (l_ok) load_from(lb);
-        }
+        lchunk++;
     };
-    issue();
-    issue(); // the rest follows the barriers, one chunk at a time
-
+    auto next_to_load = [&]() __attribute__((always_inline)) {
+        if (lchunk < l_chunks) return;
+        lb++;
+        if (lb > ahead) return;
+        auto of = [&](int x1, int x2, int x3) __attribute__((always_inline)) { return lb == 1 ? x1 : lb == 2 ? x2 : x3; };
+        load_from(of(n1.t0, n2.t0, n3.t0), of(n1.kvh, n2.kvh, n3.kvh), of(n1.len, n2.len, n3.len), of(n1.chunks(), n2.chunks(), n3.chunks()));
+    };
+    auto issue = [&]() __attribute__((always_inline)) { // ... if there is one
+        if (lb > ahead) return;
+        load_chunk();
+        next_to_load();
+    };
     // The ring.  While a wave is in step s it reads V of stage s and K of stage s + 1.  The barrier that opens chunk
     // c (before the first step that reads its K) says that every wave's loads of the chunk have landed and that
     // every wave has left the last step that read chunk c - 2, whose slot then takes chunk c + 2 (the first two
@@ -533,13 +567,22 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     // to the first use it would sit inside a block and wait for younger loads as well.)
     PfState<D> st;
     bf16x8 qn[D / 16];
-    int head, T;        // of the current block: the wave's head and tile
+    int head, T;    // of the current block: the wave's head and tile
+    int chunk0 = 0; // number of the current block's first chunk
+    load_from(cb.t0, cb.kvh, cb.len, cb.chunks());
+    load_chunk(); // (the second one follows below, the rest the barriers, one chunk at a time)
     bool own = unit_of(cb, head, T);
     load_q(cb, head, T, st.qf);
+    if (STAY) {
+#pragma unroll 1
+        for (int i = 0; i < 3; i++) { // while they are on their way
+            n1 = n2, n2 = n3;
+            look_ahead(n3);
+        }
+    }
+    next_to_load();
+    issue();
     keep_q(cb, T, st.qf);
-    PfBlock nb;
-    bool n_ok = STAY && pf_next(a, deal, ncur, nb);
-    int chunk0 = 0; // number of the current block's first chunk
 
     for (;;) {
         const int nst = cb.nst;
@@ -573,9 +616,10 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
         }
         int nhead = 0, nT = 0;
         bool nown = false;
-        if (n_ok) {
-            nown = unit_of(nb, nhead, nT);
-            load_q(nb, nhead, nT, qn);
+        const bool more = ahead > 0;
+        if (more) {
+            nown = unit_of(n1, nhead, nT);
+            load_q(n1, nhead, nT, qn);
         }
         // every wave keeps the ring going for all the stages; it computes up to its own last stage: full steps, then
         // the step whose new scores cross the diagonal, then the step without new scores
@@ -602,15 +646,16 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
 
         // the next block's query rows take their place
         const int t0 = cb.t0, len = own ? cb.len : 0, dhead = head, tile_row = kPfRows * T;
-        const bool more = n_ok;
         if (more) {
+            PfBlock n4;
+            look_ahead(n4); // (while the query rows may still be on their way)
 #pragma unroll
             for (int i = 0; i < D / 16; i++) st.qf[i] = qn[i];
-            keep_q(nb, nT, st.qf);
+            keep_q(n1, nT, st.qf);
             chunk0 += cb.chunks();
-            cb = nb;
+            cb = n1, n1 = n2, n2 = n3, n3 = n4;
             head = nhead, T = nT, own = nown;
-            n_ok = STAY && pf_next(a, deal, ncur, nb);
+            ahead--, lb--;
         }
 
         // a row's sum is spread over its two lanes
@@ -687,6 +732,7 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     const int gg = (a.Hkv & 7) == 0 ? 8 : (a.Hkv & 3) == 0 ? 4 : (a.Hkv & 1) == 0 ? 2 : 1, share = 8 / gg;
     const int64_t per_pair = (rows / 32 * a.G + 7) / 8;
     const int64_t blocks = (int64_t)a.num_prompts * (a.Hkv / gg) * ((per_pair + share - 1) / share);
+    a.levels = (int)((per_pair + share - 1) / share);
     int64_t per_die = a.num_cus / 8;
     per_die = per_die < 1 ? 1 : per_die;
     if (a.stay > 0 && a.stay < per_die) per_die = a.stay;    // fewer were asked for
