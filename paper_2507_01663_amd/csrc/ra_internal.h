@@ -75,7 +75,8 @@ struct PrefillLaunch {
     int32_t limit;               // max_len rounded up to 256 rows: a prompt's rows past it are left alone (set by launch_prefill)
     int32_t group;               // prompts whose blocks are dealt together (set by launch_prefill)
     int32_t levels;              // blocks of one (prompt, kv head) that a die takes, at most (set by launch_prefill)
-    uint32_t magic_g, magic_heads; // ceil(2^32 / n) for n = G and n = Hkv / gcd(Hkv, 8) (set by launch_prefill)
+    uint32_t magic_g, magic_heads, magic_wgs; // ceil(2^32 / n) for n = G, Hkv / gcd(Hkv, 8) and the workgroups of a die
+                                              // (set by launch_prefill)
     const uint16_t *q, *k, *v;   // bf16 [T][Hq][D], [T][Hkv][D]
     const int32_t *cu;           // [num_prompts + 1] first token of each prompt
     float scale_log2;            // softmax_scale * log2(e)

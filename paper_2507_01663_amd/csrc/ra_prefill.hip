@@ -318,7 +318,7 @@ __device__ __forceinline__ void pf_take(const PrefillLaunch &a, const PfDeal &d,
 // (Walked to prompt by prompt, by two cursors, 25 votes to a group of 16, against so: 876 -> 71 us for 4096 prompts of 16
 // tokens, four heads on one kv head, D = 64; 421 -> 260 for 1024 of 64 and 110 -> 104 for 32 of 512, 28 on four, D = 128.
 // A call of this is about 0.3 us.)
-__device__ __forceinline__ bool pf_next(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, PfBlock &b)
+template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, PfBlock &b)
 {
     // back and forth: places wg, 2 wgs - 1 - wg, 2 wgs + wg, ...
     const int place = c.round * d.wgs + (c.round & 1 ? d.wgs - 1 - d.wg : d.wg);
@@ -352,7 +352,13 @@ __device__ __forceinline__ bool pf_next(const PrefillLaunch &a, const PfDeal &d,
         c.before = c.lane0 ? __builtin_amdgcn_readlane(c.sum, c.lane0 - 1) * d.heads : 0;
         c.blocks = __builtin_amdgcn_readlane(c.sum, c.lane0 + a.group - 1) * d.heads - c.before;
         c.up = from_level(d.lane * step);
-        c.turned = (c.base + c.lane0) / a.group & 1; // every other group runs from short to long
+        // Every other group, if it starts in the middle of a round, runs from short to long: its first blocks go to the
+        // workgroups that got the last and shortest ones of the group before.  (Turned about, a group of one round that
+        // starts with a round would give its longest blocks to the workgroups that have just had the longest ones: 32
+        // prompts of 512 tokens and eight heads without sharing, two rounds of 32 blocks for a die,
+        // 60.1 -> 54.7 us; 58 of 792 tokens 241 -> 191.)
+        const int at = c.done + c.before, phase = 4 * (at - pf_div(at, d.wgs, a.magic_wgs) * d.wgs);
+        c.turned = STAY && ((c.base + c.lane0) / a.group & 1) && phase > d.wgs && phase < 3 * d.wgs;
     }
     o -= c.before;
     if (c.turned) o = c.blocks - 1 - o;
@@ -401,12 +407,12 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     pf_ask(a, deal, cur, 0);
     pf_take(a, deal, cur);
     PfBlock cb, n1, n2, n3;
-    if (__builtin_expect(!pf_next(a, deal, cur, cb), 0)) return; // the whole workgroup
+    if (__builtin_expect(!pf_next<STAY>(a, deal, cur, cb), 0)) return; // the whole workgroup
     int ahead = 0;      // blocks in n1, n2, n3: three until there are no more (STAY)
     bool last_known = false;
     auto look_ahead = [&](PfBlock &b) __attribute__((always_inline)) {
         if (!STAY || last_known) return;
-        last_known = !pf_next(a, deal, cur, b);
+        last_known = !pf_next<STAY>(a, deal, cur, b);
         if (!last_known) ahead++;
     };
 
@@ -745,6 +751,7 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     a.group = (int64_t)16 * a.max_len * 4 * a.D * (a.Hkv / gg) <= (4 << 20) ? 16 : 8;
     const bool one_each = blocks <= per_die || (a.stay == 0 && blocks <= INT32_MAX / 16);
     if (one_each) per_die = blocks;
+    a.magic_wgs = (uint32_t)((((uint64_t)1 << 32) + per_die - 1) / per_die);
 #define RA_PF_LAUNCH(DD, ST)                                                                                                \
     hipLaunchKernelGGL((prefill_kernel<DD, ST>), dim3(8u * (unsigned)per_die), dim3(64 * kPfWaves), prefill_lds_bytes<DD>(), s, a)
     if (a.D == 128) {
