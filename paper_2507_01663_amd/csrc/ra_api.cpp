@@ -26,7 +26,7 @@ struct ra_ctx {
     int xcd_w[8];              // default share of the page stream per accelerator die, per mille of the mean
     int32_t *wave_cum[2][2];   // device: running sums of the workgroups' shares, [e4m3 KV][D == 128], kMaxWaves + 1 each
     uint32_t *tickets;         // device: the streaming probe's ticket counter (cleared by every launch that uses it)
-    int prefill_stay;          // -1: one prefill workgroup per compute unit; else ROLLOUT_ATTN_PREFILL_WGS_PER_DIE
+    int prefill_stay;          // -1: the prefill launch chooses by the batch; else ROLLOUT_ATTN_PREFILL_WGS_PER_DIE
     void *zeros;  // 256 bytes of zeros on the device
     int self_plan; // attention waves may plan their spans themselves (no schedule kernel)
     int direct;    // the smallest batches may go without a schedule
@@ -503,7 +503,7 @@ ra_status rollout_attn_prefill(ra_ctx *c, const ra_prefill *p, void *stream)
     if (p->num_prompts == 0 || p->total_tokens == 0 || p->max_prompt_len == 0) return RA_OK;
     ra::PrefillLaunch a;
     memset(&a, 0, sizeof a);
-    a.num_prompts = p->num_prompts; a.max_len = p->max_prompt_len; a.Hq = p->Hq; a.Hkv = p->Hkv; a.D = p->D; a.G = p->Hq / p->Hkv;
+    a.num_prompts = p->num_prompts; a.total_tokens = p->total_tokens; a.max_len = p->max_prompt_len; a.Hq = p->Hq; a.Hkv = p->Hkv; a.D = p->D; a.G = p->Hq / p->Hkv;
     a.q = (const uint16_t *)p->q; a.k = (const uint16_t *)p->k; a.v = (const uint16_t *)p->v;
     a.cu = p->cu_seqlens;
     a.scale_log2 = p->softmax_scale * 1.4426950408889634f;

@@ -67,10 +67,10 @@ struct Launch {
 
 // Prompt prefill: packed prompts, their causal attention, and where their K and V rows go in the cache.
 struct PrefillLaunch {
-    int32_t num_prompts, max_len, Hq, Hkv, D, G;
+    int32_t num_prompts, total_tokens, max_len, Hq, Hkv, D, G;
     int32_t num_cus;             // compute units of the device
     int32_t stay;                // prefill workgroups per die that stay and take block after block (at most one per
-                                 // compute unit); 0: one workgroup per block; -1: as many as there are compute units
+                                 // compute unit); 0: one workgroup per block; -1: chosen by the batch
     int32_t fused_write;         // the attention kernel writes the cache too (set by launch_prefill)
     int32_t limit;               // max_len rounded up to 256 rows: a prompt's rows past it are left alone (set by launch_prefill)
     int32_t group;               // prompts whose blocks are dealt together (set by launch_prefill)

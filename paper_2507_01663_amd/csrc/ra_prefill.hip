@@ -734,22 +734,37 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     a.fused_write = prefill_writes_cache(a);
     if (a.fused_write && ((int64_t)a.max_len + kPage - 1) / kPage * pairs > INT32_MAX) return hipErrorInvalidValue;
     a.limit = (int32_t)rows;
-    // blocks of a die at most: its kv heads' share of every prompt's
-    const int gg = (a.Hkv & 7) == 0 ? 8 : (a.Hkv & 3) == 0 ? 4 : (a.Hkv & 1) == 0 ? 2 : 1, share = 8 / gg;
-    const int64_t per_pair = (rows / 32 * a.G + 7) / 8;
-    const int64_t blocks = (int64_t)a.num_prompts * (a.Hkv / gg) * ((per_pair + share - 1) / share);
-    a.levels = (int)((per_pair + share - 1) / share);
+    const int gg = (a.Hkv & 7) == 0 ? 8 : (a.Hkv & 3) == 0 ? 4 : (a.Hkv & 1) == 0 ? 2 : 1, share = 8 / gg, heads = a.Hkv / gg;
     int64_t per_die = a.num_cus / 8;
     per_die = per_die < 1 ? 1 : per_die;
-    if (a.stay > 0 && a.stay < per_die) per_die = a.stay;    // fewer were asked for
+    if (a.stay > 0 && a.stay < per_die) per_die = a.stay; // fewer were asked for
+    // blocks of a (prompt, kv head) and of a die, at most; blocks of the batch, about (by its tokens)
+    const int64_t per_pair = (rows / 32 * a.G + 7) / 8;
+    const int64_t blocks = heads * (a.num_prompts * (per_pair / share) + ((int64_t)a.num_prompts + share - 1) / share * (per_pair % share));
+    const int64_t about = ((int64_t)a.total_tokens + 31 * (int64_t)a.num_prompts) / 32 * a.Hq / 8;
+    a.levels = (int)((per_pair + share - 1) / share);
     a.magic_g = (uint32_t)((((uint64_t)1 << 32) + a.G - 1) / a.G);
-    a.magic_heads = (uint32_t)((((uint64_t)1 << 32) + a.Hkv / gg - 1) / (a.Hkv / gg));
-    // Prompts whose blocks are dealt together: few enough for their K and V to stay in a die's 4 MB L2 while the die's
-    // workgroups share them, enough for an even deal of ragged lengths.  Measured with 64, 16, 8 and 4: 121.0, 115.5, 119.9,
-    // 131.3 us on 32 prompts of 512 tokens (seven heads per kv head), 1287, 1289, 1268, 1277 us on 16 of 2048 (eight),
-    // 28.7, 28.7, 28.7, 35.8 us on 8 of 37 to 701.
-    a.group = (int64_t)16 * a.max_len * 4 * a.D * (a.Hkv / gg) <= (4 << 20) ? 16 : 8;
-    const bool one_each = blocks <= per_die || (a.stay == 0 && blocks <= INT32_MAX / 16);
+    a.magic_heads = (uint32_t)((((uint64_t)1 << 32) + heads - 1) / heads);
+    // Workgroups that stay, or one per block.  Those that stay load the next block's inputs under the current one, but which
+    // blocks each of them takes is fixed beforehand; with one per block the hardware hands them out as units become free.
+    // That pays where a fixed deal comes out uneven: long prompts of unlike lengths, as long as a workgroup has few blocks.
+    // Staying against one each, us: 29 prompts of 339 to 1876 tokens, four heads on two, D = 64 (two blocks a workgroup)
+    // 96.1, 56.5; 50 of 200 to 1500, eight heads (five) 226.9, 188.9; 24 of 200 to 1500, 28 on four (nine) 232.0, 216.8; 100
+    // of 200 to 1500, eight (ten) 422.7, 397.8; but 100 of 20 to 1500, 32 on two, D = 64 (37) 524, 546.  Not with short or
+    // like ones: 64 of 50 to 500, 40 on eight (eleven) 150.9, 177.5; 32 of 512, 28 on four (seven) 105.2, 123.1; 16 of 2048,
+    // 64 on eight 1228, 1297.  And with at most a block for every unit there is nothing to load ahead: 60 of 60 to 100
+    // tokens, four on two 10.9, 9.9.  The launch must not be empty workgroups mostly, so the bound on the lengths has to be a
+    // near one.
+    const bool alike = 8 * (int64_t)a.total_tokens >= 7 * (int64_t)a.num_prompts * a.max_len;
+    const bool uneven = !alike && a.max_len > 2 * kPfBlock && about <= 12 * (int64_t)a.num_cus, few = about <= a.num_cus;
+    const bool one_each = blocks <= per_die || (a.stay == 0 && blocks <= INT32_MAX / 16) ||
+                          (a.stay < 0 && (few || uneven) && 2 * blocks <= about + per_die);
+    // Prompts whose blocks are dealt together.  One workgroup per block: as many as there are, so that the longest blocks
+    // start first.  Else few enough for their K and V to stay in a die's 4 MB L2 while the die's workgroups share them, enough
+    // for an even deal of ragged lengths.  Measured with 64, 16, 8 and 4: 121.0, 115.5, 119.9, 131.3 us on 32 prompts of
+    // 512 tokens (seven heads per kv head), 1287, 1289, 1268, 1277 us on 16 of 2048 (eight), 28.7, 28.7, 28.7, 35.8 us on 8
+    // of 37 to 701.
+    a.group = one_each && !few ? 64 : (int64_t)16 * a.max_len * 4 * a.D * heads <= (4 << 20) ? 16 : 8;
     if (one_each) per_die = blocks;
     a.magic_wgs = (uint32_t)((((uint64_t)1 << 32) + per_die - 1) / per_die);
 #define RA_PF_LAUNCH(DD, ST)                                                                                                \
