@@ -74,6 +74,7 @@ struct PrefillLaunch {
     int32_t fused_write;         // the attention kernel writes the cache too (set by launch_prefill)
     int32_t limit;               // max_len rounded up to 256 rows: a prompt's rows past it are left alone (set by launch_prefill)
     int32_t group;               // prompts whose blocks are dealt together (set by launch_prefill)
+    int32_t units, units_shift;  // (32-row tile, head) units of a block, 4 or 8, and the logarithm (set by launch_prefill)
     int32_t levels;              // blocks of one (prompt, kv head) that a die takes, at most (set by launch_prefill)
     uint32_t magic_g, magic_heads, magic_wgs; // ceil(2^32 / n) for n = G, Hkv / gcd(Hkv, 8) and the workgroups of a die
                                               // (set by launch_prefill)

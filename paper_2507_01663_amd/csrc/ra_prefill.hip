@@ -306,7 +306,7 @@ __device__ __forceinline__ void pf_take(const PrefillLaunch &a, const PfDeal &d,
     // this die's share of a pair's blocks: numbers s, s + S, ... (s moves on with the prompt, or one die would get every
     // pair's longest block)
     const int S = 1 << d.s_shift, s = (d.share + c.base + d.lane) & (S - 1);
-    const int nb = (((c.len + 31) >> 5) * a.G + 7) >> 3;
+    const int nb = (((c.len + 31) >> 5) * a.G + a.units - 1) >> a.units_shift;
     c.cnt = nb > s ? (nb - s + S - 1) >> d.s_shift : 0;
     c.sum = c.cnt + wave_scan(c.cnt, d.lane, c.all);
     c.all *= d.heads;
@@ -380,7 +380,7 @@ template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch
     b.t0 = __builtin_amdgcn_readlane(c.first, l);
     b.len = __builtin_amdgcn_readlane(c.len, l);
     b.kvh = ((int)blockIdx.x & ((1 << d.gg_shift) - 1)) + (x << d.gg_shift);
-    b.u0 = (((d.share + b.g) & ((1 << d.s_shift) - 1)) + ((__builtin_amdgcn_readlane(c.cnt, l) - 1 - j) << d.s_shift)) << 3;
+    b.u0 = (((d.share + b.g) & ((1 << d.s_shift) - 1)) + ((__builtin_amdgcn_readlane(c.cnt, l) - 1 - j) << d.s_shift)) << a.units_shift;
     b.nst = b.tiles() - pf_div(b.u0, a.G, a.magic_g);
     return true;
 }
@@ -472,7 +472,7 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     // blocks; wave w takes tile w of the chunk that has just been opened.
     int w_lo = 1 << 30, w_hi = -1; // the block's stages to be written
     auto pages_of_block = [&]() __attribute__((always_inline)) {
-        const int units = cb.tiles() * a.G, end = (cb.u0 + 8 < units ? cb.u0 + 8 : units) - 1;
+        const int units = cb.tiles() * a.G, end = (cb.u0 + a.units < units ? cb.u0 + a.units : units) - 1;
         w_hi = cb.tiles() - 1 - pf_div(cb.u0 + a.G - 1, a.G, a.magic_g);
         w_lo = cb.tiles() - 1 - pf_div(end, a.G, a.magic_g);
     };
@@ -536,12 +536,12 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     };
 
     // The wave's unit of a block: waves w and w + 4 share a SIMD, so the longest and the shortest go together.  Past the
-    // pair's last unit a wave repeats that one and stores nothing.
+    // block's last unit a wave has none: it keeps the ring going and computes nothing.
     const int order = wave < 4 ? wave : 11 - wave;
     auto unit_of = [&](const PfBlock &b, int &head, int &tile_q) -> bool {
         const int units = b.tiles() * a.G;
         int u = b.u0 + order;
-        const bool own = u < units;
+        const bool own = order < a.units && u < units;
         u = own ? u : units - 1;
         const int q = pf_div(u, a.G, a.magic_g);
         tile_q = b.tiles() - 1 - q;
@@ -605,7 +605,7 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
 
         if (a.fused_write) pages_of_block();
         open_chunk(chunk0, 0);
-        pf_scores<D>(lds + (stage0 & (2 * NSL - 1)) * G::kStage, pl, st.qf, st.s);
+        if (own) pf_scores<D>(lds + (stage0 & (2 * NSL - 1)) * G::kStage, pl, st.qf, st.s);
         if (last == 0) {
 #pragma unroll
             for (int e = 0; e < 16; e++) {
@@ -625,7 +625,7 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
         const bool more = ahead > 0;
         if (more) {
             nown = unit_of(n1, nhead, nT);
-            load_q(n1, nhead, nT, qn);
+            if (nown) load_q(n1, nhead, nT, qn);
         }
         // every wave keeps the ring going for all the stages; it computes up to its own last stage: full steps, then
         // the step whose new scores cross the diagonal, then the step without new scores
@@ -636,18 +636,21 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     pf_step<D, MASK, NEXT>(st, lds + ((stage0 + s + 1) & (2 * NSL - 1)) * G::kStage,                                       \
                            lds_addr + ((stage0 + s) & (2 * NSL - 1)) * G::kStage + 2 * G::kTile, pl, a.scale_log2, 32 * (s + 1), row)
         int s = 0;
-        for (; s + 1 < last; s++) {
+        if (own) {
+            for (; s + 1 < last; s++) {
+                ring(s);
+                PF_STEP(false, true);
+            }
+            if (s + 1 == last) {
+                ring(s);
+                PF_STEP(true, true);
+                s++;
+            }
             ring(s);
-            PF_STEP(false, true);
-        }
-        if (s + 1 == last) {
-            ring(s);
-            PF_STEP(true, true);
+            PF_STEP(false, false);
             s++;
         }
-        ring(s);
-        PF_STEP(false, false);
-        for (s++; s < nst; s++) ring(s);
+        for (; s < nst; s++) ring(s);
 #undef PF_STEP
 
         // the next block's query rows take their place
@@ -664,42 +667,44 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
             ahead--, lb--;
         }
 
-        // a row's sum is spread over its two lanes
-        float l;
-        {
-            const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(st.lsum), __float_as_uint(st.lsum), false, false);
-            l = __uint_as_float(r[0]) + __uint_as_float(r[1]);
-        }
-        const float inv = 1.0f / l;
-        const int64_t rh = (int64_t)(t0 + row) * a.Hq + dhead;
-        // Results go through the wave's staging area, 64 d (128 bytes of every row) at a time: a lane holds four consecutive
-        // d of its own row per accumulator quarter, and storing from there is 32 separate pieces of 16 bytes per
-        // instruction, which keeps the compute unit's one memory pipeline busy for microseconds per block; read back eight
-        // lanes to a row, an instruction stores whole 128-byte lines.
-        int sl = lane;
-        asm volatile("" : "+v"(sl));
-        const int sn = sl & 31, sh = sl >> 5;
+        if (len > 0) {
+            // a row's sum is spread over its two lanes
+            float l;
+            {
+                const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(st.lsum), __float_as_uint(st.lsum), false, false);
+                l = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+            }
+            const float inv = 1.0f / l;
+            const int64_t rh = (int64_t)(t0 + row) * a.Hq + dhead;
+            // Results go through the wave's staging area, 64 d (128 bytes of every row) at a time: a lane holds four consecutive
+            // d of its own row per accumulator quarter, and storing from there is 32 separate pieces of 16 bytes per
+            // instruction, which keeps the compute unit's one memory pipeline busy for microseconds per block; read back eight
+            // lanes to a row, an instruction stores whole 128-byte lines.
+            int sl = lane;
+            asm volatile("" : "+v"(sl));
+            const int sn = sl & 31, sh = sl >> 5;
 #pragma unroll
-        for (int p = 0; p < D / 64; p++) {
+            for (int p = 0; p < D / 64; p++) {
 #pragma unroll
-            for (int dtl = 0; dtl < 2; dtl++) {
+                for (int dtl = 0; dtl < 2; dtl++) {
 #pragma unroll
-                for (int j = 0; j < 4; j++) {
-                    f32x4 v;
+                    for (int j = 0; j < 4; j++) {
+                        f32x4 v;
 #pragma unroll
-                    for (int x = 0; x < 4; x++) v[x] = st.o[2 * p + dtl][4 * j + x] * inv; // d = 64 p + 32 dtl + 8 j + 4 hh + x
-                    *(bf16x4 *)(stage + kPfStageRow * sn + 16 * ((4 * dtl + j) ^ pf_stage_swz(sn)) + 8 * sh) = __builtin_convertvector(v, bf16x4);
+                        for (int x = 0; x < 4; x++) v[x] = st.o[2 * p + dtl][4 * j + x] * inv; // d = 64 p + 32 dtl + 8 j + 4 hh + x
+                        *(bf16x4 *)(stage + kPfStageRow * sn + 16 * ((4 * dtl + j) ^ pf_stage_swz(sn)) + 8 * sh) = __builtin_convertvector(v, bf16x4);
+                    }
+                }
+#pragma unroll
+                for (int m = 0; m < 4; m++) {
+                    const int r = 8 * m + (sl >> 3), c = sl & 7; // row of the tile, 16-byte piece of its 128 bytes
+                    const u32x4 v = *(const u32x4 *)(stage + kPfStageRow * r + 16 * (c ^ pf_stage_swz(r)));
+                    const int orow = tile_row + r;
+                    if (orow < len) *(u32x4 *)(a.out + ((int64_t)(t0 + orow) * a.Hq + dhead) * D + 64 * p + 8 * c) = v;
                 }
             }
-#pragma unroll
-            for (int m = 0; m < 4; m++) {
-                const int r = 8 * m + (sl >> 3), c = sl & 7; // row of the tile, 16-byte piece of its 128 bytes
-                const u32x4 v = *(const u32x4 *)(stage + kPfStageRow * r + 16 * (c ^ pf_stage_swz(r)));
-                const int orow = tile_row + r;
-                if (orow < len) *(u32x4 *)(a.out + ((int64_t)(t0 + orow) * a.Hq + dhead) * D + 64 * p + 8 * c) = v;
-            }
+            if (row < len && hh == 0) a.lse[rh] = (st.m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
         }
-        if (row < len && hh == 0) a.lse[rh] = (st.m + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
         if (!more) break;
     }
     wait_vmcnt<0>(); // nothing may land in LDS after the workgroup has left
@@ -739,9 +744,17 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     per_die = per_die < 1 ? 1 : per_die;
     if (a.stay > 0 && a.stay < per_die) per_die = a.stay; // fewer were asked for
     // blocks of a (prompt, kv head) and of a die, at most; blocks of the batch, about (by its tokens)
-    const int64_t per_pair = (rows / 32 * a.G + 7) / 8;
-    const int64_t blocks = heads * (a.num_prompts * (per_pair / share) + ((int64_t)a.num_prompts + share - 1) / share * (per_pair % share));
-    const int64_t about = ((int64_t)a.total_tokens + 31 * (int64_t)a.num_prompts) / 32 * a.Hq / 8;
+    // Units of a block: eight, or four where the compute units still get at most a block each (a die a quarter more by the
+    // bound): such a call lasts as long as its longest block, and four waves with a SIMD each take less time over it than
+    // eight that share (one prompt of 300 tokens, 28 heads on four, 14.4 -> 12.5 us; three of 700, six on three, 28.0 -> 24.9).
+    int64_t per_pair, blocks, about;
+    for (a.units_shift = 2;; a.units_shift++) {
+        a.units = 1 << a.units_shift;
+        per_pair = (rows / 32 * a.G + a.units - 1) / a.units;
+        blocks = heads * (a.num_prompts * (per_pair / share) + ((int64_t)a.num_prompts + share - 1) / share * (per_pair % share));
+        about = ((int64_t)a.total_tokens + 31 * (int64_t)a.num_prompts) / 32 * a.Hq / a.units;
+        if (a.units == kPfWaves || (about <= a.num_cus && 4 * blocks <= 5 * per_die)) break;
+    }
     a.levels = (int)((per_pair + share - 1) / share);
     a.magic_g = (uint32_t)((((uint64_t)1 << 32) + a.G - 1) / a.G);
     a.magic_heads = (uint32_t)((((uint64_t)1 << 32) + heads - 1) / heads);

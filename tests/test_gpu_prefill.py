@@ -371,6 +371,25 @@ def test_deal_of_many_and_of_few_prompts(dec, Hq, Hkv, D, n, longest):
     check_all(dec, b, "%d prompts, Hq=%d Hkv=%d" % (n, Hq, Hkv))
 
 
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("Hq,Hkv,D,lens", [(28, 4, 128, [1]), (28, 4, 128, [33, 95]), (8, 2, 64, [31, 0, 129]), (16, 1, 64, [200]),
+                                           (64, 8, 128, [100]), (4, 4, 64, [97, 5]), (5, 1, 128, [257])])
+def test_calls_of_few_blocks(dec, kv_dtype, Hq, Hkv, D, lens):
+    # so few that a block takes four (tile, head) units instead of eight where the library chooses: waves 4 to 7 have none, a
+    # last block one to three; the cache is written from the ring (four query heads per kv head and more) or not
+    b = workload.build_prefill("pf", Hq, Hkv, D, lens, seed=Hq + len(lens))
+    d = DevicePrefill(b, kv_dtype=kv_dtype)
+    dec.prefill(d.c)
+    compare(*d.results(), *oracle.prefill(b.q, b.k, b.v, b.cu_seqlens, b.softmax_scale), "few blocks, %s" % lens)
+    kp, vp, ks, vs = expected_pools(b, kv_dtype)
+    view = (lambda t: t.view(torch.int16).cpu().numpy().view(np.uint16)) if kv_dtype == "bf16" else (lambda t: t.cpu().numpy())
+    np.testing.assert_array_equal(view(d.k_pool), kp)
+    np.testing.assert_array_equal(view(d.v_pool), vp)
+    if kv_dtype != "bf16":
+        np.testing.assert_array_equal(d.k_scale.cpu().numpy().view(np.uint32), ks.view(np.uint32))
+        np.testing.assert_array_equal(d.v_scale.cpu().numpy().view(np.uint32), vs.view(np.uint32))
+
+
 def test_a_row_maximum_that_keeps_growing(dec):
     # the exponent's reference point follows the row maximum from a distance: keys whose scores grow by several powers of two
     # from stage to stage, past the float range of exp if the point stayed
