@@ -60,11 +60,13 @@ typedef enum { RA_KV_BF16 = 0, RA_KV_FP8_E4M3 = 1 } ra_kv_dtype;
 enum {
     RA_FLAG_VALIDATE = 1u,          /* check device-side lengths / page ids / hint first (one extra kernel + a
                                        stream synchronisation) */
-    RA_FLAG_NO_PREFIX_SHARING = 2u, /* ignore the prompt-group hint (for A/B comparison) */
+    RA_FLAG_NO_PREFIX_SHARING = 2u, /* ignore the prompt-group hint (for A/B comparison; the smallest batches, which have
+                                       no schedule, ignore it anyway: see ROLLOUT_ATTN_DIRECT) */
     RA_FLAG_REUSE_SCHEDULE = 4u     /* skip the schedule (its kernels for a large batch; for a smaller one, which the
                                        attention workgroups plan for themselves, their planning pass: each takes the
-                                       list it kept; the smallest have none) and use the schedule that the previous rollout_attn_decode call
-                                       without this flag on the same context left in the same workspace.
+                                       list it kept; the smallest have none) and use the schedule that the previous
+                                       rollout_attn_decode call without this flag on the same context left in the same
+                                       workspace.
                                        For the layers of one decode step: the schedule depends only on B, the head
                                        counts, D, max_pages_per_seq, seq_lens, seq_group, prefix_page_offsets and
                                        RA_FLAG_NO_PREFIX_SHARING, which must all be what they were in that call; q,
@@ -90,7 +92,7 @@ enum {
  * results: the first page_size * n_g tokens of every member of group g live in the n_g pages
  *   prefix_pages[prefix_page_offsets[g] .. prefix_page_offsets[g+1])
  * and the member's own block_table row starts with the same ids.  Those pages are then read once per
- * group instead of once per member.
+ * group instead of once per member (but in the smallest batches, which have no schedule).
  *   seq_group           int32 [B], group id in [0, num_groups) or -1 (no group).
  *   prefix_page_offsets int32 [num_groups + 1], non-decreasing, starts at 0.
  *   prefix_pages        int32 [prefix_page_offsets[num_groups]].

@@ -4,7 +4,7 @@
 //
 // Unlike the decode step this is a dense contraction, bound by the matrix cores.  A workgroup of eight waves
 // (two per SIMD, so that one wave's vector work runs while the other's MFMAs do) takes eight (32-row tile, head) units
-// of one (prompt, kv head), one per wave.  K and V stream through an LDS ring in chunks of two stages of 32
+// of one (prompt, kv head), one per wave (in calls of few blocks four).  K and V stream through an LDS ring in chunks of two stages of 32
 // keys (K0 K1 V0 V1 | K2 K3 V2 V3, one 16-key tile loaded by each wave with direct global->LDS loads); every wave
 // multiplies every stage with its own query rows, held in registers:
 //   S^T[key, row] = K . Q^T,   O^T[d, row] += V^T . P^T     (32x32x16 MFMA, fp32 accumulation)
@@ -15,7 +15,7 @@ namespace ra {
 
 constexpr int kPfWaves = 8;                  // waves per workgroup, two per SIMD
 constexpr int kPfRows = 32;                  // query rows per wave: one 32x32 MFMA tile
-constexpr int kPfBlock = kPfRows * kPfWaves; // query rows per workgroup
+constexpr int kPfBlock = kPfRows * kPfWaves; // rows a bound on the prompt length is rounded up to
 constexpr int kPfSlots = 4;                  // ring slots of one chunk (two stages of 32 keys) each
 
 constexpr int kPfStageRow = 128;                    // bytes of a row in a wave's staging area: 64 bf16
@@ -231,8 +231,8 @@ __device__ __forceinline__ void pf_scores(const uint8_t *k_stage, const PfLane<D
 }
 
 // A unit of work of a wave: one head's 32 query rows of one tile, with the keys 0 .. its last row.  The units of a
-// (prompt, kv head) pair are numbered from the last tile down, the G heads of a tile together, and a block is eight
-// consecutive ones: under the causal mask they need the same keys but for a tile or two, so the waves of a workgroup
+// (prompt, kv head) pair are numbered from the last tile down, the G heads of a tile together, and a block is eight (or
+// four: a.units) consecutive ones: under the causal mask they need the same keys but for a tile or two, so the waves of a workgroup
 // have the same work and leave the block together.  (A block of 256 rows of one head streams the keys of its last row
 // past all of its waves: 24 stages of 32 keys for the 512 rows of a head of a 512-token prompt, 18 this way, and half
 // of the waves idle at the end of it.)
@@ -467,6 +467,7 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     // c (before the first step that reads its K) says that every wave's loads of the chunk have landed and that
     // every wave has left the last step that read chunk c - 2, whose slot then takes chunk c + 2 (the first two
     // chunks are loaded up front).  Chunks are numbered over all blocks, so the same holds across a block's end.
+    //
     // The cache write, from the tiles that stream through the ring anyway (16 keys of a kv head: a page).  A stage's K and
     // V are written by the block that holds the first head's unit of the stage's tile, which spreads them evenly over the
     // blocks; wave w takes tile w of the chunk that has just been opened.
@@ -773,10 +774,11 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     const bool one_each = blocks <= per_die || (a.stay == 0 && blocks <= INT32_MAX / 16) ||
                           (a.stay < 0 && (few || uneven) && 2 * blocks <= about + per_die);
     // Prompts whose blocks are dealt together.  One workgroup per block: as many as there are, so that the longest blocks
-    // start first.  Else few enough for their K and V to stay in a die's 4 MB L2 while the die's workgroups share them, enough
-    // for an even deal of ragged lengths.  Measured with 64, 16, 8 and 4: 121.0, 115.5, 119.9, 131.3 us on 32 prompts of
-    // 512 tokens (seven heads per kv head), 1287, 1289, 1268, 1277 us on 16 of 2048 (eight), 28.7, 28.7, 28.7, 35.8 us on 8
-    // of 37 to 701.
+    // start first.  Else few, so that a die's workgroups share their K and V in its 4 MB L2, but enough for an even deal of
+    // ragged lengths: sixteen while those fit (512 tokens, D = 128, one head a die: exactly), eight above.  Measured with 64,
+    // 16 and 8: 116.5, 109.7, 122.9 us on 32 prompts of 512 tokens (28 heads on four), 198.7, 193.6, 204.3 on 256 of 64 to
+    // 256; 322.5, 314.3, 309.3 on 64 of 512 (40 on eight), 1301, 1294, 1279 on 16 of 2048 (64 on eight), 1148, 1124, 1108 on 32
+    // of 2048 (28 on four).
     a.group = one_each && !few ? 64 : (int64_t)16 * a.max_len * 4 * a.D * heads <= (4 << 20) ? 16 : 8;
     if (one_each) per_die = blocks;
     a.magic_wgs = (uint32_t)((((uint64_t)1 << 32) + per_die - 1) / per_die);

@@ -22,13 +22,13 @@ def compare(out, lse, ref_out, ref_lse, what=""):
     return compare_decode(out, lse, ref_out, ref_lse, what, abs_rel=OUT_ULP)
 
 
-@pytest.fixture(scope="module", params=["by prompt length", "one workgroup per block", "two workgroups per die that stay",
+@pytest.fixture(scope="module", params=["the library's choice", "one workgroup per block", "two workgroups per die that stay",
                                         "one per compute unit that stays"])
 def dec(request):
     """Every test runs in the launch shape the library picks and in each of those it can be told to use: the results must
     not depend on how the blocks of query rows are dealt to workgroups (the setting is read when the context is made)."""
     import os
-    value = {"by prompt length": None, "one workgroup per block": "0", "two workgroups per die that stay": "2",
+    value = {"the library's choice": None, "one workgroup per block": "0", "two workgroups per die that stay": "2",
              "one per compute unit that stays": "64"}[request.param]
     old = os.environ.get("ROLLOUT_ATTN_PREFILL_WGS_PER_DIE")
     if value is None:
