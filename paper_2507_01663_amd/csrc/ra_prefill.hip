@@ -346,12 +346,15 @@ template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch
         }
         return n * d.heads;
     };
+    // (A call of few blocks is so short that this counts where there is but one level to try: 0.3 us of 9.7 for 30 prompts of
+    // up to 19 tokens, eight heads; workgroups that stay would pay for the question.)
+    const bool flat = !STAY && a.levels == 1;
     int step = (a.levels + 63) >> 6;
     if (o >= c.before + c.blocks) { // another group of prompts
         c.lane0 = (__ffsll((long long)__ballot(c.sum * d.heads > o)) - 1) & -a.group;
         c.before = c.lane0 ? __builtin_amdgcn_readlane(c.sum, c.lane0 - 1) * d.heads : 0;
         c.blocks = __builtin_amdgcn_readlane(c.sum, c.lane0 + a.group - 1) * d.heads - c.before;
-        c.up = from_level(d.lane * step);
+        if (!flat) c.up = from_level(d.lane * step);
         // Every other group, if it starts in the middle of a round, runs from short to long: its first blocks go to the
         // workgroups that got the last and shortest ones of the group before.  (Turned about, a group of one round that
         // starts with a round would give its longest blocks to the workgroups that have just had the longest ones: 32
@@ -362,8 +365,8 @@ template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch
     }
     o -= c.before;
     if (c.turned) o = c.blocks - 1 - o;
-    int j = 0, up = c.up, left;
-    for (;;) {
+    int j = 0, up = c.up, left = c.blocks;
+    while (!flat) {
         const int k = __popcll(__ballot(up > o)) - 1;
         left = __builtin_amdgcn_readlane(up, k); // blocks of level j and up
         j += k * step;
