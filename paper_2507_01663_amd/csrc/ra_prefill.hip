@@ -747,11 +747,10 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     int64_t per_die = a.num_cus / 8;
     per_die = per_die < 1 ? 1 : per_die;
     if (a.stay > 0 && a.stay < per_die) per_die = a.stay; // fewer were asked for
-    // blocks of a (prompt, kv head) and of a die, at most; blocks of the batch, about (by its tokens)
     // Units of a block: eight, or four where the compute units still get at most a block each (a die a quarter more by the
     // bound): such a call lasts as long as its longest block, and four waves with a SIMD each take less time over it than
     // eight that share (one prompt of 300 tokens, 28 heads on four, 14.4 -> 12.5 us; three of 700, six on three, 28.0 -> 24.9).
-    int64_t per_pair, blocks, about;
+    int64_t per_pair, blocks, about; // blocks of a (prompt, kv head) and of a die, at most; of the batch, about (by its tokens)
     for (a.units_shift = 2;; a.units_shift++) {
         a.units = 1 << a.units_shift;
         per_pair = (rows / 32 * a.G + a.units - 1) / a.units;
