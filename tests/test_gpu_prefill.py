@@ -403,8 +403,8 @@ def test_a_row_maximum_that_keeps_growing(dec):
 
 def test_very_many_short_prompts_take_no_longer_than_their_data_warrants():
     """Which blocks a workgroup takes is worked out on the device from the prompts' lengths.  With 4096 prompts of a tile
-    each there is next to nothing to do for a block, so a search that walks the prompts shows: 870 us against 13 for a copy
-    of the queries when it did, 70 to 85 without (156 for a launch of 256-row blocks whose numbers are divided out).  The
+    each there is next to nothing to do for a block, so a search that walks the prompts shows: 870 us against 10 for a copy
+    of the queries when it did, 66 without (156 for a launch of 256-row blocks whose numbers are divided out).  The
     bound of 20 copies lies a factor of three from either."""
     n, Hq, D = 4096, 4, 64
     T = 16 * n
