@@ -60,8 +60,8 @@ typedef enum { RA_KV_BF16 = 0, RA_KV_FP8_E4M3 = 1 } ra_kv_dtype;
 enum {
     RA_FLAG_VALIDATE = 1u,          /* check device-side lengths / page ids / hint first (one extra kernel + a
                                        stream synchronisation) */
-    RA_FLAG_NO_PREFIX_SHARING = 2u, /* ignore the prompt-group hint (for A/B comparison; the smallest batches, which have
-                                       no schedule, ignore it anyway: see ROLLOUT_ATTN_DIRECT) */
+    RA_FLAG_NO_PREFIX_SHARING = 2u, /* ignore the prompt-group hint (for A/B comparison; batches that have no schedule
+                                       do not read shared pages once anyway: see ROLLOUT_ATTN_DIRECT) */
     RA_FLAG_REUSE_SCHEDULE = 4u     /* skip the schedule (its kernels for a large batch; for a smaller one, which the
                                        attention workgroups plan for themselves, their planning pass: each takes the
                                        list it kept; the smallest have none) and use the schedule that the previous
@@ -139,7 +139,9 @@ uint32_t rollout_attn_abi_version(void);
  *   ROLLOUT_ATTN_COST_ITEM_PREFIX=0..1024   ... of a segment of shared-prefix pages, whose partial result is
  *                                   written in mid-stream (default: 16 for bf16 pools, 48 for e4m3 pools)
  *   ROLLOUT_ATTN_DIRECT=0           every batch has a schedule (default: the smallest batches, by what their block
- *                                   table can address, are split by the table's width instead)
+ *                                   table can address, and batches of sequences that one compute unit streams in the
+ *                                   time of a schedule, by the table's width, take a workgroup or a fixed number of
+ *                                   them per sequence and kv head instead)
  *   ROLLOUT_ATTN_SELF_PLAN=0        a batch that has a schedule gets it from the schedule kernels (default: batches of
  *                                   up to 512 sequences and 511 groups are scheduled by the attention workgroups
  *                                   themselves, each for its own share of the work, which saves a kernel; the schedule

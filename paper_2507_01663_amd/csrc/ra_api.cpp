@@ -129,7 +129,7 @@ void fill_launch(ra::Launch &a, const ra_ctx *ctx, const ra_problem *p)
     a.out = (uint16_t *)p->out; a.lse = p->lse;
     a.zeros = ctx ? ctx->zeros : nullptr;
     a.self_plan = ctx && ctx->self_plan && ra::can_self_plan(a.D, a.kv_fp8, a.stages, a.B, a.share ? a.num_groups : 0, a.members_per_row);
-    a.splits = ctx && ctx->direct ? ra::direct_splits(a.B, a.Hkv, a.D, a.kv_fp8, a.max_pages, ctx->num_cus, a.waves) : 0;
+    if (ctx && ctx->direct) ra::direct_plan(a, ctx->num_cus);
     if (a.splits) a.self_plan = 1; // (no schedule kernel)
     a.reuse_lists = a.self_plan && (p->flags & RA_FLAG_REUSE_SCHEDULE) != 0;
 }

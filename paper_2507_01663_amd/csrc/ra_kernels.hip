@@ -715,11 +715,10 @@ __device__ __forceinline__ void issue_stage(const Launch &a, const LaneConst<D, 
 // Query rows of an own-pages segment: the G heads of (b, kvh) are contiguous in q; rows G..15 read zeros.
 template <int D, int KVB, int NST>
 __device__ __forceinline__ void issue_q(const Launch &a, const uint16_t *__restrict__ q, const LaneConst<D, KVB> &lc,
-                                        const Segment &sg, uint32_t lds_addr, int lane)
+                                        const Segment &sg, uint32_t q_addr, int lane)
 {
-    using M = LdsMap<D, KVB, NST>;
     const uint8_t *src = (const uint8_t *)(q + ((int64_t)sg.b * a.Hq + (int64_t)sg.kvh * a.G) * D);
-    const uint32_t dst = lds_addr + M::kQBase;
+    const uint32_t dst = q_addr;
     // the tile in LDS: 16 rows of D bf16, 16-byte units swizzled inside the row like a bf16 K tile (worked out here,
     // once per segment, rather than kept in registers through the stream)
     constexpr int QU = D * 2 / 16, QM = QU - 1;
@@ -784,7 +783,8 @@ __device__ __forceinline__ void issue_qrows(const Launch &a, const uint16_t *__r
 template <int D, int KVB, int NQT, int NST, int NP>
 __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__restrict__ q, const Segment &cur, bool has_nxt,
                                             const Segment &nxt, Ring &ring, const LaneConst<D, KVB> &lc, uint8_t *lds,
-                                            uint32_t lds_addr, Pending<D> &ret, Pending<D> (&pk)[NP], bool park, int lane)
+                                            uint32_t lds_addr, Pending<D> &ret, Pending<D> (&pk)[NP], bool park, int lane,
+                                            int q_off = LdsMap<D, KVB, NST>::kQBase)
 {
     static_assert(NQT == 1 || NQT <= NP, "a shared-prefix partial has a waiting register set per tile");
     using G = Geo<D, KVB>;
@@ -844,7 +844,7 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
             } else if (rel == niter && nxt_ql) {
                 issue_qrows<D, KVB, NST>(a, q, lc, nxt, ring.issued % NST, lds_addr);
             } else {
-                if (rel == niter) issue_q<D, KVB, NST>(a, q, lc, nxt, lds_addr, lane);
+                if (rel == niter) issue_q<D, KVB, NST>(a, q, lc, nxt, lds_addr + q_off, lane);
                 issue_stage<D, KVB, NST>(a, lc, nxt, rel - niter - nxt_ql, nid0, nid1, ring.issued % NST, lds_addr, lane);
             }
             ring.issued++;
@@ -857,7 +857,7 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
         // anything else is issued, because the next segment's may be (there is one slot).
         WaitTail<NST - 1, G::kDmaPerStage>::run(ring.issued - base);
 #pragma unroll
-        for (int i = 0; i < G::kKSteps; i++) qf[0][i] = *(const bf16x8 *)(lds + M::kQBase + lc.kq_off[i]);
+        for (int i = 0; i < G::kKSteps; i++) qf[0][i] = *(const bf16x8 *)(lds + q_off + lc.kq_off[i]);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     } else {
         // the first ring entry holds the query rows
@@ -1438,7 +1438,7 @@ template <int D, int KVB, int NST, int NPEND, bool SELF> __device__ __forceinlin
         bool has_cur = advance(cur);
         if (has_cur) {
             // prime the ring with the first segment
-            if (!cur.prefix) issue_q<D, KVB, NST>(a, q, lc, cur, lds_addr, ln);
+            if (!cur.prefix) issue_q<D, KVB, NST>(a, q, lc, cur, lds_addr + M::kQBase, ln);
             const int n = min(NST - 1, cur.entries());
             for (int k = 0; k < n; k++) {
                 const int st = k - cur.prefix;
@@ -1612,51 +1612,107 @@ __device__ __forceinline__ void merge_write(const Launch &a, int64_t bh, int d4,
 }
 
 // ------------------------------------------------------------------------------------------------------
-// Small batches: no schedule at all.
+// Batches without a schedule.
 //
-// What bounds a small step is the chain of dependent trips, not bytes: planning (7 us: rows, cut, list) and the merge of
-// many short spans (4 to 10 us and a launch) took most of the 33 us of a step over eight sequences of 500 to 2000 tokens.
-// Here a workgroup of four waves takes one (sequence, kv head), or a fixed part of it, straight from the block table: its
-// waves stream equal numbers of stages and meet in LDS.  With one workgroup per item that is the whole step (one kernel);
-// otherwise the workgroups' partials go to the merge kernels like spans do.  The split is by the table's width (the host
-// does not know the lengths), and shared prompt pages are read once per member, from the caches mostly: so this is for
-// batches whose pages take little longer than planning even if every sequence were as long as the table is wide.  (A
-// caller whose table has one width for all steps, wide enough for the longest response, is scheduled however short the
-// sequences are.)  With
-// more than a quarter as many items as compute units, one long sequence among short ones has few units: a lower bound.
+// A step over few pages, or over sequences that one compute unit streams in the time a schedule takes, is a chain of trips,
+// not a stream: planning (7 us: rows, cut, list; 15 and a launch beyond 512 sequences) and the merge (5 us and a launch)
+// were half of a step of 64 sequences of 300 to 1500 tokens.  Here a workgroup takes one (sequence, kv head), or a fixed
+// part of it, straight from the block table: its waves stream equal numbers of stages and meet in LDS.  With one workgroup
+// per item that is the whole step (one kernel); otherwise the workgroups' partials go to the merge kernels like spans do.
+// The hardware deals the workgroups out, so what bounds a call is its longest item (one compute unit streams bf16 pages of
+// 128 at 66 B/ns, e4m3 ones at 33 with four waves and 55 with eight: the waves' arithmetic) or the whole stream, whichever
+// is longer.  The host knows the table's width, not the lengths, so the rules (direct_plan) are by width.  (A caller whose
+// table has one width for all steps, wide enough for the longest response, is scheduled however short the sequences are.)
+// Shared prompt pages are read once per member, from the caches mostly.
+//
+// Waves: as many rings as fit, eight, where a wave's arithmetic bounds it (e4m3, or head dim 64) and the items are few: 64
+// sequences of four kv heads, e4m3, D = 128, one of them 3072 tokens, 27.0 us with four and 20.4 with eight; all full 33 and
+// 34.  Four, and more workgroups to a compute unit, where there are more items or short ones: 100 such sequences of 1024
+// tokens 26.6 with eight, 21.8 with four.
+//
 // Measured (MI355X, scheduled -> here, us a step): four sequences of up to 256 tokens, D = 64: 15.7 -> 6.5; eight of one
-// prompt, 500 to 2000, D = 128: 33.4 -> 10.7; 256 items of up to 256 tokens, D = 128: 19 -> 7; 1024 items of 32 tokens,
-// D = 128: 20 -> 14, D = 64: 18 -> 8; 8 to 64 items whose table addresses 80 MB: all full 25 to 28 -> 19 (bf16), 28 to 32
-// -> 20 (e4m3), all but one of them short 19 to 22 -> 13 (bf16), 20 to 26 -> 17 (e4m3); 128 MB: 33 to 36 -> 26 and 20 to
-// 25 -> 17 (bf16), but 20 -> 23 where one of 64 e4m3 items is long.
+// prompt, 500 to 2000, D = 128: 33.4 -> 10.7; 64 of U[0, 1536], 28 heads on four, bf16: 28.5 -> 21.6 (all full 42 -> 32, one
+// long 20.1 -> 16.1); 100 of U[0, 3072], e4m3: 40 -> 33; 300 of U[0, 1024], eight heads on two, D = 64, bf16: 24.4 -> 16.4;
+// 1024 of U[0, 1536], the same, e4m3: 59 -> 40; eight groups of eight, 300 + U[0, 1200], 28 on four, bf16: 35 -> 20.8.
 // ------------------------------------------------------------------------------------------------------
 
-constexpr int kDirectWaves = 4;                  // waves of a workgroup, one per SIMD
-constexpr int kDirectItems = 4;                  // items per compute unit at most (its LDS holds one workgroup to three)
-constexpr int64_t kDirectBytes = (int64_t)32 << 20;    // K and V that the batch's table can address, at most ...
-constexpr int64_t kDirectFewBytes = (int64_t)96 << 20; // ... and where every item has four compute units or more to itself
+// Batches that a schedule would not pay for even with every table row full: up to so many items per compute unit and bytes
+// of K and V that the table can address, more bytes while every item has four compute units or more to itself (8 to 64 items
+// whose table addresses 80 MB: all full 25 to 28 -> 19 us (bf16), 28 to 32 -> 20 (e4m3), all but one of them short 19 to 22
+// -> 13 (bf16), 20 to 26 -> 17 (e4m3); 128 MB: 33 to 36 -> 26 and 20 to 25 -> 17 (bf16), but 20 -> 23 where one of 64 e4m3
+// items is long).
+constexpr int kDirectItems = 4;
+constexpr int64_t kDirectBytes = (int64_t)32 << 20, kDirectFewBytes = (int64_t)96 << 20;
 constexpr int kDirectStages = 4;                 // stages of a wave up to which an item is not split over workgroups
+constexpr int kDirectSort = 512;                 // sequences that a wave can put in order, at most
 
-template <int D, int KVB> struct DirectLds {
-    using M = LdsMap<D, KVB, 2>;
-    static constexpr int kWave = M::kQBase + M::kQTile; // a wave's ring and query slot
-    static constexpr int kBytes = kDirectWaves * kWave;
-    static_assert(kWave % 256 == 0 && kPage * D * 4 + 64 <= M::kQBase, "a wave's partial fits its ring");
+template <int D, int KVB, int W> struct DirectLds {
+    using G = Geo<D, KVB>;
+    static constexpr int kWave = 2 * G::kStage;            // a wave's ring
+    static constexpr int kQBase = W * kWave;               // the query rows, one copy for all
+    static constexpr int kBytes = kQBase + kPage * D * 2;
+    static_assert(kWave % 256 == 0 && kPage * D * 4 + 64 <= kWave, "a wave's partial fits its ring");
 };
 
-template <int D, int KVB>
-__global__ __launch_bounds__(64 * kDirectWaves) void direct_kernel(Launch a, const uint16_t *__restrict__ q,
-                                                                   const int32_t *__restrict__ block_table)
+template <int D, int KVB, int W, bool SORTED>
+__global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t *__restrict__ q, const int32_t *__restrict__ block_table)
 {
-    using X = DirectLds<D, KVB>;
+    using X = DirectLds<D, KVB, W>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     touch_args(a);
-    const int item = blockIdx.x / a.splits, part = blockIdx.x - item * a.splits, b = item / a.Hkv, kvh = item - b * a.Hkv;
-    int L = uniform_load(a.seq_lens, b);
-    L = L < 0 ? 0 : (L > a.max_pages * kPage ? a.max_pages * kPage : L); // never walk past the table row
+    int item = blockIdx.x / a.splits;
+    const int part = blockIdx.x - item * a.splits;
+    // Workgroups are dealt to the dies by number: turned about in every eight, a pattern in the lengths meets all dies (256
+    // sequences of four kv heads, e4m3, every 16th of them 1536 tokens and the rest 96: 38 us as they come, 28 turned).  Not
+    // where prompts are shared: a group's members find its pages in their die's L2 (64 sequences in eight groups 20.8 us, turned 24.5).
+    if (a.splits == 1 && !a.share && item < (a.B * a.Hkv & ~7)) item = (item & ~7) | ((item + (item >> 3) + (item >> 6)) & 7);
+    int b = item / a.Hkv;
+    const int kvh = item - b * a.Hkv;
+    int L;
+    if (SORTED) {
+        // The b-th longest sequence, to within a sixteenth of the table's width (ties by number): a lane holds every 64th
+        // length, and the wave looks for the level by halves, then for the place inside it.
+        constexpr int N = kDirectSort / 64;
+        const int most = a.max_pages * kPage;
+        int len[N];
+#pragma unroll
+        for (int k = 0; k < N; k++) len[k] = 64 * k + lane < a.B ? a.seq_lens[64 * k + lane] : 0;
+#pragma unroll
+        for (int k = 0; k < N; k++) len[k] = 64 * k + lane >= a.B ? -1 : (len[k] < 0 ? 0 : (len[k] > most ? most : len[k]));
+        const int shift = max(0, 28 - __builtin_clz(most | 1));
+        int level = 0, above = 0; // ... and the sequences of higher levels
+#pragma unroll
+        for (int w = 8; w; w >>= 1) {
+            int c = 0; // sequences of level + w and up
+#pragma unroll
+            for (int k = 0; k < N; k++)
+                if (64 * k < a.B) c += __popcll(__ballot(len[k] >= (level + w) << shift));
+            if (c > b) level += w;
+            else above = c;
+        }
+        int r = b - above;
+        L = 0;
+#pragma unroll
+        for (int k = 0; k < N; k++) {
+            if (64 * k >= a.B || r < 0) continue;
+            const bool is = len[k] >= 0 && len[k] >> shift == level;
+            const unsigned long long m = __ballot(is);
+            const int c = __popcll(m);
+            if (r < c) {
+                const int l = __ffsll((long long)__ballot(is && __popcll(m & ((1ull << lane) - 1ull)) == r)) - 1;
+                b = 64 * k + l;
+                L = __builtin_amdgcn_readlane(len[k], l);
+            }
+            r -= c;
+        }
+        item = b * a.Hkv + kvh;
+    } else {
+        L = uniform_load(a.seq_lens, b);
+        L = L < 0 ? 0 : (L > a.max_pages * kPage ? a.max_pages * kPage : L); // never walk past the table row
+    }
     const int n = (L + kPage - 1) / kPage, nst = (n + 1) >> 1;
-    const int k = part * kDirectWaves + wave, all = a.splits * kDirectWaves;
+    const int k = part * W + wave, all = a.splits * W;
     uint8_t *const mine = lds + wave * X::kWave;
     const uint32_t mine_addr = (uint32_t)(uintptr_t)mine;
     Segment sg;
@@ -1674,11 +1730,13 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_kernel(Launch a, con
         LaneConst<D, KVB> lc;
         lane_setup<D, KVB>(lc, lane, a.stride_token_b);
         Ring ring = {0, 0};
-        issue_q<D, KVB, 2>(a, q, lc, sg, mine_addr, lane);
+        // (every wave brings the query rows, all to one place: the same bytes, so each needs to wait for its own loads only)
+        const int q_off = X::kQBase - wave * X::kWave;
+        issue_q<D, KVB, 2>(a, q, lc, sg, mine_addr + q_off, lane);
         const int id0 = uniform_load(sg.pages, sg.pg_lo), id1 = sg.pg_lo + 1 < sg.pg_hi ? uniform_load(sg.pages, sg.pg_lo + 1) : 0;
         issue_stage<D, KVB, 2>(a, lc, sg, 0, id0, id1, 0, mine_addr, lane);
         ring.issued++;
-        run_segment<D, KVB, 1, 2>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane);
+        run_segment<D, KVB, 1, 2>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane, q_off);
     }
     // every wave's partial into its own ring (nothing is in flight any more), then the workgroup adds them up
     {
@@ -1690,17 +1748,17 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_kernel(Launch a, con
     }
     __syncthreads();
     constexpr int TPR = D / 4;
-    for (int t = threadIdx.x; t < a.G * TPR; t += 64 * kDirectWaves) {
+    for (int t = threadIdx.x; t < a.G * TPR; t += 64 * W) {
         const int hl = t / TPR, d4 = (t % TPR) * 4;
-        float l[kDirectWaves], M = -INFINITY, wsum = 0.f;
-        f32x4 v[kDirectWaves], acc = {0.f, 0.f, 0.f, 0.f};
+        float l[W], M = -INFINITY, wsum = 0.f;
+        f32x4 v[W], acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < kDirectWaves; w++) {
+        for (int w = 0; w < W; w++) {
             const float *const o = (const float *)(lds + w * X::kWave);
             l[w] = o[kPage * D + hl];
             v[w] = *(const f32x4 *)(o + hl * D + d4);
         }
-        merge_add<kDirectWaves>(l, v, M, wsum, acc);
+        merge_add<W>(l, v, M, wsum, acc);
         if (a.splits == 1) {
             merge_write(a, (int64_t)b * a.Hq + kvh * a.G + hl, d4, M, wsum, acc);
         } else {
@@ -1717,40 +1775,91 @@ __global__ __launch_bounds__(64 * kDirectWaves) void direct_kernel(Launch a, con
     }
 }
 
+// Waves of a workgroup: eight where the items are long or just fill the chip (see above; eight rings of bf16 pages of 128 do
+// not fit), but more workgroups of four where an item gets four of them or more: 24 items of up to 2000 tokens, D = 128, e4m3,
+// 10.0 us with four waves, 11.5 with eight; 80 of 1024 10.2, 11.1; 80 of up to 4096 18.7, 17.4.
+static int direct_waves(int64_t items, int D, int kv_fp8, int max_pages, int num_cus)
+{
+    if ((!kv_fp8 && D == 128) || 4 * items <= num_cus) return 4;
+    const int stages = (max_pages + 1) / 2;
+    const int64_t side = (int64_t)(kv_fp8 && D == 64 ? 2 : 1) * num_cus; // workgroups of eight that run side by side
+    return (items <= num_cus && stages > (2 * items > num_cus ? 12 : 32)) || (items <= 2 * side && stages > 48) ? 8 : 4;
+}
+// Workgroups per item: as many as run side by side, with two stages for a wave, and what the workspace has room for.
+static int direct_share(int64_t items, int per_wave, int num_cus, int waves)
+{
+    if (per_wave <= kDirectStages) return 1;
+    int64_t s = num_cus / items;
+    if (s > (per_wave + 1) / 2) s = (per_wave + 1) / 2;
+    if (items * (s - 1) > waves) s = 1 + waves / items;
+    return s < 1 ? 1 : (int)s;
+}
+
 int direct_splits(int B, int Hkv, int D, int kv_fp8, int max_pages, int num_cus, int waves)
 {
     const int64_t items = (int64_t)B * Hkv;
     if (items < 1 || max_pages < 1) return 0;
     const int64_t bytes = items * max_pages * (2 * kPage * D * (kv_fp8 ? 1 : 2));
     if (items > kDirectItems * num_cus || bytes > (4 * items <= num_cus ? kDirectFewBytes : kDirectBytes)) return 0;
-    const int per_wave = ((max_pages + 1) / 2 + kDirectWaves - 1) / kDirectWaves;
-    if (per_wave <= kDirectStages) return 1;
-    int64_t s = num_cus / items;                         // workgroups that run side by side
-    if (s > (per_wave + 1) / 2) s = (per_wave + 1) / 2;  // two stages for a wave
-    if (items * (s - 1) > waves) s = 1 + waves / items;  // what the workspace has room for
-    return s < 1 ? 1 : (int)s;
+    const int W = direct_waves(items, D, kv_fp8, max_pages, num_cus);
+    return direct_share(items, ((max_pages + 1) / 2 + W - 1) / W, num_cus, waves);
 }
+
+void direct_plan(Launch &a, int num_cus)
+{
+    a.splits = a.sorted = 0;
+    const int64_t items = (int64_t)a.B * a.Hkv;
+    if (items < 1 || a.max_pages < 1) return;
+    const bool big = !a.kv_fp8 && a.D == 128;
+    const int W = direct_waves(items, a.D, a.kv_fp8, a.max_pages, num_cus), per_wave = ((a.max_pages + 1) / 2 + W - 1) / W;
+    a.direct_waves = W;
+    a.splits = direct_splits(a.B, a.Hkv, a.D, a.kv_fp8, a.max_pages, num_cus, a.waves);
+    if (!a.splits) {
+        // Larger batches of items that their workgroups stream in the time of a schedule and a merge: one long item among short
+        // ones lasts as long as those alone.  A workgroup to an item: up to twelve stages a wave (sixteen of the half as large
+        // ones of head dim 64): one of 64 sequences of 28 heads on four, bf16: 12 stages (1536 tokens) 20.1 us scheduled, 16.1
+        // here; 15 20.4, 19.6; 24 21, 28.  Several, and the merge: up to eight, e4m3 and bf16 alike (16 sequences of eight
+        // heads, e4m3, U[0, 4096], 24.5 us, 21.7, all full 33, 27, one long 19.1, 19.1; twice the length 36, 36, 56, 47, 19.8,
+        // 28.9; 30 of 28 heads on four, bf16, eight stages: 23.8, 18.4, full 32, 24, one long 20.3, 15.4).
+        // Beyond four rounds of workgroups (sixteen where a compute unit holds several) their starts add up: 500 sequences of
+        // eight kv heads, bf16, U[0, 1536]: 261 us, 250, but one long among short 39, 55.
+        const int splits = direct_share(items, per_wave, num_cus, a.waves), longest = (per_wave + splits - 1) / splits;
+        if (longest > (splits > 1 ? 8 : a.D == 64 ? 16 : 12) || items > (int64_t)(big ? 4 : 16) * num_cus) return;
+        // Every member of a group reads the shared pages here: all in all no more than the caches take, and not where the merge
+        // comes on top.  16 groups of 8, 512 + U[0, 500], 40 heads on eight, bf16 (528 MB at most) 39 us scheduled, 43 here; 32
+        // of 8, 512 + U[0, 100], 28 on four (318 MB) 42, 40; 16 of 8, 1024 + U[0, 100] (293 MB) 38, 31.  e4m3: 688 MB 56, 63;
+        // 369 MB 59, 46.
+        const int64_t bytes = items * a.max_pages * (2 * kPage * a.D * (a.kv_fp8 ? 1 : 2));
+        if (a.share && (splits > 1 || bytes > (int64_t)(a.kv_fp8 ? 480 : 320) << 20)) return;
+        a.splits = splits;
+    }
+    // The longest first, where a workgroup takes items one after the other and they are long enough for it: working the order
+    // out takes 1.1 us of every workgroup.  100 sequences of 28 heads on four, bf16, U[0, 1536]: 34 us as they come, 29.6 in
+    // order; all full 52, 55; 512 tokens at most (four stages a wave) 16.2, 15.6 and 21.3, 23.6.  (Groups stay together.)
+    const int64_t side = (int64_t)(big ? 1 : a.D == 128 ? 8 / W : (a.kv_fp8 ? 16 : 8) / W) * num_cus;
+    a.sorted = a.splits == 1 && !a.share && items > side && a.B <= kDirectSort && per_wave > 6;
+}
+
+#define RA_DIRECT_KERNELS_OF(X, S) X(128, 2, 4, S) X(128, 1, 4, S) X(128, 1, 8, S) X(64, 2, 4, S) X(64, 2, 8, S) X(64, 1, 4, S) X(64, 1, 8, S)
+#define RA_DIRECT_KERNELS(X) RA_DIRECT_KERNELS_OF(X, false) RA_DIRECT_KERNELS_OF(X, true)
 
 static hipError_t launch_direct(const Launch &a, hipStream_t s)
 {
-#define RA_DIRECT(DD, KVB) hipLaunchKernelGGL((direct_kernel<DD, KVB>), dim3(a.B * a.Hkv * a.splits), dim3(64 * kDirectWaves), (DirectLds<DD, KVB>::kBytes), s, a, a.q, a.block_table)
-    if (a.D == 128) {
-        if (a.kv_fp8) RA_DIRECT(128, 1);
-        else RA_DIRECT(128, 2);
-    } else {
-        if (a.kv_fp8) RA_DIRECT(64, 1);
-        else RA_DIRECT(64, 2);
-    }
+#define RA_DIRECT(DD, KVB, W, S)                                                                                          \
+    if (a.D == DD && a.kv_fp8 == (KVB == 1) && a.direct_waves == W && (a.sorted != 0) == S)                               \
+        hipLaunchKernelGGL((direct_kernel<DD, KVB, W, S>), dim3(a.B * a.Hkv * a.splits), dim3(64 * W), (DirectLds<DD, KVB, W>::kBytes), s, a, a.q, a.block_table);
+    RA_DIRECT_KERNELS(RA_DIRECT)
 #undef RA_DIRECT
     return hipGetLastError();
 }
 
 hipError_t direct_config()
 {
-    hipError_t e = hipFuncSetAttribute((const void *)direct_kernel<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<128, 2>::kBytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)direct_kernel<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<128, 1>::kBytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)direct_kernel<64, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<64, 2>::kBytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)direct_kernel<64, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<64, 1>::kBytes);
+    hipError_t e = hipSuccess;
+#define RA_DIRECT(DD, KVB, W, S)                                                                                          \
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)direct_kernel<DD, KVB, W, S>, hipFuncAttributeMaxDynamicSharedMemorySize, DirectLds<DD, KVB, W>::kBytes);
+    RA_DIRECT_KERNELS(RA_DIRECT)
+#undef RA_DIRECT
     return e;
 }
 

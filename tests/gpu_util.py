@@ -30,8 +30,9 @@ def context(**env):
 
 
 def scheduled(dec, p):
-    """Whether a decode step of this problem has a schedule (the smallest batches have none), by the library's own rule:
-    the function is no entry point of the C ABI, so it is called by the name the compiler gave it."""
+    """Whether a decode step of this problem has a schedule as far as the rule for the smallest batches goes (larger ones of
+    short sequences may go without one too: tests/test_gpu_direct.py), by the library's own function: it is no entry point
+    of the C ABI, so it is called by the name the compiler gave it."""
     if str(getattr(dec, "settings", {}).get("DIRECT", 1)) == "0":
         return True
     fp8 = p.kv_dtype != "bf16"
