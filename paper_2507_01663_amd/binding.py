@@ -320,7 +320,9 @@ class Decoder:
         self.device_ordinal = device_ordinal
         self.ctx = rollout_attn_create(device_ordinal)
         self._ws = None
+        self._ws_ptr, self._ws_bytes = None, 0
         self._retired = []
+        self._raw_stream = None
 
     def close(self):
         if self.ctx is not None:
@@ -329,6 +331,7 @@ class Decoder:
             rollout_attn_destroy(self.ctx)
             self.ctx = None
             self._ws = None
+            self._ws_ptr, self._ws_bytes = None, 0
             self._retired = []
 
     def __del__(self):
@@ -344,20 +347,37 @@ class Decoder:
             if self._ws is not None:
                 self._retired.append(self._ws)
             self._ws = torch.empty(need, dtype=torch.uint8, device="cuda:%d" % self.device_ordinal)
+            self._ws_ptr, self._ws_bytes = self._ws.data_ptr(), need
         return self._ws
+
+    def _hip_stream(self, stream):
+        """The hipStream_t of the given (or the current) torch stream."""
+        if stream is not None:
+            return stream.cuda_stream
+        if self._raw_stream is None:
+            # (a stream object costs a microsecond a call, as much as a small step has host time to spare; the first call
+            # makes one, which also sets torch's device side up)
+            import torch
+            torch.cuda.current_stream(self.device_ordinal)
+            self._raw_stream = torch._C._cuda_getCurrentRawStream
+        return self._raw_stream(self.device_ordinal)
 
     def decode(self, problem, stream=None):
         """Enqueues one decode step on the given (or the current) torch stream."""
-        import torch
+        s = self._hip_stream(stream)
+        if self._ws is not None:
+            # the library knows what the step needs and enqueues nothing in a workspace that is too small
+            status = load_library().rollout_attn_decode(self.ctx, problem, self._ws_ptr, self._ws_bytes, s)
+            if status == RA_OK:
+                return
+            if status != RA_ERR_WORKSPACE_TOO_SMALL:
+                _check(status, self.ctx)
         ws = self.workspace(problem)
-        s = stream if stream is not None else torch.cuda.current_stream(self.device_ordinal)
-        rollout_attn_decode(self.ctx, problem, ctypes.c_void_p(ws.data_ptr()), ws.numel(), ctypes.c_void_p(s.cuda_stream))
+        rollout_attn_decode(self.ctx, problem, ctypes.c_void_p(ws.data_ptr()), ws.numel(), ctypes.c_void_p(s))
 
     def decode_static(self, problem, stream=None):
         """The same step on the library's built-in workspace (no allocation anywhere)."""
-        import torch
-        s = stream if stream is not None else torch.cuda.current_stream(self.device_ordinal)
-        rollout_attn_decode_static(self.ctx, problem, ctypes.c_void_p(s.cuda_stream))
+        _check(load_library().rollout_attn_decode_static(self.ctx, problem, self._hip_stream(stream)), self.ctx)
 
     def schedule(self, problem, stream=None):
         """Runs only the schedule; returns (ra_schedule_info, the workspace tensor it was written to)."""
@@ -369,15 +389,13 @@ class Decoder:
 
     def append(self, problem, k_new, v_new, stream=None):
         """Enqueues the KV append of one token per sequence (k_new, v_new: bf16 tensors [B, Hkv, D])."""
-        import torch
-        s = stream if stream is not None else torch.cuda.current_stream(self.device_ordinal)
-        rollout_attn_append(self.ctx, problem, _ptr(k_new), _ptr(v_new), ctypes.c_void_p(s.cuda_stream))
+        s = self._hip_stream(stream)
+        _check(load_library().rollout_attn_append(self.ctx, problem, None if k_new is None else k_new.data_ptr(),
+                                                  None if v_new is None else v_new.data_ptr(), s), self.ctx)
 
     def prefill(self, prefill, stream=None):
         """Enqueues the prompts' causal attention (and the cache write, if the ra_prefill names pools)."""
-        import torch
-        s = stream if stream is not None else torch.cuda.current_stream(self.device_ordinal)
-        rollout_attn_prefill(self.ctx, prefill, ctypes.c_void_p(s.cuda_stream))
+        _check(load_library().rollout_attn_prefill(self.ctx, prefill, self._hip_stream(stream)), self.ctx)
 
     def debug_gather(self, problem, b, kv_head, k_out, v_out, stream=None):
         import torch
