@@ -1783,13 +1783,13 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
 
 // Waves of a workgroup: eight where the items are long or just fill the chip (see above; eight rings of bf16 pages of 128 do
 // not fit), but more workgroups of four where an item gets four of them or more: 24 items of up to 2000 tokens, D = 128, e4m3,
-// 10.0 us with four waves, 11.5 with eight; 80 of 1024 10.2, 11.1; 80 of up to 4096 18.7, 17.4.
+// 10.0 us with four waves, 11.5 with eight; 80 of 1024 10.2, 11.1; 80 of up to 4096 18.7, 17.4; 256 of 512 (16 stages) 7.9, 8.3.
 static int direct_waves(int64_t items, int D, int kv_fp8, int max_pages, int num_cus)
 {
     if ((!kv_fp8 && D == 128) || 4 * items <= num_cus) return 4;
     const int stages = (max_pages + 1) / 2;
     const int64_t side = (int64_t)(kv_fp8 && D == 64 ? 2 : 1) * num_cus; // workgroups of eight that run side by side
-    return (items <= num_cus && stages > (2 * items > num_cus ? 12 : 32)) || (items <= 2 * side && stages > 48) ? 8 : 4;
+    return (items <= num_cus && stages > (2 * items > num_cus ? 20 : 32)) || (items <= 2 * side && stages > 48) ? 8 : 4;
 }
 // Workgroups per item: as many as run side by side, with two stages for a wave, and what the workspace has room for.
 static int direct_share(int64_t items, int per_wave, int num_cus, int waves)
