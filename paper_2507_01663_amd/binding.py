@@ -320,7 +320,7 @@ class Decoder:
         self.device_ordinal = device_ordinal
         self.ctx = rollout_attn_create(device_ordinal)
         self._ws = None
-        self._ws_ptr, self._ws_bytes = None, 0
+        self._ws_at = None           # its address and size, always those of one tensor
         self._retired = []
         self._raw_stream = None
 
@@ -330,8 +330,7 @@ class Decoder:
             torch.cuda.synchronize(self.device_ordinal)      # nothing enqueued may outlive the buffers
             rollout_attn_destroy(self.ctx)
             self.ctx = None
-            self._ws = None
-            self._ws_ptr, self._ws_bytes = None, 0
+            self._ws = self._ws_at = None
             self._retired = []
 
     def __del__(self):
@@ -347,7 +346,7 @@ class Decoder:
             if self._ws is not None:
                 self._retired.append(self._ws)
             self._ws = torch.empty(need, dtype=torch.uint8, device="cuda:%d" % self.device_ordinal)
-            self._ws_ptr, self._ws_bytes = self._ws.data_ptr(), need
+            self._ws_at = (self._ws.data_ptr(), need)
         return self._ws
 
     def _hip_stream(self, stream):
@@ -365,9 +364,10 @@ class Decoder:
     def decode(self, problem, stream=None):
         """Enqueues one decode step on the given (or the current) torch stream."""
         s = self._hip_stream(stream)
-        if self._ws is not None:
+        at = self._ws_at             # (read once: another thread's call may put a larger one there)
+        if at is not None:
             # the library knows what the step needs and enqueues nothing in a workspace that is too small
-            status = load_library().rollout_attn_decode(self.ctx, problem, self._ws_ptr, self._ws_bytes, s)
+            status = load_library().rollout_attn_decode(self.ctx, problem, at[0], at[1], s)
             if status == RA_OK:
                 return
             if status != RA_ERR_WORKSPACE_TOO_SMALL:

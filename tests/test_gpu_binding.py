@@ -28,7 +28,7 @@ def test_workspace_grows_with_the_problems():
         d.decode(dp.c)
         got = results(dp)
         assert torch.equal(got[0], w[0]) and torch.equal(got[1], w[1])
-        assert d.workspace(dp.c).data_ptr() == d._ws_ptr and d._ws_bytes >= ra.rollout_attn_workspace_size(d.ctx, dp.c)
+        assert d.workspace(dp.c) is d._ws and d._ws.data_ptr() == d._ws_at[0] and d._ws.numel() >= ra.rollout_attn_workspace_size(d.ctx, dp.c)
     assert len(d._retired) == 1                      # the one that was too small, and nothing since
     large.c.D = 96
     for _ in range(2):
