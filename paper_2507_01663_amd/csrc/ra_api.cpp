@@ -129,7 +129,10 @@ void fill_launch(ra::Launch &a, const ra_ctx *ctx, const ra_problem *p)
     a.out = (uint16_t *)p->out; a.lse = p->lse;
     a.zeros = ctx ? ctx->zeros : nullptr;
     a.self_plan = ctx && ctx->self_plan && ra::can_self_plan(a.D, a.kv_fp8, a.stages, a.B, a.share ? a.num_groups : 0, a.members_per_row);
-    if (ctx && ctx->direct) ra::direct_plan(a, ctx->num_cus);
+    if (ctx && ctx->direct) {
+        const ra::DirectPlan d = ra::direct_plan(a.B, a.Hkv, a.G, a.D, a.kv_fp8, a.max_pages, a.share, ctx->num_cus, a.waves);
+        a.splits = d.splits; a.direct_waves = d.waves; a.sorted = d.sorted; a.turned = d.turned;
+    }
     if (a.splits) a.self_plan = 1; // (no schedule kernel)
     a.reuse_lists = a.self_plan && (p->flags & RA_FLAG_REUSE_SCHEDULE) != 0;
 }

@@ -60,8 +60,8 @@ struct Launch {
     float *lse;
     const void *zeros;                    // >= 16 bytes of zeros
     int32_t self_plan;                    // the attention waves plan their spans themselves: no schedule kernel
-    int32_t splits;                       // > 0: no schedule: workgroups per (sequence, kv head)
-    int32_t direct_waves, sorted;         // ... their waves, and whether the longest sequences come first
+    int32_t splits;                       // > 0: no schedule (see DirectPlan): workgroups per (sequence, kv head)
+    int32_t direct_waves, sorted, turned; // ... their waves, and the order they come in
     int32_t reuse_lists;                  // ... and take the lists that an earlier call's waves kept in the workspace
     Workspace ws;
 };
@@ -105,11 +105,13 @@ size_t carve_workspace(Workspace &ws, void *base, int B, int Hkv, int G, int D, 
 // launch on the current device, for head dim D: as many as are resident at once (bf16 pools: one per SIMD; e4m3 pools:
 // up to two per SIMD, as many as the ring's LDS lets in).
 hipError_t attention_config(int D, int kv_fp8, int num_cus, int *stages, int *waves);
-// Workgroups per (sequence, kv head) of a batch so small that a schedule would not pay even if every sequence were as long
-// as the table is wide; 0: it is not.
-int direct_splits(int B, int Hkv, int D, int kv_fp8, int max_pages, int num_cus, int waves);
-// Whether and how a batch, one of those or another, goes without a schedule: sets splits (0: it does not), direct_waves, sorted.
-void direct_plan(Launch &a, int num_cus);
+// Whether and how a batch goes without a schedule: workgroups per (sequence, kv head) (0: it has a schedule), waves of a
+// workgroup, whether the longest sequences come first and whether workgroups are turned about over the dies.  share: its
+// groups' hint is in use.
+struct DirectPlan {
+    int32_t splits, waves, sorted, turned;
+};
+DirectPlan direct_plan(int B, int Hkv, int G, int D, int kv_fp8, int max_pages, int share, int num_cus, int waves);
 hipError_t direct_config(); // once per device, before the first such launch
 // Whether a batch's schedule tables fit in the LDS of an attention wave (then no schedule kernel is needed).
 bool can_self_plan(int D, int kv_fp8, int stages, int B, int num_groups, int members_per_row);

@@ -1672,7 +1672,7 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
     // Workgroups are dealt to the dies by number: turned about in every eight, a pattern in the lengths meets all dies (256
     // sequences of four kv heads, e4m3, every 16th of them 1536 tokens and the rest 96: 38 us as they come, 28 turned).  Not
     // where prompts are shared: a group's members find its pages in their die's L2 (64 sequences in eight groups 20.8 us, turned 24.5).
-    if (a.splits == 1 && !a.share && item < (a.B * a.Hkv & ~7)) item = (item & ~7) | ((item + (item >> 3) + (item >> 6)) & 7);
+    if (a.turned && item < (a.B * a.Hkv & ~7)) item = (item & ~7) | ((item + (item >> 3) + (item >> 6)) & 7);
     int b = item / a.Hkv;
     const int kvh = item - b * a.Hkv;
     int L;
@@ -1801,26 +1801,22 @@ static int direct_share(int64_t items, int per_wave, int num_cus, int waves)
     return s < 1 ? 1 : (int)s;
 }
 
-int direct_splits(int B, int Hkv, int D, int kv_fp8, int max_pages, int num_cus, int waves)
+DirectPlan direct_plan(int B, int Hkv, int G, int D, int kv_fp8, int max_pages, int share, int num_cus, int waves)
 {
+    DirectPlan p = {0, 0, 0, 0};
     const int64_t items = (int64_t)B * Hkv;
-    if (items < 1 || max_pages < 1) return 0;
+    if (items < 1 || max_pages < 1) return p;
+    const bool big = !kv_fp8 && D == 128;
     const int64_t bytes = items * max_pages * (2 * kPage * D * (kv_fp8 ? 1 : 2));
-    if (items > kDirectItems * num_cus || bytes > (4 * items <= num_cus ? kDirectFewBytes : kDirectBytes)) return 0;
-    const int W = direct_waves(items, D, kv_fp8, max_pages, num_cus);
-    return direct_share(items, ((max_pages + 1) / 2 + W - 1) / W, num_cus, waves);
-}
-
-void direct_plan(Launch &a, int num_cus)
-{
-    a.splits = a.sorted = 0;
-    const int64_t items = (int64_t)a.B * a.Hkv;
-    if (items < 1 || a.max_pages < 1) return;
-    const bool big = !a.kv_fp8 && a.D == 128;
-    const int W = direct_waves(items, a.D, a.kv_fp8, a.max_pages, num_cus), per_wave = ((a.max_pages + 1) / 2 + W - 1) / W;
-    a.direct_waves = W;
-    a.splits = direct_splits(a.B, a.Hkv, a.D, a.kv_fp8, a.max_pages, num_cus, a.waves);
-    if (!a.splits) {
+    const bool small = items <= kDirectItems * num_cus && bytes <= (4 * items <= num_cus ? kDirectFewBytes : kDirectBytes);
+    const int W = direct_waves(items, D, kv_fp8, max_pages, num_cus), per_wave = ((max_pages + 1) / 2 + W - 1) / W;
+    const int splits = direct_share(items, per_wave, num_cus, waves), longest = (per_wave + splits - 1) / splits;
+    const int64_t side = (int64_t)(big ? 1 : D == 128 ? 8 / W : (kv_fp8 ? 16 : 8) / W) * num_cus; // workgroups that run side by side
+    // The longest first, where a workgroup takes items one after the other and they are long enough for it: working the order
+    // out takes 1.1 us of every workgroup.  100 sequences of 28 heads on four, bf16, U[0, 1536]: 34 us as they come, 29.6 in
+    // order; all full 52, 55; 512 tokens at most (four stages a wave) 16.2, 15.6 and 21.3, 23.6.  (Groups stay together.)
+    const bool sorted = splits == 1 && !share && items > side && B <= kDirectSort && per_wave > 6;
+    if (!small) {
         // Larger batches of items that their workgroups stream in the time of a schedule and a merge: one long item among short
         // ones lasts as long as those alone.  A workgroup to an item: up to twelve stages a wave (sixteen of the half as large
         // ones of head dim 64): one of 64 sequences of 28 heads on four, bf16: 12 stages (1536 tokens) 20.1 us scheduled, 16.1
@@ -1829,21 +1825,18 @@ void direct_plan(Launch &a, int num_cus)
         // 28.9; 30 of 28 heads on four, bf16, eight stages: 23.8, 18.4, full 32, 24, one long 20.3, 15.4).
         // Beyond four rounds of workgroups (sixteen where a compute unit holds several) their starts add up: 500 sequences of
         // eight kv heads, bf16, U[0, 1536]: 261 us, 250, but one long among short 39, 55.
-        const int splits = direct_share(items, per_wave, num_cus, a.waves), longest = (per_wave + splits - 1) / splits;
-        if (longest > (splits > 1 ? 8 : a.D == 64 ? 16 : 12) || items > (int64_t)(big ? 4 : 16) * num_cus) return;
+        if (longest > (splits > 1 ? 8 : D == 64 ? 16 : 12) || items > (int64_t)(big ? 4 : 16) * num_cus) return p;
         // Every member of a group reads the shared pages here: all in all no more than the caches take, and not where the merge
         // comes on top.  16 groups of 8, 512 + U[0, 500], 40 heads on eight, bf16 (528 MB at most) 39 us scheduled, 43 here; 32
         // of 8, 512 + U[0, 100], 28 on four (318 MB) 42, 40; 16 of 8, 1024 + U[0, 100] (293 MB) 38, 31.  e4m3: 688 MB 56, 63;
         // 369 MB 59, 46.
-        const int64_t bytes = items * a.max_pages * (2 * kPage * a.D * (a.kv_fp8 ? 1 : 2));
-        if (a.share && (splits > 1 || bytes > (int64_t)(a.kv_fp8 ? 480 : 320) << 20)) return;
-        a.splits = splits;
+        if (share && (splits > 1 || bytes > (int64_t)(kv_fp8 ? 480 : 320) << 20)) return p;
     }
-    // The longest first, where a workgroup takes items one after the other and they are long enough for it: working the order
-    // out takes 1.1 us of every workgroup.  100 sequences of 28 heads on four, bf16, U[0, 1536]: 34 us as they come, 29.6 in
-    // order; all full 52, 55; 512 tokens at most (four stages a wave) 16.2, 15.6 and 21.3, 23.6.  (Groups stay together.)
-    const int64_t side = (int64_t)(big ? 1 : a.D == 128 ? 8 / W : (a.kv_fp8 ? 16 : 8) / W) * num_cus;
-    a.sorted = a.splits == 1 && !a.share && items > side && a.B <= kDirectSort && per_wave > 6;
+    p.splits = splits;
+    p.waves = W;
+    p.sorted = sorted;
+    p.turned = splits == 1 && !share;
+    return p;
 }
 
 #define RA_DIRECT_KERNELS_OF(X, S) X(128, 2, 4, S) X(128, 1, 4, S) X(128, 1, 8, S) X(64, 2, 4, S) X(64, 2, 8, S) X(64, 1, 4, S) X(64, 1, 8, S)

@@ -1,4 +1,5 @@
 """Helpers for the GPU tests: upload a workload.Problem, run the HIP library through its C ABI, compare."""
+import ctypes
 import os
 
 import numpy as np
@@ -29,17 +30,34 @@ def context(**env):
     return d
 
 
-def scheduled(dec, p):
-    """Whether a decode step of this problem has a schedule as far as the rule for the smallest batches goes (larger ones of
-    short sequences may go without one too: tests/test_gpu_direct.py), by the library's own function: it is no entry point
-    of the C ABI, so it is called by the name the compiler gave it."""
+class DirectPlan(ctypes.Structure):
+    """How a batch goes without a schedule: workgroups per (sequence, kv head) (0: it has a schedule), waves of a workgroup,
+    whether the longest sequences come first, whether the workgroups are turned about over the dies."""
+    _fields_ = [(n, ctypes.c_int32) for n in ("splits", "waves", "sorted", "turned")]
+
+
+def direct_plan(B, Hkv, G, D, fp8, max_pages, share, cus, waves):
+    """The library's own rule; it is no entry point of the C ABI, so it is called by the name the compiler gave it."""
+    f = ra.load_library()._ZN2ra11direct_planEiiiiiiiii
+    f.restype = DirectPlan
+    return f(B, Hkv, G, D, int(fp8), max_pages, int(share), cus, waves)
+
+
+def plan_of(dec, p, use_hint=True):
+    """What the library does with a decode step of this problem: a DirectPlan."""
     if str(getattr(dec, "settings", {}).get("DIRECT", 1)) == "0":
-        return True
+        return DirectPlan()
+    import torch
     fp8 = p.kv_dtype != "bf16"
     waves = ra.rollout_attn_wave_count(dec.ctx, ra.RA_KV_FP8_E4M3 if fp8 else ra.RA_KV_BF16, p.D)
-    import torch
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    return ra.load_library()._ZN2ra13direct_splitsEiiiiiii(p.B, p.Hkv, p.D, int(fp8), p.block_table.shape[1], cus, waves) == 0
+    share = use_hint and p.prefix_page_offsets.size > 1      # (a hint is used if it names groups, whatever they share)
+    return direct_plan(p.B, p.Hkv, p.Hq // p.Hkv, p.D, fp8, p.block_table.shape[1], share, cus, waves)
+
+
+def scheduled(dec, p, use_hint=True):
+    """Whether a decode step of this problem has a schedule."""
+    return plan_of(dec, p, use_hint).splits == 0
 
 
 def compare(out, lse, ref_out, ref_lse, what="", abs_rel=0.0):

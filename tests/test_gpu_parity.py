@@ -634,7 +634,8 @@ def test_merge_of_items_cut_into_many_spans(dec, kvd, Hq, Hkv, D, prompts, R, re
     (8, 4, 128, [0] * 25, 1, [641] * 12 + [1] * 12 + [623]),    # ... and a page past it: scheduled
     (4, 1, 64, [0], 1, [12000]),                                # one item over as many as there may be
     (4, 1, 64, [0] * 1024, 1, [127, 128] * 512),                # four items per compute unit
-    (4, 1, 64, [0] * 1025, 1, [127, 128, 0, 1, 33] * 205),      # one more than that: scheduled
+    (4, 1, 64, [0] * 1025, 1, [127, 128, 0, 1, 33] * 205),      # one more than that
+    (4, 1, 64, [0] * 4097, 1, ([127, 128, 0, 1, 33] * 820)[:4097]),  # more than sixteen per compute unit: scheduled
     (2, 2, 128, [0] * 4, 1, [24560, 3, 24576, 70]),             # few items, the table's bytes at their bound (bf16) ...
     (2, 2, 128, [0] * 4, 1, [24560, 3, 24577, 70]),             # ... and a page past it: scheduled
     (8, 4, 64, [0] * 16, 1, [3000, 1, 0, 900] * 4),             # the most items that count as few ...
@@ -645,8 +646,9 @@ def test_small_batches_without_a_schedule(dec_default, kvd, Hq, Hkv, D, prompts,
     dec = dec_default
     p = workload.build_problem("small", Hq, Hkv, D, prompts, R, resp, kv_dtype=kvd, seed=37)
     log("case", Hq, Hkv, D, R, resp[:3], kvd)
-    # the rows said to be scheduled are, in e4m3 (half the bytes) those two that are beyond the bound there as well
-    assert scheduled(dec, p) == (p.B in (17, 1025) or (kvd == "bf16" and max(resp) in (641, 24577)))
+    # the rows said to be scheduled are (as batches with a hint: those of several workgroups per item have a schedule past the
+    # bounds on the table), in e4m3 (half the bytes) those two that are beyond the bound there as well
+    assert scheduled(dec, p) == (p.B in (17, 4097) or (kvd == "bf16" and max(resp) in (641, 24577)))
     # (outputs of one to three tokens are as large as single V entries: rounding them to bf16 alone is 2^-9 of that)
     ref_out, ref_lse = oracle.decode(p)
     compare(*run(dec, p).results(), ref_out, ref_lse, "small", abs_rel=2.0 ** -8)
