@@ -1784,9 +1784,13 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
 // Waves of a workgroup: eight where the items are long or just fill the chip (see above; eight rings of bf16 pages of 128 do
 // not fit), but more workgroups of four where an item gets four of them or more: 24 items of up to 2000 tokens, D = 128, e4m3,
 // 10.0 us with four waves, 11.5 with eight; 80 of 1024 10.2, 11.1; 80 of up to 4096 18.7, 17.4; 256 of 512 (16 stages) 7.9, 8.3.
-static int direct_waves(int64_t items, int D, int kv_fp8, int max_pages, int num_cus)
+// A small batch (see kDirectItems) takes eight only at head dim 64, bf16 only unsplit: 80 of 1498, D = 128, e4m3, all full
+// 11.8 us with four and 12.2 with eight, U[0, 1498] 10.3 and 11.0; 160 of 1504, D = 64, e4m3, 12.9 and 10.0; 80 of 1441, D =
+// 64, bf16 (three workgroups each) 10.5 and 10.4, U 9.4 and 9.5.
+static int direct_waves(int64_t items, int D, int kv_fp8, int max_pages, int num_cus, bool small)
 {
     if ((!kv_fp8 && D == 128) || 4 * items <= num_cus) return 4;
+    if (small && (D == 128 || (!kv_fp8 && 2 * items <= num_cus))) return 4;
     const int stages = (max_pages + 1) / 2;
     const int64_t side = (int64_t)(kv_fp8 && D == 64 ? 2 : 1) * num_cus; // workgroups of eight that run side by side
     return (items <= num_cus && stages > (2 * items > num_cus ? 20 : 32)) || (items <= 2 * side && stages > 48) ? 8 : 4;
@@ -1809,7 +1813,7 @@ DirectPlan direct_plan(int B, int Hkv, int G, int D, int kv_fp8, int max_pages, 
     const bool big = !kv_fp8 && D == 128;
     const int64_t bytes = items * max_pages * (2 * kPage * D * (kv_fp8 ? 1 : 2));
     const bool small = items <= kDirectItems * num_cus && bytes <= (4 * items <= num_cus ? kDirectFewBytes : kDirectBytes);
-    const int W = direct_waves(items, D, kv_fp8, max_pages, num_cus), per_wave = ((max_pages + 1) / 2 + W - 1) / W;
+    const int W = direct_waves(items, D, kv_fp8, max_pages, num_cus, small), per_wave = ((max_pages + 1) / 2 + W - 1) / W;
     const int splits = direct_share(items, per_wave, num_cus, waves), longest = (per_wave + splits - 1) / splits;
     const int64_t side = (int64_t)(big ? 1 : D == 128 ? 8 / W : (kv_fp8 ? 16 : 8) / W) * num_cus; // workgroups that run side by side
     // The longest first, where a workgroup takes items one after the other and they are long enough for it: working the order
@@ -1835,7 +1839,8 @@ DirectPlan direct_plan(int B, int Hkv, int G, int D, int kv_fp8, int max_pages, 
     p.splits = splits;
     p.waves = W;
     p.sorted = sorted;
-    p.turned = splits == 1 && !share;
+    // (see the kernel; small batches as they come: 80 items of 349 tokens, bf16 of 128, 7.4 us, turned about 7.9)
+    p.turned = splits == 1 && !share && !small;
     return p;
 }
 
