@@ -1638,7 +1638,7 @@ __device__ __forceinline__ void merge_write(const Launch &a, int64_t bh, int d4,
 //
 // Measured (MI355X, scheduled -> here, us a step): four sequences of up to 256 tokens, D = 64: 15.7 -> 6.5; eight of one
 // prompt, 500 to 2000, D = 128: 33.4 -> 10.7; 64 of U[0, 1536], 28 heads on four, bf16: 28.5 -> 21.6 (all full 42 -> 32, one
-// long 20.1 -> 16.1); 100 of U[0, 3072], e4m3: 40 -> 33; 300 of U[0, 1024], eight heads on two, D = 64, bf16: 24.4 -> 16.4;
+// long 20.1 -> 16.1); 104 of U[0, 2475], e4m3: 38 -> 30; 300 of U[0, 1024], eight heads on two, D = 64, bf16: 24.4 -> 16.4;
 // 1024 of U[0, 1536], the same, e4m3: 59 -> 40; eight groups of eight, 300 + U[0, 1200], 28 on four, bf16: 35 -> 20.8.
 // ------------------------------------------------------------------------------------------------------
 
@@ -1669,9 +1669,9 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
     touch_args(a);
     int item = blockIdx.x / a.splits;
     const int part = blockIdx.x - item * a.splits;
-    // Workgroups are dealt to the dies by number: turned about in every eight, a pattern in the lengths meets all dies (256
-    // sequences of four kv heads, e4m3, every 16th of them 1536 tokens and the rest 96: 38 us as they come, 28 turned).  Not
-    // where prompts are shared: a group's members find its pages in their die's L2 (64 sequences in eight groups 20.8 us, turned 24.5).
+    // Workgroups are dealt to the dies by number: turned about in every eight, a pattern in the lengths meets all dies (1290
+    // sequences of two kv heads, D = 64, e4m3, every 16th of them 1305 tokens and the rest 81: 47 us as they come, 28 turned).
+    // Not where prompts are shared: a group's members find its pages in their die's L2 (64 sequences in eight groups 20.8 us, turned 24.5).
     if (a.turned && item < (a.B * a.Hkv & ~7)) item = (item & ~7) | ((item + (item >> 3) + (item >> 6)) & 7);
     int b = item / a.Hkv;
     const int kvh = item - b * a.Hkv;
@@ -1821,20 +1821,43 @@ DirectPlan direct_plan(int B, int Hkv, int G, int D, int kv_fp8, int max_pages, 
     // order; all full 52, 55; 512 tokens at most (four stages a wave) 16.2, 15.6 and 21.3, 23.6.  (Groups stay together.)
     const bool sorted = splits == 1 && !share && items > side && B <= kDirectSort && per_wave > 6;
     if (!small) {
-        // Larger batches of items that their workgroups stream in the time of a schedule and a merge: one long item among short
-        // ones lasts as long as those alone.  A workgroup to an item: up to twelve stages a wave (sixteen of the half as large
-        // ones of head dim 64): one of 64 sequences of 28 heads on four, bf16: 12 stages (1536 tokens) 20.1 us scheduled, 16.1
-        // here; 15 20.4, 19.6; 24 21, 28.  Several, and the merge: up to eight, e4m3 and bf16 alike (16 sequences of eight
-        // heads, e4m3, U[0, 4096], 24.5 us, 21.7, all full 33, 27, one long 19.1, 19.1; twice the length 36, 36, 56, 47, 19.8,
-        // 28.9; 30 of 28 heads on four, bf16, eight stages: 23.8, 18.4, full 32, 24, one long 20.3, 15.4).
-        // Beyond four rounds of workgroups (sixteen where a compute unit holds several) their starts add up: 500 sequences of
-        // eight kv heads, bf16, U[0, 1536]: 261 us, 250, but one long among short 39, 55.
-        if (longest > (splits > 1 ? 8 : D == 64 ? 16 : 12) || items > (int64_t)(big ? 4 : 16) * num_cus) return p;
-        // Every member of a group reads the shared pages here: all in all no more than the caches take, and not where the merge
-        // comes on top.  16 groups of 8, 512 + U[0, 500], 40 heads on eight, bf16 (528 MB at most) 39 us scheduled, 43 here; 32
-        // of 8, 512 + U[0, 100], 28 on four (318 MB) 42, 40; 16 of 8, 1024 + U[0, 100] (293 MB) 38, 31.  e4m3: 688 MB 56, 63;
-        // 369 MB 59, 46.
-        if (share && (splits > 1 || bytes > (int64_t)(kv_fp8 ? 480 : 320) << 20)) return p;
+        // Larger batches, if no pattern of lengths (any up to the table's width, all of them full, one long among short ones, every
+        // sixteenth) makes them slower than a schedule does.  (us scheduled, us here, where a line lies:)
+        // - One long item lasts as long as its workgroups' longest wave.  A workgroup to an item: twelve stages a wave (sixteen
+        //   of the half as large ones of head dim 64): one of 64 sequences of 28 heads on four, bf16: 12 stages (1536 tokens)
+        //   20.1, 16.1; 15 20.4, 19.6; 24 21, 28.  Ten where the workgroups have eight waves and come in no order: a few long
+        //   ones may meet on a compute unit (192 items, D = 64, bf16: 13 stages 16.4, 19.1; 432, e4m3: 15 19.9, 27.6; 272, D =
+        //   128, e4m3, in order: 12 full 0.87 times as fast, one long 0.89).  Twelve of bf16 beyond one round in no order (1698
+        //   items, D = 64: 16 stages, every sixteenth long, 34.5, 39.2).  Several workgroups, and the merge: eight (16 sequences
+        //   of eight heads, e4m3, U[0, 4096] 24.5, 21.7, all full 33, 27, one long 19.1, 19.1; twice the length 36, 36, 56, 47,
+        //   19.8, 28.9).
+        const bool in_turn = sorted || items <= side;
+        if (longest > (splits > 1 ? 8 : W == 8 ? (sorted && side > num_cus ? 16 : 10) : D == 64 && (kv_fp8 || in_turn) ? 16 : 12)) return p;
+        // - Rounds of workgroups: their starts add up before a long one's.  bf16 of 128 three, two and a half with few query heads
+        //   to a page: 120 sequences of eight heads, 817 tokens (3.75 rounds), U 41.6, 42.7, every sixteenth 21.8, 22.9; 92 of
+        //   679, one head each (2.9), every sixteenth 19.5, 21.0, 84 of 1041 (2.6) 1.0 to 1.4 times as fast.  Three and a half (of e4m3 at
+        //   head dim 64 four) where a wave has more than four stages or a page few query heads: 459 of eight, D = 64, bf16, 2011
+        //   tokens (7.2 rounds), one long 27.5, 35.2; 136 of sixteen, 1411 (4.2), 20.0, 21.1; 478 of eight, e4m3, 740 (7.5), every
+        //   sixteenth 46.8, 50.0; 474 of eight, one head each, e4m3, 481 (7.4), 36.3, 41.8, but 482 of 372 with eight each 42.7,
+        //   39.8.
+        if (2 * items > (int64_t)(big ? (G < 4 ? 5 : 6) : (kv_fp8 && D == 64) || (per_wave <= 4 && G >= 4) ? 32 : 14) * num_cus) return p;
+        // - A last round that is nearly empty leaves the chip idle where items are long and a compute unit holds one workgroup:
+        //   34 of eight, bf16 of 128, 1089 tokens (1.06 rounds), all full 34.0, 37.6; 35 1191 (1.09) 36.8, 41.0; 1.2 rounds
+        //   1.01 to 1.09 times as fast; 129 of four, 1311 (2.02) 67.9, 73.2; 2.25 55.8, 59.6.  Workgroups of eight waves, or few
+        //   query heads: 1.25 55.5, 59.8 and 44.6, 46.0, 1.4 rounds 1.0 to 1.1 times as fast.
+        const int64_t rest = items % side;
+        if (side == num_cus && items > side && per_wave > 6 && rest && 5 * rest < (W == 8 || G < 4 || items > 2 * side ? 2 : 1) * side) return p;
+        // - Every member of a group reads the shared pages here: all in all no more than the caches take.  16 groups of 8, 512 +
+        //   U[0, 500], 40 heads on eight, bf16 (528 MB at most) 39, 43; 32 of 8, 512 + U[0, 100], 28 on four (318 MB) 42, 40; 16
+        //   of 8, 1024 + U[0, 100] (293 MB) 38, 31.  Of 39 drawn ones of 320 to 400 MB five were slower here, down to 0.85 times
+        //   as fast, of 22 of e4m3 pools of 320 to 480 six, down to 0.89, but of 61 of 200 to 320 two, 0.91 the least.
+        //   Few query heads to a kv head, and a prefix row of the schedule holds many members: eight of 16, one head each, 32
+        //   kv heads, e4m3 (272 MB) 0.67 times as fast; 33 of 4, 1377 + U[0, 29], eight (363 MB) 0.77.
+        //   Eight waves beyond one round: 50 of 4, 1198 + 348, eight heads on two, bf16 29.2, 32.1; e4m3 of more than eight
+        //   stages 58 of 2, 1405 + 950, 28 on four 49.4, 50.9.
+        //   Where several workgroups take an item, grouped batches keep their schedule, though not because it is faster: 120
+        //   drawn ones of up to 120 MB took 1.0 to 2.4 times as long scheduled.
+        if (share && (splits > 1 || (W == 8 && items > side && (!kv_fp8 || per_wave > 8)) || bytes > (int64_t)(G < 4 ? 128 : 320) << 20)) return p;
     }
     p.splits = splits;
     p.waves = W;

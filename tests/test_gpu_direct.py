@@ -30,10 +30,10 @@ def lens(n, top, seed):
     (8, 4, 128, [0] * 40, 1, lens(40, 1536, 1), (True, True)),          # side by side: four waves (bf16), eight (e4m3); longest item
     (8, 4, 128, [0] * 40, 1, lens(40, 1537, 2), (False, True)),         # ... and a page past it
     (7, 1, 128, [0] * 200, 1, lens(200, 3073, 3), (False, False)),
-    (8, 4, 128, [0] * 67, 1, lens(67, 900, 4), (True, True)),           # more items than compute units, not a multiple of eight: in order (bf16)
-    (2, 1, 128, [0] * 300, 1, lens(300, 1601, 5), (False, True)),       # in order, eight waves (e4m3)
-    (8, 2, 64, [0] * 100, 1, lens(100, 4096, 6), (True, True)),         # eight waves, sixteen stages each
-    (8, 2, 64, [0] * 100, 1, lens(100, 4097, 7), (False, False)),
+    (8, 4, 128, [0] * 77, 1, lens(77, 900, 4), (True, True)),           # more items than compute units, not a multiple of eight: in order (bf16)
+    (2, 1, 128, [0] * 360, 1, lens(360, 1601, 5), (False, True)),       # in order, eight waves (e4m3)
+    (8, 2, 64, [0] * 100, 1, lens(100, 2560, 6), (True, True)),         # eight waves, ten stages each
+    (8, 2, 64, [0] * 100, 1, lens(100, 2561, 7), (False, False)),
     (8, 4, 128, [0] * 30, 1, lens(30, 2048, 10), (False, False)),               # two or three workgroups to an item and the merge
     (8, 4, 128, [0] * 30, 1, lens(30, 2049, 11), (False, False)),       # ... and a page past it (bf16)
     (4, 2, 64, [0] * 60, 1, lens(60, 4096, 12), (False, False)),
