@@ -35,6 +35,9 @@ class DirectPlan(ctypes.Structure):
     whether the longest sequences come first, whether the workgroups are turned about over the dies."""
     _fields_ = [(n, ctypes.c_int32) for n in ("splits", "waves", "sorted", "turned")]
 
+    def __iter__(self):
+        return iter((self.splits, self.waves, self.sorted, self.turned))
+
 
 def direct_plan(B, Hkv, G, D, fp8, max_pages, share, cus, waves):
     """The library's own rule; it is no entry point of the C ABI, so it is called by the name the compiler gave it."""

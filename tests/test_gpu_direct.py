@@ -6,7 +6,7 @@ import torch
 
 import oracle
 import workload
-from gpu_util import DeviceProblem, compare, context
+from gpu_util import DeviceProblem, compare, context, plan_of
 
 pytestmark = pytest.mark.gpu
 
@@ -25,36 +25,71 @@ def lens(n, top, seed):
     return [int(x) for x in r]
 
 
+S = (0, 0, 0, 0)             # has a schedule; otherwise workgroups per item, their waves, longest first, turned about
+
+
 @pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
-@pytest.mark.parametrize("Hq,Hkv,D,prompts,R,resp,whole", [
-    (8, 4, 128, [0] * 40, 1, lens(40, 1536, 1), (True, True)),          # side by side: four waves (bf16), eight (e4m3); longest item
-    (8, 4, 128, [0] * 40, 1, lens(40, 1537, 2), (False, True)),         # ... and a page past it
-    (7, 1, 128, [0] * 200, 1, lens(200, 3073, 3), (False, False)),
-    (8, 4, 128, [0] * 77, 1, lens(77, 900, 4), (True, True)),           # more items than compute units, not a multiple of eight: in order (bf16)
-    (2, 1, 128, [0] * 360, 1, lens(360, 1601, 5), (False, True)),       # in order, eight waves (e4m3)
-    (8, 2, 64, [0] * 100, 1, lens(100, 2560, 6), (True, True)),         # eight waves, ten stages each
-    (8, 2, 64, [0] * 100, 1, lens(100, 2561, 7), (False, False)),
-    (8, 4, 128, [0] * 30, 1, lens(30, 2048, 10), (False, False)),               # two or three workgroups to an item and the merge
-    (8, 4, 128, [0] * 30, 1, lens(30, 2049, 11), (False, False)),       # ... and a page past it (bf16)
-    (4, 2, 64, [0] * 60, 1, lens(60, 4096, 12), (False, False)),
-    (2, 1, 64, [0] * 512, 1, [0] * 9 + [700] * 495 + [32 * 64 // 2] * 8, (True, True)),  # as many as are put in order, levels full of equals
-    (2, 1, 64, [0] * 517, 1, lens(517, 1024, 8), (True, True)),         # more than that
-    (4, 1, 64, [0] * 2049, 1, [33, 0, 17] * 683, (True, True)),
-    (4, 2, 64, [100, 0, 333], 100, lens(300, 300, 9), (True, True)),    # groups: a member reads all its pages; some shorter than the prompt
+@pytest.mark.parametrize("Hq,Hkv,D,prompts,R,resp,plans", [
+    (8, 4, 128, [0] * 40, 1, lens(40, 1536, 1), ((1, 4, 0, 1), (1, 8, 0, 1))),   # side by side: four waves (bf16), eight (e4m3); longest item
+    (8, 4, 128, [0] * 40, 1, lens(40, 1537, 2), (S, (1, 8, 0, 1))),              # ... and a page past it
+    (7, 1, 128, [0] * 200, 1, lens(200, 3073, 3), (S, S)),
+    (8, 4, 128, [0] * 90, 1, lens(90, 900, 4), ((1, 4, 1, 1), (1, 4, 0, 1))),    # more items than compute units, in order (bf16)
+    (8, 4, 128, [0] * 131, 1, lens(131, 900, 13), (S, (1, 4, 1, 1))),            # ... e4m3; not a multiple of eight
+    (2, 1, 128, [0] * 360, 1, lens(360, 1601, 5), (S, (1, 8, 1, 1))),            # in order, eight waves (e4m3)
+    (8, 2, 64, [0] * 100, 1, lens(100, 2560, 6), ((1, 8, 0, 1), (1, 8, 0, 1))),  # eight waves, ten stages each
+    (8, 2, 64, [0] * 100, 1, lens(100, 2561, 7), (S, S)),
+    (8, 2, 64, [0] * 180, 1, lens(180, 1700, 14), ((1, 8, 1, 1), (1, 8, 0, 1))),  # ... in order (bf16)
+    (4, 2, 64, [0] * 512, 1, lens(512, 1760, 15), ((1, 4, 1, 1), (1, 8, 1, 1))),  # as many as are put in order; eight waves (e4m3)
+    (4, 4, 64, [0] * 257, 1, lens(257, 1024, 16), ((1, 4, 1, 1), (1, 4, 1, 1))),  # in order, four waves
+    (4, 2, 64, [0] * 512, 1, [0] * 9 + [700] * 487 + [1760] * 16, ((1, 4, 1, 1), (1, 8, 1, 1))),  # levels full of equals
+    (4, 4, 64, [0] * 300, 1, [800] * 300, ((1, 4, 1, 1), (1, 4, 1, 1))),         # ... one level for all, of a width that is no power of two
+    (8, 4, 128, [0] * 30, 1, lens(30, 2048, 10), ((2, 4, 0, 0), (2, 8, 0, 0))),  # two or three workgroups to an item and the merge
+    (8, 4, 128, [0] * 30, 1, lens(30, 2049, 11), (S, (2, 8, 0, 0))),             # ... and a page past it (bf16)
+    (4, 2, 64, [0] * 60, 1, lens(60, 4096, 12), ((2, 8, 0, 0), (2, 8, 0, 0))),
+    (2, 1, 64, [0] * 512, 1, [0] * 9 + [700] * 495 + [32 * 64 // 2] * 8, ((1, 4, 0, 1), (1, 4, 0, 1))),  # no more than run side by side: as they come
+    (2, 1, 64, [0] * 517, 1, lens(517, 1024, 8), ((1, 4, 0, 1), (1, 4, 0, 1))),  # more sequences than are put in order
+    (4, 1, 64, [0] * 2049, 1, [33, 0, 17] * 683, ((1, 4, 0, 1), (1, 4, 0, 1))),
+    (4, 2, 64, [100, 0, 333], 100, lens(300, 300, 9), ((1, 4, 0, 0), (1, 4, 0, 0))),  # groups: a member reads all its pages; some shorter than the prompt
 ])
-def test_a_workgroup_per_item(dec, kvd, Hq, Hkv, D, prompts, R, resp, whole):
+def test_a_workgroup_per_item(dec, kvd, Hq, Hkv, D, prompts, R, resp, plans):
     p = workload.build_problem("direct", Hq, Hkv, D, prompts, R, resp, kv_dtype=kvd, seed=41)
     dp = DeviceProblem(p, use_hint=any(prompts))
+    plan = plan_of(dec, p, use_hint=any(prompts))
+    assert (tuple(plan) if plan.splits else S) == plans[kvd != "bf16"]
     ws = dec.workspace(dp.c)
     ws.fill_(0xA5)
     print("case", Hq, Hkv, D, p.B, p.block_table.shape[1], kvd, flush=True)
     dec.decode(dp.c)
     out, lse = dp.results()
     # a step of one workgroup per item leaves the workspace alone: no schedule, no partials
-    assert bool((ws == 0xA5).all()) == whole[kvd != "bf16"]
+    assert bool((ws == 0xA5).all()) == (plan.splits == 1)
     # (outputs of one to three tokens are as large as single V entries: rounding them to bf16 alone is 2^-9 of that)
     compare(out, lse, *oracle.decode(p), "direct", abs_rel=2.0 ** -8)
     first = dp.out.clone()
     dec.decode(dp.c)
     torch.cuda.synchronize()
     assert torch.equal(first.view(torch.int16), dp.out.view(torch.int16))
+
+
+@pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("Hq,Hkv,D,B,top,plans", [
+    (4, 2, 64, 70, 1500, ((1, 8, 0, 1), (1, 8, 0, 0))),
+    (8, 4, 128, 40, 1537, (S, (1, 8, 0, 1))),
+    (4, 2, 64, 300, 1600, ((1, 4, 1, 1), (1, 8, 1, 1))),
+    (8, 4, 128, 90, 900, ((1, 4, 1, 1), (1, 4, 0, 1))),
+])
+def test_strided_pools(dec, kvd, Hq, Hkv, D, B, top, plans):
+    """K and V interleaved page by page and a row of slack behind every slot's: every stride is used as given."""
+    p = workload.build_problem("strided", Hq, Hkv, D, [0] * B, 1, lens(B, top, 17), kv_dtype=kvd, seed=43)
+    dp = DeviceProblem(p, use_hint=False)
+    plan = plan_of(dec, p, use_hint=False)
+    assert (tuple(plan) if plan.splits else S) == plans[kvd != "bf16"]
+    n, slack = p.num_pages, 16 // dp.k_pool.element_size()
+    both = torch.zeros((n, 2, Hkv, 16, D + slack), dtype=dp.k_pool.dtype, device="cuda:0")
+    both[:, 0, :, :, :D], both[:, 1, :, :, :D] = dp.k_pool, dp.v_pool
+    dp.k_pool, dp.v_pool = both[:, 0, :, :, :D], both[:, 1, :, :, :D]
+    dp.set(use_hint=False)
+    assert dp.c.kv_stride_token == D + slack and dp.c.kv_stride_page == 2 * Hkv * 16 * (D + slack)
+    print("case", Hq, Hkv, D, B, top, kvd, flush=True)
+    dec.decode(dp.c)
+    compare(*dp.results(), *oracle.decode(p), "strided", abs_rel=2.0 ** -8)
