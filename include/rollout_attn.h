@@ -60,18 +60,20 @@ typedef enum { RA_KV_BF16 = 0, RA_KV_FP8_E4M3 = 1 } ra_kv_dtype;
 enum {
     RA_FLAG_VALIDATE = 1u,          /* check device-side lengths / page ids / hint first (one extra kernel + a
                                        stream synchronisation) */
-    RA_FLAG_NO_PREFIX_SHARING = 2u, /* ignore the prompt-group hint (for A/B comparison; batches that have no schedule
-                                       do not read shared pages once anyway: see ROLLOUT_ATTN_DIRECT) */
+    RA_FLAG_NO_PREFIX_SHARING = 2u, /* ignore the prompt-group hint (for A/B comparison).  Batches that have no schedule
+                                       do not read shared pages once anyway, and whether a batch has one may depend on
+                                       the hint: to compare sharing alone, let every batch have one
+                                       (ROLLOUT_ATTN_DIRECT=0) */
     RA_FLAG_REUSE_SCHEDULE = 4u     /* skip the schedule (its kernels for a large batch; for a smaller one, which the
                                        attention workgroups plan for themselves, their planning pass: each takes the
-                                       list it kept; the smallest have none) and use the schedule that the previous
-                                       rollout_attn_decode call without this flag on the same context left in the same
-                                       workspace.
-                                       For the layers of one decode step: the schedule depends only on B, the head
-                                       counts, D, max_pages_per_seq, seq_lens, seq_group, prefix_page_offsets and
-                                       RA_FLAG_NO_PREFIX_SHARING, which must all be what they were in that call; q,
-                                       out, lse, the pools, the scales and the page ids in block_table and
-                                       prefix_pages may differ.  Nothing checks this. */
+                                       list it kept; small batches and batches of short sequences have none: see
+                                       ROLLOUT_ATTN_DIRECT) and use the schedule that the previous rollout_attn_decode
+                                       call without this flag on the same context left in the same workspace.
+                                       For the layers of one decode step: the schedule, and whether there is one,
+                                       depends only on B, the head counts, D, max_pages_per_seq, kv_dtype, seq_lens,
+                                       num_groups, seq_group, prefix_page_offsets and RA_FLAG_NO_PREFIX_SHARING, which
+                                       must all be what they were in that call; q, out, lse, the pools, the scales and
+                                       the page ids in block_table and prefix_pages may differ.  Nothing checks this. */
 };
 
 /*
@@ -92,7 +94,7 @@ enum {
  * results: the first page_size * n_g tokens of every member of group g live in the n_g pages
  *   prefix_pages[prefix_page_offsets[g] .. prefix_page_offsets[g+1])
  * and the member's own block_table row starts with the same ids.  Those pages are then read once per
- * group instead of once per member (but in the smallest batches, which have no schedule).
+ * group instead of once per member (but in batches that have no schedule: see ROLLOUT_ATTN_DIRECT).
  *   seq_group           int32 [B], group id in [0, num_groups) or -1 (no group).
  *   prefix_page_offsets int32 [num_groups + 1], non-decreasing, starts at 0.
  *   prefix_pages        int32 [prefix_page_offsets[num_groups]].
@@ -141,7 +143,9 @@ uint32_t rollout_attn_abi_version(void);
  *   ROLLOUT_ATTN_DIRECT=0           every batch has a schedule (default: the smallest batches, by what their block
  *                                   table can address, and batches of sequences that one compute unit streams in the
  *                                   time of a schedule, by the table's width, take a workgroup or a fixed number of
- *                                   them per sequence and kv head instead)
+ *                                   them per sequence and kv head instead; rollout_attn_set_wave_weights and the
+ *                                   knobs above, which shape the schedule and its workgroups, do nothing for those,
+ *                                   but that the number of workgroups bounds how many take one item)
  *   ROLLOUT_ATTN_SELF_PLAN=0        a batch that has a schedule gets it from the schedule kernels (default: batches of
  *                                   up to 512 sequences and 511 groups are scheduled by the attention workgroups
  *                                   themselves, each for its own share of the work, which saves a kernel; the schedule
@@ -172,8 +176,8 @@ ra_status rollout_attn_check_problem(const ra_problem *problem, char *msg, size_
 ra_status rollout_attn_workspace_size(const ra_ctx *ctx, const ra_problem *shape_only, size_t *bytes);
 
 /* Enqueues the whole step (schedule, attention over shared prompt pages and over each sequence's own
- * pages, log-sum-exp merge: two kernels for batches of up to 512 sequences, where the attention workgroups schedule
- * themselves, else three or four) on hip_stream (a hipStream_t, NULL = default stream) and returns without
+ * pages, log-sum-exp merge: one or two kernels for batches that have no schedule, see ROLLOUT_ATTN_DIRECT, two for
+ * batches of up to 512 sequences, where the attention workgroups schedule themselves, else three or four) on hip_stream (a hipStream_t, NULL = default stream) and returns without
  * waiting; out and lse are valid once the stream has reached that point.  workspace is dev memory of at
  * least rollout_attn_workspace_size() bytes, 256-byte aligned, contents irrelevant on entry and undefined
  * afterwards; calls that overlap in time need distinct workspaces.  Results are deterministic: the same
@@ -320,7 +324,8 @@ ra_status rollout_attn_balance(const int64_t *weights, int64_t n, int32_t k, int
  * workgroups the launch for (kv_dtype, head_dim) has, rollout_attn_set_wave_weights sets their shares (weights: HOST
  * int32 [n], per mille of the mean, clamped to 700..1400; n must equal the wave count).  Default: a fixed share per
  * die.  The weights only move work between workgroups (paper Sec. 4.4 balances tokens between workers the same way);
- * results stay within rounding of each other, and identical for identical weights.  Copies to the device
+ * results stay within rounding of each other, and identical for identical weights.  Batches that have no schedule
+ * (ROLLOUT_ATTN_DIRECT) do not read them.  Copies to the device
  * synchronously: call it while no work of the context is in flight. */
 ra_status rollout_attn_wave_count(const ra_ctx *ctx, int32_t kv_dtype, int32_t head_dim, int32_t *waves);
 ra_status rollout_attn_set_wave_weights(ra_ctx *ctx, int32_t kv_dtype, int32_t head_dim, const int32_t *weights, int32_t n);
@@ -350,12 +355,12 @@ ra_status rollout_attn_debug_stream_tail(ra_ctx *ctx, const void *buf, size_t bu
                                          int32_t static_entries, int32_t chunk_entries, void *hip_stream, size_t *bytes_read);
 
 /* Per-kernel timing for benchmarks.  While enabled, rollout_attn_decode records HIP events on its stream
- * around its three phases (schedule, attention, merge); rollout_attn_get_timing waits for the events of the
- * most recent decode call and returns the three durations in milliseconds (schedule: 0 when that call launched
- * no schedule kernel, because its attention workgroups planned their spans themselves, the batch was too small to need
- * a schedule or the schedule was reused; the attention phase then starts at the call's first event).  Off by default: the events cost
- * a little time between kernels.  The numbers are measurements, not part of the result (the decode step is
- * memory-bound, paper Sec. 2.1.1, so the attention phase is the one to watch). */
+ * around its three phases (schedule, attention, merge); rollout_attn_get_timing waits for the events of the most
+ * recent decode call and returns the three durations in milliseconds (schedule: 0 when that call launched no
+ * schedule kernel, because its attention workgroups planned their spans themselves, the batch has no schedule
+ * (ROLLOUT_ATTN_DIRECT) or the schedule was reused; the attention phase then starts at the call's first event).
+ * Off by default: the events cost a little time between kernels.  The numbers are measurements, not part of the
+ * result (the decode step is memory-bound, paper Sec. 2.1.1, so the attention phase is the one to watch). */
 ra_status rollout_attn_set_timing(ra_ctx *ctx, int enable);
 ra_status rollout_attn_get_timing(ra_ctx *ctx, float phase_ms[3]);
 

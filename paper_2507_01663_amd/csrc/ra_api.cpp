@@ -29,7 +29,7 @@ struct ra_ctx {
     int prefill_stay;          // -1: the prefill launch chooses by the batch; else ROLLOUT_ATTN_PREFILL_WGS_PER_DIE
     void *zeros;  // 256 bytes of zeros on the device
     int self_plan; // attention waves may plan their spans themselves (no schedule kernel)
-    int direct;    // the smallest batches may go without a schedule
+    int direct;    // batches that direct_plan says so may go without a schedule
     int32_t *host_flags; // pinned, for RA_FLAG_VALIDATE
     int timing;          // record events around the phases
     int timed;           // a decode call has recorded them (2: with a schedule launch between the first two)
