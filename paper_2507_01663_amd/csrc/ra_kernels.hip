@@ -1677,8 +1677,8 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
     const int kvh = item - b * a.Hkv;
     int L;
     if (SORTED) {
-        // The b-th longest sequence, to within a sixteenth of the table's width (ties by number): a lane holds every 64th
-        // length, and the wave looks for the level by halves, then for the place inside it.
+        // The b-th longest sequence, to within a sixteenth to an eighth of the table's width (a power of two of tokens; ties by
+        // number): a lane holds every 64th length, and the wave looks for the level by halves, then for the place inside it.
         constexpr int N = kDirectSort / 64;
         const int most = a.max_pages * kPage;
         int len[N];

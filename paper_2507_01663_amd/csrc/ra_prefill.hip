@@ -492,7 +492,8 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
     // The cache write, from the tiles that stream through the ring anyway (16 keys of a kv head: a page).  A stage's K and
     // V are written by the block that holds the first head's unit of the stage's tile, which spreads them evenly over the
     // blocks; wave w takes tile w of the chunk that has just been opened.  The stores go past the caches, like the results':
-    // 64 prompts of 50 to 500 tokens, 40 heads on eight, 146.9 -> 131.3 us, 32 of 512, 28 on four, 98.7 -> 97.0.
+    // 64 prompts of 50 to 500 tokens, 40 heads on eight, 143.7 -> 131.3 us (with a decode step over the pages 155.5 -> 149.1),
+    // 32 of 512, 28 on four, 96.1 -> 96.2 (104.3 -> 104.5), 64 of 256 75.4 -> 74.4 (84.7 -> 84.5).
     int w_lo = 1 << 30, w_hi = -1; // the block's stages to be written
     auto pages_of_block = [&]() __attribute__((always_inline)) {
         const int units = cb.tiles() * a.G, end = (cb.u0 + a.units < units ? cb.u0 + a.units : units) - 1;
@@ -735,8 +736,13 @@ template <int D, bool STAY> __global__ __launch_bounds__(64 * kPfWaves) void pre
                     const int r = 8 * m + (sl >> 3), c = sl & 7; // row of the tile, 16-byte piece of its 128 bytes
                     const u32x4 v = *(const u32x4 *)(stage + kPfStageRow * r + 16 * (c ^ pf_stage_swz(r)));
                     const int orow = tile_row + r;
-                    // (Past the caches: K, V and the queries are read from them meanwhile.  32 prompts of 512 tokens, 28 heads on
-                    // four, 106.5 -> 101.5 us, 64 of 256 79.2 -> 73.5, 24 of 200 to 1500 218.7 -> 197.2.)
+                    // (Past the caches: K, V and the queries are read from them meanwhile.  Same inputs call after call, in turn
+                    // on one card: 32 prompts of 512 tokens, 28 heads on four, 99.8 -> 94.4 us, 64 of 256 79.8 -> 74.7, 24 of
+                    // 200 to 1500 206.6 -> 195.6, 64 of 50 to 500, 40 on eight, 146.0 -> 129.7.  A matrix product over the
+                    // results (their heads' width square) finds those that the last-level cache would have held no longer
+                    // there; both calls: 436.4 -> 438.4, 413.7 -> 416.8, 672.3 -> 669.8, 861.6 -> 858.8, 16 of 512 219.9 ->
+                    // 218.1, eight of 37 to 701 107.0 -> 106.2; a copy of them 135.6 -> 143.8, 118.3 -> 126.8, 252.7 -> 245.5,
+                    // 208.1 -> 207.3.)
                     if (orow < len) __builtin_nontemporal_store(v, (u32x4 *)(a.out + ((int64_t)(t0 + orow) * a.Hq + dhead) * D + 64 * p + 8 * c));
                 }
             }
