@@ -1805,6 +1805,43 @@ static int direct_share(int64_t items, int per_wave, int num_cus, int waves)
     return s < 1 ? 1 : (int)s;
 }
 
+// Limits of larger batches.  A decode iteration runs many layers on one schedule (RA_FLAG_REUSE_SCHEDULE): the first pays for
+// it, the others do not, and here none does.  So the lines lie where neither a step alone nor four layers on one schedule get
+// slower by any length up to the table's width (U), by all of them full or by one long among short ones, and four layers with
+// every sixteenth long (which may meet on a unit or a die) by little.  Four layers, us on one schedule and here:
+//
+// Stages of an item's longest wave: one long item lasts as long as its workgroups alone.  Four waves, D = 128: 12 stages (one
+// of 64 sequences of 28 heads on four, bf16, 1536 tokens, a step alone 20.1, 16.1; 15 20.4, 19.6; 24 21, 28); ten of e4m3 with
+// shared prompts (39 groups of 4, 1331 + U[0, 69], 28 on four: eleven stages 129, 147).  D = 64: eight (548 sequences of two kv
+// heads, bf16, every sixteenth of 1342, eleven stages, 71.9, 92.0; 62 of sixteen, e4m3, 1178, ten, 64.9, 78.8), nine in one round
+// of workgroups, twelve of e4m3 with shared prompts (there the schedule reads a prompt more than once: seven drawn ones of nine
+// to twelve stages 1.1 to 1.4 times as fast).  Eight waves: eight (353 of two, e4m3, one of 3926, 16 stages 68.5, 82.5; 51 of
+// eight, every sixteenth of 2364, ten, 63.5, 79.3), ten at D = 128 (28 of 2439, 40 heads on eight, e4m3, 0.97 to 1.3
+// times as fast; with shared prompts only in one round: 13 groups of 4, 1429 + 1119, 40 on eight, 132, 155) and where the
+// longest come first, but six with few query heads to a page of 128 (13 of 32, 1961, every sixteenth, eight stages 64.5, 71.4).  Several workgroups, and the merge: six (D = 64, e4m3, 0.98 to 1.3
+// times as fast), five of bf16 at head dim 64 (16 of eight, one of 2943, six stages 53.2, 57.9; nine of 4949, seven, 54.3, 62.1).
+static int direct_longest(int G, int D, int kv_fp8, int W, int splits, int share, bool sorted, bool one_round)
+{
+    if (splits > 1) return D == 64 && !kv_fp8 ? 5 : 6;
+    if (W == 8) return D == 128 ? (G < 4 ? 6 : share && !one_round ? 8 : 10) : kv_fp8 && sorted ? 10 : 8;
+    if (D == 128) return share && kv_fp8 ? 10 : 12;
+    return share && kv_fp8 ? 12 : one_round ? 9 : 8;
+}
+// Items, in quarters of the number of compute units: workgroups go round by round (one of bf16 pages of 128 to a unit, two of
+// the others' four waves, four of e4m3 at head dim 64) and their starts add up before a long one's, the more the longer the
+// items are and the fewer query heads a page serves.  bf16 of 128: 92 sequences of eight heads, 688 tokens, every sixteenth (2.9
+// rounds, six stages) 73.6, 87.6, 178 of four, 751 (2.8) 76.7, 88.9; of up to four stages 103 of 147 (3.2), U 0.98, full 0.95, one
+// long 1.2 times as fast.  e4m3 of 128: 487 of eight, 270 (7.6), every sixteenth 134, 152; 259 of eight, one query head each, 431
+// (4.0) 83.1, 96.6.  D = 64 in bf16: 446 of two, one of 1941 (1.7, sixteen stages) 58.9, 67.9; 718 of 865 (2.8, seven) 71.9, 82.4,
+// U 1.1 times as fast; 1242 of 486 (4.9, four) 82.6, 93.4, U 1.14.
+static int direct_items(int G, int D, int kv_fp8, int per_wave, int share)
+{
+    if (D == 128 && !kv_fp8) return per_wave <= 4 && G >= 4 ? 15 : share ? 9 : 10;
+    if (D == 64 && kv_fp8) return 64;
+    if (per_wave > 6) return kv_fp8 ? 28 : 20;
+    return D == 64 ? (per_wave <= 4 ? 44 : 32) : G >= 4 ? 44 : per_wave <= 4 ? 28 : 20;
+}
+
 DirectPlan direct_plan(int B, int Hkv, int G, int D, int kv_fp8, int max_pages, int share, int num_cus, int waves)
 {
     DirectPlan p = {0, 0, 0, 0};
@@ -1821,43 +1858,27 @@ DirectPlan direct_plan(int B, int Hkv, int G, int D, int kv_fp8, int max_pages, 
     // order; all full 52, 55; 512 tokens at most (four stages a wave) 16.2, 15.6 and 21.3, 23.6.  (Groups stay together.)
     const bool sorted = splits == 1 && !share && items > side && B <= kDirectSort && per_wave > 6;
     if (!small) {
-        // Larger batches, if no pattern of lengths (any up to the table's width, all of them full, one long among short ones, every
-        // sixteenth) makes them slower than a schedule does.  (us scheduled, us here, where a line lies:)
-        // - One long item lasts as long as its workgroups' longest wave.  A workgroup to an item: twelve stages a wave (sixteen
-        //   of the half as large ones of head dim 64): one of 64 sequences of 28 heads on four, bf16: 12 stages (1536 tokens)
-        //   20.1, 16.1; 15 20.4, 19.6; 24 21, 28.  Ten where the workgroups have eight waves and come in no order: a few long
-        //   ones may meet on a compute unit (192 items, D = 64, bf16: 13 stages 16.4, 19.1; 432, e4m3: 15 19.9, 27.6; 272, D =
-        //   128, e4m3, in order: 12 full 0.87 times as fast, one long 0.89).  Twelve of bf16 beyond one round in no order (1698
-        //   items, D = 64: 16 stages, every sixteenth long, 34.5, 39.2).  Several workgroups, and the merge: eight (16 sequences
-        //   of eight heads, e4m3, U[0, 4096] 24.5, 21.7, all full 33, 27, one long 19.1, 19.1; twice the length 36, 36, 56, 47,
-        //   19.8, 28.9).
-        const bool in_turn = sorted || items <= side;
-        if (longest > (splits > 1 ? 8 : W == 8 ? (sorted && side > num_cus ? 16 : 10) : D == 64 && (kv_fp8 || in_turn) ? 16 : 12)) return p;
-        // - Rounds of workgroups: their starts add up before a long one's.  bf16 of 128 three, two and a half with few query heads
-        //   to a page: 120 sequences of eight heads, 817 tokens (3.75 rounds), U 41.6, 42.7, every sixteenth 21.8, 22.9; 92 of
-        //   679, one head each (2.9), every sixteenth 19.5, 21.0, 84 of 1041 (2.6) 1.0 to 1.4 times as fast.  Three and a half (of e4m3 at
-        //   head dim 64 four) where a wave has more than four stages or a page few query heads: 459 of eight, D = 64, bf16, 2011
-        //   tokens (7.2 rounds), one long 27.5, 35.2; 136 of sixteen, 1411 (4.2), 20.0, 21.1; 478 of eight, e4m3, 740 (7.5), every
-        //   sixteenth 46.8, 50.0; 474 of eight, one head each, e4m3, 481 (7.4), 36.3, 41.8, but 482 of 372 with eight each 42.7,
-        //   39.8.
-        if (2 * items > (int64_t)(big ? (G < 4 ? 5 : 6) : (kv_fp8 && D == 64) || (per_wave <= 4 && G >= 4) ? 32 : 14) * num_cus) return p;
-        // - A last round that is nearly empty leaves the chip idle where items are long and a compute unit holds one workgroup:
-        //   34 of eight, bf16 of 128, 1089 tokens (1.06 rounds), all full 34.0, 37.6; 35 1191 (1.09) 36.8, 41.0; 1.2 rounds
-        //   1.01 to 1.09 times as fast; 129 of four, 1311 (2.02) 67.9, 73.2; 2.25 55.8, 59.6.  Workgroups of eight waves, or few
-        //   query heads: 1.25 55.5, 59.8 and 44.6, 46.0, 1.4 rounds 1.0 to 1.1 times as fast.
+        if (longest > direct_longest(G, D, kv_fp8, W, splits, share, sorted, items <= side) ||
+            4 * items > (int64_t)direct_items(G, D, kv_fp8, per_wave, share) * num_cus) return p;
+        // (Us of a step alone, scheduled and here.)
+        // A last round that is nearly empty leaves the chip idle where items are long and a compute unit holds one workgroup: 34
+        // of eight, bf16 of 128, 1089 tokens (1.06 rounds), all full 34.0, 37.6; 35 of 1191 (1.09) 36.8, 41.0; 1.2 rounds 1.01 to
+        // 1.09 times as fast; 129 of four, 1311 (2.02) 67.9, 73.2; 2.25 55.8, 59.6.  Workgroups of eight waves, or few query
+        // heads: 1.25 55.5, 59.8 and 44.6, 46.0, 1.4 rounds 1.0 to 1.1 times as fast.
         const int64_t rest = items % side;
         if (side == num_cus && items > side && per_wave > 6 && rest && 5 * rest < (W == 8 || G < 4 || items > 2 * side ? 2 : 1) * side) return p;
-        // - Every member of a group reads the shared pages here: all in all no more than the caches take.  16 groups of 8, 512 +
-        //   U[0, 500], 40 heads on eight, bf16 (528 MB at most) 39, 43; 32 of 8, 512 + U[0, 100], 28 on four (318 MB) 42, 40; 16
-        //   of 8, 1024 + U[0, 100] (293 MB) 38, 31.  Of 39 drawn ones of 320 to 400 MB five were slower here, down to 0.85 times
-        //   as fast, of 22 of e4m3 pools of 320 to 480 six, down to 0.89, but of 61 of 200 to 320 two, 0.91 the least.
-        //   Few query heads to a kv head, and a prefix row of the schedule holds many members: eight of 16, one head each, 32
-        //   kv heads, e4m3 (272 MB) 0.67 times as fast; 33 of 4, 1377 + U[0, 29], eight (363 MB) 0.77.
-        //   Eight waves beyond one round: 50 of 4, 1198 + 348, eight heads on two, bf16 29.2, 32.1; e4m3 of more than eight
-        //   stages 58 of 2, 1405 + 950, 28 on four 49.4, 50.9.
-        //   Where several workgroups take an item, grouped batches keep their schedule, though not because it is faster: 120
-        //   drawn ones of up to 120 MB took 1.0 to 2.4 times as long scheduled.
-        if (share && (splits > 1 || (W == 8 && items > side && (!kv_fp8 || per_wave > 8)) || bytes > (int64_t)(G < 4 ? 128 : 320) << 20)) return p;
+        // Every member of a group reads the shared pages here: all in all no more than the caches take.  16 groups of 8, 512 +
+        // U[0, 500], 40 heads on eight, bf16 (528 MB at most) 39, 43; 32 of 8, 512 + U[0, 100], 28 on four (318 MB) 42, 40; 16
+        // of 8, 1024 + U[0, 100] (293 MB) 38, 31.  Of 39 drawn ones of 320 to 400 MB five were slower here, down to 0.85 times
+        // as fast, of 22 of e4m3 pools of 320 to 480 six, down to 0.89, but of 61 of 200 to 320 two, 0.91 the least.
+        // Few query heads to a kv head, and a prefix row of the schedule holds many members: eight of 16, one head each, 32
+        // kv heads, e4m3 (272 MB) 0.67 times as fast; 33 of 4, 1377 + U[0, 29], eight (363 MB) 0.77; four layers of 18
+        // of 8, 330 + 57, eight (118 MB) 0.92, but in one round two of 16, 236 + 790, eight, bf16 (130 MB) a step 23.7, 14.7.
+        // Eight waves, bf16, beyond one round: 50 of 4, 1198 + 348, eight heads on two 29.2, 32.1, but 24 of 8, 58 + 1900, 32 on two
+        // 1.4 times as fast.
+        // Where several workgroups take an item, grouped batches keep their schedule, though not because it is faster: 120
+        // drawn ones of up to 120 MB took 1.0 to 2.4 times as long scheduled.
+        if (share && (splits > 1 || (W == 8 && !kv_fp8 && G < 16 && items > side) || bytes > (int64_t)(G < 4 && items > side ? 96 : 320) << 20)) return p;
     }
     p.splits = splits;
     p.waves = W;

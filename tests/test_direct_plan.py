@@ -30,47 +30,70 @@ def plan(B, Hkv, G, D, fp8, tokens, share=0):
     ((25, 4, 2, 128, 0, 641, 1), SCHEDULED),              # ... keep the schedule where prompts are shared)
     ((4, 2, 1, 128, 0, 24576, 1), (32, 4, 0, 0)),
     ((4, 2, 1, 128, 0, 24577, 1), SCHEDULED),
-    # an item's stages: twelve a wave, sixteen at head dim 64
+    # an item's stages: twelve a wave at head dim 128 (ten of e4m3 with shared prompts), eight at 64 (twelve)
     ((64, 4, 7, 128, 0, 1536), (1, 4, 0, 1)),
     ((64, 4, 7, 128, 0, 1537), SCHEDULED),
-    ((300, 4, 1, 64, 1, 2048), (1, 4, 1, 1)),
-    ((300, 4, 1, 64, 1, 2049), SCHEDULED),
-    # ... ten of eight waves in no order, sixteen in order
-    ((29, 16, 1, 64, 1, 2560), (1, 8, 0, 1)),
-    ((29, 16, 1, 64, 1, 2561), SCHEDULED),
-    ((100, 2, 4, 64, 0, 2560), (1, 8, 0, 1)),
-    ((100, 2, 4, 64, 0, 2561), SCHEDULED),
-    ((45, 8, 8, 128, 1, 2560), (1, 8, 1, 1)),
+    ((64, 4, 7, 128, 0, 1536, 1), (1, 4, 0, 0)),
+    ((100, 4, 7, 128, 1, 1536), (1, 4, 0, 1)),
+    ((100, 8, 7, 128, 1, 1280, 1), (1, 4, 0, 0)),
+    ((100, 8, 7, 128, 1, 1281, 1), SCHEDULED),
+    ((300, 2, 4, 64, 0, 1024), (1, 4, 1, 1)),
+    ((300, 2, 4, 64, 0, 1025), SCHEDULED),
+    ((240, 2, 4, 64, 0, 1152), (1, 4, 0, 1)),             # (nine in one round)
+    ((240, 2, 4, 64, 0, 1153), SCHEDULED),
+    ((300, 4, 1, 64, 1, 1024), (1, 4, 1, 1)),
+    ((300, 4, 1, 64, 1, 1025), SCHEDULED),
+    ((520, 2, 4, 64, 1, 1536, 1), (1, 4, 0, 0)),
+    ((520, 2, 4, 64, 1, 1537, 1), SCHEDULED),
+    # ... eight of eight waves
+    ((29, 16, 1, 64, 1, 2048), (1, 8, 0, 1)),
+    ((29, 16, 1, 64, 1, 2049), SCHEDULED),
+    ((300, 2, 1, 64, 1, 2560), (1, 8, 1, 1)),             # (ten in order)
+    ((300, 2, 1, 64, 1, 2561), SCHEDULED),
+    ((45, 8, 8, 128, 1, 2560), (1, 8, 1, 1)),             # (ten at 128)
     ((45, 8, 8, 128, 1, 2561), SCHEDULED),
-    ((300, 2, 1, 64, 1, 4096), (1, 8, 1, 1)),
-    ((300, 2, 1, 64, 1, 4097), SCHEDULED),
-    # ... twelve of bf16 beyond one round in no order
-    ((849, 2, 4, 64, 0, 1536), (1, 4, 0, 1)),
-    ((849, 2, 4, 64, 0, 1537), SCHEDULED),
-    ((849, 2, 4, 64, 1, 1958), (1, 4, 0, 1)),
-    # ... eight where several workgroups share it
-    ((30, 4, 7, 128, 0, 2048), (2, 4, 0, 0)),
-    ((30, 4, 7, 128, 0, 2049), SCHEDULED),
-    # rounds of workgroups
-    ((192, 4, 7, 128, 0, 1024), (1, 4, 1, 1)),
-    ((193, 4, 7, 128, 0, 1024), SCHEDULED),
-    ((80, 8, 1, 128, 0, 679), (1, 4, 0, 1)),
-    ((81, 8, 1, 128, 0, 679), SCHEDULED),                 # ... with few query heads to a page
+    ((32, 8, 2, 128, 1, 1536), (1, 8, 0, 1)),             # ... six with few query heads to a page of 128
+    ((32, 8, 2, 128, 1, 1537), SCHEDULED),
+    # ... six where several workgroups share it
+    ((30, 4, 7, 128, 0, 1536), (2, 4, 0, 0)),
+    ((30, 4, 7, 128, 0, 1537), SCHEDULED),
+    ((43, 2, 2, 64, 0, 2560), (2, 8, 0, 0)),
+    ((43, 2, 2, 64, 0, 2561), SCHEDULED),                 # ... five of bf16 at head dim 64
+    ((43, 2, 2, 64, 1, 3072), (2, 8, 0, 0)),
+    ((43, 2, 2, 64, 1, 3073), SCHEDULED),
+    # rounds of workgroups: of bf16 pages of 128, ...
+    ((160, 4, 7, 128, 0, 1024), (1, 4, 1, 1)),
+    ((161, 4, 7, 128, 0, 1024), SCHEDULED),
+    ((256, 4, 7, 128, 0, 64), (1, 4, 0, 0)),              # (a small batch: as many as there are)
+    ((240, 4, 7, 128, 0, 512), (1, 4, 0, 1)),
+    ((241, 4, 7, 128, 0, 512), SCHEDULED),
+    ((144, 4, 7, 128, 0, 560, 1), (1, 4, 0, 0)),
+    ((145, 4, 7, 128, 0, 560, 1), SCHEDULED),
     ((256, 4, 7, 128, 0, 1024), SCHEDULED),               # one of them long, the others short: 21.5 us scheduled, 23.1 not
     ((256, 4, 7, 128, 0, 1536), SCHEDULED),
-    ((1000, 8, 1, 128, 0, 64), SCHEDULED),
+    # ... e4m3 ones of 128, ...
     ((448, 4, 7, 128, 1, 1471), (1, 4, 1, 1)),
     ((449, 4, 7, 128, 1, 1471), SCHEDULED),
-    ((1024, 4, 7, 128, 1, 308), (1, 4, 0, 1)),
-    ((1025, 4, 7, 128, 1, 308), SCHEDULED),
-    ((474, 8, 1, 128, 1, 481), SCHEDULED),                # few query heads to a page
-    ((224, 8, 2, 64, 0, 2000), (1, 4, 1, 1)),
-    ((225, 8, 2, 64, 0, 2000), SCHEDULED),
-    ((1024, 4, 4, 64, 0, 500), (1, 4, 0, 1)),
-    ((1024, 4, 2, 64, 0, 500), SCHEDULED),
-    ((478, 8, 5, 128, 1, 740), SCHEDULED),
-    ((512, 8, 2, 64, 1, 2000), (1, 4, 1, 1)),
-    ((513, 8, 2, 64, 1, 2000), SCHEDULED),
+    ((704, 4, 7, 128, 1, 512), (1, 4, 0, 1)),
+    ((705, 4, 7, 128, 1, 512), SCHEDULED),
+    ((448, 4, 3, 128, 1, 512), (1, 4, 0, 1)),
+    ((449, 4, 3, 128, 1, 512), SCHEDULED),
+    ((320, 4, 3, 128, 1, 513), (1, 4, 0, 1)),
+    ((321, 4, 3, 128, 1, 513), SCHEDULED),
+    # ... bf16 at head dim 64, ...
+    ((704, 4, 2, 64, 0, 512), (1, 4, 0, 1)),
+    ((705, 4, 2, 64, 0, 512), SCHEDULED),
+    ((512, 4, 2, 64, 0, 513), (1, 4, 0, 1)),
+    ((513, 4, 2, 64, 0, 513), SCHEDULED),
+    ((320, 4, 2, 64, 0, 800), (1, 4, 1, 1)),
+    ((321, 4, 2, 64, 0, 800), SCHEDULED),
+    # ... e4m3 at 64
+    ((1024, 4, 2, 64, 1, 512), (1, 4, 0, 1)),
+    ((1025, 4, 2, 64, 1, 512), SCHEDULED),
+    ((512, 8, 2, 64, 1, 1000), (1, 4, 1, 1)),
+    ((513, 8, 2, 64, 1, 1000), SCHEDULED),
+    ((2048, 2, 4, 64, 1, 600, 1), (1, 4, 0, 0)),
+    ((2049, 2, 4, 64, 1, 600, 1), SCHEDULED),
     # a last round that is nearly empty, of long items
     ((64, 4, 7, 128, 0, 1191), (1, 4, 0, 1)),
     ((35, 8, 1, 128, 0, 1191), SCHEDULED),
@@ -80,21 +103,22 @@ def plan(B, Hkv, G, D, fp8, tokens, share=0):
     ((129, 4, 16, 128, 0, 1311), SCHEDULED),
     ((154, 4, 16, 128, 0, 1311), (1, 4, 1, 1)),
     ((35, 8, 1, 128, 0, 700), (1, 4, 0, 1)),              # short ones: as many as there are
-    ((35, 8, 2, 64, 0, 2300), SCHEDULED),                 # eight waves: two fifths full
-    ((45, 8, 2, 64, 0, 2300), (1, 8, 1, 1)),
+    ((35, 8, 2, 64, 0, 2000), SCHEDULED),                 # eight waves: two fifths full
+    ((45, 8, 2, 64, 0, 2000), (1, 8, 1, 1)),
     # shared pages: what the caches take, less where a page has few query heads
     ((64, 4, 7, 128, 0, 1500, 1), (1, 4, 0, 0)),
     ((1024, 2, 4, 64, 1, 1280, 1), (1, 4, 0, 0)),
-    ((175, 4, 7, 128, 0, 927, 1), (1, 4, 0, 0)),
-    ((182, 4, 7, 128, 0, 944, 1), SCHEDULED),
+    ((128, 4, 7, 128, 0, 1280, 1), (1, 4, 0, 0)),
+    ((128, 4, 7, 128, 0, 1281, 1), SCHEDULED),
     ((128, 32, 1, 128, 1, 257, 1), SCHEDULED),
-    ((32, 8, 1, 128, 0, 1024, 1), (1, 4, 0, 0)),
-    ((32, 8, 1, 128, 0, 1040, 1), SCHEDULED),
+    ((32, 8, 1, 128, 0, 1026, 1), (1, 4, 0, 0)),
+    ((40, 8, 1, 128, 0, 592, 1), (1, 4, 0, 0)),           # (beyond one round)
+    ((40, 8, 1, 128, 0, 624, 1), SCHEDULED),
     ((200, 2, 4, 64, 0, 1546, 1), SCHEDULED),             # eight waves, bf16, beyond one round
     ((128, 2, 4, 64, 0, 1546, 1), (1, 8, 0, 0)),
+    ((200, 2, 16, 64, 0, 1800, 1), (1, 8, 0, 0)),
     ((400, 2, 4, 64, 1, 1600, 1), (1, 8, 0, 0)),
     ((116, 4, 7, 128, 1, 2048, 1), (1, 8, 0, 0)),
-    ((116, 4, 7, 128, 1, 2049, 1), SCHEDULED),
     ((160, 8, 5, 128, 1, 1518, 1), SCHEDULED),
     # nothing to do
     ((0, 4, 7, 128, 0, 1024), SCHEDULED),

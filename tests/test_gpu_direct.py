@@ -31,24 +31,25 @@ S = (0, 0, 0, 0)             # has a schedule; otherwise workgroups per item, th
 @pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
 @pytest.mark.parametrize("Hq,Hkv,D,prompts,R,resp,plans", [
     (8, 4, 128, [0] * 40, 1, lens(40, 1536, 1), ((1, 4, 0, 1), (1, 8, 0, 1))),   # side by side: four waves (bf16), eight (e4m3); longest item
-    (8, 4, 128, [0] * 40, 1, lens(40, 1537, 2), (S, (1, 8, 0, 1))),              # ... and a page past it
-    (7, 1, 128, [0] * 200, 1, lens(200, 3073, 3), (S, S)),
+    (16, 4, 128, [0] * 40, 1, lens(40, 1537, 2), (S, (1, 8, 0, 1))),              # ... and a page past it
+    (16, 4, 128, [0] * 40, 1, lens(40, 2561, 3), (S, S)),
     (8, 4, 128, [0] * 90, 1, lens(90, 900, 4), ((1, 4, 1, 1), (1, 4, 0, 1))),    # more items than compute units, in order (bf16)
     (8, 4, 128, [0] * 131, 1, lens(131, 900, 13), (S, (1, 4, 1, 1))),            # ... e4m3; not a multiple of eight
-    (2, 1, 128, [0] * 360, 1, lens(360, 1601, 5), (S, (1, 8, 1, 1))),            # in order, eight waves (e4m3)
-    (8, 2, 64, [0] * 100, 1, lens(100, 2560, 6), ((1, 8, 0, 1), (1, 8, 0, 1))),  # eight waves, ten stages each
-    (8, 2, 64, [0] * 100, 1, lens(100, 2561, 7), (S, S)),
+    (4, 1, 128, [0] * 360, 1, lens(360, 1601, 5), (S, (1, 8, 1, 1))),            # in order, eight waves (e4m3)
+    (8, 2, 64, [0] * 100, 1, lens(100, 2048, 6), ((1, 8, 0, 1), (1, 8, 0, 1))),  # eight waves, eight stages each
+    (8, 2, 64, [0] * 100, 1, lens(100, 2049, 7), (S, S)),
     (8, 2, 64, [0] * 180, 1, lens(180, 1700, 14), ((1, 8, 1, 1), (1, 8, 0, 1))),  # ... in order (bf16)
-    (4, 2, 64, [0] * 512, 1, lens(512, 1760, 15), ((1, 4, 1, 1), (1, 8, 1, 1))),  # as many as are put in order; eight waves (e4m3)
-    (4, 4, 64, [0] * 257, 1, lens(257, 1024, 16), ((1, 4, 1, 1), (1, 4, 1, 1))),  # in order, four waves
-    (4, 2, 64, [0] * 512, 1, [0] * 9 + [700] * 487 + [1760] * 16, ((1, 4, 1, 1), (1, 8, 1, 1))),  # levels full of equals
-    (4, 4, 64, [0] * 300, 1, [800] * 300, ((1, 4, 1, 1), (1, 4, 1, 1))),         # ... one level for all, of a width that is no power of two
-    (8, 4, 128, [0] * 30, 1, lens(30, 2048, 10), ((2, 4, 0, 0), (2, 8, 0, 0))),  # two or three workgroups to an item and the merge
-    (8, 4, 128, [0] * 30, 1, lens(30, 2049, 11), (S, (2, 8, 0, 0))),             # ... and a page past it (bf16)
-    (4, 2, 64, [0] * 60, 1, lens(60, 4096, 12), ((2, 8, 0, 0), (2, 8, 0, 0))),
+    (4, 2, 64, [0] * 512, 1, lens(512, 1760, 15), (S, (1, 8, 1, 1))),            # as many as are put in order, eight waves
+    (2, 2, 64, [0] * 512, 1, lens(512, 1000, 16), ((1, 4, 1, 1), (1, 4, 0, 1))),  # ... four waves (bf16)
+    (4, 4, 64, [0] * 300, 1, lens(300, 1000, 18), ((1, 4, 1, 1), (1, 4, 1, 1))),            # ... e4m3
+    (2, 2, 64, [0] * 512, 1, [0] * 9 + [700] * 487 + [1000] * 16, ((1, 4, 1, 1), (1, 4, 0, 1))),  # levels full of equals
+    (4, 4, 64, [0] * 300, 1, [800] * 300, ((1, 4, 1, 1), (1, 4, 1, 1))),                    # ... one level for all, of a width that is no power of two
+    (8, 4, 128, [0] * 30, 1, lens(30, 1536, 10), ((2, 4, 0, 0), (2, 8, 0, 0))),  # two or three workgroups to an item and the merge
+    (8, 4, 128, [0] * 30, 1, lens(30, 1537, 11), (S, (2, 8, 0, 0))),             # ... and a page past it (bf16)
+    (4, 2, 64, [0] * 60, 1, lens(60, 2560, 12), ((2, 8, 0, 0), (2, 8, 0, 0))),
     (2, 1, 64, [0] * 512, 1, [0] * 9 + [700] * 495 + [32 * 64 // 2] * 8, ((1, 4, 0, 1), (1, 4, 0, 1))),  # no more than run side by side: as they come
-    (2, 1, 64, [0] * 517, 1, lens(517, 1024, 8), ((1, 4, 0, 1), (1, 4, 0, 1))),  # more sequences than are put in order
-    (4, 1, 64, [0] * 2049, 1, [33, 0, 17] * 683, ((1, 4, 0, 1), (1, 4, 0, 1))),
+    (2, 1, 64, [0] * 517, 1, lens(517, 768, 8), ((1, 4, 0, 1), (1, 4, 0, 1))),   # more sequences than are put in order
+    (4, 1, 64, [0] * 1789, 1, [33, 0, 17] * 596 + [33], ((1, 4, 0, 1), (1, 4, 0, 1))),
     (4, 2, 64, [100, 0, 333], 100, lens(300, 300, 9), ((1, 4, 0, 0), (1, 4, 0, 0))),  # groups: a member reads all its pages; some shorter than the prompt
 ])
 def test_a_workgroup_per_item(dec, kvd, Hq, Hkv, D, prompts, R, resp, plans):
@@ -74,8 +75,9 @@ def test_a_workgroup_per_item(dec, kvd, Hq, Hkv, D, prompts, R, resp, plans):
 @pytest.mark.parametrize("kvd", ["bf16", "fp8_e4m3"])
 @pytest.mark.parametrize("Hq,Hkv,D,B,top,plans", [
     (4, 2, 64, 70, 1500, ((1, 8, 0, 1), (1, 8, 0, 0))),
-    (8, 4, 128, 40, 1537, (S, (1, 8, 0, 1))),
-    (4, 2, 64, 300, 1600, ((1, 4, 1, 1), (1, 8, 1, 1))),
+    (16, 4, 128, 40, 1537, (S, (1, 8, 0, 1))),
+    (4, 2, 64, 300, 1600, (S, (1, 8, 1, 1))),
+    (8, 2, 64, 180, 1700, ((1, 8, 1, 1), (1, 8, 0, 1))),
     (8, 4, 128, 90, 900, ((1, 4, 1, 1), (1, 4, 0, 1))),
 ])
 def test_strided_pools(dec, kvd, Hq, Hkv, D, B, top, plans):
