@@ -1639,7 +1639,7 @@ __device__ __forceinline__ void merge_write(const Launch &a, int64_t bh, int d4,
 // Measured (MI355X, scheduled -> here, us a step): four sequences of up to 256 tokens, D = 64: 15.7 -> 6.5; eight of one
 // prompt, 500 to 2000, D = 128: 33.4 -> 10.7; 64 of U[0, 1536], 28 heads on four, bf16: 28.5 -> 21.6 (all full 42 -> 32, one
 // long 20.1 -> 16.1); 104 of U[0, 2475], e4m3: 38 -> 30; 300 of U[0, 1024], eight heads on two, D = 64, bf16: 24.4 -> 16.4;
-// 1024 of U[0, 1536], the same, e4m3: 59 -> 40; eight groups of eight, 300 + U[0, 1200], 28 on four, bf16: 35 -> 20.8.
+// 1004 of U[0, 797], the same, e4m3: 42 -> 23; eight groups of eight, 300 + U[0, 1200], 28 on four, bf16: 35 -> 20.8.
 // ------------------------------------------------------------------------------------------------------
 
 // Batches that a schedule would not pay for even with every table row full: up to so many items per compute unit and bytes
@@ -1669,8 +1669,8 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
     touch_args(a);
     int item = blockIdx.x / a.splits;
     const int part = blockIdx.x - item * a.splits;
-    // Workgroups are dealt to the dies by number: turned about in every eight, a pattern in the lengths meets all dies (1290
-    // sequences of two kv heads, D = 64, e4m3, every 16th of them 1305 tokens and the rest 81: 47 us as they come, 28 turned).
+    // Workgroups are dealt to the dies by number: turned about in every eight, a pattern in the lengths meets all dies (1450
+    // sequences of two kv heads, D = 64, e4m3, every 16th of them 827 tokens and the rest 51: 37 us as they come, 23 turned).
     // Not where prompts are shared: a group's members find its pages in their die's L2 (64 sequences in eight groups 20.8 us, turned 24.5).
     if (a.turned && item < (a.B * a.Hkv & ~7)) item = (item & ~7) | ((item + (item >> 3) + (item >> 6)) & 7);
     int b = item / a.Hkv;
