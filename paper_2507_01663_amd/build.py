@@ -11,7 +11,9 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
           "-Wall", "-Wno-inline-asm", "-Wno-int-to-pointer-cast", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option"]
 # The decode kernels keep their few MFMA accumulators in ordinary vector registers; the prefill kernel has more
 # accumulators than those hold and leaves them in the accumulation registers, where the matrix cores reach them directly.
-EXTRA = {"ra_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"], "ra_prefill.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+# kernarg-preload-count: a kernel's leading plain arguments are in registers when its waves start (see the kernels that have any).
+EXTRA = {"ra_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-kernarg-preload-count=14"],
+         "ra_prefill.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def flags_for(source: str):

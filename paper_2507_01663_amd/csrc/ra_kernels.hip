@@ -780,11 +780,15 @@ __device__ __forceinline__ void issue_qrows(const Launch &a, const uint16_t *__r
 // min(NST-1, entries) entries of this segment are in flight; on exit the same holds for `nxt`.  Query rows of an
 // own-pages segment (NQT == 1) wait in the query slot; those of a shared-pages segment are its first ring entry.
 // A one-tile partial goes back in `ret` (normalised, with its log2-sum-exp); a shared-prefix partial is stored.
-template <int D, int KVB, int NQT, int NST, int NP>
+// page_of(segment, p) is the id of page p of a segment's work row.
+struct ScalarPages {
+    __device__ __forceinline__ int operator()(const Segment &sg, int p) const { return uniform_load(sg.pages, p); }
+};
+template <int D, int KVB, int NQT, int NST, int NP, class PageOf = ScalarPages>
 __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__restrict__ q, const Segment &cur, bool has_nxt,
                                             const Segment &nxt, Ring &ring, const LaneConst<D, KVB> &lc, uint8_t *lds,
                                             uint32_t lds_addr, Pending<D> &ret, Pending<D> (&pk)[NP], bool park, int lane,
-                                            int q_off = LdsMap<D, KVB, NST>::kQBase)
+                                            int q_off = LdsMap<D, KVB, NST>::kQBase, const PageOf &page_of = PageOf())
 {
     static_assert(NQT == 1 || NQT <= NP, "a shared-prefix partial has a waiting register set per tile");
     using G = Geo<D, KVB>;
@@ -809,10 +813,10 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
         int id = 0;
         if (rel < niter) {
             const int st = rel - QL, p = cur.pg_lo + 2 * st + h;
-            if (st >= 0 && p < cur.pg_hi) id = uniform_load(cur.pages, p);
+            if (st >= 0 && p < cur.pg_hi) id = page_of(cur, p);
         } else if (rel < total) {
             const int st = rel - niter - nxt_ql, p = nxt.pg_lo + 2 * st + h;
-            if (st >= 0 && p < nxt.pg_hi) id = uniform_load(nxt.pages, p);
+            if (st >= 0 && p < nxt.pg_hi) id = page_of(nxt, p);
         }
         return id;
     };
@@ -1660,13 +1664,31 @@ template <int D, int KVB, int W> struct DirectLds {
     static_assert(kWave % 256 == 0 && kPage * D * 4 + 64 <= kWave, "a wave's partial fits its ring");
 };
 
+// Page ids of a wave's part of an item in registers, the first 64 of them, a lane each.  A short call is a chain of trips to
+// memory: arguments, length, page ids, pages, and with several workgroups to an item a second kernel's arguments, descriptor
+// and partials.  With the table's row asked for beside the length, what the first loads need among the leading arguments
+// (those are in registers when a wave starts) and the partials' places known without a descriptor: eight sequences of one
+// prompt, 500 to 2000 tokens, 28 heads on four, bf16, 11.2 -> 10.6 us, four of up to 3000 without one 10.95 -> 10.25, 30 of U[0,
+// 1536], e4m3, two layers 28.1 -> 27.3; where the stream or one long item bounds a call nothing (64 of U[0, 1536], bf16, 22.7).
+struct LanePages {
+    int id, base; // lane i: page base + i of the row
+    __device__ __forceinline__ int operator()(const Segment &sg, int p) const
+    {
+        return p - base < 64 ? __builtin_amdgcn_readlane(id, p - base) : uniform_load(sg.pages, p);
+    }
+};
+
 template <int D, int KVB, int W, bool SORTED>
-__global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t *__restrict__ q, const int32_t *__restrict__ block_table)
+__global__ __launch_bounds__(64 * W) void direct_kernel(const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ block_table,
+                                                        const uint16_t *__restrict__ q, const void *zeros, int Hq, int Hkv, int G, int max_pages,
+                                                        int splits, int turned, Launch given)
 {
+    Launch a = given; // (what comes first by the arguments that are there when the wave starts)
+    a.zeros = zeros, a.Hq = Hq, a.Hkv = Hkv, a.G = G, a.max_pages = max_pages, a.splits = splits, a.turned = turned;
     using X = DirectLds<D, KVB, W>;
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    touch_args(a);
+    touch_args(given);
     int item = blockIdx.x / a.splits;
     const int part = blockIdx.x - item * a.splits;
     // Workgroups are dealt to the dies by number: turned about in every eight, a pattern in the lengths meets all dies (1450
@@ -1683,7 +1705,7 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
         const int most = a.max_pages * kPage;
         int len[N];
 #pragma unroll
-        for (int k = 0; k < N; k++) len[k] = 64 * k + lane < a.B ? a.seq_lens[64 * k + lane] : 0;
+        for (int k = 0; k < N; k++) len[k] = 64 * k + lane < a.B ? seq_lens[64 * k + lane] : 0;
 #pragma unroll
         for (int k = 0; k < N; k++) len[k] = 64 * k + lane >= a.B ? -1 : (len[k] < 0 ? 0 : (len[k] > most ? most : len[k]));
         const int shift = max(0, 28 - __builtin_clz(most | 1));
@@ -1714,36 +1736,51 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
         }
         item = b * a.Hkv + kvh;
     } else {
-        L = uniform_load(a.seq_lens, b);
-        L = L < 0 ? 0 : (L > a.max_pages * kPage ? a.max_pages * kPage : L); // never walk past the table row
+        L = uniform_load(seq_lens, b);
     }
-    const int n = (L + kPage - 1) / kPage, nst = (n + 1) >> 1;
-    const int k = part * W + wave, all = a.splits * W;
-    uint8_t *const mine = lds + wave * X::kWave;
-    const uint32_t mine_addr = (uint32_t)(uintptr_t)mine;
     Segment sg;
     sg.pages = block_table + (int64_t)b * a.max_pages;
+    sg.kvh = kvh, sg.prefix = 0, sg.b = b, sg.moff = 0, sg.nrows = a.G, sg.slot = 0, sg.mvec = 0;
+    uint8_t *const mine = lds + wave * X::kWave;
+    const uint32_t mine_addr = (uint32_t)(uintptr_t)mine;
+    const int q_off = X::kQBase - wave * X::kWave;
+    LaneConst<D, KVB> lc;
+    // The query rows, and a short table row whole, are asked for beside the length: one trip for all three.
+    // (Every wave brings the query rows, all to one place: the same bytes, so each needs to wait for its own loads only.)
+    issue_q<D, KVB, 2>(a, q, lc, sg, mine_addr + q_off, lane);
+    const bool whole = a.max_pages <= 128;
+    int row0 = 0, row1 = 0;
+    if (whole && lane < a.max_pages) row0 = sg.pages[lane];
+    if (whole && 64 + lane < a.max_pages) row1 = sg.pages[64 + lane];
+    L = L < 0 ? 0 : (L > a.max_pages * kPage ? a.max_pages * kPage : L); // never walk past the table row
+    const int n = (L + kPage - 1) / kPage, nst = (n + 1) >> 1;
+    const int k = part * W + wave, all = a.splits * W;
     const int lo = (int)((int64_t)nst * k / all), hi = (int)((int64_t)nst * (k + 1) / all);
     sg.pg_lo = 2 * lo;
     sg.pg_hi = 2 * hi < n ? 2 * hi : n;
     sg.limit = min(L, sg.pg_hi * kPage);
-    sg.kvh = kvh, sg.prefix = 0, sg.b = b, sg.moff = 0, sg.nrows = a.G, sg.slot = 0, sg.mvec = 0;
+    LanePages ids = {0, sg.pg_lo};
+    const int from = sg.pg_lo + lane;
+    if (whole) {
+        const int x0 = __builtin_amdgcn_ds_bpermute(4 * from, row0), x1 = __builtin_amdgcn_ds_bpermute(4 * from, row1); // (from modulo 64)
+        ids.id = from < 64 ? x0 : x1;
+    } else if (from < sg.pg_hi) {
+        ids.id = sg.pages[from];
+    }
+    asm volatile("" : "+v"(ids.id)); // (the compiler's wait for them: here, and not behind the ring's first loads)
     Pending<D> res, none[1];
     res.lse2 = -INFINITY;
 #pragma unroll
     for (int dt = 0; dt < D / 16; dt++) res.o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
     if (lo < hi) {
-        LaneConst<D, KVB> lc;
         lane_setup<D, KVB>(lc, lane, a.stride_token_b);
         Ring ring = {0, 0};
-        // (every wave brings the query rows, all to one place: the same bytes, so each needs to wait for its own loads only)
-        const int q_off = X::kQBase - wave * X::kWave;
-        issue_q<D, KVB, 2>(a, q, lc, sg, mine_addr + q_off, lane);
-        const int id0 = uniform_load(sg.pages, sg.pg_lo), id1 = sg.pg_lo + 1 < sg.pg_hi ? uniform_load(sg.pages, sg.pg_lo + 1) : 0;
+        const int id0 = ids(sg, sg.pg_lo), id1 = sg.pg_lo + 1 < sg.pg_hi ? ids(sg, sg.pg_lo + 1) : 0;
         issue_stage<D, KVB, 2>(a, lc, sg, 0, id0, id1, 0, mine_addr, lane);
         ring.issued++;
-        run_segment<D, KVB, 1, 2>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane, q_off);
+        run_segment<D, KVB, 1, 2>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane, q_off, ids);
     }
+    wait_vmcnt<0>(); // (a wave without pages has brought the query rows all the same)
     // every wave's partial into its own ring (nothing is in flight any more), then the workgroup adds them up
     {
         const int row = lane & 15, j = lane >> 4;
@@ -1768,16 +1805,11 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(Launch a, const uint16_t
         if (a.splits == 1) {
             merge_write(a, (int64_t)b * a.Hq + kvh * a.G + hl, d4, M, wsum, acc);
         } else {
-            // (slot item + span with span = item * (splits - 1) + part: see the descriptor below)
+            // (slot item + span with span = item * (splits - 1) + part: see merge_lists)
             const int64_t row = ((int64_t)item * a.splits + part) * a.G + hl;
             *(f32x4 *)(a.ws.suf_o + row * D + d4) = wsum == 0.f ? acc : acc * (1.0f / wsum);
             if (d4 == 0) a.ws.suf_lse[row] = wsum == 0.f ? -INFINITY : M + __builtin_amdgcn_logf(wsum);
         }
-    }
-    if (a.splits > 1 && part == 0 && threadIdx.x == 0) {
-        const int first = item * (a.splits - 1);
-        a.ws.merge_desc[2 * item] = make_int4(n, first, first + a.splits - 1, 0);
-        a.ws.merge_desc[2 * item + 1] = make_int4(0, 0, -1, 0);
     }
 }
 
@@ -1895,7 +1927,7 @@ static hipError_t launch_direct(const Launch &a, hipStream_t s)
 {
 #define RA_DIRECT(DD, KVB, W, S)                                                                                          \
     if (a.D == DD && a.kv_fp8 == (KVB == 1) && a.direct_waves == W && (a.sorted != 0) == S)                               \
-        hipLaunchKernelGGL((direct_kernel<DD, KVB, W, S>), dim3(a.B * a.Hkv * a.splits), dim3(64 * W), (DirectLds<DD, KVB, W>::kBytes), s, a, a.q, a.block_table);
+        hipLaunchKernelGGL((direct_kernel<DD, KVB, W, S>), dim3(a.B * a.Hkv * a.splits), dim3(64 * W), (DirectLds<DD, KVB, W>::kBytes), s, a.seq_lens, a.block_table, a.q, a.zeros, a.Hq, a.Hkv, a.G, a.max_pages, a.splits, a.turned, a);
     RA_DIRECT_KERNELS(RA_DIRECT)
 #undef RA_DIRECT
     return hipGetLastError();
@@ -2040,8 +2072,14 @@ __device__ __forceinline__ void merge_lists(const Launch &a, const int4 *__restr
 {
     const Workspace &w = a.ws;
     const int D = a.D;
+    if (a.splits) {
+        // a batch without a schedule: every item has a.splits partials in a row, the places are known without a trip to memory
+        const int first = item * (a.splits - 1);
+        pl[1] = {first, first + a.splits - 1, w.suf_o + (int64_t)item * a.G * D, w.suf_lse + (int64_t)item * a.G, (int64_t)a.G * D, a.G};
+        pl[0] = {0, -1, w.pfx_o, w.pfx_lse, 0, 0};
+        return;
+    }
     int4 own = merge_desc[2 * item], pfx = merge_desc[2 * item + 1];
-    // (a batch without a schedule has nothing in these two: its shared lists are empty, so what they address is not read)
     int prow = seq_pfx_row[b];
     const int row0 = seq_rank_in_row[b] * a.G;
     if (a.self_plan) {
@@ -2069,11 +2107,12 @@ __device__ __forceinline__ void merge_lists(const Launch &a, const int4 *__restr
     }
 }
 
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const int4 *__restrict__ merge_desc,
-                                                               const int32_t *__restrict__ seq_pfx_row,
-                                                               const int32_t *__restrict__ seq_rank_in_row)
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
+    const int32_t *__restrict__ seq_rank_in_row, float *suf_o, float *suf_lse, int Hkv, int G, int D_, int splits, Launch given)
 {
-    touch_args(a);
+    Launch a = given;
+    a.ws.suf_o = suf_o, a.ws.suf_lse = suf_lse, a.Hkv = Hkv, a.G = G, a.D = D_, a.splits = splits;
+    touch_args(given);
     const int item = blockIdx.x, b = item / a.Hkv, kvh = item - b * a.Hkv;
     const int D = a.D, tpr = D / 4; // threads per output row
     PartList pl[2];
@@ -2122,11 +2161,12 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(Launch a, const in
 // workgroup takes one head of one item; its threads form lanes of D / 4, which take the partials turn about, four at a
 // time each, so that up to 32 (D = 128) are on their way together; the lanes' sums meet in LDS, in lane order.  One
 // partial after the other is what bound the kernel above there: 13.2 us for 48 items of 21 spans (D = 128, five heads), 4.7 here.
-__global__ __launch_bounds__(kMergeThreads) void merge_wide_kernel(Launch a, const int4 *__restrict__ merge_desc,
-                                                                   const int32_t *__restrict__ seq_pfx_row,
-                                                                   const int32_t *__restrict__ seq_rank_in_row)
+__global__ __launch_bounds__(kMergeThreads) void merge_wide_kernel(const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
+    const int32_t *__restrict__ seq_rank_in_row, float *suf_o, float *suf_lse, int Hkv, int G, int D_, int splits, Launch given)
 {
-    touch_args(a);
+    Launch a = given;
+    a.ws.suf_o = suf_o, a.ws.suf_lse = suf_lse, a.Hkv = Hkv, a.G = G, a.D = D_, a.splits = splits;
+    touch_args(given);
     __shared__ f32x4 s_acc[kMergeThreads];
     __shared__ float s_m[kMergeThreads / 16], s_w[kMergeThreads / 16];
     const int item = blockIdx.x / a.G, hl = blockIdx.x - item * a.G, b = item / a.Hkv, kvh = item - b * a.Hkv;
@@ -2182,10 +2222,11 @@ hipError_t launch_merge(const Launch &a, hipStream_t s)
     // 45.2 -> 45.0 at 5000; 2560 (512 items of 5, e4m3) 20.3 -> 24.2 and 80.7 -> 92.8.
     const int64_t items = (int64_t)a.B * a.Hkv;
     if (items * a.G <= kMergeWideMax && (a.splits ? a.splits > 4 : a.waves >= 3 * items))
-        hipLaunchKernelGGL(merge_wide_kernel, dim3(a.B * a.Hkv * a.G), dim3(kMergeThreads), 0, s, a, w.merge_desc, w.seq_pfx_row,
-                           w.seq_rank_in_row);
+        hipLaunchKernelGGL(merge_wide_kernel, dim3(a.B * a.Hkv * a.G), dim3(kMergeThreads), 0, s, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row, w.suf_o,
+                           w.suf_lse, a.Hkv, a.G, a.D, a.splits, a);
     else
-        hipLaunchKernelGGL(merge_kernel, dim3(a.B * a.Hkv), dim3(kMergeThreads), 0, s, a, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row);
+        hipLaunchKernelGGL(merge_kernel, dim3(a.B * a.Hkv), dim3(kMergeThreads), 0, s, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row, w.suf_o,
+                           w.suf_lse, a.Hkv, a.G, a.D, a.splits, a);
     return hipGetLastError();
 }
 

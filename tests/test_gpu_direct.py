@@ -95,3 +95,19 @@ def test_strided_pools(dec, kvd, Hq, Hkv, D, B, top, plans):
     print("case", Hq, Hkv, D, B, top, kvd, flush=True)
     dec.decode(dp.c)
     compare(*dp.results(), *oracle.decode(p), "strided", abs_rel=2.0 ** -8)
+
+
+@pytest.mark.parametrize("kvd,Hq,Hkv,D", [("bf16", 28, 4, 128), ("fp8_e4m3", 8, 2, 64)])
+@pytest.mark.parametrize("pages", [1, 2, 63, 64, 65, 127, 128, 129, 193])
+def test_widths_of_the_table(dec, kvd, Hq, Hkv, D, pages):
+    """Rows of up to 128 page ids are read whole, beside the length; of a longer one a wave reads the first 64 entries of its part.
+    One sequence fills its row, others end anywhere; several workgroups share an item and the merge adds them up."""
+    top = 16 * pages
+    p = workload.build_problem("width", Hq, Hkv, D, [0] * 4, 1, [top - 3, 0, 1, top // 2 + 1], kv_dtype=kvd, seed=47)
+    plan = plan_of(dec, p, use_hint=False)
+    assert plan.splits == 1 if pages < 63 else plan.splits > 1
+    dp = DeviceProblem(p, use_hint=False)
+    dec.workspace(dp.c).fill_(0xA5)
+    print("case", kvd, Hq, Hkv, D, pages, flush=True)
+    dec.decode(dp.c)
+    compare(*dp.results(), *oracle.decode(p), "width", abs_rel=2.0 ** -8)
