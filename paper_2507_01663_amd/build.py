@@ -5,15 +5,15 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librollout_attn.so")
-SOURCES = ["ra_kernels.hip", "ra_prefill.hip", "ra_api.cpp", "ra_balance.cpp"]
+SOURCES = ["ra_kernels.hip", "ra_prefill.hip", "ra_prefill_four.hip", "ra_api.cpp", "ra_balance.cpp"]
 COMMON = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-Wall", "-Wno-inline-asm", "-Wno-int-to-pointer-cast", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option"]
 # The decode kernels keep their few MFMA accumulators in ordinary vector registers; the prefill kernel has more
 # accumulators than those hold and leaves them in the accumulation registers, where the matrix cores reach them directly.
 # kernarg-preload-count: a kernel's leading plain arguments are in registers when its waves start (see the kernels that have any).
-EXTRA = {"ra_kernels.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-kernarg-preload-count=14"],
-         "ra_prefill.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
+KERNELS = ["-mllvm", "-amdgpu-mfma-vgpr-form=1", "-mllvm", "-amdgpu-kernarg-preload-count=14"]
+EXTRA = {s: KERNELS for s in SOURCES if s.endswith(".hip")}
 
 
 def flags_for(source: str):

@@ -129,6 +129,15 @@ hipError_t launch_append(const Launch &a, const void *k_new, const void *v_new, 
 // Causal attention of the packed prompts (prefill_kernel) and the write of their K/V rows into pages.
 // Once per device, before the first launch_prefill: lets the prefill kernels have the LDS they ask for.
 hipError_t prefill_config();
+// How a prefill call is launched: waves of a workgroup (eight that stay and take block after block, or one workgroup per block
+// of four or, where two waves share a unit's keys, eight), those parts of the keys, blocks of one (prompt, kv head) that a die
+// takes at most, workgroups per die.  stay: as in PrefillLaunch.
+struct PrefillShape {
+    int32_t waves, parts, levels, per_die;
+};
+PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int Hkv, int G, int D, int num_cus, int stay);
+hipError_t prefill_four_config();
+hipError_t launch_prefill_four(const PrefillLaunch &a, unsigned workgroups, hipStream_t s);
 hipError_t launch_prefill(const PrefillLaunch &a, hipStream_t s);
 // Whether launch_prefill writes the cache as well (then launch_prefill_write is not called).
 bool prefill_writes_cache(const PrefillLaunch &a);

@@ -1,0 +1,92 @@
+"""Prefill calls of few blocks: workgroups of four waves, and two waves to a unit's keys, against the oracle at the edges of
+tiles and stages, with cache writes bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2507_01663_amd as ra
+import workload
+from test_gpu_prefill import DevicePrefill, compare, expected_pools
+from test_prefill_shape import kind
+from workload.gen import bf16_bits_to_f32
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dec():
+    d = ra.Decoder(0)
+    yield d
+    d.close()
+
+
+def check(dec, b, want, kv_dtype=None, what="", bound=None):
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert kind([int(x) for x in b.lens], b.Hq, b.Hkv, b.D, bound, cus=cus) == want
+    d = DevicePrefill(b, kv_dtype, max_len=bound)
+    print("case", what, b.Hq, b.Hkv, b.D, list(b.lens), kv_dtype, flush=True)
+    dec.prefill(d.c)
+    out, lse = d.results()
+    compare(out, lse, *oracle.prefill(b.q, b.k, b.v, b.cu_seqlens, b.softmax_scale), what)
+    first = d.out.clone()
+    dec.prefill(d.c)
+    torch.cuda.synchronize()
+    assert torch.equal(first.view(torch.int16), d.out.view(torch.int16))
+    return d
+
+
+@pytest.mark.parametrize("Hq,Hkv,D", [(28, 4, 128), (4, 2, 64), (3, 1, 128), (8, 8, 64), (16, 1, 128), (10, 2, 128)])
+@pytest.mark.parametrize("lens,want", [
+    ([1], "four"), ([31, 0, 33], "four"), ([64, 65], "four"), ([256], "four"),
+    ([257], "halves"), ([288], "halves"), ([289], "halves"), ([320, 31], "halves"), ([33, 415], "halves"), ([640], "halves"),
+])
+def test_edges_of_tiles_and_stages(dec, Hq, Hkv, D, lens, want):
+    check(dec, workload.build_prefill("few", Hq, Hkv, D, lens, seed=21), want, what="few")
+
+
+@pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
+@pytest.mark.parametrize("Hq,Hkv,D,lens,want", [
+    (28, 4, 128, [300, 17], "halves"), (8, 2, 64, [17, 290, 16, 1], "halves"), (28, 4, 128, [100, 31, 0, 50], "four"), (16, 2, 64, [47, 128], "four"),
+    (28, 4, 128, [600, 30, 333, 80, 200, 513, 47], "four"),
+])
+def test_cache_writes(dec, kv_dtype, Hq, Hkv, D, lens, want):
+    b = workload.build_prefill("few", Hq, Hkv, D, lens, seed=23)
+    d = check(dec, b, want, kv_dtype, "write")
+    k, v, ks, vs = expected_pools(b, kv_dtype)
+    for got, ref in ((d.k_pool, k), (d.v_pool, v)):
+        got = got.view(torch.int16).cpu().numpy().view(np.uint16) if kv_dtype == "bf16" else got.cpu().numpy()
+        assert np.array_equal(got, ref)
+    if ks is not None:
+        assert np.array_equal(d.k_scale.cpu().numpy(), ks, equal_nan=True) and np.array_equal(d.v_scale.cpu().numpy(), vs, equal_nan=True)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_keys_of_one_part_that_dwarf_the_other_parts(dec, D):
+    """The parts' reference points lie far apart: the one with the small scores has to vanish, whichever it is."""
+    for t in (5, 40, 70, 299):
+        b = workload.build_prefill("few", 8, 2, D, [300], seed=25)
+        k = bf16_bits_to_f32(b.k).copy()
+        k[t] *= 1000.0
+        b.k = workload.f32_to_bf16_bits(k)
+        check(dec, b, "halves", what="dominant key %d" % t)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_scores_of_minus_infinity_in_one_part(dec, D):
+    """All keys of the odd stages score -inf: their weights are zero and the results those of the even stages' keys alone."""
+    b = workload.build_prefill("few", 4, 1, D, [300], seed=27)
+    d = DevicePrefill(b)
+    odd = (torch.arange(300, device="cuda:0") // 32) % 2 == 1
+    d.q[..., 0] = 1.0
+    d.k[odd] = 0.0
+    d.k[odd, :, 0] = float("-inf")
+    dec.prefill(d.c)
+    torch.cuda.synchronize()
+    q, k, v = d.q.double().transpose(0, 1), d.k[:, 0].double(), d.v[:, 0].double()
+    s = torch.where(odd[None, None, :], float("-inf"), (q @ torch.where(odd[:, None], 0.0, k).t().contiguous()) * float(b.softmax_scale))
+    s = s.masked_fill(torch.ones((300, 300), dtype=torch.bool, device="cuda:0").triu(1), float("-inf"))
+    ref = (s.softmax(-1) @ v).transpose(0, 1)
+    assert torch.isfinite(d.out).all()
+    assert float((d.out.double() - ref).norm() / ref.norm()) < 1e-2
+    assert float((d.lse.double() - torch.logsumexp(s, -1).t()).abs().max()) < 1e-3

@@ -1,0 +1,84 @@
+"""Which launch shape a prefill call takes (CPU: the rule is a function of the sizes): its edges, and that what it says is
+consistent over drawn calls."""
+import ctypes
+import random
+
+import pytest
+
+import paper_2507_01663_amd as ra
+
+CUS = 256
+AUTO = -1
+
+
+class Shape(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int32) for n in ("waves", "parts", "levels", "per_die")]
+
+
+def shape(lens, Hq, Hkv, D, bound=None, stay=AUTO, cus=CUS):
+    """The library's own rule; it is no entry point of the C ABI, so it is called by the name the compiler gave it."""
+    f = ra.load_library()._ZN2ra13prefill_shapeEiiiiiiii
+    f.restype = Shape
+    return f(len(lens), sum(lens), max(lens) if bound is None else bound, Hkv, Hq // Hkv, D, cus, stay)
+
+
+def kind(*a, **k):
+    s = shape(*a, **k)
+    return {(8, 1): "stay", (4, 1): "four", (8, 2): "halves"}[s.waves, s.parts]
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,D,bound,want", [
+    ([256], 28, 4, 128, None, "four"),            # short: four waves, also with a compute unit to each block
+    ([257], 28, 4, 128, None, "halves"),
+    ([701], 28, 4, 128, None, "halves"),
+    ([1100], 28, 4, 128, None, "halves"),         # 247 blocks
+    ([1200], 28, 4, 128, None, "four"),           # 269
+    ([128] * 8, 28, 4, 128, None, "four"),
+    ([368] * 6, 28, 4, 128, None, "four"),        # 487 blocks by the tokens: two to a compute unit
+    ([368] * 8, 28, 4, 128, None, "stay"),
+    ([60] * 37, 32, 2, 64, None, "four"),         # three to a compute unit at head dim 64
+    ([60] * 60, 32, 2, 64, None, "stay"),
+    ([100, 300, 500, 700] * 3, 28, 4, 128, None, "four"),   # long prompts of unlike lengths
+    ([20, 100, 200, 500] * 3, 28, 4, 128, None, "stay"),    # none of them longer than 512
+    ([200, 500, 900, 1500] * 12, 28, 4, 128, None, "stay"), # ... and many blocks
+    ([512] * 32, 28, 4, 128, None, "stay"),
+    ([2048] * 16, 64, 8, 128, None, "stay"),
+    ([16] * 4096, 4, 1, 64, None, "stay"),
+    ([10] * 8, 28, 4, 128, 4096, "stay"),         # a bound far above the lengths: next to all workgroups would be empty
+])
+def test_edges(lens, Hq, Hkv, D, bound, want):
+    assert kind(lens, Hq, Hkv, D, bound) == want
+
+
+def test_what_was_asked_for():
+    lens = [512] * 32
+    assert kind(lens, 28, 4, 128, stay=0) == "four"
+    assert shape(lens, 28, 4, 128, stay=2).per_die == 2 and kind(lens, 28, 4, 128, stay=2) == "stay"
+    assert shape(lens, 28, 4, 128, stay=64).per_die == CUS // 8
+
+
+def test_every_block_has_a_workgroup():
+    """With a workgroup per block a die has as many as it can have blocks: units of 32 rows and a head, four to a block, the
+    blocks of a (prompt, kv head) dealt to the dies that share its heads in turn."""
+    r = random.Random(5)
+    for _ in range(3000):
+        Hkv, G = r.choice([1, 2, 3, 4, 8, 6, 16]), r.choice([1, 2, 3, 4, 5, 7, 8, 16])
+        n, longest = int(2 ** r.uniform(0, 6)), int(2 ** r.uniform(0, 11))
+        lens = [r.randint(0, longest) for _ in range(n)]
+        bound = longest + r.choice([0, 0, 1, 100])
+        s = shape(lens, Hkv * G, Hkv, r.choice([64, 128]), bound, r.choice([AUTO, AUTO, 0]))
+        assert s.per_die >= 1 and s.levels >= 1
+        units = 8 if (s.waves, s.parts) == (8, 1) else 4
+        gg = next(g for g in (8, 4, 2, 1) if Hkv % g == 0)
+        share = 8 // gg
+        most = 0
+        for die in range(share):
+            blocks = 0
+            for g, L in enumerate(lens):
+                nb, first = -(-(-(-L // 32) * G) // units), (die + g) % share
+                mine = max(0, -(-(nb - first) // share))
+                assert mine <= s.levels
+                blocks += mine * (Hkv // gg)
+            most = max(most, blocks)
+        if units == 4:
+            assert most <= s.per_die
