@@ -63,6 +63,17 @@ __device__ __forceinline__ void dma4(const void *gptr, uint32_t lds_addr) // 4 b
     asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" ::"v"(gptr), "s"(m0) : "memory", "m0");
 }
 
+// max(a, b, c) as the instruction computes it.  (Through fmaxf the compiler first quiets possible signalling NaNs of
+// every operand with an instruction of its own, which doubles the cost of the reduction.)  The compiler does not
+// look inside: it pads the distance between an MFMA and a vector instruction that reads its result only for
+// instructions it knows, so the first read of an MFMA's accumulator must not be one of these.
+__device__ __forceinline__ float max3(float a, float b, float c)
+{
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+
 // Reductions over the four lanes that own one query row (l, l^16, l^32, l^48), on the VALU (no LDS trip).
 __device__ __forceinline__ float row_max(float x)
 {
@@ -70,6 +81,13 @@ __device__ __forceinline__ float row_max(float x)
     x = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
     r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float row_max3(float x) // (the same by max3)
+{
+    u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = max3(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[1]));
+    r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return max3(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float row_sum(float x)
 {
@@ -183,6 +201,13 @@ __device__ __forceinline__ void issue_tile(const LaneConst<D, KVB> &lc, const ui
             dma16<STREAM>(src, lds_addr + 1024 * n);
         }
     }
+}
+
+// A tile of sixteen rows that exist, of a page that is read once.
+template <int D, int KVB> __device__ __forceinline__ void issue_whole_tile(const LaneConst<D, KVB> &lc, const uint8_t *tile, uint32_t lds_addr)
+{
+#pragma unroll
+    for (int n = 0; n < Geo<D, KVB>::kDmaPerTile; n++) dma16_base<true>((uint32_t)lc.dma_off[n], tile, lds_addr + 1024 * n);
 }
 
 // Wave-uniform lookups in read-only tables (block table, schedule): read through the constant address space

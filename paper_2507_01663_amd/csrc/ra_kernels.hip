@@ -8,6 +8,7 @@
 #include "ra_device.h"
 
 #include <stdlib.h>
+#include <type_traits>
 
 namespace ra {
 
@@ -684,7 +685,8 @@ template <int D, int NQT, int NP> __device__ __forceinline__ void store_prefix_p
 }
 
 // Loads of one stage (two pages: K0 K1 V0 V1, and for e4m3 the four scales) of a segment into a ring slot.
-template <int D, int KVB, int NST>
+// LEAN: whole pages, the usual case, are asked about once and not tile by tile (see ALONE in run_segment).
+template <int D, int KVB, int NST, bool LEAN = false>
 __device__ __forceinline__ void issue_stage(const Launch &a, const LaneConst<D, KVB> &lc, const Segment &sg, int st, int pid0,
                                             int pid1, int ring_slot, uint32_t lds_addr, int lane)
 {
@@ -699,10 +701,17 @@ __device__ __forceinline__ void issue_stage(const Launch &a, const LaneConst<D, 
     // (A decode step reads every page once: streaming loads.  Without a schedule a shared prompt page is read once per
     // member instead; without the hint 16 sequences of 2500 shared tokens and up to 400 of their own, 28 heads on four, take
     // 14.5 us there instead of 15.1, but 16 of up to 2900 that share nothing 19.1 instead of 17.2.)
-    issue_tile<D, KVB, true>(lc, a.k_pool + off0, nv0, sb, a.zeros);
-    issue_tile<D, KVB, true>(lc, a.k_pool + off1, nv1, sb + G::kTile, a.zeros);
-    issue_tile<D, KVB, true>(lc, a.v_pool + off0, nv0, sb + 2 * G::kTile, a.zeros);
-    issue_tile<D, KVB, true>(lc, a.v_pool + off1, nv1, sb + 3 * G::kTile, a.zeros);
+    if (LEAN && sg.limit - p0 * kPage >= 2 * kPage) {
+        issue_whole_tile<D, KVB>(lc, a.k_pool + off0, sb);
+        issue_whole_tile<D, KVB>(lc, a.k_pool + off1, sb + G::kTile);
+        issue_whole_tile<D, KVB>(lc, a.v_pool + off0, sb + 2 * G::kTile);
+        issue_whole_tile<D, KVB>(lc, a.v_pool + off1, sb + 3 * G::kTile);
+    } else {
+        issue_tile<D, KVB, true>(lc, a.k_pool + off0, nv0, sb, a.zeros);
+        issue_tile<D, KVB, true>(lc, a.k_pool + off1, nv1, sb + G::kTile, a.zeros);
+        issue_tile<D, KVB, true>(lc, a.v_pool + off0, nv0, sb + 2 * G::kTile, a.zeros);
+        issue_tile<D, KVB, true>(lc, a.v_pool + off1, nv1, sb + 3 * G::kTile, a.zeros);
+    }
     if (KVB == 1) {
         // the pages' scales land behind the tiles: lanes 0..3 bring k0, v0, k1, v1
         const int64_t si = (int64_t)((lane & 2) ? pid1 : pid0) * a.Hkv + sg.kvh;
@@ -820,7 +829,23 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
         }
         return id;
     };
-    int nid0 = page_id(ring.issued - base, 0), nid1 = page_id(ring.issued - base, 1); // one entry ahead of their use
+    // A segment that nothing follows, its entries two pages each, in a ring of two: one entry to a turn, of this segment, and a
+    // last page without a second is looked up twice (no row of it is read then).  Where a workgroup's waves stream on their own
+    // that takes a sixth of the instructions and most of the branches out of a turn: 1024 sequences of two heads, D = 64, e4m3, 38.9 ->
+    // 38.0 us, four layers of 64 of 28 heads on four, bf16, 88.9 -> 87.7.  In the scheduled kernels' longer form of it the waves
+    // that plan lost what it gave (7B-shaped batch, e4m3, 102.1 -> 102.9).
+    constexpr bool ALONE = !std::is_same<PageOf, ScalarPages>::value;
+    static_assert(!ALONE || (NQT == 1 && NST == 2), "see above");
+    int nid0, nid1; // one entry ahead of their use
+    auto look_up = [&](int rel) __attribute__((always_inline)) {
+        if (!ALONE) {
+            nid0 = page_id(rel, 0), nid1 = page_id(rel, 1);
+        } else if (rel < niter) {
+            const int p = cur.pg_lo + 2 * rel;
+            nid0 = page_of(cur, p), nid1 = page_of(cur, p + 1 < cur.pg_hi ? p + 1 : p);
+        }
+    };
+    look_up(ring.issued - base);
 
     // Q^T operand: for k-step i, lane (row = lane%16, j) holds the eight d values that its K operand holds.
     // bf16 K: d = 32*i + 8*j .. +7.  e4m3 K: one 16-byte K read carries 16 d values and feeds two k-steps, so
@@ -839,6 +864,14 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
 
     // keeps NST-1 entries in flight beyond entry `it` (this segment's own first entries were issued before it began)
     auto issue_ahead = [&](int it) {
+        if (ALONE) {
+            if (it + 1 < niter) {
+                issue_stage<D, KVB, NST, true>(a, lc, cur, it + 1, nid0, nid1, ring.issued % NST, lds_addr, lane);
+                ring.issued++;
+                look_up(it + 2);
+            }
+            return;
+        }
         int want = it + NST;
         want = want < total ? want : total;
         while (ring.issued - base < want) {
@@ -852,8 +885,7 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
                 issue_stage<D, KVB, NST>(a, lc, nxt, rel - niter - nxt_ql, nid0, nid1, ring.issued % NST, lds_addr, lane);
             }
             ring.issued++;
-            nid0 = page_id(ring.issued - base, 0);
-            nid1 = page_id(ring.issued - base, 1);
+            look_up(ring.issued - base);
         }
     };
     if (!QL) {
@@ -937,8 +969,9 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
                     if (tok0 + kPage + e >= cur.limit) v[4 + e] = -INFINITY;
                 }
             }
-            const float mx = row_max(fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7]))));
-            const float mn = fmaxf(m[t], mx);
+            const float mx = ALONE ? row_max3(max3(max3(v[0], v[1], v[2]), max3(v[3], v[4], v[5]), max3(v[6], v[7], v[7])))
+                                   : row_max(fmaxf(fmaxf(fmaxf(v[0], v[1]), fmaxf(v[2], v[3])), fmaxf(fmaxf(v[4], v[5]), fmaxf(v[6], v[7]))));
+            const float mn = ALONE ? max3(m[t], mx, mx) : fmaxf(m[t], mx);
             f32x8 p;
 #pragma unroll
             for (int e = 0; e < 8; e++) p[e] = __builtin_amdgcn_exp2f(v[e] - mn);

@@ -68,16 +68,6 @@ template <int D> struct PfState {
 // the same piece of different rows nor the eight lanes that read one row meet in a bank.
 __device__ __forceinline__ int pf_stage_swz(int r) { return (r + (r >> 3)) & 7; }
 
-// max(a, b, c) as the instruction computes it.  (Through fmaxf the compiler first quiets possible signalling NaNs of
-// every operand with an instruction of its own, which doubles the cost of the reduction.)  The compiler does not
-// look inside: it pads the distance between an MFMA and a vector instruction that reads its result only for
-// instructions it knows, so the first read of an MFMA's accumulator must not be one of these (see first_max).
-__device__ __forceinline__ float max3(float a, float b, float c)
-{
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
 // The first step of a maximum over fresh MFMA results, by an instruction the compiler knows; once it has run, the
 // whole accumulator (one MFMA writes all of it) is safe to read.
 __device__ __forceinline__ float first_max(float a, float b) { return fmaxf(a, b); }
