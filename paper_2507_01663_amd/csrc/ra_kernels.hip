@@ -8,7 +8,6 @@
 #include "ra_device.h"
 
 #include <stdlib.h>
-#include <type_traits>
 
 namespace ra {
 
@@ -774,6 +773,20 @@ __device__ __forceinline__ void issue_qrows(const Launch &a, const uint16_t *__r
     for (int k = NQT * PER; k < G::kDmaPerStage; k++) dma4(a.zeros, sb + 4 * G::kTile);
 }
 
+// Page ids of a wave's part of an item in registers, the first 64 of them, a lane each.  A short call is a chain of trips to
+// memory: arguments, length, page ids, pages, and with several workgroups to an item a second kernel's arguments, descriptor
+// and partials.  With the table's row asked for beside the length, what the first loads need among the leading arguments
+// (those are in registers when a wave starts) and the partials' places known without a descriptor: eight sequences of one
+// prompt, 500 to 2000 tokens, 28 heads on four, bf16, 11.2 -> 10.6 us, four of up to 3000 without one 10.95 -> 10.25, 30 of U[0,
+// 1536], e4m3, two layers 28.1 -> 27.3; where the stream or one long item bounds a call nothing (64 of U[0, 1536], bf16, 22.7).
+struct LanePages {
+    int id, base; // lane i: page base + i of the row
+    __device__ __forceinline__ int operator()(const Segment &sg, int p) const
+    {
+        return p - base < 64 ? __builtin_amdgcn_readlane(id, p - base) : uniform_load(sg.pages, p);
+    }
+};
+
 // Attention of NQT*16 query rows over one segment.  Two pages (32 keys) per ring stage:
 //   S^T[key, row] = K_tile . Q^T      (16x16x32 MFMA over D, per page; A = K rows straight from LDS, B = Q in
 //                                      registers)
@@ -789,15 +802,12 @@ __device__ __forceinline__ void issue_qrows(const Launch &a, const uint16_t *__r
 // min(NST-1, entries) entries of this segment are in flight; on exit the same holds for `nxt`.  Query rows of an
 // own-pages segment (NQT == 1) wait in the query slot; those of a shared-pages segment are its first ring entry.
 // A one-tile partial goes back in `ret` (normalised, with its log2-sum-exp); a shared-prefix partial is stored.
-// page_of(segment, p) is the id of page p of a segment's work row.
-struct ScalarPages {
-    __device__ __forceinline__ int operator()(const Segment &sg, int p) const { return uniform_load(sg.pages, p); }
-};
-template <int D, int KVB, int NQT, int NST, int NP, class PageOf = ScalarPages>
+// ALONE: a segment that nothing follows, its page ids from `ids`.
+template <int D, int KVB, int NQT, int NST, int NP, bool ALONE = false>
 __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__restrict__ q, const Segment &cur, bool has_nxt,
                                             const Segment &nxt, Ring &ring, const LaneConst<D, KVB> &lc, uint8_t *lds,
                                             uint32_t lds_addr, Pending<D> &ret, Pending<D> (&pk)[NP], bool park, int lane,
-                                            int q_off = LdsMap<D, KVB, NST>::kQBase, const PageOf &page_of = PageOf())
+                                            int q_off = LdsMap<D, KVB, NST>::kQBase, LanePages ids = LanePages{0, 0})
 {
     static_assert(NQT == 1 || NQT <= NP, "a shared-prefix partial has a waiting register set per tile");
     using G = Geo<D, KVB>;
@@ -817,35 +827,30 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
     const int total = niter + nxt_pre;
     const int ntiles = NQT > 1 ? (cur.nrows + 15) >> 4 : 1; // tiles in use (the others hold zeros and are skipped)
 
-    // page id of page h of the entry with number base + rel (this segment's entries first, then the next one's)
-    auto page_id = [&](int rel, int h) {
-        int id = 0;
-        if (rel < niter) {
-            const int st = rel - QL, p = cur.pg_lo + 2 * st + h;
-            if (st >= 0 && p < cur.pg_hi) id = page_of(cur, p);
-        } else if (rel < total) {
-            const int st = rel - niter - nxt_ql, p = nxt.pg_lo + 2 * st + h;
-            if (st >= 0 && p < nxt.pg_hi) id = page_of(nxt, p);
-        }
-        return id;
-    };
-    // A segment that nothing follows, its entries two pages each, in a ring of two: one entry to a turn, of this segment, and a
+    // ALONE: a segment that nothing follows, its entries two pages each, in a ring of two: one entry to a turn, of this segment, and a
     // last page without a second is looked up twice (no row of it is read then).  Where a workgroup's waves stream on their own
     // that takes a sixth of the instructions and most of the branches out of a turn: 1024 sequences of two heads, D = 64, e4m3, 38.9 ->
     // 38.0 us, four layers of 64 of 28 heads on four, bf16, 88.9 -> 87.7.  In the scheduled kernels' longer form of it the waves
     // that plan lost what it gave (7B-shaped batch, e4m3, 102.1 -> 102.9).
-    constexpr bool ALONE = !std::is_same<PageOf, ScalarPages>::value;
     static_assert(!ALONE || (NQT == 1 && NST == 2), "see above");
-    int nid0, nid1; // one entry ahead of their use
-    auto look_up = [&](int rel) __attribute__((always_inline)) {
-        if (!ALONE) {
-            nid0 = page_id(rel, 0), nid1 = page_id(rel, 1);
-        } else if (rel < niter) {
-            const int p = cur.pg_lo + 2 * rel;
-            nid0 = page_of(cur, p), nid1 = page_of(cur, p + 1 < cur.pg_hi ? p + 1 : p);
+
+    // page id of page h of the entry with number base + rel (this segment's entries first, then the next one's)
+    auto page_id = [&](int rel, int h) {
+        int id = 0;
+        if (ALONE) {
+            const int p = cur.pg_lo + 2 * rel + h;
+            return rel < niter ? ids(cur, p < cur.pg_hi ? p : p - 1) : 0;
         }
+        if (rel < niter) {
+            const int st = rel - QL, p = cur.pg_lo + 2 * st + h;
+            if (st >= 0 && p < cur.pg_hi) id = uniform_load(cur.pages, p);
+        } else if (rel < total) {
+            const int st = rel - niter - nxt_ql, p = nxt.pg_lo + 2 * st + h;
+            if (st >= 0 && p < nxt.pg_hi) id = uniform_load(nxt.pages, p);
+        }
+        return id;
     };
-    look_up(ring.issued - base);
+    int nid0 = page_id(ring.issued - base, 0), nid1 = page_id(ring.issued - base, 1); // one entry ahead of their use
 
     // Q^T operand: for k-step i, lane (row = lane%16, j) holds the eight d values that its K operand holds.
     // bf16 K: d = 32*i + 8*j .. +7.  e4m3 K: one 16-byte K read carries 16 d values and feeds two k-steps, so
@@ -868,7 +873,8 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
             if (it + 1 < niter) {
                 issue_stage<D, KVB, NST, true>(a, lc, cur, it + 1, nid0, nid1, ring.issued % NST, lds_addr, lane);
                 ring.issued++;
-                look_up(it + 2);
+                nid0 = page_id(it + 2, 0);
+                nid1 = page_id(it + 2, 1);
             }
             return;
         }
@@ -885,7 +891,8 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
                 issue_stage<D, KVB, NST>(a, lc, nxt, rel - niter - nxt_ql, nid0, nid1, ring.issued % NST, lds_addr, lane);
             }
             ring.issued++;
-            look_up(ring.issued - base);
+            nid0 = page_id(ring.issued - base, 0);
+            nid1 = page_id(ring.issued - base, 1);
         }
     };
     if (!QL) {
@@ -1697,20 +1704,6 @@ template <int D, int KVB, int W> struct DirectLds {
     static_assert(kWave % 256 == 0 && kPage * D * 4 + 64 <= kWave, "a wave's partial fits its ring");
 };
 
-// Page ids of a wave's part of an item in registers, the first 64 of them, a lane each.  A short call is a chain of trips to
-// memory: arguments, length, page ids, pages, and with several workgroups to an item a second kernel's arguments, descriptor
-// and partials.  With the table's row asked for beside the length, what the first loads need among the leading arguments
-// (those are in registers when a wave starts) and the partials' places known without a descriptor: eight sequences of one
-// prompt, 500 to 2000 tokens, 28 heads on four, bf16, 11.2 -> 10.6 us, four of up to 3000 without one 10.95 -> 10.25, 30 of U[0,
-// 1536], e4m3, two layers 28.1 -> 27.3; where the stream or one long item bounds a call nothing (64 of U[0, 1536], bf16, 22.7).
-struct LanePages {
-    int id, base; // lane i: page base + i of the row
-    __device__ __forceinline__ int operator()(const Segment &sg, int p) const
-    {
-        return p - base < 64 ? __builtin_amdgcn_readlane(id, p - base) : uniform_load(sg.pages, p);
-    }
-};
-
 template <int D, int KVB, int W, bool SORTED>
 __global__ __launch_bounds__(64 * W) void direct_kernel(const int32_t *__restrict__ seq_lens, const int32_t *__restrict__ block_table,
                                                         const uint16_t *__restrict__ q, const void *zeros, int Hq, int Hkv, int G, int max_pages,
@@ -1811,7 +1804,7 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(const int32_t *__restric
         const int id0 = ids(sg, sg.pg_lo), id1 = sg.pg_lo + 1 < sg.pg_hi ? ids(sg, sg.pg_lo + 1) : 0;
         issue_stage<D, KVB, 2>(a, lc, sg, 0, id0, id1, 0, mine_addr, lane);
         ring.issued++;
-        run_segment<D, KVB, 1, 2>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane, q_off, ids);
+        run_segment<D, KVB, 1, 2, 1, true>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane, q_off, ids);
     }
     wait_vmcnt<0>(); // (a wave without pages has brought the query rows all the same)
     // every wave's partial into its own ring (nothing is in flight any more), then the workgroup adds them up
