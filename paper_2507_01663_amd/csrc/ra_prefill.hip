@@ -3,10 +3,6 @@
 
 namespace ra {
 
-// The attention kernel writes the cache from its ring where a block has few stages to write; with fewer than four query
-// heads per kv head it would be up to eight of them per block (a block is eight units), and the copy kernel below does it.
-bool prefill_writes_cache(const PrefillLaunch &a) { return a.k_pool && a.G >= 4; }
-
 // The launch shape of a call.  Workgroups that stay load the next block's inputs under the current one, but which blocks each
 // of them takes is fixed beforehand; with one per block the hardware hands them out as units become free, two or three of
 // four waves to a compute unit, so that one's start and end (a block's fixed part is 4 to 5 us, its stages 0.6 each) run under
@@ -18,6 +14,12 @@ bool prefill_writes_cache(const PrefillLaunch &a) { return a.k_pool && a.G >= 4;
 //   two, D = 64, 93.5, 45.7; 24 of 200 to 1500, 32 on two, D = 64, 146, 143.5; 50 of 200 to 1500, eight heads, 235, 219; 17 of 59
 //   to 1204, 40 on eight, 170, 161; 24 of 200 to 1500, 28 on four, 227, 230 (blocks of eight waves one each: 49.9, 162, 222, 168,
 //   229).  Not like ones: 16 of 860, eight heads, 63.2, 68.3; 32 of 512, 28 on four, 106, 122; 16 of 2048, 64 on eight 1182, 1320.
+// - shorter ones of unlike lengths, up to fewer blocks (of eight units) to a compute unit, more at head dim 64: 24 of 16 to 300, 28
+//   on four (2.1 to a unit), 33.1, 21.7; 16 of 50 to 500 (2.2) 31.4, 28.4; 20 of 150 to 480 (3.1) 50.5, 38.1; 64 of 50 to 500, eight
+//   heads (2.5), 96.6, 76.8; but 14 of 124 to 413, 64 on eight (3.7), 35.1, 37.6, 32 of 50
+//   to 500, 28 on four (4.3), 51.5, 54.9, 64 of 20 to 300, 64 on eight (12.8), 120, 145; D = 64:
+//   32 of 30 to 400, 32 on two (3.8), 29.5, 22.8, 64 of 50 to 500 (10.1) 75.9, 69.9; nearly alike, eight of 300 to 500, 28 on four,
+//   22.0, 23.1.
 // The launch must not be empty workgroups mostly, so the bound on the lengths has to be a near one.
 // A call of so few blocks that each has a compute unit to itself lasts as long as its longest block: beyond 256 tokens two
 // waves share a unit's keys.  One prompt, 28 heads on four, four waves and eight: 256 tokens 10.8, 10.8; 400 13.5, 12.8; 701
@@ -41,7 +43,8 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
     count(kPfWaves);
     const bool fit = blocks <= per_die; // (a block for every compute unit at most: there is nothing to load ahead)
     const bool alike = 8 * (int64_t)total_tokens >= 7 * (int64_t)num_prompts * max_len;
-    const bool uneven = !alike && max_len > 2 * kPfBlock && about <= 12 * (int64_t)num_cus;
+    const bool uneven = max_len > 2 * kPfBlock ? !alike && about <= 12 * (int64_t)num_cus
+                                               : 5 * (int64_t)total_tokens < 4 * (int64_t)num_prompts * max_len && 2 * about <= (D == 64 ? 24 : 7) * (int64_t)num_cus;
     const PrefillShape staying = {8, 1, p.levels, (int)per_die};
     count(4);
     const bool few = 8 * about <= 9 * (D == 64 ? 3 : 2) * (int64_t)num_cus; // (by the tokens it is a little more than it is)
@@ -50,6 +53,18 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
     p.waves = 4 * p.parts;
     p.per_die = (int)blocks;
     return p;
+}
+
+// The attention kernel writes the cache from its ring where a block has few stages to write: with fewer than four query
+// heads per kv head it would be up to eight of them per block of eight units, and the copy kernel below does it.  Not where
+// blocks go one to a workgroup: those have four units, and such a call is mostly the cost of a second launch: five
+// prompts of 15 to 32 tokens, four heads on two, D = 64, 7.7 -> 4.6 us; one of 600, eight heads, e4m3, 22.8 -> 20.9, 21 of 195 to 419
+// 34.5 -> 22.8 (bf16 33.7 -> 17.6), 50 of 200 to 1500 219 -> 206 (bf16 219 -> 190).
+bool prefill_writes_cache(const PrefillLaunch &a)
+{
+    if (!a.k_pool || a.G >= 4) return a.k_pool != nullptr;
+    const PrefillShape p = prefill_shape(a.num_prompts, a.total_tokens, a.max_len, a.Hkv, a.G, a.D, a.num_cus, a.stay);
+    return p.waves != 8 || p.parts != 1;
 }
 
 hipError_t prefill_config()

@@ -39,7 +39,11 @@ def kind(*a, **k):
     ([60] * 37, 32, 2, 64, None, "four"),         # three to a compute unit at head dim 64
     ([60] * 60, 32, 2, 64, None, "stay"),
     ([100, 300, 500, 700] * 3, 28, 4, 128, None, "four"),   # long prompts of unlike lengths
-    ([20, 100, 200, 500] * 3, 28, 4, 128, None, "stay"),    # none of them longer than 512
+    ([20, 100, 200, 500] * 3, 28, 4, 128, None, "four"),    # shorter ones too
+    ([20, 100, 200, 500] * 8, 28, 4, 128, None, "four"),    # 3.2 blocks of eight units to a compute unit
+    ([20, 100, 200, 500] * 10, 28, 4, 128, None, "stay"),   # 4.0
+    ([20, 100, 200, 500] * 12, 32, 2, 64, None, "four"),    # head dim 64
+    ([350, 390, 400, 500] * 3, 28, 4, 128, None, "stay"),   # nearly alike
     ([200, 500, 900, 1500] * 12, 28, 4, 128, None, "stay"), # ... and many blocks
     ([512] * 32, 28, 4, 128, None, "stay"),
     ([2048] * 16, 64, 8, 128, None, "stay"),
