@@ -778,7 +778,8 @@ __device__ __forceinline__ void issue_qrows(const Launch &a, const uint16_t *__r
 // and partials.  With the table's row asked for beside the length, what the first loads need among the leading arguments
 // (those are in registers when a wave starts) and the partials' places known without a descriptor: eight sequences of one
 // prompt, 500 to 2000 tokens, 28 heads on four, bf16, 11.2 -> 10.6 us, four of up to 3000 without one 10.95 -> 10.25, 30 of U[0,
-// 1536], e4m3, two layers 28.1 -> 27.3; where the stream or one long item bounds a call nothing (64 of U[0, 1536], bf16, 22.7).
+// 1536], e4m3, two layers 28.1 -> 27.3; where the stream or one long item bounds a call nothing (64 of U[0, 1536], bf16, 22.7), and
+// 0.3 of 24.8 lost where most waves have no page (345 of up to 57 tokens, eight heads, e4m3) and now bring query rows all the same.
 struct LanePages {
     int id, base; // lane i: page base + i of the row
     __device__ __forceinline__ int operator()(const Segment &sg, int p) const

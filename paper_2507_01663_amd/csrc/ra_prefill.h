@@ -423,7 +423,7 @@ template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void 
     constexpr int NSL = kPfSlots, CS = R::kChunk; // ring slots of one chunk; stage number s (counted over all the blocks of
                                                   // the workgroup) lives at (s % (CS * NSL)) * G::kStage
     static_assert(CS == 2 || !STAY, "V's addresses serve two steps: a block's first stage lies at an even place of the ring");
-    auto chunks = [](const PfBlock &b) __attribute__((always_inline)) { return (b.nst + CS - 1) / CS; };
+    auto chunks = [](const PfBlock &b) __attribute__((always_inline)) { return (b.nst + CS - 1) >> (CS - 1); };
     static_assert((NSL & (NSL - 1)) == 0, "slot arithmetic by masking");
     extern __shared__ __attribute__((aligned(16384))) uint8_t lds[]; // the step forms LDS addresses by XOR
     const uint32_t lds_addr = (uint32_t)(uintptr_t)lds;
@@ -638,7 +638,7 @@ template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void 
         // The wave's stages of the block: number i is stage KP * i + part.  The last one is the one that holds the tile's
         // diagonal, or with two parts the one before it; earlier ones lie wholly below it.
         const int last = KP == 1 ? T : (T - part) >> 1;
-        const bool works = own && T >= part;
+        const bool works = own && (KP == 1 || T >= part);
 
         if (a.fused_write) pages_of_block();
         open_chunk(chunk0, 0);
@@ -671,7 +671,7 @@ template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void 
         auto ring = [&](int s) __attribute__((always_inline)) { // before step s
             if (KP == 2) {
                 if (2 * (s + 1) < nst) open_chunk(chunk0 + s + 1, 2 * (s + 1));
-            } else if ((CS == 1 || (s & 1)) && s + 1 < nst) open_chunk(chunk0 + (s + 1) / CS, s + 1);
+            } else if ((CS == 1 || (s & 1)) && s + 1 < nst) open_chunk(chunk0 + ((s + 1) >> (CS - 1)), s + 1);
         };
         constexpr bool EACH = KP == 2 || CS == 1; // a chunk opens before every step
 #define PF_STEP(MASK, NEXT, SECOND)                                                                                                \

@@ -49,6 +49,8 @@ def test_edges_of_tiles_and_stages(dec, Hq, Hkv, D, lens, want):
 @pytest.mark.parametrize("Hq,Hkv,D,lens,want", [
     (28, 4, 128, [300, 17], "halves"), (8, 2, 64, [17, 290, 16, 1], "halves"), (28, 4, 128, [100, 31, 0, 50], "four"), (16, 2, 64, [47, 128], "four"),
     (28, 4, 128, [600, 30, 333, 80, 200, 513, 47], "four"),
+    (8, 8, 128, [290], "halves"), (6, 2, 64, [300, 31], "halves"), (4, 2, 64, [600, 30, 333, 80, 200], "halves"),  # few heads to a kv head:
+    (8, 8, 128, [33, 250, 0, 16], "four"), (6, 2, 64, [129, 1], "four"),                                            # up to four stages a block
 ])
 def test_cache_writes(dec, kv_dtype, Hq, Hkv, D, lens, want):
     b = workload.build_prefill("few", Hq, Hkv, D, lens, seed=23)
