@@ -2094,12 +2094,12 @@ struct PartList {
 };
 
 // The partials of (sequence b, kv head kvh) = `item`: pl[0] of its shared-prefix row, pl[1] of its own pages.
-__device__ __forceinline__ void merge_lists(const Launch &a, const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
+template <bool SPLIT> __device__ __forceinline__ void merge_lists(const Launch &a, const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
                                             const int32_t *__restrict__ seq_rank_in_row, int item, int b, int kvh, PartList (&pl)[2])
 {
     const Workspace &w = a.ws;
     const int D = a.D;
-    if (a.splits) {
+    if (SPLIT) {
         // a batch without a schedule: every item has a.splits partials in a row, the places are known without a trip to memory
         const int first = item * (a.splits - 1);
         pl[1] = {first, first + a.splits - 1, w.suf_o + (int64_t)item * a.G * D, w.suf_lse + (int64_t)item * a.G, (int64_t)a.G * D, a.G};
@@ -2134,16 +2134,13 @@ __device__ __forceinline__ void merge_lists(const Launch &a, const int4 *__restr
     }
 }
 
-__global__ __launch_bounds__(kMergeThreads) void merge_kernel(const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
-    const int32_t *__restrict__ seq_rank_in_row, float *suf_o, float *suf_lse, int Hkv, int G, int D_, int splits, Launch given)
+template <bool SPLIT> __device__ __forceinline__ void merge_items(const Launch &a, const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
+                                                              const int32_t *__restrict__ seq_rank_in_row)
 {
-    Launch a = given;
-    a.ws.suf_o = suf_o, a.ws.suf_lse = suf_lse, a.Hkv = Hkv, a.G = G, a.D = D_, a.splits = splits;
-    touch_args(given);
     const int item = blockIdx.x, b = item / a.Hkv, kvh = item - b * a.Hkv;
     const int D = a.D, tpr = D / 4; // threads per output row
     PartList pl[2];
-    merge_lists(a, merge_desc, seq_pfx_row, seq_rank_in_row, item, b, kvh, pl);
+    merge_lists<SPLIT>(a, merge_desc, seq_pfx_row, seq_rank_in_row, item, b, kvh, pl);
     const int npfx = pl[0].c_hi - pl[0].c_lo + 1, nown = pl[1].c_hi - pl[1].c_lo + 1;
     for (int hl = threadIdx.x / tpr; hl < a.G; hl += kMergeThreads / tpr) {
         const int d4 = (threadIdx.x % tpr) * 4;
@@ -2188,19 +2185,16 @@ __global__ __launch_bounds__(kMergeThreads) void merge_kernel(const int4 *__rest
 // workgroup takes one head of one item; its threads form lanes of D / 4, which take the partials turn about, four at a
 // time each, so that up to 32 (D = 128) are on their way together; the lanes' sums meet in LDS, in lane order.  One
 // partial after the other is what bound the kernel above there: 13.2 us for 48 items of 21 spans (D = 128, five heads), 4.7 here.
-__global__ __launch_bounds__(kMergeThreads) void merge_wide_kernel(const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
-    const int32_t *__restrict__ seq_rank_in_row, float *suf_o, float *suf_lse, int Hkv, int G, int D_, int splits, Launch given)
+template <bool SPLIT> __device__ __forceinline__ void merge_heads(const Launch &a, const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row,
+                                                              const int32_t *__restrict__ seq_rank_in_row)
 {
-    Launch a = given;
-    a.ws.suf_o = suf_o, a.ws.suf_lse = suf_lse, a.Hkv = Hkv, a.G = G, a.D = D_, a.splits = splits;
-    touch_args(given);
     __shared__ f32x4 s_acc[kMergeThreads];
     __shared__ float s_m[kMergeThreads / 16], s_w[kMergeThreads / 16];
     const int item = blockIdx.x / a.G, hl = blockIdx.x - item * a.G, b = item / a.Hkv, kvh = item - b * a.Hkv;
     const int D = a.D, tpr = D / 4, lanes = kMergeThreads / tpr;
     const int me = threadIdx.x / tpr, d4 = (threadIdx.x % tpr) * 4;
     PartList pl[2];
-    merge_lists(a, merge_desc, seq_pfx_row, seq_rank_in_row, item, b, kvh, pl);
+    merge_lists<SPLIT>(a, merge_desc, seq_pfx_row, seq_rank_in_row, item, b, kvh, pl);
     const int npfx = pl[0].c_hi - pl[0].c_lo + 1, nown = pl[1].c_hi - pl[1].c_lo + 1, total = npfx + nown;
     float M = -INFINITY, wsum = 0.f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -2235,6 +2229,26 @@ __global__ __launch_bounds__(kMergeThreads) void merge_wide_kernel(const int4 *_
     merge_write(a, (int64_t)b * a.Hq + kvh * a.G + hl, d4, Mt, wt, at);
 }
 
+// The two for scheduled batches, and for items that several workgroups share (SPLIT: no descriptors, the places by the leading
+// arguments, which are in registers when a wave starts).
+#define RA_MERGE_KERNELS(NAME, BODY)                                                                                          \
+    __global__ __launch_bounds__(kMergeThreads) void NAME(Launch a, const int4 *__restrict__ merge_desc, const int32_t *__restrict__ seq_pfx_row, \
+                                                           const int32_t *__restrict__ seq_rank_in_row)                         \
+    {                                                                                                                         \
+        touch_args(a);                                                                                                        \
+        BODY<false>(a, merge_desc, seq_pfx_row, seq_rank_in_row);                                                               \
+    }                                                                                                                         \
+    __global__ __launch_bounds__(kMergeThreads) void NAME##_split(float *suf_o, float *suf_lse, int Hkv, int G, int D, int splits, Launch given) \
+    {                                                                                                                         \
+        touch_args(given);                                                                                                    \
+        Launch a = given;                                                                                                     \
+        a.ws.suf_o = suf_o, a.ws.suf_lse = suf_lse, a.Hkv = Hkv, a.G = G, a.D = D, a.splits = splits;                              \
+        BODY<true>(a, nullptr, nullptr, nullptr);                                                                             \
+    }
+RA_MERGE_KERNELS(merge_kernel, merge_items)
+RA_MERGE_KERNELS(merge_wide_kernel, merge_heads)
+#undef RA_MERGE_KERNELS
+
 constexpr int kMergeWideMax = 512; // workgroups of merge_wide_kernel, at most
 
 hipError_t launch_merge(const Launch &a, hipStream_t s)
@@ -2248,12 +2262,15 @@ hipError_t launch_merge(const Launch &a, hipStream_t s)
     // -> 20.1 at 1500 tokens and 31.1 -> 28.3 at 5000, but 18.9 -> 19.2 at 250; 896 (128 items of 7) 18.9 -> 19.4 at 250 and
     // 45.2 -> 45.0 at 5000; 2560 (512 items of 5, e4m3) 20.3 -> 24.2 and 80.7 -> 92.8.
     const int64_t items = (int64_t)a.B * a.Hkv;
-    if (items * a.G <= kMergeWideMax && (a.splits ? a.splits > 4 : a.waves >= 3 * items))
-        hipLaunchKernelGGL(merge_wide_kernel, dim3(a.B * a.Hkv * a.G), dim3(kMergeThreads), 0, s, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row, w.suf_o,
-                           w.suf_lse, a.Hkv, a.G, a.D, a.splits, a);
-    else
-        hipLaunchKernelGGL(merge_kernel, dim3(a.B * a.Hkv), dim3(kMergeThreads), 0, s, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row, w.suf_o,
-                           w.suf_lse, a.Hkv, a.G, a.D, a.splits, a);
+    const bool wide = items * a.G <= kMergeWideMax && (a.splits ? a.splits > 4 : a.waves >= 3 * items);
+    const dim3 grid((unsigned)(items * (wide ? a.G : 1))), block(kMergeThreads);
+    if (a.splits) {
+        if (wide) hipLaunchKernelGGL(merge_wide_kernel_split, grid, block, 0, s, w.suf_o, w.suf_lse, a.Hkv, a.G, a.D, a.splits, a);
+        else hipLaunchKernelGGL(merge_kernel_split, grid, block, 0, s, w.suf_o, w.suf_lse, a.Hkv, a.G, a.D, a.splits, a);
+    } else {
+        if (wide) hipLaunchKernelGGL(merge_wide_kernel, grid, block, 0, s, a, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row);
+        else hipLaunchKernelGGL(merge_kernel, grid, block, 0, s, a, w.merge_desc, w.seq_pfx_row, w.seq_rank_in_row);
+    }
     return hipGetLastError();
 }
 
