@@ -773,21 +773,6 @@ __device__ __forceinline__ void issue_qrows(const Launch &a, const uint16_t *__r
     for (int k = NQT * PER; k < G::kDmaPerStage; k++) dma4(a.zeros, sb + 4 * G::kTile);
 }
 
-// Page ids of a wave's part of an item in registers, the first 64 of them, a lane each.  A short call is a chain of trips to
-// memory: arguments, length, page ids, pages, and with several workgroups to an item a second kernel's arguments, descriptor
-// and partials.  With the table's row asked for beside the length, what the first loads need among the leading arguments
-// (those are in registers when a wave starts) and the partials' places known without a descriptor: eight sequences of one
-// prompt, 500 to 2000 tokens, 28 heads on four, bf16, 11.2 -> 10.6 us, four of up to 3000 without one 10.95 -> 10.25, 30 of U[0,
-// 1536], e4m3, two layers 28.1 -> 27.3; where the stream or one long item bounds a call nothing (64 of U[0, 1536], bf16, 22.7), and
-// 0.3 of 24.8 lost where most waves have no page (345 of up to 57 tokens, eight heads, e4m3) and now bring query rows all the same.
-struct LanePages {
-    int id, base; // lane i: page base + i of the row
-    __device__ __forceinline__ int operator()(const Segment &sg, int p) const
-    {
-        return p - base < 64 ? __builtin_amdgcn_readlane(id, p - base) : uniform_load(sg.pages, p);
-    }
-};
-
 // Attention of NQT*16 query rows over one segment.  Two pages (32 keys) per ring stage:
 //   S^T[key, row] = K_tile . Q^T      (16x16x32 MFMA over D, per page; A = K rows straight from LDS, B = Q in
 //                                      registers)
@@ -803,12 +788,12 @@ struct LanePages {
 // min(NST-1, entries) entries of this segment are in flight; on exit the same holds for `nxt`.  Query rows of an
 // own-pages segment (NQT == 1) wait in the query slot; those of a shared-pages segment are its first ring entry.
 // A one-tile partial goes back in `ret` (normalised, with its log2-sum-exp); a shared-prefix partial is stored.
-// ALONE: a segment that nothing follows, its page ids from `ids`.
+// ALONE: a segment that nothing follows.
 template <int D, int KVB, int NQT, int NST, int NP, bool ALONE = false>
 __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__restrict__ q, const Segment &cur, bool has_nxt,
                                             const Segment &nxt, Ring &ring, const LaneConst<D, KVB> &lc, uint8_t *lds,
                                             uint32_t lds_addr, Pending<D> &ret, Pending<D> (&pk)[NP], bool park, int lane,
-                                            int q_off = LdsMap<D, KVB, NST>::kQBase, LanePages ids = LanePages{0, 0})
+                                            int q_off = LdsMap<D, KVB, NST>::kQBase)
 {
     static_assert(NQT == 1 || NQT <= NP, "a shared-prefix partial has a waiting register set per tile");
     using G = Geo<D, KVB>;
@@ -840,7 +825,7 @@ __device__ __forceinline__ void run_segment(const Launch &a, const uint16_t *__r
         int id = 0;
         if (ALONE) {
             const int p = cur.pg_lo + 2 * rel + h;
-            return rel < niter ? ids(cur, p < cur.pg_hi ? p : p - 1) : 0;
+            return rel < niter ? uniform_load(cur.pages, p < cur.pg_hi ? p : p - 1) : 0;
         }
         if (rel < niter) {
             const int st = rel - QL, p = cur.pg_lo + 2 * st + h;
@@ -1676,6 +1661,14 @@ __device__ __forceinline__ void merge_write(const Launch &a, int64_t bh, int d4,
 // table has one width for all steps, wide enough for the longest response, is scheduled however short the sequences are.)
 // Shared prompt pages are read once per member, from the caches mostly.
 //
+// A short call is a chain of trips to memory: arguments, length, page ids, pages, and with several workgroups to an item a second
+// kernel's arguments, descriptor and partials.  What the first loads need is among the leading arguments (in registers when a
+// wave starts), the query rows come beside the length, and the partials' places are known without a descriptor: eight
+// sequences of one prompt, 500 to 2000 tokens, 28 heads on four, bf16, 11.2 -> 10.4 us, four of up to 3000 without one 10.9 -> 9.9,
+// 30 of U[0, 1536], e4m3, two layers 28.0 -> 26.1, 1000 of up to 60, eight heads on two, D = 64, bf16, 13.4 -> 12.9.  Page ids
+// wait for the length, one scalar lookup each: a table row may end with its last page in use, so no entry behind that is read.
+// (The first 64 of a part in a vector register, by one load, were slower: 13.8 for the last of these.)
+//
 // Waves: as many rings as fit, eight, where a wave's arithmetic bounds it (e4m3, or head dim 64) and the items are few: 64
 // sequences of four kv heads, e4m3, D = 128, one of them 3072 tokens, 27.0 us with four and 20.4 with eight; all full 33 and
 // 34.  Four, and more workgroups to a compute unit, where there are more items or short ones: 100 such sequences of 1024
@@ -1772,13 +1765,9 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(const int32_t *__restric
     const uint32_t mine_addr = (uint32_t)(uintptr_t)mine;
     const int q_off = X::kQBase - wave * X::kWave;
     LaneConst<D, KVB> lc;
-    // The query rows, and a short table row whole, are asked for beside the length: one trip for all three.
-    // (Every wave brings the query rows, all to one place: the same bytes, so each needs to wait for its own loads only.)
+    // The query rows are asked for beside the length.  (Every wave brings them, all to one place: the same bytes, so each needs
+    // to wait for its own loads only.)
     issue_q<D, KVB, 2>(a, q, lc, sg, mine_addr + q_off, lane);
-    const bool whole = a.max_pages <= 128;
-    int row0 = 0, row1 = 0;
-    if (whole && lane < a.max_pages) row0 = sg.pages[lane];
-    if (whole && 64 + lane < a.max_pages) row1 = sg.pages[64 + lane];
     L = L < 0 ? 0 : (L > a.max_pages * kPage ? a.max_pages * kPage : L); // never walk past the table row
     const int n = (L + kPage - 1) / kPage, nst = (n + 1) >> 1;
     const int k = part * W + wave, all = a.splits * W;
@@ -1786,15 +1775,6 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(const int32_t *__restric
     sg.pg_lo = 2 * lo;
     sg.pg_hi = 2 * hi < n ? 2 * hi : n;
     sg.limit = min(L, sg.pg_hi * kPage);
-    LanePages ids = {0, sg.pg_lo};
-    const int from = sg.pg_lo + lane;
-    if (whole) {
-        const int x0 = __builtin_amdgcn_ds_bpermute(4 * from, row0), x1 = __builtin_amdgcn_ds_bpermute(4 * from, row1); // (from modulo 64)
-        ids.id = from < 64 ? x0 : x1;
-    } else if (from < sg.pg_hi) {
-        ids.id = sg.pages[from];
-    }
-    asm volatile("" : "+v"(ids.id)); // (the compiler's wait for them: here, and not behind the ring's first loads)
     Pending<D> res, none[1];
     res.lse2 = -INFINITY;
 #pragma unroll
@@ -1802,10 +1782,10 @@ __global__ __launch_bounds__(64 * W) void direct_kernel(const int32_t *__restric
     if (lo < hi) {
         lane_setup<D, KVB>(lc, lane, a.stride_token_b);
         Ring ring = {0, 0};
-        const int id0 = ids(sg, sg.pg_lo), id1 = sg.pg_lo + 1 < sg.pg_hi ? ids(sg, sg.pg_lo + 1) : 0;
+        const int id0 = uniform_load(sg.pages, sg.pg_lo), id1 = sg.pg_lo + 1 < sg.pg_hi ? uniform_load(sg.pages, sg.pg_lo + 1) : 0;
         issue_stage<D, KVB, 2>(a, lc, sg, 0, id0, id1, 0, mine_addr, lane);
         ring.issued++;
-        run_segment<D, KVB, 1, 2, 1, true>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane, q_off, ids);
+        run_segment<D, KVB, 1, 2, 1, true>(a, q, sg, false, sg, ring, lc, mine, mine_addr, res, none, false, lane, q_off);
     }
     wait_vmcnt<0>(); // (a wave without pages has brought the query rows all the same)
     // every wave's partial into its own ring (nothing is in flight any more), then the workgroup adds them up

@@ -69,6 +69,16 @@ def test_e4m3_kernels_fit_two_waves_per_simd(isa):
         assert regs <= 256 and scratch == 0, (name, regs, scratch)
 
 
+def test_steps_without_a_schedule_look_up_pages_one_by_one(isa):
+    """A table row may end with the sequence's last page in use: entries are looked up as the pages exist, by scalar loads behind the
+    length, and never as a row of lanes.  The only vector loads into registers are those of the lengths that a wave sorts, 64 each."""
+    found = re.findall(r"^_ZN2ra\d+direct_kernelILi\d+ELi\d+ELi\d+ELb([01])E\w+:(.*?)s_endpgm", isa, flags=re.S | re.M)
+    assert len(found) == 14                                  # seven shapes, as they come and the longest first
+    for order, body in found:
+        before = body[:body.index("s_barrier")]              # (behind it the waves' partials)
+        assert len(re.findall(r"(?:global|flat)_load_(?!lds)\w+ v", before)) == (8 if order == "1" else 0)
+
+
 def test_prefill_kernels_keep_their_accumulators_in_registers():
     import tempfile
     from paper_2507_01663_amd import build

@@ -100,8 +100,7 @@ def test_strided_pools(dec, kvd, Hq, Hkv, D, B, top, plans):
 @pytest.mark.parametrize("kvd,Hq,Hkv,D", [("bf16", 28, 4, 128), ("fp8_e4m3", 8, 2, 64)])
 @pytest.mark.parametrize("pages", [1, 2, 63, 64, 65, 127, 128, 129, 193])
 def test_widths_of_the_table(dec, kvd, Hq, Hkv, D, pages):
-    """Rows of up to 128 page ids are read whole, beside the length; of a longer one a wave reads the first 64 entries of its part.
-    One sequence fills its row, others end anywhere; several workgroups share an item and the merge adds them up."""
+    """One sequence fills its row, others end anywhere; of wide tables several workgroups share an item and the merge adds them up."""
     top = 16 * pages
     p = workload.build_problem("width", Hq, Hkv, D, [0] * 4, 1, [top - 3, 0, 1, top // 2 + 1], kv_dtype=kvd, seed=47)
     plan = plan_of(dec, p, use_hint=False)
