@@ -20,7 +20,18 @@ namespace ra {
 //   to 500, 28 on four (4.3), 51.5, 54.9, 64 of 20 to 300, 64 on eight (12.8), 120, 145; D = 64:
 //   32 of 30 to 400, 32 on two (3.8), 29.5, 22.8, 64 of 50 to 500 (10.1) 75.9, 69.9; nearly alike, eight of 300 to 500, 28 on four,
 //   22.0, 23.1.
-// The launch must not be empty workgroups mostly, so the bound on the lengths has to be a near one.
+// The launch is sized by the tokens as well as by the bound on the lengths, which counts 256 rows for the shortest prompt.  By the
+// bound alone calls of short prompts were empty workgroups mostly: 221 of 14 to 63 tokens, 32 heads on two, D = 64, 41.2 -> 29.1 us,
+// 442 of 31 to 61, sixteen on one, 56.9 -> 40.0.  (What is still empty: a prompt may have 31 tokens in a tile of its own, and the
+// dies that share a pair take its blocks in turn.)  Blocks by the bound of more than about four times those by the tokens, in
+// blocks of four units and in blocks of eight, leave the call to workgroups that stay; with the former alone few prompts of a
+// tile stayed too: ten of 10 to 13 tokens, 28 heads on four, 7.75, 5.4, 38 of up to 9, eight heads, 13.4, 5.7.
+// Not many short prompts either: a workgroup passes all prompts before its own, 64 to a trip.  Trips to a round of workgroups side by
+// side (rounds times prompts / 64), us, staying and four waves: with four query heads to a kv head and more 351 prompts of 22
+// to 43, eight on one (28), 24.0, 21.6; 391 of 18 to 58 (36) 22.4, 24.9; 442 of 31 to 61, sixteen on one, D = 64 (52) 38.5, 35.5; 1225
+// of 28 to 57, eight on two, D = 64 (231) 54.4, 72.0; with fewer, where a block of eight units is mostly empty, 1037 of 24 to 59, four
+// on four, D = 64 (159) 81.0, 56.1; 964 of 32 to 57, four on two (120) 43.7, 45.0; 1032 of 9 to 294 (208) 119, 108; 1226 of 40 to 135
+// (235) 77.6, 94.7; 6693 of 14 to 56, one head (1824) 139, 333.
 // A call of so few blocks that each has a compute unit to itself lasts as long as its longest block: beyond 256 tokens two
 // waves share a unit's keys.  One prompt, 28 heads on four, four waves and eight: 256 tokens 10.8, 10.8; 400 13.5, 12.8; 701
 // 20.1, 17.6; 1400 34.9, 28.2; 593, four on two, D = 64, 15.4, 14.2 (before: 10.9, 13.8, 19.7, 38.5, 14.8); beyond a unit each,
@@ -33,25 +44,38 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
     int64_t per_die = num_cus / 8;
     per_die = per_die < 1 ? 1 : per_die;
     if (stay > 0 && stay < per_die) per_die = stay; // fewer were asked for
-    int64_t blocks, about; // blocks of a die, at most; of the batch, about (by its tokens)
+    // Blocks of a die at most (by the bound on the lengths, and by the tokens too) and of the batch about (by its tokens).
+    int64_t by_bound, blocks, about;
     auto count = [&](int units) {
-        const int64_t per_pair = (rows / 32 * G + units - 1) / units; // blocks of a (prompt, kv head), at most
-        blocks = heads * (num_prompts * (per_pair / share) + ((int64_t)num_prompts + share - 1) / share * (per_pair % share));
-        about = ((int64_t)total_tokens + 31 * (int64_t)num_prompts) / 32 * Hkv * G / units;
+        const int64_t n = num_prompts, tiles = ((int64_t)total_tokens + 31 * n) / 32, per_pair = (rows / 32 * G + units - 1) / units;
+        by_bound = heads * (n * (per_pair / share) + (n + share - 1) / share * (per_pair % share));
+        about = tiles * Hkv * G / units;
         p.levels = (int)((per_pair + share - 1) / share);
+        // A pair's units are a multiple of G, so its last block lacks units - gcd(G, units) at most.  A die takes the numbers s,
+        // s + share, ... of a pair's blocks, another s for every prompt in turn: (blocks - s + share - 1) / share of them.
+        const int gcd = G % units == 0 ? units : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+        const int64_t all = (tiles * G + n * (units - gcd)) / units, rest = n % share;
+        const int64_t in_turn = n / share * (share * (share - 1) / 2) + rest * (share - 1) - rest * (rest - 1) / 2;
+        const int64_t by_tokens = heads * ((all + in_turn) / share);
+        blocks = by_bound < by_tokens ? by_bound : by_tokens;
     };
+    auto near = [&]() { return 2 * by_bound <= about + per_die; };
     count(kPfWaves);
-    const bool fit = blocks <= per_die; // (a block for every compute unit at most: there is nothing to load ahead)
+    const bool fit = by_bound <= per_die; // (a block for every compute unit at most: there is nothing to load ahead)
     const bool alike = 8 * (int64_t)total_tokens >= 7 * (int64_t)num_prompts * max_len;
     const bool uneven = max_len > 2 * kPfBlock ? !alike && about <= 12 * (int64_t)num_cus
                                                : 5 * (int64_t)total_tokens < 4 * (int64_t)num_prompts * max_len && 2 * about <= (D == 64 ? 24 : 7) * (int64_t)num_cus;
+    const bool near_by_eight = near();
     const PrefillShape staying = {8, 1, p.levels, (int)per_die};
     count(4);
-    const bool few = 8 * about <= 9 * (D == 64 ? 3 : 2) * (int64_t)num_cus; // (by the tokens it is a little more than it is)
-    if (!fit && !(stay == 0 && blocks <= INT32_MAX / 16) && !(stay < 0 && (few || uneven) && 2 * blocks <= about + per_die)) return staying;
-    p.parts = about <= num_cus && 4 * blocks <= 5 * per_die && max_len > kPfBlock ? 2 : 1;
+    const int64_t side = (D == 64 ? 3 : 2) * (int64_t)num_cus; // workgroups of four waves that run side by side
+    const bool few = 8 * about <= 9 * side; // (by the tokens it is a little more than it is)
+    const bool many = max_len <= 2 * kPfBlock && 8 * blocks > (G >= 4 ? 32 : 220) * 64 * side / num_prompts;
+    const bool one_each = fit || (stay == 0 ? blocks <= INT32_MAX / 16 : stay < 0 && (few || uneven) && !many && (near_by_eight || near()));
+    if (!one_each) return staying;
+    p.parts = about <= num_cus && 4 * by_bound <= 5 * per_die && max_len > kPfBlock ? 2 : 1;
     p.waves = 4 * p.parts;
-    p.per_die = (int)blocks;
+    p.per_die = blocks < 1 ? 1 : (int)blocks;
     return p;
 }
 

@@ -49,6 +49,12 @@ def kind(*a, **k):
     ([2048] * 16, 64, 8, 128, None, "stay"),
     ([16] * 4096, 4, 1, 64, None, "stay"),
     ([10] * 8, 28, 4, 128, 4096, "stay"),         # a bound far above the lengths: next to all workgroups would be empty
+    ([21] * 63, 8, 2, 64, None, "four"),          # ... nearer, though the bound is rounded up to 256 rows
+    ([20, 60, 100] * 120, 16, 2, 64, None, "stay"),  # many short prompts: 38 trips past them, over all rounds of workgroups
+    ([20, 60, 100] * 60, 16, 2, 64, None, "four"),   # 9.5
+    ([20, 40, 60] * 300, 4, 2, 64, None, "four"),    # ... few query heads to a kv head: 102
+    ([20, 40, 60] * 500, 4, 2, 64, None, "stay"),    # 285
+    ([40] * 6000, 1, 1, 64, None, "stay"),
 ])
 def test_edges(lens, Hq, Hkv, D, bound, want):
     assert kind(lens, Hq, Hkv, D, bound) == want
@@ -86,3 +92,19 @@ def test_every_block_has_a_workgroup():
             most = max(most, blocks)
         if units == 4:
             assert most <= s.per_die
+
+
+def test_no_more_workgroups_than_the_tokens_can_fill():
+    """A prompt has at most 31 tokens more than fill its tiles, a pair's last block three units fewer than four, and of a pair's
+    blocks the dies that share it take one more than their share: beyond that no workgroup is launched, however far the bound on
+    the lengths lies above them."""
+    r = random.Random(9)
+    for _ in range(2000):
+        Hkv, G = r.choice([1, 2, 3, 4, 8, 6, 16]), r.choice([1, 2, 3, 4, 5, 7, 8, 16])
+        n, longest = int(2 ** r.uniform(0, 10)), int(2 ** r.uniform(0, 9))
+        lens = [r.randint(1, longest) for _ in range(n)]
+        s = shape(lens, Hkv * G, Hkv, r.choice([64, 128]), longest, r.choice([AUTO, 0]))
+        if (s.waves, s.parts) == (8, 1):
+            continue
+        tiles, share = (sum(lens) + 31 * n) / 32, 8 // next(g for g in (8, 4, 2, 1) if Hkv % g == 0)
+        assert 8 * s.per_die <= Hkv * ((tiles * G + 3 * n) / 4 + n * (share - 1) / 2 + share * (share - 1) / 2)
