@@ -154,8 +154,8 @@ uint32_t rollout_attn_abi_version(void);
  *   ROLLOUT_ATTN_PREFILL_WGS_PER_DIE=0..64   prefill: one workgroup per block of query rows (0), or that many
  *                                   per die (at most one per compute unit) that stay and take block after block,
  *                                   loading the next one's inputs under the current one's last keys; default: one
- *                                   per compute unit, or one per block for few blocks and for long prompts of
- *                                   unlike lengths
+ *                                   per compute unit, or one per block for few blocks and for prompts of unlike
+ *                                   lengths while each would have few blocks
  *   ROLLOUT_ATTN_VERBOSE            print the die weights to stderr */
 ra_status rollout_attn_create(ra_ctx **ctx, int device_ordinal);
 

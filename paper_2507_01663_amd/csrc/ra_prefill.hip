@@ -71,7 +71,7 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
     const int64_t side = (D == 64 ? 3 : 2) * (int64_t)num_cus; // workgroups of four waves that run side by side
     const bool few = 8 * about <= 9 * side; // (by the tokens it is a little more than it is)
     const bool many = max_len <= 2 * kPfBlock && 8 * blocks > (G >= 4 ? 32 : 220) * 64 * side / num_prompts;
-    const bool one_each = fit || (stay == 0 ? blocks <= INT32_MAX / 16 : stay < 0 && (few || uneven) && !many && (near_by_eight || near()));
+    const bool one_each = stay == 0 ? blocks <= INT32_MAX / 16 : stay < 0 && (fit || ((few || uneven) && !many && (near_by_eight || near())));
     if (!one_each) return staying;
     p.parts = about <= num_cus && 4 * by_bound <= 5 * per_die && max_len > kPfBlock ? 2 : 1;
     p.waves = 4 * p.parts;

@@ -65,6 +65,12 @@ def test_what_was_asked_for():
     assert kind(lens, 28, 4, 128, stay=0) == "four"
     assert shape(lens, 28, 4, 128, stay=2).per_die == 2 and kind(lens, 28, 4, 128, stay=2) == "stay"
     assert shape(lens, 28, 4, 128, stay=64).per_die == CUS // 8
+    # workgroups that stay also where a workgroup per block would have been the library's choice, and no more than asked for
+    for lens, Hq, Hkv in (([257], 8, 8), ([600], 28, 4), ([1], 8, 8), ([100, 300, 500, 700] * 3, 28, 4), ([20, 100, 200, 500] * 3, 28, 4)):
+        assert kind(lens, Hq, Hkv, 128) != "stay"
+        for stay in (1, 2, 64):
+            s = shape(lens, Hq, Hkv, 128, stay=stay)
+            assert (s.waves, s.parts) == (8, 1) and s.per_die == min(stay, CUS // 8)
 
 
 def test_every_block_has_a_workgroup():
