@@ -73,7 +73,9 @@ __device__ __forceinline__ int pf_stage_swz(int r) { return (r + (r >> 3)) & 7; 
 __device__ __forceinline__ float first_max(float a, float b) { return fmaxf(a, b); }
 
 constexpr float kPfSlack = 8.0f;
-constexpr float kPfLowest = -3e38f; // least reference point of an exponent, of a wave with part of a row's keys
+// Least reference point of an exponent: keys that score -inf weigh nothing also while a row (or a wave's part of its keys) has
+// had no others, and a row without any other has lse -inf, whatever the launch shape.
+constexpr float kPfLowest = -__FLT_MAX__;
 
 // One step of a wave's software pipeline (see the kernel): weights of stage s and scores of stage s + 1 (NEXT; MASK:
 // that stage is the wave's diagonal one), then O += P V of stage s and the row maxima of the new scores.
@@ -664,9 +666,8 @@ template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void 
             for (int e = 3; e < 15; e += 2) mx = max3(mx, st.s[e], st.s[e + 1]);
             mx = max3(mx, st.s[15], st.s[15]);
             const u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-            st.m = max3(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[1])) * a.scale_log2;
-            // (a part whose scores are all -inf has weights of zero, not of NaN: the other part's may be finite)
-            if (KP == 2) st.m = works ? fmaxf(st.m, kPfLowest) : kPfLowest;
+            st.m = fmaxf(max3(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[1])) * a.scale_log2, kPfLowest);
+            if (KP == 2 && !works) st.m = kPfLowest;
         }
         int nhead = 0, nT = 0;
         bool nown = false;

@@ -390,6 +390,35 @@ def test_calls_of_few_blocks(dec, kv_dtype, Hq, Hkv, D, lens):
         np.testing.assert_array_equal(d.v_scale.cpu().numpy().view(np.uint32), vs.view(np.uint32))
 
 
+def check_minus_infinity(dec, D, stages, n):
+    """Keys of the even (0) or the odd (1) stages of 32 score -inf: they weigh nothing.  Rows with no other key, the first 32 if it
+    is the even stages, have lse -inf and no finite output."""
+    b = workload.build_prefill("few", 4, 1, D, [n], seed=27)
+    d = DevicePrefill(b)
+    off = (torch.arange(n, device=DEV) // 32) % 2 == stages
+    d.q[..., 0] = 1.0
+    d.k[off] = 0.0
+    d.k[off, :, 0] = float("-inf")
+    dec.prefill(d.c)
+    torch.cuda.synchronize()
+    q, k, v = d.q.double().transpose(0, 1), d.k[:, 0].double(), d.v[:, 0].double()
+    s = torch.where(off[None, None, :], float("-inf"), (q @ torch.where(off[:, None], 0.0, k).t().contiguous()) * float(b.softmax_scale))
+    s = s.masked_fill(torch.ones((n, n), dtype=torch.bool, device=DEV).triu(1), float("-inf"))
+    ref, ref_lse = (s.softmax(-1) @ v).transpose(0, 1), torch.logsumexp(s, -1).t()
+    first = 0 if stages else 32
+    assert torch.isfinite(d.out[first:]).all()
+    assert float((d.out[first:].double() - ref[first:]).norm() / ref[first:].norm()) < 1e-2
+    assert float((d.lse[first:].double() - ref_lse[first:]).abs().max()) < 1e-3
+    assert torch.isnan(d.out[:first]).all() and bool((d.lse[:first] == float("-inf")).all())
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("stages", [0, 1])
+@pytest.mark.parametrize("n", [250, 300])    # where the library chooses: four waves, and two to a unit
+def test_keys_that_score_minus_infinity(dec, D, stages, n):
+    check_minus_infinity(dec, D, stages, n)
+
+
 def test_a_row_maximum_that_keeps_growing(dec):
     # the exponent's reference point follows the row maximum from a distance: keys whose scores grow by several powers of two
     # from stage to stage, past the float range of exp if the point stayed

@@ -7,7 +7,7 @@ import torch
 import oracle
 import paper_2507_01663_amd as ra
 import workload
-from test_gpu_prefill import DevicePrefill, compare, expected_pools
+from test_gpu_prefill import DevicePrefill, check_minus_infinity, compare, expected_pools
 from test_prefill_shape import kind
 from workload.gen import bf16_bits_to_f32
 
@@ -75,20 +75,8 @@ def test_keys_of_one_part_that_dwarf_the_other_parts(dec, D):
 
 
 @pytest.mark.parametrize("D", [64, 128])
-def test_scores_of_minus_infinity_in_one_part(dec, D):
-    """All keys of the odd stages score -inf: their weights are zero and the results those of the even stages' keys alone."""
-    b = workload.build_prefill("few", 4, 1, D, [300], seed=27)
-    d = DevicePrefill(b)
-    odd = (torch.arange(300, device="cuda:0") // 32) % 2 == 1
-    d.q[..., 0] = 1.0
-    d.k[odd] = 0.0
-    d.k[odd, :, 0] = float("-inf")
-    dec.prefill(d.c)
-    torch.cuda.synchronize()
-    q, k, v = d.q.double().transpose(0, 1), d.k[:, 0].double(), d.v[:, 0].double()
-    s = torch.where(odd[None, None, :], float("-inf"), (q @ torch.where(odd[:, None], 0.0, k).t().contiguous()) * float(b.softmax_scale))
-    s = s.masked_fill(torch.ones((300, 300), dtype=torch.bool, device="cuda:0").triu(1), float("-inf"))
-    ref = (s.softmax(-1) @ v).transpose(0, 1)
-    assert torch.isfinite(d.out).all()
-    assert float((d.out.double() - ref).norm() / ref.norm()) < 1e-2
-    assert float((d.lse.double() - torch.logsumexp(s, -1).t()).abs().max()) < 1e-3
+@pytest.mark.parametrize("stages", [0, 1])
+def test_scores_of_minus_infinity_in_one_part(dec, D, stages):
+    """All keys of one of the two waves score -inf: their weights are zero and the results those of the other wave's keys alone."""
+    assert kind([300], 4, 1, D, cus=torch.cuda.get_device_properties(0).multi_processor_count) == "halves"
+    check_minus_infinity(dec, D, stages, 300)
