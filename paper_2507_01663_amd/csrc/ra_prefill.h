@@ -421,14 +421,9 @@ template <int D, int W> struct PfRing {
 // V of one block after the other stream through one ring, so the first chunks of the next block (and its query rows,
 // into registers) are loaded while the last stages of the current one are being multiplied: a block starts without a
 // trip to memory.  Without STAY there is a workgroup per block.  max_len is the host's upper bound of a prompt's length.
-template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(const int32_t *__restrict__ cu, int num_prompts, int limit, int G_, int Hkv,
-                                                                                              int units_shift, PrefillLaunch given)
+template <int D, bool STAY, int W> __device__ __forceinline__ void prefill_blocks(PrefillLaunch a)
 {
     constexpr int KP = W == 8 && !STAY ? 2 : 1; // parts that a unit's keys are in, each with a wave of its own
-    // (Without STAY what the first trip needs comes in arguments that are in registers when a wave starts: one prompt of 32 tokens 6.0
-    // -> 5.8 us; a workgroup that stays is no faster for it.)
-    PrefillLaunch a = given;
-    if (!STAY) a.cu = cu, a.num_prompts = num_prompts, a.limit = limit, a.G = G_, a.Hkv = Hkv, a.units_shift = units_shift, a.units = 1 << units_shift;
     using G = Geo<D, 2>;
     using R = PfRing<D, W>;
     constexpr int NSL = kPfSlots, CS = R::kChunk; // ring slots of one chunk; stage number s (counted over all the blocks of
@@ -828,6 +823,18 @@ template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void 
         if (!more) break;
     }
     wait_vmcnt<0>(); // nothing may land in LDS after the workgroup has left
+}
+
+// Without STAY what the first trip needs comes in arguments that are in registers when a wave starts: one prompt of 32 tokens 6.0
+// -> 5.8 us; a workgroup that stays is no faster for it.  (The blocks' function has the arguments by value.  With its body in here,
+// or by reference, the compiler keeps others of them in registers and spills more: workgroups that stay, D = 64, 32 heads on two,
+// 16 prompts of 1024 tokens 105.2 us, so 104.5, 64 of 200 to 210 48.6, 48.2, 60 of 512, e4m3, 134.5, 131.7.)
+template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(const int32_t *__restrict__ cu, int num_prompts, int limit, int G, int Hkv,
+                                                                                              int units_shift, PrefillLaunch given)
+{
+    PrefillLaunch a = given;
+    if (!STAY) a.cu = cu, a.num_prompts = num_prompts, a.limit = limit, a.G = G, a.Hkv = Hkv, a.units_shift = units_shift, a.units = 1 << units_shift;
+    prefill_blocks<D, STAY, W>(a);
 }
 
 } // namespace ra
