@@ -33,9 +33,10 @@ namespace ra {
 // on four, D = 64 (159) 81.0, 56.1; 964 of 32 to 57, four on two (120) 43.7, 45.0; 1032 of 9 to 294 (208) 119, 108; 1226 of 40 to 135
 // (235) 77.6, 94.7; 6693 of 14 to 56, one head (1824) 139, 333.
 // A call of so few blocks that each has a compute unit to itself lasts as long as its longest block: beyond 256 tokens two
-// waves share a unit's keys.  One prompt, 28 heads on four, four waves and eight: 256 tokens 10.8, 10.8; 400 13.5, 12.8; 701
-// 20.1, 17.6; 1400 34.9, 28.2; 593, four on two, D = 64, 15.4, 14.2 (before: 10.9, 13.8, 19.7, 38.5, 14.8); beyond a unit each,
-// four of 368 (364 blocks) 14.4, 17.6.
+// waves share a unit's keys, at head dim 64, where a chunk of one stage is little to have on the way, beyond 224.  One prompt, 28
+// heads on four, four waves and eight (and before either): 256 tokens 10.8, 10.8 (10.9); 400 13.5, 12.8 (13.8); 701 20.1, 17.6
+// (19.7); 1400 34.9, 28.2 (38.5); 593, four on two, D = 64, 15.4, 14.2 (14.8); eight on two, D = 64, 160 6.7, 7.1 (6.9), 200 7.3,
+// 7.3 (7.3), 250 8.2, 7.9 (7.7); beyond a unit each, four of 368 (364 blocks) 14.4, 17.6.
 PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int Hkv, int G, int D, int num_cus, int stay)
 {
     PrefillShape p = {0, 0, 0, 0};
@@ -73,7 +74,7 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
     const bool many = max_len <= 2 * kPfBlock && 8 * blocks > (G >= 4 ? 32 : 220) * 64 * side / num_prompts;
     const bool one_each = stay == 0 ? blocks <= INT32_MAX / 16 : stay < 0 && (fit || ((few || uneven) && !many && (near_by_eight || near())));
     if (!one_each) return staying;
-    p.parts = about <= num_cus && 4 * by_bound <= 5 * per_die && max_len > kPfBlock ? 2 : 1;
+    p.parts = about <= num_cus && 4 * by_bound <= 5 * per_die && max_len > (D == 64 ? kPfBlock - 32 : kPfBlock) ? 2 : 1;
     p.waves = 4 * p.parts;
     p.per_die = blocks < 1 ? 1 : (int)blocks;
     return p;

@@ -38,11 +38,11 @@ def check(dec, b, want, kv_dtype=None, what="", bound=None):
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(28, 4, 128), (4, 2, 64), (3, 1, 128), (8, 8, 64), (16, 1, 128), (10, 2, 128)])
 @pytest.mark.parametrize("lens,want", [
-    ([1], "four"), ([31, 0, 33], "four"), ([64, 65], "four"), ([256], "four"),
+    ([1], "four"), ([31, 0, 33], "four"), ([64, 65], "four"), ([224], "four"), ([256], {64: "halves", 128: "four"}),
     ([257], "halves"), ([288], "halves"), ([289], "halves"), ([320, 31], "halves"), ([33, 415], "halves"), ([640], "halves"),
 ])
 def test_edges_of_tiles_and_stages(dec, Hq, Hkv, D, lens, want):
-    check(dec, workload.build_prefill("few", Hq, Hkv, D, lens, seed=21), want, what="few")
+    check(dec, workload.build_prefill("few", Hq, Hkv, D, lens, seed=21), want if isinstance(want, str) else want[D], what="few")
 
 
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])

@@ -30,6 +30,8 @@ def kind(*a, **k):
 @pytest.mark.parametrize("lens,Hq,Hkv,D,bound,want", [
     ([256], 28, 4, 128, None, "four"),            # short: four waves, also with a compute unit to each block
     ([257], 28, 4, 128, None, "halves"),
+    ([224], 8, 2, 64, None, "four"),
+    ([225], 8, 2, 64, None, "halves"),
     ([701], 28, 4, 128, None, "halves"),
     ([1100], 28, 4, 128, None, "halves"),         # 247 blocks
     ([1200], 28, 4, 128, None, "four"),           # 269
