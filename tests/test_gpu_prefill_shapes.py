@@ -51,6 +51,7 @@ def test_edges_of_tiles_and_stages(dec, Hq, Hkv, D, lens, want):
     (28, 4, 128, [600, 30, 333, 80, 200, 513, 47], "four"),
     (8, 8, 128, [290], "halves"), (6, 2, 64, [300, 31], "halves"), (4, 2, 64, [600, 30, 333, 80, 200], "halves"),  # few heads to a kv head:
     (8, 8, 128, [33, 250, 0, 16], "four"), (6, 2, 64, [129, 1], "four"),                                            # up to four stages a block
+    (8, 8, 64, [33, 200, 0, 16], "four"), (8, 8, 128, [96, 5], "four"), (8, 8, 128, [97, 5], "four"), (16, 16, 128, [140, 97, 111, 30, 99, 100, 128], "four"),
 ])
 def test_cache_writes(dec, kv_dtype, Hq, Hkv, D, lens, want):
     b = workload.build_prefill("few", Hq, Hkv, D, lens, seed=23)
