@@ -77,6 +77,7 @@ struct PrefillLaunch {
     int32_t group;               // prompts whose blocks are dealt together (set by launch_prefill)
     int32_t units, units_shift;  // (32-row tile, head) units of a block, 4 or 8, and the logarithm (set by launch_prefill)
     int32_t levels;              // blocks of one (prompt, kv head) that a die takes, at most (set by launch_prefill)
+    int32_t votes;               // a block's level is found by votes (see pf_next; set by launch_prefill)
     uint32_t magic_g, magic_heads, magic_wgs; // ceil(2^32 / n) for n = G, Hkv / gcd(Hkv, 8) and the workgroups of a die
                                               // (set by launch_prefill)
     const uint16_t *q, *k, *v;   // bf16 [T][Hq][D], [T][Hkv][D]

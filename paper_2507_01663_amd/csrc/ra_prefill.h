@@ -277,8 +277,6 @@ struct PfCursor {
     int nfirst, nend;    // first token and end for the 64 prompts after these: asked for when these are taken into use
 };
 
-constexpr int kPfFewLevels = 16; // see pf_next
-
 struct PfDeal {
     int lane, wg, wgs, gg_shift, heads, s_shift, share; // see pf_deal
 };
@@ -362,16 +360,14 @@ template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch
         }
         return n * d.heads;
     };
-    // Few levels, as short prompts have: from the lowest up, a vote each.  (The sums over a group of 64 prompts are several hundred
-    // instructions; 267 prompts of 29 to 81 tokens, 32 heads on two, D = 64, a workgroup per block, 45.4 -> 39.9 us, 154 of up to
-    // 86, eight heads, 25.2 -> 23.1.  Workgroups that stay sum over fewer, and would pay for the question.)
-    const bool few = !STAY && a.levels <= kPfFewLevels;
+    // ... or few levels are voted on, the lowest first (launch_prefill says when).
+    const bool votes = !STAY && a.votes;
     int step = (a.levels + 63) >> 6;
     if (o >= c.before + c.blocks) { // another group of prompts
         c.lane0 = (__ffsll((long long)__ballot(c.sum * d.heads > o)) - 1) & -a.group;
         c.before = c.lane0 ? __builtin_amdgcn_readlane(c.sum, c.lane0 - 1) * d.heads : 0;
         c.blocks = __builtin_amdgcn_readlane(c.sum, c.lane0 + a.group - 1) * d.heads - c.before;
-        if (!few) c.up = from_level(d.lane * step);
+        if (!votes) c.up = from_level(d.lane * step);
         // Every other group, if it starts in the middle of a round, runs from short to long: its first blocks go to the
         // workgroups that got the last and shortest ones of the group before.  (Turned about, a group of one round that
         // starts with a round would give its longest blocks to the workgroups that have just had the longest ones: 32
@@ -384,12 +380,12 @@ template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch
     if (c.turned) o = c.blocks - 1 - o;
     int j = 0, up = c.up, left = c.blocks;
     const bool mine = (d.lane & -a.group) == c.lane0;
-    while (few) { // (left > o >= 0 blocks are of level j and up, so some are of level j)
+    while (votes) { // (left > o >= 0 blocks are of level j and up, so some are of level j)
         const int below = left - __popcll(__ballot(mine && c.cnt > j)) * d.heads;
         if (below <= o) break;
         left = below, j++;
     }
-    while (!few) {
+    while (!votes) {
         const int k = __popcll(__ballot(up > o)) - 1;
         left = __builtin_amdgcn_readlane(up, k); // blocks of level j and up
         j += k * step;

@@ -123,6 +123,12 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     a.units_shift = stays ? 3 : 2;
     a.units = 1 << a.units_shift;
     a.levels = p.levels;
+    // Few levels of many prompts, as short ones have: a vote for each level from the lowest up.  (The sums over a group of 64 prompts
+    // are several hundred instructions; 267 prompts of 29 to 81 tokens, 32 heads on two, D = 64, a workgroup per block, 45.4 -> 39.9
+    // us, 154 of up to 86, eight heads, 25.2 -> 23.1, 25 of 20 to 100, 40 on eight, ten levels, 16.0 -> 15.1; 24 of 16 to 300, 28 on
+    // four, fourteen levels, 21.3 either way.  Of few prompts they are fewer than the votes: four of 86 to 254, 64 on eight, sixteen
+    // levels, 11.4, with votes 12.1.  Workgroups that stay sum over fewer, and would pay for the question.)
+    a.votes = !stays && (p.levels == 1 || 2 * p.levels <= (a.num_prompts < 32 ? a.num_prompts : 32));
     a.magic_g = (uint32_t)((((uint64_t)1 << 32) + a.G - 1) / a.G);
     a.magic_heads = (uint32_t)((((uint64_t)1 << 32) + heads - 1) / heads);
     a.magic_wgs = (uint32_t)((((uint64_t)1 << 32) + p.per_die - 1) / p.per_die);

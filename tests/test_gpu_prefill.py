@@ -361,10 +361,10 @@ def test_cache_write_of_every_head_ratio(dec, kv_dtype, Hq, Hkv, D):
 
 
 @pytest.mark.parametrize("Hq,Hkv,D,n,longest", [(14, 2, 64, 150, 70), (6, 3, 128, 70, 40), (16, 1, 64, 3, 700), (5, 1, 128, 1, 1000), (12, 12, 64, 17, 90),
-                                                  (8, 8, 64, 70, 1100)])
+                                                  (8, 8, 64, 70, 1100), (32, 8, 64, 16, 100), (32, 8, 64, 15, 100)])
 def test_deal_of_many_and_of_few_prompts(dec, Hq, Hkv, D, n, longest):
     # every block of every prompt is taken once: more prompts than a wave has lanes, kv heads that share dies or not,
-    # fewer blocks than workgroups, long prompts of unlike lengths
+    # fewer blocks than workgroups, long prompts of unlike lengths, levels found by votes (eight of sixteen prompts) or by sums
     lens = np.random.default_rng(n).integers(0, longest + 1, size=n).tolist()
     lens[0], lens[-1] = longest, max(1, lens[-1])
     b = workload.build_prefill("pf", Hq, Hkv, D, lens, seed=n)
