@@ -525,7 +525,6 @@ ra_status rollout_attn_prefill(ra_ctx *c, const ra_prefill *p, void *stream)
     int prev = 0;
     hipError_t e = hipGetDevice(&prev);
     if (e == hipSuccess && prev != c->device) e = hipSetDevice(c->device);
-    if (e == hipSuccess && p->k_pool && !ra::prefill_writes_cache(a)) e = ra::launch_prefill_write(a, (hipStream_t)stream);
     if (e == hipSuccess) e = ra::launch_prefill(a, (hipStream_t)stream);
     if (prev != c->device) (void)hipSetDevice(prev);
     if (e != hipSuccess) { set_err(c, "HIP: %s", hipGetErrorString(e)); return RA_ERR_DEVICE; }

@@ -77,7 +77,6 @@ struct PrefillLaunch {
     int32_t group;               // prompts whose blocks are dealt together (set by launch_prefill)
     int32_t units, units_shift;  // (32-row tile, head) units of a block, 4 or 8, and the logarithm (set by launch_prefill)
     int32_t levels;              // blocks of one (prompt, kv head) that a die takes, at most (set by launch_prefill)
-    int32_t votes;               // a block's level is found by votes (see pf_next; set by launch_prefill)
     uint32_t magic_g, magic_heads, magic_wgs; // ceil(2^32 / n) for n = G, Hkv / gcd(Hkv, 8) and the workgroups of a die
                                               // (set by launch_prefill)
     const uint16_t *q, *k, *v;   // bf16 [T][Hq][D], [T][Hkv][D]
@@ -138,11 +137,8 @@ struct PrefillShape {
 };
 PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int Hkv, int G, int D, int num_cus, int stay);
 hipError_t prefill_four_config();
-hipError_t launch_prefill_four(const PrefillLaunch &a, unsigned workgroups, hipStream_t s);
+hipError_t launch_prefill_four(const PrefillLaunch &a, bool votes, unsigned workgroups, hipStream_t s);
 hipError_t launch_prefill(const PrefillLaunch &a, hipStream_t s);
-// Whether launch_prefill writes the cache as well (then launch_prefill_write is not called).
-bool prefill_writes_cache(const PrefillLaunch &a);
-hipError_t launch_prefill_write(const PrefillLaunch &a, hipStream_t s);
 hipError_t launch_gather(const Launch &a, int b, int kvh, void *k_out, void *v_out, int64_t cap, hipStream_t s);
 
 } // namespace ra

@@ -332,7 +332,7 @@ __device__ __forceinline__ void pf_take(const PrefillLaunch &a, const PfDeal &d,
 // (Walked to prompt by prompt, by two cursors, 25 votes to a group of 16, against so: 876 -> 71 us for 4096 prompts of 16
 // tokens, four heads on one kv head, D = 64; 421 -> 260 for 1024 of 64 and 110 -> 104 for 32 of 512, 28 on four, D = 128.
 // A call of this is about 0.3 us.)
-template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, PfBlock &b)
+template <bool STAY, bool VOTES> __device__ __forceinline__ bool pf_next(const PrefillLaunch &a, const PfDeal &d, PfCursor &c, PfBlock &b)
 {
     // back and forth: places wg, 2 wgs - 1 - wg, 2 wgs + wg, ...
     const int place = c.round * d.wgs + (c.round & 1 ? d.wgs - 1 - d.wg : d.wg);
@@ -360,14 +360,15 @@ template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch
         }
         return n * d.heads;
     };
-    // ... or few levels are voted on, the lowest first (launch_prefill says when).
-    const bool votes = !STAY && a.votes;
+    // (A call of few blocks is so short that it counts where there is but one level to try: 0.3 us of 9.7 for 30 prompts of up to 19
+    // tokens, eight heads; workgroups that stay would pay for the question.)
+    const bool flat = !STAY && a.levels == 1;
     int step = (a.levels + 63) >> 6;
     if (o >= c.before + c.blocks) { // another group of prompts
         c.lane0 = (__ffsll((long long)__ballot(c.sum * d.heads > o)) - 1) & -a.group;
         c.before = c.lane0 ? __builtin_amdgcn_readlane(c.sum, c.lane0 - 1) * d.heads : 0;
         c.blocks = __builtin_amdgcn_readlane(c.sum, c.lane0 + a.group - 1) * d.heads - c.before;
-        if (!votes) c.up = from_level(d.lane * step);
+        if (!VOTES && !flat) c.up = from_level(d.lane * step);
         // Every other group, if it starts in the middle of a round, runs from short to long: its first blocks go to the
         // workgroups that got the last and shortest ones of the group before.  (Turned about, a group of one round that
         // starts with a round would give its longest blocks to the workgroups that have just had the longest ones: 32
@@ -380,12 +381,12 @@ template <bool STAY> __device__ __forceinline__ bool pf_next(const PrefillLaunch
     if (c.turned) o = c.blocks - 1 - o;
     int j = 0, up = c.up, left = c.blocks;
     const bool mine = (d.lane & -a.group) == c.lane0;
-    while (votes) { // (left > o >= 0 blocks are of level j and up, so some are of level j)
+    while (VOTES) { // (left > o >= 0 blocks are of level j and up, so some are of level j)
         const int below = left - __popcll(__ballot(mine && c.cnt > j)) * d.heads;
         if (below <= o) break;
         left = below, j++;
     }
-    while (!votes) {
+    while (!VOTES && !flat) {
         const int k = __popcll(__ballot(up > o)) - 1;
         left = __builtin_amdgcn_readlane(up, k); // blocks of level j and up
         j += k * step;
@@ -416,8 +417,10 @@ template <int D, int W> struct PfRing {
 // STAY: the workgroups stay: as many per die as it has compute units, each taking its blocks one after the other.  K and
 // V of one block after the other stream through one ring, so the first chunks of the next block (and its query rows,
 // into registers) are loaded while the last stages of the current one are being multiplied: a block starts without a
-// trip to memory.  Without STAY there is a workgroup per block.  max_len is the host's upper bound of a prompt's length.
-template <int D, bool STAY, int W> __device__ __forceinline__ void prefill_blocks(PrefillLaunch a)
+// trip to memory.  Without STAY there is a workgroup per block, which finds it by sums or (VOTES) by votes: see
+// launch_prefill.  max_len
+// is the host's upper bound of a prompt's length.
+template <int D, bool STAY, int W, bool VOTES> __device__ __forceinline__ void prefill_blocks(PrefillLaunch a)
 {
     constexpr int KP = W == 8 && !STAY ? 2 : 1; // parts that a unit's keys are in, each with a wave of its own
     using G = Geo<D, 2>;
@@ -439,12 +442,12 @@ template <int D, bool STAY, int W> __device__ __forceinline__ void prefill_block
     pf_ask(a, deal, cur, 0);
     pf_take(a, deal, cur);
     PfBlock cb, n1, n2, n3;
-    if (__builtin_expect(!pf_next<STAY>(a, deal, cur, cb), 0)) return; // the whole workgroup
+    if (__builtin_expect(!pf_next<STAY, VOTES>(a, deal, cur, cb), 0)) return; // the whole workgroup
     int ahead = 0;      // blocks in n1, n2, n3: three until there are no more (STAY)
     bool last_known = false;
     auto look_ahead = [&](PfBlock &b) __attribute__((always_inline)) {
         if (!STAY || last_known) return;
-        last_known = !pf_next<STAY>(a, deal, cur, b);
+        last_known = !pf_next<STAY, VOTES>(a, deal, cur, b);
         if (!last_known) ahead++;
     };
 
@@ -825,12 +828,12 @@ template <int D, bool STAY, int W> __device__ __forceinline__ void prefill_block
 // -> 5.8 us; a workgroup that stays is no faster for it.  (The blocks' function has the arguments by value.  With its body in here,
 // or by reference, the compiler keeps others of them in registers and spills more: workgroups that stay, D = 64, 32 heads on two,
 // 16 prompts of 1024 tokens 105.2 us, so 104.5, 64 of 200 to 210 48.6, 48.2, 60 of 512, e4m3, 134.5, 131.7.)
-template <int D, bool STAY, int W> __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(const int32_t *__restrict__ cu, int num_prompts, int limit, int G, int Hkv,
+template <int D, bool STAY, int W, bool VOTES = false> __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(const int32_t *__restrict__ cu, int num_prompts, int limit, int G, int Hkv,
                                                                                               int units_shift, PrefillLaunch given)
 {
     PrefillLaunch a = given;
     if (!STAY) a.cu = cu, a.num_prompts = num_prompts, a.limit = limit, a.G = G, a.Hkv = Hkv, a.units_shift = units_shift, a.units = 1 << units_shift;
-    prefill_blocks<D, STAY, W>(a);
+    prefill_blocks<D, STAY, W, VOTES>(a);
 }
 
 } // namespace ra

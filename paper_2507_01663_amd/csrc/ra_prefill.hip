@@ -41,37 +41,37 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
 {
     PrefillShape p = {0, 0, 0, 0};
     const int64_t rows = ((int64_t)max_len + kPfBlock - 1) / kPfBlock * kPfBlock;
-    const int gg = (Hkv & 7) == 0 ? 8 : (Hkv & 3) == 0 ? 4 : (Hkv & 1) == 0 ? 2 : 1, share = 8 / gg, heads = Hkv / gg;
+    const int gg_shift = (Hkv & 7) == 0 ? 3 : (Hkv & 3) == 0 ? 2 : (Hkv & 1) == 0 ? 1 : 0, s_shift = 3 - gg_shift, share = 1 << s_shift, heads = Hkv >> gg_shift;
     int64_t per_die = num_cus / 8;
     per_die = per_die < 1 ? 1 : per_die;
     if (stay > 0 && stay < per_die) per_die = stay; // fewer were asked for
-    // Blocks of a die at most (by the bound on the lengths, and by the tokens too) and of the batch about (by its tokens).
+    // Blocks of a die at most (by the bound on the lengths, and by the tokens too) and of the batch about (by its tokens).  (Shifts
+    // for divisions: with those a call's host side took 0.2 us longer.)
     int64_t by_bound, blocks, about;
-    auto count = [&](int units) {
-        const int64_t n = num_prompts, tiles = ((int64_t)total_tokens + 31 * n) / 32, per_pair = (rows / 32 * G + units - 1) / units;
-        by_bound = heads * (n * (per_pair / share) + (n + share - 1) / share * (per_pair % share));
-        about = tiles * Hkv * G / units;
-        p.levels = (int)((per_pair + share - 1) / share);
-        // A pair's units are a multiple of G, so its last block lacks units - gcd(G, units) at most.  A die takes the numbers s,
-        // s + share, ... of a pair's blocks, another s for every prompt in turn: (blocks - s + share - 1) / share of them.
-        const int gcd = G % units == 0 ? units : G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
-        const int64_t all = (tiles * G + n * (units - gcd)) / units, rest = n % share;
-        const int64_t in_turn = n / share * (share * (share - 1) / 2) + rest * (share - 1) - rest * (rest - 1) / 2;
-        const int64_t by_tokens = heads * ((all + in_turn) / share);
+    auto count = [&](int shift) { // ... of 2^shift units
+        const int64_t n = num_prompts, tiles = ((int64_t)total_tokens + 31 * n) >> 5, most = (1 << shift) - 1, per_pair = (rows / 32 * G + most) >> shift;
+        by_bound = heads * (n * (per_pair >> s_shift) + ((n + share - 1) >> s_shift) * (per_pair & (share - 1)));
+        about = tiles * Hkv * G >> shift;
+        p.levels = (int)((per_pair + share - 1) >> s_shift);
+        // A pair's units are a multiple of G, so its last block lacks 2^shift - gcd(G, 2^shift) at most.  A die takes the numbers
+        // s, s + share, ... of a pair's blocks, another s for every prompt in turn: (blocks - s + share - 1) / share of them.
+        const int64_t lacks = (G & most) == 0 ? 0 : most + 1 - (G & -G), rest = n & (share - 1);
+        const int64_t in_turn = (n >> s_shift) * (share * (share - 1) / 2) + rest * (share - 1) - rest * (rest - 1) / 2;
+        const int64_t by_tokens = heads * ((((tiles * G + n * lacks) >> shift) + in_turn) >> s_shift);
         blocks = by_bound < by_tokens ? by_bound : by_tokens;
     };
     auto near = [&]() { return 2 * by_bound <= about + per_die; };
-    count(kPfWaves);
+    count(3);
     const bool fit = by_bound <= per_die; // (a block for every compute unit at most: there is nothing to load ahead)
     const bool alike = 8 * (int64_t)total_tokens >= 7 * (int64_t)num_prompts * max_len;
     const bool uneven = max_len > 2 * kPfBlock ? !alike && about <= 12 * (int64_t)num_cus
                                                : 5 * (int64_t)total_tokens < 4 * (int64_t)num_prompts * max_len && 2 * about <= (D == 64 ? 24 : 7) * (int64_t)num_cus;
     const bool near_by_eight = near();
     const PrefillShape staying = {8, 1, p.levels, (int)per_die};
-    count(4);
+    count(2);
     const int64_t side = (D == 64 ? 3 : 2) * (int64_t)num_cus; // workgroups of four waves that run side by side
     const bool few = 8 * about <= 9 * side; // (by the tokens it is a little more than it is)
-    const bool many = max_len <= 2 * kPfBlock && 8 * blocks > (G >= 4 ? 32 : 220) * 64 * side / num_prompts;
+    const bool many = max_len <= 2 * kPfBlock && 8.0 * (double)blocks * num_prompts > (G >= 4 ? 32 : 220) * 64.0 * (double)side;
     const bool one_each = stay == 0 ? blocks <= INT32_MAX / 16 : stay < 0 && (fit || ((few || uneven) && !many && (near_by_eight || near())));
     if (!one_each) return staying;
     p.parts = about <= num_cus && 4 * by_bound <= 5 * per_die && max_len > (D == 64 ? kPfBlock - 32 : kPfBlock) ? 2 : 1;
@@ -85,10 +85,9 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
 // blocks go one to a workgroup: those have four units, and such a call is mostly the cost of a second launch: five
 // prompts of 15 to 32 tokens, four heads on two, D = 64, 7.7 -> 4.6 us; one of 600, eight heads, e4m3, 22.8 -> 20.9, 21 of 195 to 419
 // 34.5 -> 22.8 (bf16 33.7 -> 17.6), 50 of 200 to 1500 219 -> 206 (bf16 219 -> 190).
-bool prefill_writes_cache(const PrefillLaunch &a)
+static bool writes_cache(const PrefillLaunch &a, const PrefillShape &p)
 {
-    if (!a.k_pool || a.G >= 4) return a.k_pool != nullptr;
-    const PrefillShape p = prefill_shape(a.num_prompts, a.total_tokens, a.max_len, a.Hkv, a.G, a.D, a.num_cus, a.stay);
+    if (a.G >= 4) return true;
     // One query head to a kv head, D = 128: a block of four waves quantises up to four stages, 1.2 us each, and where it has a compute
     // unit to itself all of it shows.  E4m3, copied first and written by the block: one prompt of 100 tokens, eight heads, 12.3, 13.6,
     // 250 15.1, 16.5, four of 100 to 250 14.7, 15.8, eight 16.0, 16.5, but twelve 18.2, 17.2, one of 70 11.5, 11.3, of 40 10.8, 8.9.
@@ -107,28 +106,28 @@ hipError_t prefill_config()
     return e;
 }
 
+static hipError_t launch_prefill_write(const PrefillLaunch &a, hipStream_t s);
+
 hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
 {
     const int64_t pairs = (int64_t)given.num_prompts * given.Hkv;
     const int64_t rows = ((int64_t)given.max_len + kPfBlock - 1) / kPfBlock * kPfBlock;
     if (pairs == 0 || rows == 0) return hipSuccess;
     if (rows > INT32_MAX || (pairs + 7) / 8 * (rows / kPfBlock) * given.G > INT32_MAX / 16) return hipErrorInvalidValue;
+    if (given.k_pool && ((int64_t)given.max_len + kPage - 1) / kPage * pairs > INT32_MAX) return hipErrorInvalidValue;
     PrefillLaunch a = given;
-    a.fused_write = prefill_writes_cache(a);
-    if (a.fused_write && ((int64_t)a.max_len + kPage - 1) / kPage * pairs > INT32_MAX) return hipErrorInvalidValue;
     a.limit = (int32_t)rows;
     const PrefillShape p = prefill_shape(a.num_prompts, a.total_tokens, a.max_len, a.Hkv, a.G, a.D, a.num_cus, a.stay);
+    a.fused_write = a.k_pool && writes_cache(a, p);
+    if (a.k_pool && !a.fused_write) {
+        const hipError_t e = launch_prefill_write(a, s);
+        if (e != hipSuccess) return e;
+    }
     const bool stays = p.waves == 8 && p.parts == 1;
     const int heads = a.Hkv / ((a.Hkv & 7) == 0 ? 8 : (a.Hkv & 3) == 0 ? 4 : (a.Hkv & 1) == 0 ? 2 : 1);
     a.units_shift = stays ? 3 : 2;
     a.units = 1 << a.units_shift;
     a.levels = p.levels;
-    // Few levels of many prompts, as short ones have: a vote for each level from the lowest up.  (The sums over a group of 64 prompts
-    // are several hundred instructions; 267 prompts of 29 to 81 tokens, 32 heads on two, D = 64, a workgroup per block, 45.4 -> 39.9
-    // us, 154 of up to 86, eight heads, 25.2 -> 23.1, 25 of 20 to 100, 40 on eight, ten levels, 16.0 -> 15.1; 24 of 16 to 300, 28 on
-    // four, fourteen levels, 21.3 either way.  Of few prompts they are fewer than the votes: four of 86 to 254, 64 on eight, sixteen
-    // levels, 11.4, with votes 12.1.  Workgroups that stay sum over fewer, and would pay for the question.)
-    a.votes = !stays && (p.levels == 1 || 2 * p.levels <= (a.num_prompts < 32 ? a.num_prompts : 32));
     a.magic_g = (uint32_t)((((uint64_t)1 << 32) + a.G - 1) / a.G);
     a.magic_heads = (uint32_t)((((uint64_t)1 << 32) + heads - 1) / heads);
     a.magic_wgs = (uint32_t)((((uint64_t)1 << 32) + p.per_die - 1) / p.per_die);
@@ -139,7 +138,13 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     // 256; 322.5, 314.3, 309.3 on 64 of 512 (40 on eight), 1301, 1294, 1279 on 16 of 2048 (64 on eight), 1148, 1124, 1108 on 32
     // of 2048 (28 on four).
     a.group = !stays ? 64 : (int64_t)16 * a.max_len * 4 * a.D * heads <= (4 << 20) ? 16 : 8;
-    if (p.waves == 4) return launch_prefill_four(a, 8u * (unsigned)p.per_die, s);
+    // How a workgroup of four waves finds its block's level.  Few levels of many prompts, as short ones have: a vote for each from the
+    // lowest up.  (The sums over a group of 64 prompts are several hundred instructions; 267 prompts of 29 to 81 tokens, 32 heads on
+    // two, D = 64, 45.4 -> 39.9 us, 154 of up to 86, eight heads, 25.2 -> 23.1, 25 of 20 to 100, 40 on eight, ten levels, 16.0 -> 15.1;
+    // 24 of 16 to 300, 28 on four, fourteen levels, 21.3 either way.  Of few prompts they are fewer than the votes: four of 86 to 254,
+    // 64 on eight, sixteen levels, 11.4, with votes 12.1.  One kernel that does either takes 0.1 us longer over the shortest calls.)
+    const bool votes = 2 * p.levels <= (a.num_prompts < 32 ? a.num_prompts : 32);
+    if (p.waves == 4) return launch_prefill_four(a, votes, 8u * (unsigned)p.per_die, s);
 #define RA_PF_LAUNCH(DD, ST)                                                                                                 \
     hipLaunchKernelGGL((prefill_kernel<DD, ST, 8>), dim3(8u * (unsigned)p.per_die), dim3(64 * 8), (PfRing<DD, 8>::kBytes), s, a.cu, a.num_prompts, \
                        a.limit, a.G, a.Hkv, a.units_shift, a)
@@ -230,12 +235,9 @@ template <int D> __global__ __launch_bounds__(64) void prefill_write_kernel(Pref
     write_tile<D>(a, a.v + src, n, a.v_pool + off, a.kv_fp8 ? a.v_scale + si : nullptr, lane);
 }
 
-hipError_t launch_prefill_write(const PrefillLaunch &a, hipStream_t s)
+static hipError_t launch_prefill_write(const PrefillLaunch &a, hipStream_t s) // (launch_prefill has seen that its workgroups can be counted)
 {
-    const int npg = (a.max_len + kPage - 1) / kPage;
-    const int64_t blocks = (int64_t)npg * a.num_prompts * a.Hkv;
-    if (blocks == 0) return hipSuccess;
-    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const int64_t blocks = (int64_t)((a.max_len + kPage - 1) / kPage) * a.num_prompts * a.Hkv;
     if (a.D == 128) hipLaunchKernelGGL(prefill_write_kernel<128>, dim3((unsigned)blocks), dim3(64), 0, s, a);
     else hipLaunchKernelGGL(prefill_write_kernel<64>, dim3((unsigned)blocks), dim3(64), 0, s, a);
     return hipGetLastError();
