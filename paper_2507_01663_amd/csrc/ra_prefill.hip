@@ -23,7 +23,9 @@ namespace ra {
 // The launch is sized by the tokens as well as by the bound on the lengths, which counts 256 rows for the shortest prompt.  By the
 // bound alone calls of short prompts were empty workgroups mostly: 221 of 14 to 63 tokens, 32 heads on two, D = 64, 41.2 -> 29.1 us,
 // 442 of 31 to 61, sixteen on one, 56.9 -> 40.0.  (What is still empty: a prompt may have 31 tokens in a tile of its own, and the
-// dies that share a pair take its blocks in turn.)  Blocks by the bound of more than about four times those by the tokens, in
+// dies that share a pair take its blocks in turn; and as many as run side by side are launched if the bound has them: two prompts
+// of 13 to 17 tokens, 64 on eight, take 5.4 us with 256 workgroups and 5.6 with the 32 that have a block, two of 231 to 367 13.0
+// with 512 and 13.4 with 368.)  Blocks by the bound of more than about four times those by the tokens, in
 // blocks of four units and in blocks of eight, leave the call to workgroups that stay; with the former alone few prompts of a
 // tile stayed too: ten of 10 to 13 tokens, 28 heads on four, 7.75, 5.4, 38 of up to 9, eight heads, 13.4, 5.7.
 // Not many short prompts either: a workgroup passes all prompts before its own, 64 to a trip.  Trips to a round of workgroups side by
@@ -76,7 +78,9 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
     if (!one_each) return staying;
     p.parts = about <= num_cus && 4 * by_bound <= 5 * per_die && max_len > (D == 64 ? kPfBlock - 32 : kPfBlock) ? 2 : 1;
     p.waves = 4 * p.parts;
-    p.per_die = blocks < 1 ? 1 : (int)blocks;
+    const int64_t fill = by_bound < side / 8 ? by_bound : side / 8; // (see above)
+    p.per_die = (int)(blocks < fill ? fill : blocks);
+    p.per_die = p.per_die < 1 ? 1 : p.per_die;
     return p;
 }
 
