@@ -79,20 +79,30 @@ def test_steps_without_a_schedule_look_up_pages_one_by_one(isa):
         assert len(re.findall(r"(?:global|flat)_load_(?!lds)\w+ v", before)) == (8 if order == "1" else 0)
 
 
-def test_prefill_kernels_keep_their_accumulators_in_registers():
+# Registers that the designed occupancy leaves a lane: workgroups of eight waves are two waves to a SIMD; of those of four, two share
+# a compute unit at head dim 128 (two waves to a SIMD) and three at head dim 64, as their LDS lets in.
+@pytest.mark.parametrize("source,kernels,unscratched,registers", [
+    ("ra_prefill.hip", 4, 6, {64: 256, 128: 256}),           # workgroups that stay and two waves to a unit's keys, D = 64 and 128; the cache write
+    ("ra_prefill_four.hip", 4, 4, {64: 168, 128: 256}),      # workgroups of four waves, levels by sums and by votes
+])
+def test_prefill_kernels_keep_their_accumulators_in_registers(source, kernels, unscratched, registers):
     import tempfile
     from paper_2507_01663_amd import build
     with tempfile.TemporaryDirectory() as tmp:
-        out = os.path.join(tmp, "ra_prefill.s")
-        flags = [f for f in build.flags_for("ra_prefill.hip") if f != "-fPIC"]
+        out = os.path.join(tmp, source + ".s")
+        flags = [f for f in build.flags_for(source) if f != "-fPIC"]
         subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")] + flags + ["-S", "--cuda-device-only", "-o", out,
-                                                                                  os.path.join(build.CSRC, "ra_prefill.hip")],
+                                                                                  os.path.join(build.CSRC, source)],
                        check=True, stderr=subprocess.DEVNULL)
         text = open(out).read()
     found = re.findall(r"^(_ZN2ra14prefill_kernel\w+):.*?s_endpgm", text, flags=re.S | re.M)
-    assert len(found) == 4                                   # D = 64 and D = 128, workgroups that stay or not
+    assert len(found) == kernels
     for m in re.finditer(r"^(_ZN2ra14prefill_kernel\w+):(.*?)s_endpgm", text, flags=re.S | re.M):
         assert "scratch_" not in m.group(2), m.group(1)
         assert "v_mfma_f32_32x32x16_bf16" in m.group(2), m.group(1)
         assert re.search(r"s_waitcnt vmcnt\([1-9][0-9]*\)", m.group(2)), m.group(1)
-    assert text.count(".private_segment_fixed_size: 0") == 6  # the four attention and the two cache-write kernels
+    assert text.count(".private_segment_fixed_size: 0") == unscratched
+    desc = descriptors(text, r"_ZN2ra14prefill_kernel")
+    assert len(desc) == kernels
+    for name, (regs, scratch) in desc.items():
+        assert scratch == 0 and regs <= registers[int(re.search(r"kernelILi(\d+)E", name).group(1))], (name, regs, scratch)

@@ -334,7 +334,8 @@ def test_bounds_far_above_the_lengths_and_very_many_heads(dec):
 @pytest.mark.parametrize("kv_dtype", ["bf16", "fp8_e4m3"])
 @pytest.mark.parametrize("Hq,Hkv,D", [(3, 3, 128), (8, 4, 64), (12, 4, 128), (8, 2, 128), (10, 2, 64), (21, 3, 128), (16, 1, 64), (48, 6, 128)])
 def test_cache_write_of_every_head_ratio(dec, kv_dtype, Hq, Hkv, D):
-    # written by the attention kernel (four query heads per kv head and more) or by the copy kernel: the same bits.  Values
+    # written by the attention kernel (four query heads per kv head and more, and most calls of one workgroup per block) or by the
+    # copy kernel: the same bits.  Values
     # that a quantiser may treat apart: a page of zeros, signed zeros, scales far below and above the usual range,
     # magnitudes that differ by 2^40 inside a page, NaN.  (Only the pools are looked at: no output is finite here.)
     b = workload.build_prefill("pf", Hq, Hkv, D, [1, 31, 32, 33, 0, 300, 47, 129], seed=Hq + D)
@@ -375,8 +376,9 @@ def test_deal_of_many_and_of_few_prompts(dec, Hq, Hkv, D, n, longest):
 @pytest.mark.parametrize("Hq,Hkv,D,lens", [(28, 4, 128, [1]), (28, 4, 128, [33, 95]), (8, 2, 64, [31, 0, 129]), (16, 1, 64, [200]),
                                            (64, 8, 128, [100]), (4, 4, 64, [97, 5]), (5, 1, 128, [257])])
 def test_calls_of_few_blocks(dec, kv_dtype, Hq, Hkv, D, lens):
-    # so few that a block takes four (tile, head) units instead of eight where the library chooses: waves 4 to 7 have none, a
-    # last block one to three; the cache is written from the ring (four query heads per kv head and more) or not
+    # so few that a block takes four (tile, head) units instead of eight where the library chooses, by four waves or by eight, two
+    # to a unit's keys; a last block has one to three; the cache is written from the ring whatever the head ratio, and not with
+    # the settings that make workgroups stay where a kv head has fewer than four query heads
     b = workload.build_prefill("pf", Hq, Hkv, D, lens, seed=Hq + len(lens))
     d = DevicePrefill(b, kv_dtype=kv_dtype)
     dec.prefill(d.c)
