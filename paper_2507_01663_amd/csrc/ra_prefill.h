@@ -418,8 +418,7 @@ template <int D, int W> struct PfRing {
 // V of one block after the other stream through one ring, so the first chunks of the next block (and its query rows,
 // into registers) are loaded while the last stages of the current one are being multiplied: a block starts without a
 // trip to memory.  Without STAY there is a workgroup per block, which finds it by sums or (VOTES) by votes: see
-// launch_prefill.  max_len
-// is the host's upper bound of a prompt's length.
+// launch_prefill.  max_len is the host's upper bound of a prompt's length.
 template <int D, bool STAY, int W, bool VOTES> __device__ __forceinline__ void prefill_blocks(PrefillLaunch a)
 {
     constexpr int KP = W == 8 && !STAY ? 2 : 1; // parts that a unit's keys are in, each with a wave of its own
@@ -824,16 +823,24 @@ template <int D, bool STAY, int W, bool VOTES> __device__ __forceinline__ void p
     wait_vmcnt<0>(); // nothing may land in LDS after the workgroup has left
 }
 
-// Without STAY what the first trip needs comes in arguments that are in registers when a wave starts: one prompt of 32 tokens 6.0
-// -> 5.8 us; a workgroup that stays is no faster for it.  (The blocks' function has the arguments by value.  With its body in here,
-// or by reference, the compiler keeps others of them in registers and spills more: workgroups that stay, D = 64, 32 heads on two,
-// 16 prompts of 1024 tokens 105.2 us, so 104.5, 64 of 200 to 210 48.6, 48.2, 60 of 512, e4m3, 134.5, 131.7.)
-template <int D, bool STAY, int W, bool VOTES = false> __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(const int32_t *__restrict__ cu, int num_prompts, int limit, int G, int Hkv,
+// A workgroup per block: what the first trip needs comes in arguments that are in registers when a wave starts: one prompt of 32
+// tokens 6.0 -> 5.8 us.
+template <int D, int W, bool VOTES = false> __global__ __launch_bounds__(64 * W, 2) void prefill_kernel(const int32_t *__restrict__ cu, int num_prompts, int limit, int G, int Hkv,
                                                                                               int units_shift, PrefillLaunch given)
 {
     PrefillLaunch a = given;
-    if (!STAY) a.cu = cu, a.num_prompts = num_prompts, a.limit = limit, a.G = G, a.Hkv = Hkv, a.units_shift = units_shift, a.units = 1 << units_shift;
-    prefill_blocks<D, STAY, W, VOTES>(a);
+    a.cu = cu, a.num_prompts = num_prompts, a.limit = limit, a.G = G, a.Hkv = Hkv, a.units_shift = units_shift, a.units = 1 << units_shift;
+    prefill_blocks<D, false, W, VOTES>(a);
+}
+
+// Workgroups that stay are no faster for such arguments, and slower beside them, read or not: the compiler keeps others of the
+// launch's fields in registers.  D = 64, 32 heads on two, us with them in the signature and without: 64 prompts of 200 to 210
+// tokens 48.5, 48.0, 60 of 512, e4m3, 131.6, 130.9; D = 128, 32 of 512, 28 on four, 101.7, 102.2, spread 1.  (The blocks' function
+// has its arguments by value.  By reference, spilling more: 48.4, 130.2, 102.4; 16 of 2048, 64 on eight, e4m3, D = 128, 1202, by
+// value 1206, spread 2.)
+template <int D> __global__ __launch_bounds__(64 * 8) void prefill_kernel(PrefillLaunch a)
+{
+    prefill_blocks<D, true, 8, false>(a);
 }
 
 } // namespace ra

@@ -103,9 +103,10 @@ static bool writes_cache(const PrefillLaunch &a, const PrefillShape &p)
 hipError_t prefill_config()
 {
     hipError_t e = prefill_four_config();
-#define RA_PF_CONFIG(DD, ST)                                                                                                 \
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_kernel<DD, ST, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, PfRing<DD, 8>::kBytes);
-    RA_PF_CONFIG(128, false) RA_PF_CONFIG(128, true) RA_PF_CONFIG(64, false) RA_PF_CONFIG(64, true)
+#define RA_PF_CONFIG(DD)                                                                                                     \
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_kernel<DD>, hipFuncAttributeMaxDynamicSharedMemorySize, PfRing<DD, 8>::kBytes); \
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)prefill_kernel<DD, 8>, hipFuncAttributeMaxDynamicSharedMemorySize, PfRing<DD, 8>::kBytes);
+    RA_PF_CONFIG(128) RA_PF_CONFIG(64)
 #undef RA_PF_CONFIG
     return e;
 }
@@ -149,15 +150,14 @@ hipError_t launch_prefill(const PrefillLaunch &given, hipStream_t s)
     // 64 on eight, sixteen levels, 11.4, with votes 12.1.  One kernel that does either takes 0.1 us longer over the shortest calls.)
     const bool votes = 2 * p.levels <= (a.num_prompts < 32 ? a.num_prompts : 32);
     if (p.waves == 4) return launch_prefill_four(a, votes, 8u * (unsigned)p.per_die, s);
-#define RA_PF_LAUNCH(DD, ST)                                                                                                 \
-    hipLaunchKernelGGL((prefill_kernel<DD, ST, 8>), dim3(8u * (unsigned)p.per_die), dim3(64 * 8), (PfRing<DD, 8>::kBytes), s, a.cu, a.num_prompts, \
-                       a.limit, a.G, a.Hkv, a.units_shift, a)
+    const dim3 grid(8u * (unsigned)p.per_die), block(64 * 8);
+#define RA_PF_LAUNCH(DD)                                                                                                     \
+    if (stays) hipLaunchKernelGGL((prefill_kernel<DD>), grid, block, (PfRing<DD, 8>::kBytes), s, a);                            \
+    else hipLaunchKernelGGL((prefill_kernel<DD, 8>), grid, block, (PfRing<DD, 8>::kBytes), s, a.cu, a.num_prompts, a.limit, a.G, a.Hkv, a.units_shift, a)
     if (a.D == 128) {
-        if (stays) RA_PF_LAUNCH(128, true);
-        else RA_PF_LAUNCH(128, false);
+        RA_PF_LAUNCH(128);
     } else {
-        if (stays) RA_PF_LAUNCH(64, true);
-        else RA_PF_LAUNCH(64, false);
+        RA_PF_LAUNCH(64);
     }
 #undef RA_PF_LAUNCH
     return hipGetLastError();
