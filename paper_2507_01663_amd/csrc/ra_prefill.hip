@@ -7,9 +7,13 @@ namespace ra {
 // of them takes is fixed beforehand; with one per block the hardware hands them out as units become free, two or three of
 // four waves to a compute unit, so that one's start and end (a block's fixed part is 4 to 5 us, its stages 0.6 each) run under
 // another's stages.  Us, staying against four waves a block:
-// - calls whose blocks all run side by side, about: 28 prompts of 57 to 71 tokens, 28 heads on four, 17.6, 13.3; eight of 128
-//   11.9, 8.7; six of 368 (504 blocks of four units) 18.5, 15.4, but eight of 368 (702) 20.8, 21.9; 32 of 128 (1008) 18.2, 20.1;
-//   with D = 64, three to a unit, 37 of 50 to 65, 32 on two (650), 12.0, 8.0, 16 of 1024 (4224) 107, 117;
+// - calls whose blocks all run side by side, about: 24 prompts of 57 to 71 tokens, 28 heads on four, 10.5, 9.1; eight of 128
+//   11.9, 8.7; six of 368 (504 blocks of four units) 18.5, 15.4, but eight of 368 (702) 20.8, 21.9, ten of 256 15.8, 17.6;
+// - short prompts, and any at head dim 64, up to a few rounds of such workgroups, two to a compute unit, three at D = 64: 28 of 57 to
+//   71, 28 on four (1.1 rounds), 15.5, 11.9; five of 4, 64 on eight, 7.4, 5.4; 38 of up to 9, eight heads, 13.4, 5.7; 73 of 21, 40 on
+//   eight (3.2), 21.0, 17.5; 42 of 37 to 49, 64 on eight (3.0), 19.1, 19.5; 127 of 18 to 24, 28 on four (4.1), 16.1, 17.3; 38 of 128 (2.5)
+//   24.8, 24.4, but 24 of 97, 64 on eight (3.0), 23.2, 25.1; D = 64, 32 on two: 60 of 50 to 65 (1.7) 12.2, 10.0, 38 of 211 (3.1)
+//   35.8, 27.6, twelve of 1024 (4.0) 83.2, 81.1, but 16 (5.5) 107, 117;
 // - long prompts of unlike lengths, as long as a workgroup that stayed would have few blocks: 29 of 339 to 1876, four heads on
 //   two, D = 64, 93.5, 45.7; 24 of 200 to 1500, 32 on two, D = 64, 146, 143.5; 50 of 200 to 1500, eight heads, 235, 219; 17 of 59
 //   to 1204, 40 on eight, 170, 161; 24 of 200 to 1500, 28 on four, 227, 230 (blocks of eight waves one each: 49.9, 162, 222, 168,
@@ -21,13 +25,13 @@ namespace ra {
 //   32 of 30 to 400, 32 on two (3.8), 29.5, 22.8, 64 of 50 to 500 (10.1) 75.9, 69.9; nearly alike, eight of 300 to 500, 28 on four,
 //   22.0, 23.1.
 // The launch is sized by the tokens as well as by the bound on the lengths, which counts 256 rows for the shortest prompt.  By the
-// bound alone calls of short prompts were empty workgroups mostly: 221 of 14 to 63 tokens, 32 heads on two, D = 64, 41.2 -> 29.1 us,
-// 442 of 31 to 61, sixteen on one, 56.9 -> 40.0.  (What is still empty: a prompt may have 31 tokens in a tile of its own, and the
+// bound alone calls of short prompts were empty workgroups mostly: 221 of 14 to 63 tokens, 32 heads on two, D = 64, 41.2 -> 29.1 us.
+// (What is still empty: a prompt may have 31 tokens in a tile of its own, and the
 // dies that share a pair take its blocks in turn; and as many as run side by side are launched if the bound has them: two prompts
 // of 13 to 17 tokens, 64 on eight, take 5.4 us with 256 workgroups and 5.6 with the 32 that have a block, two of 231 to 367 13.0
-// with 512 and 13.4 with 368.)  Blocks by the bound of more than about four times those by the tokens, in
-// blocks of four units and in blocks of eight, leave the call to workgroups that stay; with the former alone few prompts of a
-// tile stayed too: ten of 10 to 13 tokens, 28 heads on four, 7.75, 5.4, 38 of up to 9, eight heads, 13.4, 5.7.
+// with 512 and 13.4 with 368.)  A bound far above the lengths leaves the call to workgroups that stay, as the levels that a
+// workgroup searches are the bound's: more than eight times the blocks by the tokens, which is what the 256 rows make of prompts of
+// one tile; where the choice is by unlike lengths, which a bound can feign, more than four times.
 // Not many short prompts either: a workgroup passes all prompts before its own, 64 to a trip.  Trips to a round of workgroups side by
 // side (rounds times prompts / 64), us, staying and four waves: with four query heads to a kv head and more 351 prompts of 22
 // to 43, eight on one (28), 24.0, 21.6; 391 of 18 to 58 (36) 22.4, 24.9; 442 of 31 to 61, sixteen on one, D = 64 (52) 38.5, 35.5; 1225
@@ -37,8 +41,10 @@ namespace ra {
 // A call of so few blocks that each has a compute unit to itself lasts as long as its longest block: beyond 256 tokens two
 // waves share a unit's keys, at head dim 64, where a chunk of one stage is little to have on the way, beyond 224.  One prompt, 28
 // heads on four, four waves and eight (and before either): 256 tokens 10.8, 10.8 (10.9); 400 13.5, 12.8 (13.8); 701 20.1, 17.6
-// (19.7); 1400 34.9, 28.2 (38.5); 593, four on two, D = 64, 15.4, 14.2 (14.8); eight on two, D = 64, 160 6.7, 7.1 (6.9), 200 7.3,
-// 7.3 (7.3), 250 8.2, 7.9 (7.7); beyond a unit each, four of 368 (364 blocks) 14.4, 17.6.
+// (19.7); 593, four on two, D = 64, 15.4, 14.2 (14.8); eight on two, D = 64, 160 6.7, 7.1 (6.9), 200 7.3,
+// 7.3 (7.3), 250 8.2, 7.9 (7.7); beyond a unit each, three of 600 18.4, 21.4, four of
+// 368 14.4, 17.6.  (The line is by blocks, whosever they are; a lone prompt would still be faster by eight: of 1200 tokens 30.1, 25.5, of
+// 1800 43.2, 36.4, but two of 900 24.6, 25.7.)
 PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int Hkv, int G, int D, int num_cus, int stay)
 {
     PrefillShape p = {0, 0, 0, 0};
@@ -49,7 +55,7 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
     if (stay > 0 && stay < per_die) per_die = stay; // fewer were asked for
     // Blocks of a die at most (by the bound on the lengths, and by the tokens too) and of the batch about (by its tokens).  (Shifts
     // for divisions: with those a call's host side took 0.2 us longer.)
-    int64_t by_bound, blocks, about;
+    int64_t by_bound, by_tokens, blocks, about;
     auto count = [&](int shift) { // ... of 2^shift units
         const int64_t n = num_prompts, tiles = ((int64_t)total_tokens + 31 * n) >> 5, most = (1 << shift) - 1, per_pair = (rows / 32 * G + most) >> shift;
         by_bound = heads * (n * (per_pair >> s_shift) + ((n + share - 1) >> s_shift) * (per_pair & (share - 1)));
@@ -59,22 +65,22 @@ PrefillShape prefill_shape(int num_prompts, int total_tokens, int max_len, int H
         // s, s + share, ... of a pair's blocks, another s for every prompt in turn: (blocks - s + share - 1) / share of them.
         const int64_t lacks = (G & most) == 0 ? 0 : most + 1 - (G & -G), rest = n & (share - 1);
         const int64_t in_turn = (n >> s_shift) * (share * (share - 1) / 2) + rest * (share - 1) - rest * (rest - 1) / 2;
-        const int64_t by_tokens = heads * ((((tiles * G + n * lacks) >> shift) + in_turn) >> s_shift);
+        by_tokens = heads * ((((tiles * G + n * lacks) >> shift) + in_turn) >> s_shift);
         blocks = by_bound < by_tokens ? by_bound : by_tokens;
     };
-    auto near = [&]() { return 2 * by_bound <= about + per_die; };
     count(3);
     const bool fit = by_bound <= per_die; // (a block for every compute unit at most: there is nothing to load ahead)
     const bool alike = 8 * (int64_t)total_tokens >= 7 * (int64_t)num_prompts * max_len;
     const bool uneven = max_len > 2 * kPfBlock ? !alike && about <= 12 * (int64_t)num_cus
                                                : 5 * (int64_t)total_tokens < 4 * (int64_t)num_prompts * max_len && 2 * about <= (D == 64 ? 24 : 7) * (int64_t)num_cus;
-    const bool near_by_eight = near();
     const PrefillShape staying = {8, 1, p.levels, (int)per_die};
     count(2);
     const int64_t side = (D == 64 ? 3 : 2) * (int64_t)num_cus; // workgroups of four waves that run side by side
-    const bool few = 8 * about <= 9 * side; // (by the tokens it is a little more than it is)
+    const int rounds = D == 64 ? 8 : max_len <= 64 ? 6 : max_len <= 128 ? 5 : 0; // (halves of one)
+    const bool few = 8 * about <= 9 * side || 16 * blocks <= rounds * side; // (by the tokens it is a little more than it is)
+    const bool near = by_bound <= (few ? 8 : 4) * by_tokens + per_die;
     const bool many = max_len <= 2 * kPfBlock && 8.0 * (double)blocks * num_prompts > (G >= 4 ? 32 : 220) * 64.0 * (double)side;
-    const bool one_each = stay == 0 ? blocks <= INT32_MAX / 16 : stay < 0 && (fit || ((few || uneven) && !many && (near_by_eight || near())));
+    const bool one_each = stay == 0 ? blocks <= INT32_MAX / 16 : stay < 0 && (fit || ((few || uneven) && !many && near));
     if (!one_each) return staying;
     p.parts = about <= num_cus && 4 * by_bound <= 5 * per_die && max_len > (D == 64 ? kPfBlock - 32 : kPfBlock) ? 2 : 1;
     p.waves = 4 * p.parts;

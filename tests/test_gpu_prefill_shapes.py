@@ -52,6 +52,9 @@ def test_edges_of_tiles_and_stages(dec, Hq, Hkv, D, lens, want):
     (8, 8, 128, [290], "halves"), (6, 2, 64, [300, 31], "halves"), (4, 2, 64, [600, 30, 333, 80, 200], "halves"),  # few heads to a kv head:
     (8, 8, 128, [33, 250, 0, 16], "four"), (6, 2, 64, [129, 1], "four"),                                            # up to four stages a block
     (8, 8, 64, [33, 200, 0, 16], "four"), (8, 8, 128, [96, 5], "four"), (8, 8, 128, [97, 5], "four"), (16, 16, 128, [140, 97, 111, 30, 99, 100, 128], "four"),
+    (64, 8, 128, [33, 5, 64, 31, 0, 17, 48] * 4, "four"), (28, 4, 128, [60] * 62, "four"), (28, 4, 128, [60] * 63, "stay"),   # more blocks than
+    (40, 8, 128, [128, 97, 65] * 4, "four"), (8, 8, 128, [9, 1, 4] * 13, "four"), (4, 4, 64, [37, 2] * 40, "four"),           # run side by side,
+    (32, 2, 64, [200, 3, 129, 256] * 5, "four"), (16, 1, 64, [700, 20, 20, 64, 1] * 4, "four"),                               # or short prompts
 ])
 def test_cache_writes(dec, kv_dtype, Hq, Hkv, D, lens, want):
     b = workload.build_prefill("few", Hq, Hkv, D, lens, seed=23)

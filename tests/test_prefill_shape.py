@@ -39,7 +39,20 @@ def kind(*a, **k):
     ([368] * 6, 28, 4, 128, None, "four"),        # 487 blocks by the tokens: two to a compute unit
     ([368] * 8, 28, 4, 128, None, "stay"),
     ([60] * 37, 32, 2, 64, None, "four"),         # three to a compute unit at head dim 64
-    ([60] * 60, 32, 2, 64, None, "stay"),
+    ([60] * 119, 32, 2, 64, None, "four"),        # ... and up to four rounds of them
+    ([60] * 120, 32, 2, 64, None, "stay"),
+    ([1024] * 12, 32, 2, 64, None, "four"),
+    ([1024] * 13, 32, 2, 64, None, "stay"),
+    ([60] * 62, 28, 4, 128, None, "four"),        # short prompts at head dim 128: three rounds
+    ([60] * 63, 28, 4, 128, None, "stay"),
+    ([65] * 20 + [1] * 5, 28, 4, 128, None, "four"),
+    ([128] * 12, 64, 8, 128, None, "four"),       # ... and two and a half
+    ([129] * 17, 28, 4, 128, None, "stay"),       # longer ones: those that run side by side
+    ([4] * 5, 64, 8, 128, None, "four"),          # one tile of the eight that the bound is rounded up to
+    ([9] * 38, 8, 8, 128, None, "four"),
+    ([10] * 8, 28, 4, 128, 512, "four"),
+    ([10] * 8, 28, 4, 128, 513, "stay"),
+    ([512] * 16, 28, 4, 128, 2560, "stay"),       # a bound that makes like lengths look unlike
     ([100, 300, 500, 700] * 3, 28, 4, 128, None, "four"),   # long prompts of unlike lengths
     ([20, 100, 200, 500] * 3, 28, 4, 128, None, "four"),    # shorter ones too
     ([20, 100, 200, 500] * 8, 28, 4, 128, None, "four"),    # 3.2 blocks of eight units to a compute unit
@@ -50,7 +63,7 @@ def kind(*a, **k):
     ([512] * 32, 28, 4, 128, None, "stay"),
     ([2048] * 16, 64, 8, 128, None, "stay"),
     ([16] * 4096, 4, 1, 64, None, "stay"),
-    ([10] * 8, 28, 4, 128, 4096, "stay"),         # a bound far above the lengths: next to all workgroups would be empty
+    ([10] * 8, 28, 4, 128, 4096, "stay"),         # a bound far above the lengths
     ([21] * 63, 8, 2, 64, None, "four"),          # ... nearer, though the bound is rounded up to 256 rows
     ([20, 60, 100] * 120, 16, 2, 64, None, "stay"),  # many short prompts: 38 trips past them, over all rounds of workgroups
     ([20, 60, 100] * 60, 16, 2, 64, None, "four"),   # 9.5
