@@ -154,8 +154,8 @@ uint32_t rollout_attn_abi_version(void);
  *   ROLLOUT_ATTN_PREFILL_WGS_PER_DIE=0..64   prefill: one workgroup per block of query rows (0), or that many
  *                                   per die (at most one per compute unit) that stay and take block after block,
  *                                   loading the next one's inputs under the current one's last keys; default: one
- *                                   per compute unit, or one per block for few blocks and for prompts of unlike
- *                                   lengths while each would have few blocks
+ *                                   per compute unit, or one per block for few blocks (more of them for short prompts
+ *                                   and at head dim 64) and for prompts of unlike lengths while each would have few
  *   ROLLOUT_ATTN_VERBOSE            print the die weights to stderr */
 ra_status rollout_attn_create(ra_ctx **ctx, int device_ordinal);
 
@@ -259,7 +259,8 @@ ra_status rollout_attn_append(ra_ctx *ctx, const ra_problem *problem, const void
  * Layouts: q, out bf16 [T][Hq][D]; k, v bf16 [T][Hkv][D]; lse fp32 [T][Hq]; all contiguous, 16-byte aligned,
  * T = total_tokens = cu_seqlens[num_prompts].  cu_seqlens: dev int32 [num_prompts + 1], starts at 0,
  * non-decreasing.  max_prompt_len is a HOST-side upper bound of every prompt's length (the launch is sized by
- * it and by total_tokens; a prompt's tokens at or past it may be left unprocessed, in whole blocks of query rows and whole pages).
+ * it and by total_tokens; a prompt's tokens at or past it may be left unprocessed, in whole blocks of query rows
+ * and whole pages).
  * Cache write (k_pool != NULL): token i of prompt g goes to page pages[page_offsets[g] + i / page_size], slot
  * i % page_size, every kv head, of pools laid out as in ra_problem (same strides, kv_dtype, scales); a prompt
  * with more tokens than its pages hold has the rest left unwritten, and so has a page id outside
